@@ -49,7 +49,7 @@
  * library owns the plan: its host tables, and - created on the first device
  * call, on the device that is current then - device memory for the tensor
  * offset tables and a scratch array of partial sums (8 bytes per 256 elements
- * of a chunk); the first call for a rank that uses the tensor layout or a
+ * of an update range); the first call for a rank that uses the tensor layout or a
  * weight-decay mask adds a per-tile table for each chunk of that rank's update
  * range (16 bytes per 256 elements, built when the chunk has at most 4 Mi
  * tiles, or at most PARO_TILE_TABLE_MAX_TILES when that environment variable

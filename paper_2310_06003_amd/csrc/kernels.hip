@@ -177,6 +177,35 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTable src, int P, int
     }
 }
 
+// Sweep 1, chunk layout, over blocks [block0, block0 + gridDim) of an update range of several chunks
+// (optimizer state sharded inside the group only, or not at all): one launch, each chunk in its own
+// fold order.  Blocks are cut from the start of the range, not of the chunk: a chunk is only a
+// multiple of 8 elements, and blocks counted from its start would straddle cache lines in every array
+// (MI355X, P = 16 fp32, chunks of 62.5 M elements: 5.1 TB/s there against 6.1).  Partial sums of blocks
+// [part0, part0 + part_n) only (both multiples of 8, block0 too); the others hold no element that counts.
+template <int DT, bool SUMSQ>
+__global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTable src, int P, const RangeMap rm, int64_t block0, int64_t n,
+                                                   float *__restrict__ g, double *__restrict__ partials, unsigned part0,
+                                                   unsigned part_n) {
+    const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
+    double acc = 0.0;
+    if (e0 < n) {
+        float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        const bool counts = fold_range<DT>(rm, src, P, e0, n, X);
+        if (e < n) {
+            store_g4(g, e0, piece_elems(e0, n), X);
+            if (SUMSQ && counts) acc = sumsq4(X);
+        }
+    }
+    if (SUMSQ) {
+        const unsigned b = blockIdx.x - part0;
+        if (b < part_n) {
+            const double s = wave_sum(acc);
+            if (lane_id() == 0) partials[(b & 7u) * (part_n >> 3) + (b >> 3)] = s;     // see partial_slot()
+        }
+    }
+}
+
 // Sweep 1, tensor layout: one block of 256 elements starting at e0 < n.  Every lane of the wave takes part.
 template <bool SUMSQ, int KB>
 __device__ __forceinline__ void reduce_piece_t(const TensorMap &tm, const Piece &pc, const SrcTable &src, int P,
@@ -313,6 +342,22 @@ __global__ __launch_bounds__(WAVE) void k_fused4(const SrcTable src, int P, int 
     update4<true>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, elems);
 }
 
+// The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
+template <int DT>
+__global__ __launch_bounds__(WAVE) void k_fused4r(const SrcTable src, int P, const RangeMap rm, int64_t block0, int64_t n,
+                                                  const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
+                                                  float *__restrict__ v, uint16_t *__restrict__ dst) {
+    const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
+    if (e0 >= n) return;
+    State4 s;
+    if (e < n) s = load_state4(p, m, v, e);
+    float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    fold_range<DT>(rm, src, P, e0, n, X);
+    if (e >= n) return;
+    const bool decays[4] = {true, true, true, true};
+    update4<true>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n));
+}
+
 // Low-precision pack alone.
 __global__ __launch_bounds__(WAVE) void k_pack(const float *__restrict__ p, uint16_t *__restrict__ dst, int64_t n,
                                                int pack_dtype) {
@@ -385,10 +430,13 @@ int check_ptr(const void *p, const char *what) {
 }
 
 // One-wave blocks of a sweep over n elements, ppw pieces per wave.
-unsigned piece_grid(int64_t n, int ppw = 1) {
+int64_t piece_count(int64_t n, int ppw = 1) {
     const int64_t nb = (n + (int64_t)PIECE * ppw - 1) / ((int64_t)PIECE * ppw);
-    return (unsigned)(nb < 1 ? 1 : nb);
+    return nb < 1 ? 1 : nb;
 }
+unsigned piece_grid(int64_t n, int ppw = 1) { return (unsigned)piece_count(n, ppw); }
+// Largest grid of a launch that can be cut into several (2^31 threads; the runtime takes fewer than 2^32).
+constexpr int64_t MAX_GRID = (int64_t)1 << 25;
 
 // Occupancy throttle for the one-wave-block sweeps: on this part the mixed read/write sweeps run
 // faster with 10-14 waves per compute unit in flight than with the 32 the registers would allow
@@ -416,6 +464,7 @@ int fold_loads(int P, int blocks_per_wave = 1) { return std::min(P, PARO_BATCH) 
 struct Scratch {
     int lds_per_cu;
     double *partials;
+    int64_t n_partials;    // a multiple of 8
     double *level2;
     double *chunk_sums;    // [PARO_MAX_RANKS] one sum per chunk of an update range of several chunks
     bool plan_tables;      // the plan's device tables (offset tables, per-tile tables) exist
@@ -424,7 +473,7 @@ struct Scratch {
 Scratch plan_scratch(const paro_plan_t *pl) {
     double *level2 = pl->dev.partials + pl->dev.n_partials;
     const int64_t n_level2 = (pl->dev.n_partials + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
-    return Scratch{pl->dev.lds_per_cu, pl->dev.partials, level2, level2 + n_level2, true};
+    return Scratch{pl->dev.lds_per_cu, pl->dev.partials, pl->dev.n_partials, level2, level2 + n_level2, true};
 }
 
 template <class T>
@@ -458,9 +507,11 @@ int fill_tables(const paro_plan_t *pl, paro_device_tables &d) {
     d.tiles_per_chunk = (pl->L + TILE - 1) / TILE;
     d.tile_tab.assign((size_t)pl->P, nullptr);
     d.tile_tab_tried.assign((size_t)pl->P, 0);
-    // one partial per block of a sweep-1 launch (a launch covers one chunk of L elements),
+    // one partial per block of a sweep-1 launch (which covers a rank's whole update range at most),
     // followed by room for the second-level sums
-    int64_t n_part = ((int64_t)piece_grid(pl->L) + 7) & ~(int64_t)7;
+    int64_t ob, on;
+    paro::letter_range(pl, 0, pl->letters[2], &ob, &on);
+    int64_t n_part = (piece_count(on) + 7) & ~(int64_t)7;
     if (n_part < PARO_MIN_PARTIALS) n_part = PARO_MIN_PARTIALS;
     d.n_partials = n_part;
     const int64_t n_level2 = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
@@ -640,6 +691,17 @@ void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int
     *group_len = gl;
 }
 
+// ... and of a launch over an update range of several chunks: pointers in rank order, the order of
+// each chunk's fold follows from the range map.
+RangeMap range_map(const paro_plan_t *pl, int64_t ob, int own, const void *const *contrib, SrcTable *tab) {
+    for (int q = 0; q < pl->P; ++q) tab->p[q] = contrib[q];
+    for (int q = pl->P; q < PARO_MAX_RANKS; ++q) tab->p[q] = nullptr;
+    const bool ring = pl->sched == PARO_RING;
+    const int first = (int)(ob / pl->L);
+    return RangeMap{pl->L, 1.0 / (double)pl->L, first, pl->G, pl->g, ring ? pl->P : pl->G, ring ? 1 : pl->g,
+                    own < 0 ? -1 : own - first};
+}
+
 #define PARO_BY_DTYPE(dt, CALL)            \
     do {                                   \
         if ((dt) == PARO_BF16) {           \
@@ -724,6 +786,21 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
                                                        pl->P, group_len, n, a, p, m, v, dst, tm));
 }
 
+// ... over an update range of several chunks (chunk layout, no decay mask).
+int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_t on, const void *const *contrib,
+                       const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
+    SrcTable tab;
+    const RangeMap rm = range_map(pl, ob, -1, contrib, &tab);
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P) + 3, PARO_FUSED_LOADS_PER_CU));
+    for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
+        const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
+        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, rm, b0, on, a,
+                                                       p, m, v, dst));
+        PARO_HIP(hipGetLastError());
+    }
+    return PARO_OK;
+}
+
 // Adds the n_part partial sums a sweep-1 launch left in the scratch array into *out (device).
 int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st) {
     if (n_part > 2 * FINALIZE_CHUNK) {       // two levels: slices of 2048 partials, then their sums
@@ -738,6 +815,47 @@ int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st
     return PARO_OK;
 }
 
+// Sweep 1 over an update range of several chunks, chunk layout: one launch, or, where the norm covers
+// the whole range and the scratch array is too small for its partial sums, one for each piece that fits.
+// own >= 0: the sum of squares of that chunk alone.
+int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_t on, int own, const void *const *contrib,
+                    float *grad_out, double *sumsq_out, hipStream_t st) {
+    int rc;
+    SrcTable tab;
+    const RangeMap rm = range_map(pl, ob, own, contrib, &tab);
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), PARO_FOLD_LOADS_PER_CU));
+    const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
+    const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
+    int n_sums = 0;
+    for (int64_t b0 = 0; b0 < blocks; b0 += step) {
+        const int64_t grid = std::min(step, blocks - b0);
+        int64_t first = b0, last = b0 + grid;                     // the blocks whose squares count
+        if (own >= 0) {
+            const int64_t lo = own * pl->L - ob;
+            first = std::max((lo / PIECE) & ~(int64_t)7, first);
+            last = std::min((piece_count(lo + pl->L) + 7) & ~(int64_t)7, last);
+        }
+        if (sumsq_out && first < last) {
+            PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true>), dim3((unsigned)grid), dim3(WAVE), lds, st, tab,
+                                                           pl->P, rm, b0, on, grad_out, sc.partials, (unsigned)(first - b0),
+                                                           (unsigned)(last - first)));
+            PARO_HIP(hipGetLastError());
+            // the next launch reuses the scratch array: this one's partials are added up first
+            if ((rc = finalize_partials(sc, (int)(last - first), step < blocks ? sc.chunk_sums + n_sums : sumsq_out, st))) return rc;
+            ++n_sums;
+        } else {
+            PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false>), dim3((unsigned)grid), dim3(WAVE), lds, st, tab,
+                                                           pl->P, rm, b0, on, grad_out, sc.partials, 0u, 0u));
+            PARO_HIP(hipGetLastError());
+        }
+    }
+    if (sumsq_out && step < blocks) {
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.chunk_sums, n_sums, n_sums, sumsq_out);
+        PARO_HIP(hipGetLastError());
+    }
+    return PARO_OK;
+}
+
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own
 // chunk only (so that the ranks' values add up to the model's) - or, with norm_over_range, every
 // chunk of the update range: one sum per chunk, added in chunk order.
@@ -748,6 +866,8 @@ int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *co
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     const int own = paro::chunk_of_rank(pl, rank);
     const int64_t c0 = ob / pl->L, c1 = (ob + on) / pl->L;
+    if (layout == PARO_CHUNK && c1 - c0 > 1)
+        return do_reduce_range(pl, sc, ob, on, norm_over_range ? -1 : own, contrib, grad_out, sumsq_out, st);
     const bool per_chunk = sumsq_out && norm_over_range && c1 - c0 > 1;
     for (int64_t c = c0; c < c1; ++c) {
         SrcTable tab;
@@ -815,6 +935,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
         return do_adam(pl, sc, rank, a, grad_scratch, sumsq_scratch, p, m, v, dst, st);
     }
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
+    if (layout == PARO_CHUNK && !pl->any_no_decay && on > pl->L) return launch_fused_range(pl, sc, ob, on, contrib, a, p, m, v, dst, st);
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {
         SrcTable tab;
         int gl;
@@ -866,7 +987,7 @@ int static_scratch(Scratch *out) {
         g_static.lds_per_cu[dev] = lds;
         g_static.ptr[dev] = ptr;
     }
-    *out = Scratch{g_static.lds_per_cu[dev], g_static.ptr[dev], g_static.ptr[dev] + STATIC_PARTIALS,
+    *out = Scratch{g_static.lds_per_cu[dev], g_static.ptr[dev], STATIC_PARTIALS, g_static.ptr[dev] + STATIC_PARTIALS,
                    g_static.ptr[dev] + STATIC_PARTIALS + STATIC_LEVEL2, false};
     return PARO_OK;
 }

@@ -273,8 +273,13 @@ struct Lane4Loader {
 // (left to right), partials into X (left to right).  The first value of a run
 // and the first partial are copied, not added to zero (that would lose -0).
 // A thread folds Ld::kElems elements (4, or 8 when the wave takes two blocks).
-template <class Ld>
-__device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, int group_len, float *X) {
+// ord: which pointer of the table the k-th contribution is (InOrder: the k-th).
+struct InOrder {
+    __device__ __forceinline__ int next(int k) { return k; }
+};
+template <class Ld, class Order = InOrder>
+__device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, int group_len, float *X,
+                                      Order ord = Order()) {
     constexpr int NE = Ld::kElems;
     float A[NE];
     int pos = 0;
@@ -283,7 +288,7 @@ __device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, 
     for (int k0 = 0; k0 < P; k0 += B) {
         typename Ld::Raw raw[B];
         static_for<0, B>([&](auto b) {
-            if (k0 + b < P) ld.load(src, k0 + b, raw[b]);
+            if (k0 + b < P) ld.load(src, ord.next(k0 + b), raw[b]);
         });
         static_for<0, B>([&](auto b) {
             if (k0 + b < P) {
@@ -309,6 +314,77 @@ __device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, 
                 }
             }
         });
+    }
+}
+
+// Fold order of a chunk, walked inside the kernel: the pointer table is in rank order, and the
+// walk starts at the successor of the chunk's owner - the next local index of the next group -
+// goes round the group, then on to the next group (a plain ring: one group of P ranks).
+struct RingWalk {
+    int G, g, grp, loc, left;          // ranks per group, groups, current group, local index, ranks left in the group
+    __device__ __forceinline__ int next(int) {
+        const int r = grp * G + loc;
+        if (++loc == G) loc = 0;
+        if (--left == 0) {
+            left = G;
+            if (++grp == g) grp = 0;
+        }
+        return r;
+    }
+};
+
+// What a launch over several chunks of an update range needs to find an element's chunk and the
+// chunk's fold order.
+struct RangeMap {
+    int64_t L;            // elements of a chunk (a multiple of 8: a thread's 4 elements share their chunk)
+    double inv_L;
+    int first_chunk;      // the chunk that the range starts with
+    int G, g;             // the plan's groups; chunk c belongs to rank (group c % g, local index c / g)
+    int walk_G, walk_g;   // the fold's groups: the plan's, or one group of P ranks (ring)
+    int own;              // the chunk, counted from first_chunk, whose squares are added up; -1: every chunk
+};
+
+// Chunk (counted from the range's first) that element e of the range lies in.  One product in
+// fp64 is off by at most one from the quotient below 2^53.
+__device__ __forceinline__ int chunk_at(const RangeMap &rm, int64_t e) {
+    int c = (int)((double)e * rm.inv_L);
+    if ((int64_t)c * rm.L > e) --c;
+    if ((int64_t)(c + 1) * rm.L <= e) ++c;
+    return uniform(c);
+}
+
+__device__ __forceinline__ RingWalk walk_of(const RangeMap &rm, int c) {
+    c += rm.first_chunk;
+    const int oi = c / rm.g, oj = c - oi * rm.g;                     // the owner's local index and group
+    RingWalk w{rm.walk_G, rm.walk_g, 0, 0, rm.walk_G};
+    if (rm.walk_g == 1) {
+        w.loc = oj * rm.G + oi + 1;
+    } else {
+        w.loc = oi + 1;
+        w.grp = oj + 1 == rm.g ? 0 : oj + 1;
+    }
+    if (w.loc == w.G) w.loc = 0;
+    return w;
+}
+
+// The ordered fold of the thread's 4 elements of an update range of several chunks (arrays in shard
+// coordinates): e0 the block's first element, n the range's length.  Nearly every block lies inside
+// one chunk; where chunks meet inside a block, its lanes take turns, chunk by chunk.  Returns
+// whether the thread's elements count for the sum of squares.
+template <int DT>
+__device__ __forceinline__ bool fold_range(const RangeMap &rm, const SrcTable &src, int P, int64_t e0, int64_t n, float X[4]) {
+    Chunk4Loader<DT> ld{e0 + lane_id() * EPT};
+    const int64_t end = min(e0 + (int64_t)PIECE, n);
+    bool counts = false;
+    int c = chunk_at(rm, e0);
+#pragma unroll 1
+    for (;; ++c) {
+        const int64_t c_lo = (int64_t)c * rm.L, c_hi = c_lo + rm.L;
+        if (ld.e >= c_lo && ld.e < min(c_hi, n)) {
+            fold4(ld, src, P, rm.walk_G, X, walk_of(rm, c));
+            counts = rm.own < 0 || rm.own == c;
+        }
+        if (c_hi >= end) return counts;
     }
 }
 

@@ -1,0 +1,35 @@
+"""Update ranges of several chunks (optimizer state sharded inside the group, or not at all), chunk
+layout: one launch covers the whole range, blocks are counted from the range's start, and every chunk
+is folded in its own owner's order.  Sizes where that can go wrong: chunks shorter than a block (many
+chunks in one block), a block more or less than a chunk, chunk ends inside a block, padding."""
+import numpy as np
+import pytest
+
+import oracle as orc
+import workloads as wl
+from harness import flat_inputs, hp_dict, np_of, run_rank
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [8, 24, 248, 256, 264, 1000, 65544])
+@pytest.mark.parametrize("P,G,strategy,sched,dtype", [
+    (8, 2, "III", orc.HORING, wl.BF16), (6, 3, "NNN", orc.HRING, wl.F32), (8, 4, "NNI", orc.RING, wl.F16),
+    (5, 5, "NNN", orc.RING, wl.BF16), (24, 2, "III", orc.HORING, wl.BF16), (4, 1, "III", orc.RING, wl.BF16)])
+def test_every_chunk_of_the_range_in_its_own_order(paro, P, G, strategy, sched, dtype, L):
+    total = P * L - (L + 3 if L > 8 and strategy == "NNN" else 3)           # the last chunk(s) end in padding
+    lay = orc.layout(P, G, [total])
+    assert lay.L == (L if total > P * (L - 8) else lay.L)
+    pl = paro.paro_plan(P, G, strategy, [total], sched=sched, grad_dtype=[dtype])
+    n = P * lay.L
+    dev, host = flat_inputs(P, n, 40 + L, dtype=dtype)
+    for t, h in zip(dev, host):
+        t[total:] = 0
+        h[total:] = 0
+    state = [np_of(t) for t in wl.master_state(n, 41 + L)]
+    for a in state:
+        a[total:] = 0
+    for rank in sorted({0, P // 2, P - 1}):
+        for max_norm in (0.0, 0.01):                                        # one sweep; two sweeps, clipped
+            run_rank(paro, pl, lay, strategy, sched, rank, dev, host, state, hp_dict(P, max_norm=max_norm), 7,
+                     check_unfused=max_norm > 0)
