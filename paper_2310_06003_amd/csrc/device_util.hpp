@@ -88,8 +88,11 @@ constexpr int WAVE = 64;              // threads of a block: every sweep kernel 
 constexpr int EPT = 4;                // elements per thread
 constexpr int PIECE = WAVE * EPT;     // elements per block
 constexpr int TILE = PARO_TILE;       // granularity of the plan's per-block table
-constexpr int FINALIZE_TPB = 256;     // threads of the kernel that adds the partial sums
-constexpr int FINALIZE_CHUNK = 2048;  // partials per block in its first level
+constexpr int FINALIZE_TPB = 1024;    // threads of the kernel that adds the partial sums
+constexpr int FINALIZE_CHUNK = 8192;  // partials per block in its first level: eight per thread, all in flight
+constexpr int NORM_DIRECT_PARTIALS = 2048;      // partials that every wave of sweep 2 adds up itself
+constexpr int NORM_SLICES = 8;                  // else: slice sums that it does (one scalar load) ...
+constexpr int NORM_SLICES_PARTIALS = 131072;    // ... up to so many partials (33.5 M elements)
 static_assert(TILE == PIECE, "the per-tile table has one entry per block");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

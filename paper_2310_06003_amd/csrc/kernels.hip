@@ -52,11 +52,33 @@
 namespace {
 
 // ---------------------------------------------------------------------- Adam
+// The global sum of squares as sweep 2 gets it: n sums to be added up in a fixed order, the same in
+// every wave.  Lanes hold the result.
+__device__ __forceinline__ double norm_total(const double *__restrict__ sums, int n) {
+    if (n == 1) return sums[0];
+    if (n == NORM_SLICES) {                                        // one scalar load
+        double s = sums[0];
+#pragma unroll
+        for (int k = 1; k < NORM_SLICES; ++k) s += sums[k];
+        return s;
+    }
+    double acc = 0.0;
+    for (int k0 = lane_id(); k0 < n; k0 += 8 * WAVE) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = (k0 + u * WAVE < n) ? sums[k0 + u * WAVE] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += x[u];
+    }
+    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, WAVE);
+    return acc;
+}
+
 // sc = grad_scale * clip coefficient, from the global sum of squares.
-__device__ __forceinline__ float scale_from_norm(const AdamConsts &a, const double *total_sumsq) {
+__device__ __forceinline__ float scale_from_norm(const AdamConsts &a, double total_sumsq) {
     double coef = 1.0;
     if (a.max_norm > 0.0f) {
-        const double norm = (double)a.grad_scale * sqrt(*total_sumsq);
+        const double norm = (double)a.grad_scale * sqrt(total_sumsq);
         const double c = (double)a.max_norm / (norm + 1e-6);
         coef = c < 1.0 ? c : 1.0;
     }
@@ -284,15 +306,14 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_finalize(const double *__restr
 }
 
 // Sweep 2: Adam on the stored gradient, optionally packing the low-precision parameters.
-// MASK: some tensors are exempt from weight decay.
+// MASK: some tensors are exempt from weight decay.  The global sum of squares comes as n_sums sums
+// (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
+// the total to sumsq_out unless that is null.
 template <bool PACK, bool MASK>
-__global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double *__restrict__ total_sumsq,
-                                                const float *__restrict__ g, float *__restrict__ p,
+__global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double *__restrict__ sums, int n_sums,
+                                                double *__restrict__ sumsq_out, const float *__restrict__ g, float *__restrict__ p,
                                                 float *__restrict__ m, float *__restrict__ v,
                                                 uint16_t *__restrict__ dst, int64_t n, const TensorMap tm) {
-    // an overflowed (non-finite) gradient makes its sum of squares non-finite: the whole step is skipped
-    if (a.skip_nonfinite && !isfinite(*total_sumsq)) return;
-    const float sc = scale_from_norm(a, total_sumsq);
     const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
     if (e0 >= n) return;
     bool decays[4] = {true, true, true, true};
@@ -302,13 +323,24 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
         pc = piece_of(tm, e0, n);
         if (pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
     }
+    u32x4 G;
+    State4 s;
+    if (e < n) {
+        G = ld_nt(reinterpret_cast<const u32x4 *>(g + e));
+        s = load_state4(p, m, v, e);
+    }
+    float sc = a.grad_scale;
+    if (n_sums > 0) {                                                                      // the whole wave
+        const double total = norm_total(sums, n_sums);
+        if (sumsq_out && blockIdx.x == 0 && lane_id() == 0) *sumsq_out = total;
+        // an overflowed (non-finite) gradient makes its sum of squares non-finite: the whole step is skipped
+        if (a.skip_nonfinite && !isfinite(total)) return;
+        sc = scale_from_norm(a, total);
+    }
     if (e >= n) return;
-    const unsigned elems = piece_elems(e0, n);
-    const u32x4 G = ld_nt(reinterpret_cast<const u32x4 *>(g + e));
-    const State4 s = load_state4(p, m, v, e);
     if (MASK) decay_flags(tm, pc, loc, decays);
     const float gg[4] = {__uint_as_float(G.x), __uint_as_float(G.y), __uint_as_float(G.z), __uint_as_float(G.w)};
-    update4<PACK>(a, sc, decays, gg, s, p, m, v, dst, e0, elems);
+    update4<PACK>(a, sc, decays, gg, s, p, m, v, dst, e0, piece_elems(e0, n));
 }
 
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
@@ -470,9 +502,15 @@ struct Scratch {
     bool plan_tables;      // the plan's device tables (offset tables, per-tile tables) exist
 };
 
+// Room for the second-level sums of n_part partials.
+constexpr int64_t level2_sums(int64_t n_part) {
+    const int64_t n = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
+    return n < NORM_SLICES ? NORM_SLICES : n;
+}
+
 Scratch plan_scratch(const paro_plan_t *pl) {
     double *level2 = pl->dev.partials + pl->dev.n_partials;
-    const int64_t n_level2 = (pl->dev.n_partials + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
+    const int64_t n_level2 = level2_sums(pl->dev.n_partials);
     return Scratch{pl->dev.lds_per_cu, pl->dev.partials, pl->dev.n_partials, level2, level2 + n_level2, true};
 }
 
@@ -514,7 +552,7 @@ int fill_tables(const paro_plan_t *pl, paro_device_tables &d) {
     int64_t n_part = (piece_count(on) + 7) & ~(int64_t)7;
     if (n_part < PARO_MIN_PARTIALS) n_part = PARO_MIN_PARTIALS;
     d.n_partials = n_part;
-    const int64_t n_level2 = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
+    const int64_t n_level2 = level2_sums(n_part);
     PARO_HIP(hipMalloc(reinterpret_cast<void **>(&d.partials), (n_part + n_level2 + PARO_MAX_RANKS) * sizeof(double)));
     return PARO_OK;
 }
@@ -801,9 +839,37 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     return PARO_OK;
 }
 
-// Adds the n_part partial sums a sweep-1 launch left in the scratch array into *out (device).
-int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st) {
-    if (n_part > 2 * FINALIZE_CHUNK) {       // two levels: slices of 2048 partials, then their sums
+// The sum of squares as sweep 1 leaves it for sweep 2: n sums on the device, whose total belongs in *out.
+// out null: the one sum is the total, in its place already.
+struct NormSums {
+    const double *sums;
+    int n;
+    double *out;
+};
+
+// Adds the n_part partial sums a sweep-1 launch left in the scratch array into *out (device) - or, with
+// `rest`, only as far as sweep 2 goes on by itself, and *rest says from where.  Every kernel more in this
+// chain of short dependent ones costs 2-3 us of a step; what a wave of sweep 2 adds up beside its state
+// loads is hidden while it is little.  Whole clipped steps at P = 8, bf16, with the chain of up to two
+// small kernels that ended in one scalar, and now:
+//   0.5 M elements (1954 partials, added up by every wave)   12.9 -> 10.4 us
+//   0.75 M (2930; eight slice sums)                          13.7 -> 13.3; added up by every wave 16.5
+//   1.5 M (5860; eight slice sums)                           21.7 -> 19.6
+//   16.8 M (65536; eight slice sums)                        135.7 -> 133.7
+// Sixteen slice sums fetched one after the other took back all of it at 16 M; eight are one scalar load.
+int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st, NormSums *rest = nullptr) {
+    if (rest && n_part <= NORM_DIRECT_PARTIALS) {
+        *rest = NormSums{sc.partials, n_part, out};
+        return PARO_OK;
+    }
+    if (rest && n_part <= NORM_SLICES_PARTIALS) {
+        const int chunk = (n_part + NORM_SLICES - 1) / NORM_SLICES;
+        hipLaunchKernelGGL(k_finalize, dim3(NORM_SLICES), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, chunk, sc.level2);
+        PARO_HIP(hipGetLastError());
+        *rest = NormSums{sc.level2, NORM_SLICES, out};
+        return PARO_OK;
+    }
+    if (n_part > 2 * FINALIZE_CHUNK) {        // two levels: slices of FINALIZE_CHUNK partials, then their sums
         const int nb = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
         hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, FINALIZE_CHUNK, sc.level2);
         PARO_HIP(hipGetLastError());
@@ -812,6 +878,18 @@ int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st
         hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, n_part, out);
     }
     PARO_HIP(hipGetLastError());
+    if (rest) *rest = NormSums{out, 1, nullptr};
+    return PARO_OK;
+}
+
+// ... and the sums of several launches, in sc.chunk_sums.
+int finalize_sums(const Scratch &sc, int n, double *out, hipStream_t st, NormSums *rest) {
+    if (rest) {
+        *rest = NormSums{sc.chunk_sums, n, out};
+        return PARO_OK;
+    }
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.chunk_sums, n, n, out);
+    PARO_HIP(hipGetLastError());
     return PARO_OK;
 }
 
@@ -819,7 +897,7 @@ int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st
 // the whole range and the scratch array is too small for its partial sums, one for each piece that fits.
 // own >= 0: the sum of squares of that chunk alone.
 int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_t on, int own, const void *const *contrib,
-                    float *grad_out, double *sumsq_out, hipStream_t st) {
+                    float *grad_out, double *sumsq_out, hipStream_t st, NormSums *rest) {
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, own, contrib, &tab);
@@ -841,33 +919,32 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
                                                            (unsigned)(last - first)));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
-            if ((rc = finalize_partials(sc, (int)(last - first), step < blocks ? sc.chunk_sums + n_sums : sumsq_out, st))) return rc;
-            ++n_sums;
+            if (step < blocks)
+                rc = finalize_partials(sc, (int)(last - first), sc.chunk_sums + n_sums++, st);
+            else
+                rc = finalize_partials(sc, (int)(last - first), sumsq_out, st, rest);
+            if (rc) return rc;
         } else {
             PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false>), dim3((unsigned)grid), dim3(WAVE), lds, st, tab,
                                                            pl->P, rm, b0, on, grad_out, sc.partials, 0u, 0u));
             PARO_HIP(hipGetLastError());
         }
     }
-    if (sumsq_out && step < blocks) {
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.chunk_sums, n_sums, n_sums, sumsq_out);
-        PARO_HIP(hipGetLastError());
-    }
-    return PARO_OK;
+    return sumsq_out && step < blocks ? finalize_sums(sc, n_sums, sumsq_out, st, rest) : PARO_OK;
 }
 
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own
 // chunk only (so that the ranks' values add up to the model's) - or, with norm_over_range, every
-// chunk of the update range: one sum per chunk, added in chunk order.
+// chunk of the update range: one sum per chunk, added in chunk order.  rest: sweep 2 finishes the norm.
 int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *const *contrib, int layout, float *grad_out,
-              double *sumsq_out, bool norm_over_range, hipStream_t st) {
+              double *sumsq_out, bool norm_over_range, hipStream_t st, NormSums *rest = nullptr) {
     int rc;
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     const int own = paro::chunk_of_rank(pl, rank);
     const int64_t c0 = ob / pl->L, c1 = (ob + on) / pl->L;
     if (layout == PARO_CHUNK && c1 - c0 > 1)
-        return do_reduce_range(pl, sc, ob, on, norm_over_range ? -1 : own, contrib, grad_out, sumsq_out, st);
+        return do_reduce_range(pl, sc, ob, on, norm_over_range ? -1 : own, contrib, grad_out, sumsq_out, st, rest);
     const bool per_chunk = sumsq_out && norm_over_range && c1 - c0 > 1;
     for (int64_t c = c0; c < c1; ++c) {
         SrcTable tab;
@@ -878,28 +955,25 @@ int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *co
             const int n_part = launch_reduce<true>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this chunk's partials are added up first
-            if ((rc = finalize_partials(sc, n_part, per_chunk ? sc.chunk_sums + (c - c0) : sumsq_out, st))) return rc;
+            rc = per_chunk ? finalize_partials(sc, n_part, sc.chunk_sums + (c - c0), st)
+                           : finalize_partials(sc, n_part, sumsq_out, st, rest);
+            if (rc) return rc;
         } else {
             launch_reduce<false>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
             PARO_HIP(hipGetLastError());
         }
     }
-    if (per_chunk) {
-        const int nc = (int)(c1 - c0);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.chunk_sums, nc, nc, sumsq_out);
-        PARO_HIP(hipGetLastError());
-    }
-    return PARO_OK;
+    return per_chunk ? finalize_sums(sc, (int)(c1 - c0), sumsq_out, st, rest) : PARO_OK;
 }
 
 template <bool PACK>
 int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad,
-                const double *total_sumsq, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
+                const NormSums &norm, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     if (!pl->any_no_decay) {
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_WAVES_PER_CU);
-        hipLaunchKernelGGL((k_adam4<PACK, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a, total_sumsq, grad, p, m, v,
+        hipLaunchKernelGGL((k_adam4<PACK, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out, grad, p, m, v,
                            dst, on, map_for(pl, sc, ob, false));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
@@ -907,7 +981,7 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {      // chunk by chunk: each has its own per-tile table
         const int64_t lo = c * pl->L - ob;
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_MASK_WAVES_PER_CU);
-        hipLaunchKernelGGL((k_adam4<PACK, true>), dim3(piece_grid(pl->L)), dim3(WAVE), lds, st, a, total_sumsq, grad + lo,
+        hipLaunchKernelGGL((k_adam4<PACK, true>), dim3(piece_grid(pl->L)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out, grad + lo,
                            p + lo, m + lo, v + lo, dst ? dst + lo : nullptr, pl->L, map_for(pl, sc, c * pl->L, true));
         PARO_HIP(hipGetLastError());
     }
@@ -915,9 +989,9 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
 }
 
 int do_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad,
-            const double *total_sumsq, float *p, float *m, float *v, uint16_t *dst /* nullable: no pack */, hipStream_t st) {
-    return dst ? launch_adam<true>(pl, sc, rank, a, grad, total_sumsq, p, m, v, dst, st)
-               : launch_adam<false>(pl, sc, rank, a, grad, total_sumsq, p, m, v, dst, st);
+            const NormSums &norm, float *p, float *m, float *v, uint16_t *dst /* nullable: no pack */, hipStream_t st) {
+    return dst ? launch_adam<true>(pl, sc, rank, a, grad, norm, p, m, v, dst, st)
+               : launch_adam<false>(pl, sc, rank, a, grad, norm, p, m, v, dst, st);
 }
 
 // The launches of the fused step, arguments already checked: two sweeps when the update waits for
@@ -931,8 +1005,9 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
     uint16_t *dst = dst_base + so;
     if (a.max_norm > 0.0f || a.skip_nonfinite) {
         // the norm this rank can form on its own: over everything it updates (its update range)
-        if ((rc = do_reduce(pl, sc, rank, contrib, layout, grad_scratch, sumsq_scratch, true, st))) return rc;
-        return do_adam(pl, sc, rank, a, grad_scratch, sumsq_scratch, p, m, v, dst, st);
+        NormSums norm{nullptr, 0, nullptr};
+        if ((rc = do_reduce(pl, sc, rank, contrib, layout, grad_scratch, sumsq_scratch, true, st, &norm))) return rc;
+        return do_adam(pl, sc, rank, a, grad_scratch, norm, p, m, v, dst, st);
     }
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     if (layout == PARO_CHUNK && !pl->any_no_decay && on > pl->L) return launch_fused_range(pl, sc, ob, on, contrib, a, p, m, v, dst, st);
@@ -955,7 +1030,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
 // elements (one per block of 256), followed by the second-level sums.  Every device the library
 // runs on holds its own copy of this array, at its own address, until the process ends.
 constexpr int64_t STATIC_PARTIALS = PARO_STATIC_MAX_CHUNK / PIECE;
-constexpr int64_t STATIC_LEVEL2 = (STATIC_PARTIALS + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
+constexpr int64_t STATIC_LEVEL2 = level2_sums(STATIC_PARTIALS);
 static __device__ __align__(256) double scratch[STATIC_PARTIALS + STATIC_LEVEL2 + PARO_MAX_RANKS];
 
 constexpr int MAX_DEVICES = 64;
@@ -1038,7 +1113,9 @@ int paro_adam_shard(paro_plan_t *pl, int rank, const paro_adam_t *hp, const floa
         paro_pack_slot(pl, rank, &dl, &so, &sl);
         dst = dst_base + so;
     }
-    return do_adam(pl, plan_scratch(pl), rank, a, grad, total_sumsq, p, m, v, dst, static_cast<hipStream_t>(stream));
+    const bool needs_norm = a.max_norm > 0.0f || a.skip_nonfinite;
+    return do_adam(pl, plan_scratch(pl), rank, a, grad, NormSums{total_sumsq, needs_norm ? 1 : 0, nullptr}, p, m, v, dst,
+                   static_cast<hipStream_t>(stream));
 }
 
 int paro_pack_params(paro_plan_t *pl, int rank, const float *p, uint16_t *dst_base, void *stream) {
