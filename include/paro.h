@@ -49,14 +49,16 @@
  * library owns the plan: its host tables, and - created on the first device
  * call, on the device that is current then - device memory for the tensor
  * offset tables and a scratch array of partial sums (8 bytes per 256 elements
- * of an update range); the first call for a rank that uses the tensor layout or a
- * weight-decay mask adds a per-tile table for each chunk of that rank's update
- * range (16 bytes per 256 elements, built when the chunk has at most 4 Mi
- * tiles, or at most PARO_TILE_TABLE_MAX_TILES when that environment variable
- * is set; without it the kernels search; PARO_PAIR_MIN_BLOCKS, also read at
- * every call, makes sweep 1 of the tensor layout give a wave two blocks from
- * that many blocks on, whatever the tensor list, instead of from the built-in
- * size on for lists of many small tensors - both exist for tests).  Those first calls allocate and copy
+ * of an update range; up to twice that for many small tensors); the first call
+ * for a rank that uses the tensor layout adds a list of pieces, the first that
+ * needs a weight-decay mask block by block (sweep 2, or the chunk layout) a
+ * per-tile table, for each chunk of that rank's update range (16 bytes per 256
+ * elements each, the list up to twice that; built when the chunk has at most
+ * 4 Mi tiles, or at most PARO_TILE_TABLE_MAX_TILES when that environment
+ * variable is set; without them the kernels search; PARO_PAIR_MIN_BLOCKS, also
+ * read at every call, makes sweep 1 of the tensor layout with up to 4 ranks give
+ * a wave two blocks from that many blocks on instead of from the built-in size
+ * on - both exist for tests).  Those first calls allocate and copy
  * synchronously - make them outside any stream capture; every later call only
  * enqueues kernels and can be captured.  Device
  * functions only enqueue work on `stream` (a hipStream_t passed as void*; NULL =

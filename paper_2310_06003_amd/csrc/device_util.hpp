@@ -29,7 +29,7 @@ namespace {
 #define PARO_BATCH 16               // contributions loaded before the first is consumed
 #endif
 #ifndef PARO_LANE_BATCH
-#define PARO_LANE_BATCH 4          // ... in a block with a tensor boundary inside (element loads; more costs registers for nothing)
+#define PARO_LANE_BATCH 2          // ... in a block that a wave takes element by element (each has its own pointer: registers)
 #endif
 // One-wave blocks in flight per compute unit (0 = as many as fit).  The mixed read/write sweeps
 // run faster with fewer requests outstanding than the registers would allow.  For the fold the
@@ -48,22 +48,18 @@ namespace {
 #ifndef PARO_ADAM_MASK_WAVES_PER_CU
 #define PARO_ADAM_MASK_WAVES_PER_CU 16   // with a decay mask: a table look-up per wave to hide as well
 #endif
-// Sweep 1 in the tensor layout.  What decides is the list: a chunk made of a few large tensors
-// ("large": at least PARO_DENSE_BLOCKS_PER_TENSOR blocks per tensor piece in the chunk, on average)
-// behaves like the chunk layout - its look-ups hit the scalar cache - and keeps the chunk layout's
-// shape and budget.  A chunk cut into many small pieces has waves that spend part of their life on
-// look-ups with no data in flight: it is launched without the throttle, and with at most
-// PARO_PAIR_MAX_RANKS contributions and at least PARO_PAIR_MIN_BLOCKS blocks a wave takes two
-// consecutive blocks under a budget twice the chunk layout's (see k_reduce4t; the two shapes cross
-// near 50 M elements: a smaller launch wants as many waves as it can get).
+// The tensor layout.  What decides is the list: a chunk made of a few large tensors ("large": at least
+// PARO_DENSE_BLOCKS_PER_TENSOR blocks per tensor piece in the chunk, on average) behaves like the chunk
+// layout - its look-ups hit the scalar cache - and keeps the chunk layout's budget.  A chunk cut into
+// many small pieces has waves that spend part of their life on look-ups with no data in flight: it is
+// launched without the throttle (the single sweep, whose waves load their state as well, only in
+// chunks of fewer than PARO_LARGE_TILES blocks).  With at most PARO_PAIR_MAX_RANKS contributions and at
+// least PARO_PAIR_MIN_BLOCKS blocks a wave takes two consecutive blocks (see k_reduce4t).
 #ifndef PARO_PAIR_MAX_RANKS
-#define PARO_PAIR_MAX_RANKS 8
+#define PARO_PAIR_MAX_RANKS 4
 #endif
 #ifndef PARO_PAIR_MIN_BLOCKS
-#define PARO_PAIR_MIN_BLOCKS 196608
-#endif
-#ifndef PARO_FOLD_T_LOADS_PER_CU
-#define PARO_FOLD_T_LOADS_PER_CU 448
+#define PARO_PAIR_MIN_BLOCKS 16384
 #endif
 #ifndef PARO_DENSE_BLOCKS_PER_TENSOR
 #define PARO_DENSE_BLOCKS_PER_TENSOR 1024
@@ -71,11 +67,20 @@ namespace {
 #ifndef PARO_FOLD_TM_LOADS_PER_CU
 #define PARO_FOLD_TM_LOADS_PER_CU 100000
 #endif
-#ifndef PARO_FUSED_T_LOADS_PER_CU      // the single sweep over many small tensors
-#define PARO_FUSED_T_LOADS_PER_CU 100000
+#ifndef PARO_LARGE_TILES
+#define PARO_LARGE_TILES 131072
 #endif
 #ifndef PARO_MIN_WAVES_PER_CU
 #define PARO_MIN_WAVES_PER_CU 8     // the throttle never goes below this
+#endif
+#ifndef PARO_PACE_SLEEP
+#define PARO_PACE_SLEEP 4           // units of 64 clocks between two loads of a paced fold
+#endif
+#ifndef PARO_PACE_MIN_BLOCKS
+#define PARO_PACE_MIN_BLOCKS 131072 // blocks of a launch from which on it is paced
+#endif
+#ifndef PARO_SPLIT_MAX
+#define PARO_SPLIT_MAX 16           // a tile with up to so many tensors inside is cut into pieces
 #endif
 #ifndef PARO_HOP_WAVES_PER_CU
 #define PARO_HOP_WAVES_PER_CU 0
@@ -103,6 +108,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // only ever indexed with wave-uniform indices, i.e. read with scalar loads.
 struct SrcTable {
     const void *p[PARO_MAX_RANKS];
+    int paced;       // the chunk layout's loads go out one by one, with a pause in between
 };
 
 struct AdamConsts {
@@ -121,6 +127,8 @@ struct TensorMap {
     int64_t total;              // Psi
     int64_t begin;              // flat index of the launch's element 0
     const paro_tile_info *tile_tab;   // the per-tile table of the launch's chunk, or null
+    const paro_piece_info *pieces;    // [n_pieces] the chunk's pieces, or null
+    unsigned n_pieces;
 };
 
 // Lane of the thread in its wave (the sweep kernels run in one-wave blocks).
@@ -173,6 +181,12 @@ template <class V>
 __device__ __forceinline__ V ld_nt(const V *p) { return __builtin_nontemporal_load(p); }
 template <class V>
 __device__ __forceinline__ V ld_nt(const __attribute__((address_space(1))) V *p) { return __builtin_nontemporal_load(p); }
+
+template <bool NT, class Ptr>
+__device__ __forceinline__ auto ld_once(Ptr p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
 
 // ---- stores through per-wave buffer descriptors.  A block's stores to one array go through a
 // descriptor that covers exactly the block's piece of it (a wave-uniform base address and a byte

@@ -124,15 +124,29 @@ __device__ __forceinline__ State4 load_state4(const float *p, const float *m, co
 }
 
 // Adam on the thread's 4 elements; state and (optionally) the low-precision copy written back.
-template <bool PACK>
+// PART: only elements [lo, hi) of the 4 are the thread's (the others are some other wave's).
+template <bool PACK, bool PART = false>
 __device__ __forceinline__ void update4(const AdamConsts &a, float sc, const bool decays[4], const float gg[4],
                                         const State4 &s, float *p, float *m, float *v, uint16_t *dst, int64_t e0,
-                                        unsigned elems) {
+                                        unsigned elems, int lo = 0, int hi = 4) {
     float pp[4] = {__uint_as_float(s.p.x), __uint_as_float(s.p.y), __uint_as_float(s.p.z), __uint_as_float(s.p.w)},
           mm[4] = {__uint_as_float(s.m.x), __uint_as_float(s.m.y), __uint_as_float(s.m.z), __uint_as_float(s.m.w)},
           vv[4] = {__uint_as_float(s.v.x), __uint_as_float(s.v.y), __uint_as_float(s.v.z), __uint_as_float(s.v.w)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) adam1(a, sc, decays[i], gg[i], pp[i], mm[i], vv[i]);
+    if (PART && (lo > 0 || hi < 4)) {
+        const int64_t e = e0 + lane_id() * EPT;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i >= lo && i < hi) {
+                p[e + i] = pp[i];
+                m[e + i] = mm[i];
+                v[e + i] = vv[i];
+                if (PACK) dst[e + i] = (uint16_t)pack2_lowp(pp[i], 0.0f, a.pack_dtype);
+            }
+        }
+        return;
+    }
     constexpr int ST = PARO_POL_STATE_ST;
     buf_store16<ST>(as_u32x4(pp[0], pp[1], pp[2], pp[3]), wave_buffer(p + e0, elems * 4), lane_id() * 16);
     buf_store16<ST>(as_u32x4(mm[0], mm[1], mm[2], mm[3]), wave_buffer(m + e0, elems * 4), lane_id() * 16);
@@ -228,57 +242,74 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTable src, int P, co
     }
 }
 
-// Sweep 1, tensor layout: one block of 256 elements starting at e0 < n.  Every lane of the wave takes part.
-template <bool SUMSQ, int KB>
-__device__ __forceinline__ void reduce_piece_t(const TensorMap &tm, const Piece &pc, const SrcTable &src, int P,
-                                               int group_len, int64_t n, int64_t e0, float *g, double &acc) {
-    const int64_t e = e0 + lane_id() * EPT;
-    Located loc;
-    if (pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
-    if (e < n) {
-        const unsigned elems = piece_elems(e0, n);
-        float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};           // padding: the sum of zeros
-        if (pc.tensor != -2) fold_tensors<KB>(pc, loc, src, P, group_len, X);
-        store_g4(g, e0, elems, X);
+// Sweep 1, tensor layout: one piece of the launch.  Every lane of the wave takes part.
+template <bool SUMSQ, int KB, bool NT>
+__device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, const SrcTable &src, int P, int group_len,
+                                           int64_t n, float *g, double &acc) {
+    const int64_t e = c.e0 + lane_id() * EPT;
+    float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};               // padding: the sum of zeros
+    if (c.whole) {
+        Located loc;
+        if (c.pc.tensor == -1) locate4(tm, c.pc.seg, tm.begin + c.e0, lane_id() * EPT, loc);     // the whole wave
+        if (e >= n) return;
+        if (c.pc.tensor != -2) fold_tensors<NT, KB>(c.pc, loc, src, P, group_len, X);
+        store_g4(g, c.e0, piece_elems(c.e0, n), X);
         if (SUMSQ) acc += sumsq4(X);
-    }
-}
-
-// A wave takes PPW consecutive blocks.  PPW = 2 is for few contributions (P <= 8) over many small tensors: where both
-// blocks lie inside one tensor - the usual case - the wave folds them as one stream of 512
-// elements per contribution: one look-up and twice the bytes in flight per wave; the cache line
-// that the two blocks share (a block does not start on a line inside its tensor) is fetched once.
-// KB: contributions loaded before the first is consumed (8 when launched for P <= 8 only: fewer
-// registers, more waves).
-template <bool SUMSQ, int PPW, int KB>
-__global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTable src, int P, int group_len, int64_t n,
-                                                   float *__restrict__ g, double *__restrict__ partials,
-                                                   const TensorMap tm) {
-    const int64_t e0 = (int64_t)blockIdx.x * (PPW * PIECE);
-    double acc = 0.0;
-    if (e0 < n) {                                            // wave-uniform
-        bool done = false;
-        if constexpr (PPW == 2) {
-            if (e0 + 2 * PIECE <= n) {                       // two whole blocks
-                const Piece pa = piece_of(tm, e0, n), pb = piece_of(tm, e0 + PIECE, n);
-                if (pa.tensor >= 0 && pb.tensor == pa.tensor) {                         // ... inside one tensor
-                    float X[8];
-                    fold_tensor_pair(pa, src, P, group_len, X);
-                    const wave_buf out = wave_buffer(g + e0, 2 * PIECE * 4);
-                    buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), out, lane_id() * 16);
-                    buf_store16<PARO_POL_G_ST>(as_u32x4(X[4], X[5], X[6], X[7]), out, PIECE * 4 + lane_id() * 16);
-                    if (SUMSQ) acc = sumsq4(X) + sumsq4(X + 4);
-                    done = true;
+    } else if (c.a < c.b) {
+        if (c.pc.tensor != -2) fold_part(c, src, P, group_len, X);
+        if (c.a == 0 && c.b == EPT) {
+            store_g4(g, c.e0, piece_elems(c.e0, n), X);
+            if (SUMSQ) acc += sumsq4(X);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i >= c.a && i < c.b) {
+                    g[e + i] = X[i];
+                    if (SUMSQ) acc += (double)X[i] * (double)X[i];
                 }
             }
         }
-        if (!done) {                                         // block by block (one copy of the code: no unrolling)
+    }
+}
+
+// A wave takes PPW consecutive pieces.  PPW = 2 is for few contributions (P <= 4): where both are whole
+// blocks that lie inside one tensor - the usual case - the wave folds them as one stream of 512 elements
+// per contribution: one look-up and twice the bytes in flight per wave.  Whole clipped steps, one and two
+// blocks per wave: P = 2, 31 M elements of tensors of 1 to 65536: 216 and 205 us; P = 4, 10 M elements of a
+// Llama-like list 73.4 and 70.0 us; at P = 8 the other way round (69 M elements: 457 and 476 us).
+// KB: contributions loaded before the first is consumed (8 when launched for P <= 8 only: fewer
+// registers, more waves).  NT: the list's blocks start on cache lines.
+// What bounds it: HBM, behind two dependent look-ups per wave (the piece, then the P pointers).  Taken one
+// by one - pointer of the table, pointer of the tensor, a branch on its alignment, the load - the second
+// was P round trips to the scalar cache in a row; now all pointers of a batch are fetched together and the
+// loads are straight-line code.  Sweep 1 over 10 000 tensors of 1 to 65536 elements (P = 8, 174 MB): 49.8
+// -> 29 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
+// (290 MB): 113 -> 86 us.
+template <bool SUMSQ, int PPW, int KB, bool NT>
+__global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTable src, int P, int group_len, int64_t n,
+                                                   float *__restrict__ g, double *__restrict__ partials,
+                                                   const TensorMap tm) {
+    const int64_t i0 = (int64_t)blockIdx.x * PPW;
+    double acc = 0.0;
+    bool done = false;
+    if constexpr (PPW == 2) {
+        Piece pc;
+        int64_t e0;
+        if (pair_of(tm, i0, n, &pc, &e0)) {                  // two whole blocks inside one tensor
+            float X[8];
+            fold_tensor_pair<NT>(pc, src, P, group_len, X);
+            const wave_buf out = wave_buffer(g + e0, 2 * PIECE * 4);
+            buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), out, lane_id() * 16);
+            buf_store16<PARO_POL_G_ST>(as_u32x4(X[4], X[5], X[6], X[7]), out, PIECE * 4 + lane_id() * 16);
+            if (SUMSQ) acc = sumsq4(X) + sumsq4(X + 4);
+            done = true;
+        }
+    }
+    if (!done) {                                             // piece by piece (one copy of the code: no unrolling)
 #pragma unroll 1
-            for (int j = 0; j < PPW; ++j) {
-                const int64_t ej = e0 + (int64_t)j * PIECE;
-                if (ej < n)
-                    reduce_piece_t<SUMSQ, KB>(tm, piece_of(tm, ej, n), src, P, group_len, n, ej, g, acc);
-            }
+        for (int j = 0; j < PPW; ++j) {
+            const Cut c = cut_of(tm, i0 + j, n);
+            if (c.e0 < n) reduce_cut<SUMSQ, KB, NT>(tm, c, src, P, group_len, n, g, acc);
         }
     }
     if (SUMSQ) {
@@ -345,26 +376,42 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
 
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
 // reduced gradient never goes to memory.  TENSORS: contributions are per-tensor gradients; else
-// arrays in shard coordinates of dtype DT.
-template <bool TENSORS, int DT, bool MASK>
+// arrays in shard coordinates of dtype DT.  NT: as for k_reduce4t.
+template <bool TENSORS, int DT, bool MASK, bool NT>
 __global__ __launch_bounds__(WAVE) void k_fused4(const SrcTable src, int P, int group_len, int64_t n,
                                                  const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
                                                  float *__restrict__ v, uint16_t *__restrict__ dst,
                                                  const TensorMap tm) {
-    const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
-    if (e0 >= n) return;
     Piece pc;
     Located loc;
-    if (TENSORS || MASK) {
-        pc = piece_of(tm, e0, n);
-        if (pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
+    int64_t e0 = block_first();
+    if constexpr (TENSORS) {
+        const Cut c = cut_of(tm, blockIdx.x, n);
+        if (c.e0 >= n) return;
+        if (!c.whole) {
+            if (c.a >= c.b) return;
+            const State4 s = load_state4(p, m, v, c.e0 + lane_id() * EPT);
+            float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (c.pc.tensor != -2) fold_part(c, src, P, group_len, X);
+            const bool d = !MASK || c.pc.tensor < 0 || tm.no_decay[c.pc.tensor] == 0;
+            const bool decays[4] = {d, d, d, d};
+            update4<true, true>(a, a.grad_scale, decays, X, s, p, m, v, dst, c.e0, piece_elems(c.e0, n), c.a, c.b);
+            return;
+        }
+        e0 = c.e0;
+        pc = c.pc;
+    } else {
+        if (e0 >= n) return;
+        if (MASK) pc = piece_of(tm, e0, n);
     }
+    const int64_t e = e0 + lane_id() * EPT;
+    if ((TENSORS || MASK) && pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
     if (e >= n) return;
     const unsigned elems = piece_elems(e0, n);
     const State4 s = load_state4(p, m, v, e);
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if constexpr (TENSORS) {
-        if (pc.tensor != -2) fold_tensors(pc, loc, src, P, group_len, X);
+        if (pc.tensor != -2) fold_tensors<NT>(pc, loc, src, P, group_len, X);
     } else {
         Chunk4Loader<DT> ld{e};
         fold4(ld, src, P, group_len, X);
@@ -486,8 +533,8 @@ int fold_waves(int per_wave, int loads_per_cu) {
     const int waves = loads_per_cu / per_wave;
     return waves >= 32 ? 0 : std::max(waves, PARO_MIN_WAVES_PER_CU);
 }
-// Loads a wave of the fold has in flight: a batch of contributions, for each block it takes.
-int fold_loads(int P, int blocks_per_wave = 1) { return std::min(P, PARO_BATCH) * blocks_per_wave; }
+// Loads a wave of the fold has in flight: a batch of contributions.
+int fold_loads(int P) { return std::min(P, PARO_BATCH); }
 
 // What a launch needs from the device besides the caller's buffers: the LDS size behind the
 // occupancy throttle and the scratch array of partial sums (per-block sums of a sweep-1 launch,
@@ -529,6 +576,7 @@ void free_tables(paro_device_tables &d) {
     (void)hipFree(d.dtype);
     (void)hipFree(d.no_decay);
     for (paro_tile_info *t : d.tile_tab) (void)hipFree(t);
+    for (paro_piece_info *t : d.piece_tab) (void)hipFree(t);
     (void)hipFree(d.partials);
     d = paro_device_tables();
 }
@@ -543,13 +591,20 @@ int fill_tables(const paro_plan_t *pl, paro_device_tables &d) {
     if ((rc = upload(&d.dtype, pl->dtype.data(), pl->dtype.size()))) return rc;
     if ((rc = upload(&d.no_decay, pl->no_decay.data(), pl->no_decay.size()))) return rc;
     d.tiles_per_chunk = (pl->L + TILE - 1) / TILE;
+    // a boundary makes one piece more; twice the tiles at most
+    d.max_pieces = d.tiles_per_chunk + std::min(d.tiles_per_chunk, (int64_t)pl->nz_tensor.size() + 1);
     d.tile_tab.assign((size_t)pl->P, nullptr);
+    d.piece_tab.assign((size_t)pl->P, nullptr);
+    d.n_pieces.assign((size_t)pl->P, 0);
+    d.on_lines.assign((size_t)pl->P, 0);
+    d.piece_tab_tried.assign((size_t)pl->P, 0);
     d.tile_tab_tried.assign((size_t)pl->P, 0);
     // one partial per block of a sweep-1 launch (which covers a rank's whole update range at most),
     // followed by room for the second-level sums
     int64_t ob, on;
     paro::letter_range(pl, 0, pl->letters[2], &ob, &on);
-    int64_t n_part = (piece_count(on) + 7) & ~(int64_t)7;
+    // (in the tensor layout one chunk, a wave for each of its pieces)
+    int64_t n_part = (std::max(piece_count(on), d.max_pieces) + 7) & ~(int64_t)7;
     if (n_part < PARO_MIN_PARTIALS) n_part = PARO_MIN_PARTIALS;
     d.n_partials = n_part;
     const int64_t n_level2 = level2_sums(n_part);
@@ -584,58 +639,126 @@ int ensure_device(paro_plan_t *pl) {
     return PARO_OK;
 }
 
-// Builds, once per chunk, the per-tile tables of the chunks of a rank's update range (for calls
-// that work tensor by tensor: the tensor layout, a weight-decay mask).  Too large a table (more
-// than 4 Mi tiles per chunk, or what the environment variable PARO_TILE_TABLE_MAX_TILES says) is
-// not built; the kernels then search the offset table for every block.
-int ensure_tile_tables(paro_plan_t *pl, int rank) {
-    std::lock_guard<std::mutex> lock(pl->dev_mutex);
-    paro_device_tables &d = pl->dev;
+// Walks the tiles of chunk c in address order: fn(i, f0, f1, k), tile i holding the flat indices
+// [f0, f1) and k the segment (non-empty tensor) that f0 lies in, or their number where f0 is padding.
+template <class F>
+void for_each_tile(const paro_plan_t *pl, int64_t c, F fn) {
+    const int64_t tiles = pl->dev.tiles_per_chunk, n_nz = (int64_t)pl->nz_tensor.size();
+    int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), c * pl->L) - pl->nz_off.begin() - 1;
+    for (int64_t i = 0; i < tiles; ++i) {
+        const int64_t f0 = c * pl->L + i * TILE, f1 = std::min(f0 + (int64_t)TILE, (c + 1) * pl->L);
+        while (k < n_nz && pl->nz_off[(size_t)k + 1] <= f0) ++k;
+        fn(i, f0, f1, k);
+    }
+}
+
+// One entry per tile, for the weight-decay mask.
+void list_tiles(const paro_plan_t *pl, int64_t c, std::vector<paro_tile_info> *tab) {
+    const int64_t n_nz = (int64_t)pl->nz_tensor.size();
+    tab->reserve((size_t)pl->dev.tiles_per_chunk);
+    for_each_tile(pl, c, [&](int64_t, int64_t f0, int64_t f1, int64_t k) {
+        if (k == n_nz)
+            tab->push_back({0, -2, (int32_t)n_nz});
+        else if (f1 <= pl->nz_off[(size_t)k + 1])
+            tab->push_back({f0 - pl->nz_off[(size_t)k], pl->nz_tensor[(size_t)k], pl->dtype[(size_t)pl->nz_tensor[(size_t)k]]});
+        else
+            tab->push_back({0, -1, (int32_t)k});
+    });
+}
+
+// The chunk's pieces, for the tensor layout.  A tile with a boundary inside is cut where the tensors
+// meet: taken by one wave, its lanes would each have pointers of their own to fetch, element by element,
+// P times over (P = 64, 1.4 M elements of tensors of 1 to 65536 elements: sweep 1 in 195 us, a handful of
+// such waves keeping the rest waiting; cut, 85 us).  With few contributions that fetching is short, and in a
+// large chunk the cut's partial cache lines of g cost more (P = 2, 59 M elements: whole step 370 us, cut
+// 395; P = 4, 4 M elements, though: 22.6 us, cut 20.2).  A tile of more tensors than PARO_SPLIT_MAX stays whole.
+void list_pieces(const paro_plan_t *pl, int64_t c, std::vector<paro_piece_info> *tab) {
+    const int64_t n_nz = (int64_t)pl->nz_tensor.size(), most = pl->dev.max_pieces;
+    int64_t spare = most - pl->dev.tiles_per_chunk;
+    const bool cut = pl->P > PARO_PAIR_MAX_RANKS || pl->dev.tiles_per_chunk < PARO_LARGE_TILES;
+    tab->reserve((size_t)most);
+    auto add = [&](int64_t off, int64_t dt, int64_t lo, int64_t hi, int32_t tensor, int64_t i) {
+        tab->push_back({off * ((int64_t)1 << 19) + (dt << 17 | hi << 8 | lo), tensor, (uint32_t)i});
+    };
+    for_each_tile(pl, c, [&](int64_t i, int64_t f0, int64_t f1, int64_t k) {
+        if (k == n_nz) return add(0, 0, 0, TILE, -2, i);
+        const int32_t t = pl->nz_tensor[(size_t)k];
+        if (f1 <= pl->nz_off[(size_t)k + 1]) return add(f0 - pl->nz_off[(size_t)k], pl->dtype[(size_t)t], 0, TILE, t, i);
+        int64_t end = k;                                         // one past the tile's last segment
+        while (end < n_nz && pl->nz_off[(size_t)end] < f1) ++end;
+        const bool pad = f1 > pl->total;
+        if (!cut || end - k + pad > PARO_SPLIT_MAX || end - k + pad - 1 > spare) return add(k, 0, 0, TILE, -1, i);
+        spare -= end - k + pad - 1;
+        for (int64_t q = k; q < end; ++q) {
+            const int64_t begin = pl->nz_off[(size_t)q];
+            const int32_t u = pl->nz_tensor[(size_t)q];
+            add(f0 - begin, pl->dtype[(size_t)u], std::max(begin - f0, (int64_t)0), std::min(pl->nz_off[(size_t)q + 1], f1) - f0, u, i);
+        }
+        if (pad) add(0, 0, pl->total - f0, f1 - f0, -2, i);
+    });
+    // a small launch ends sooner when its slow waves start first (step over 10 000 tensors, P = 8, 7.4 M
+    // elements: 80.0 -> 75.5 us); a large one is slower for fetching the cache lines around a cut twice
+    // (160 000 tensors, single sweep: 925 -> 958 us)
+    if (cut && pl->dev.tiles_per_chunk < PARO_LARGE_TILES)
+        std::stable_partition(tab->begin(), tab->end(), [](const paro_piece_info &x) { return (x.where & 0x1FFFF) != TILE << 8 || x.tensor == -1; });
+}
+
+// Whether nearly every piece starts on a multiple of 64 elements inside its tensor: on a cache line, if
+// the tensor does.
+bool mostly_on_lines(const std::vector<paro_piece_info> &tab) {
+    size_t on = 0;
+    for (const paro_piece_info &x : tab) on += x.tensor >= 0 && (x.where >> 19) % 64 == 0;
+    return on >= tab.size() - tab.size() / 8;
+}
+
+// Builds, once per chunk, a table of the chunks of a rank's update range.  Too large a one (chunks of more
+// than 4 Mi tiles, or what the environment variable PARO_TILE_TABLE_MAX_TILES says) is not built; the
+// kernels then search the offset table for every block.
+template <class Info, class List>
+int ensure_table(paro_plan_t *pl, int rank, std::vector<Info *> &tabs, std::vector<uint8_t> &tried, List list) {
+    const paro_device_tables &d = pl->dev;
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     int64_t max_tiles = (int64_t)4 << 20;                   // 64 MB of table
     if (const char *env = std::getenv("PARO_TILE_TABLE_MAX_TILES")) max_tiles = std::atoll(env);
-    const int64_t n_nz = (int64_t)pl->nz_tensor.size();
-    std::vector<paro_tile_info> tab;
+    std::vector<Info> tab;
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {
-        if (d.tile_tab_tried[(size_t)c]) continue;
+        if (tried[(size_t)c]) continue;
         if (d.tiles_per_chunk > max_tiles) {
-            d.tile_tab_tried[(size_t)c] = 1;         // decided: this chunk works without a table
+            tried[(size_t)c] = 1;                    // decided: this chunk works without a table
             continue;
         }
+        tab.clear();
         try {
-            tab.resize((size_t)d.tiles_per_chunk);
+            list(pl, c, &tab);
         } catch (const std::bad_alloc &) {
             return fail(PARO_ENOMEM, "out of host memory while building the per-tile table");
         }
-        for (int64_t i = 0; i < d.tiles_per_chunk; ++i) {
-            const int64_t f0 = c * pl->L + i * TILE;
-            const int64_t f1 = std::min(f0 + (int64_t)TILE, (c + 1) * pl->L);   // end of the tile
-            paro_tile_info &ti = tab[(size_t)i];
-            ti.toff = 0;
-            ti.tensor = -2;
-            ti.first_seg = (int32_t)n_nz;
-            if (f0 >= pl->total) continue;
-            const int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), f0) - pl->nz_off.begin() - 1;
-            if (f1 <= pl->nz_off[k + 1]) {
-                ti.tensor = pl->nz_tensor[k];
-                ti.toff = f0 - pl->nz_off[k];
-                ti.first_seg = pl->dtype[ti.tensor];
-            } else {
-                ti.tensor = -1;
-                ti.first_seg = (int32_t)k;
-            }
-        }
-        paro_tile_info *dev_tab = nullptr;
+        Info *dev_tab = nullptr;
         const int rc = upload(&dev_tab, tab.data(), tab.size());
         if (rc != PARO_OK) {                         // the next call tries again (and reports again)
             (void)hipFree(dev_tab);
             return rc;
         }
-        d.tile_tab[(size_t)c] = dev_tab;
-        d.tile_tab_tried[(size_t)c] = 1;
+        tabs[(size_t)c] = dev_tab;
+        if constexpr (std::is_same_v<Info, paro_piece_info>) {
+            pl->dev.n_pieces[(size_t)c] = (uint32_t)tab.size();
+            pl->dev.on_lines[(size_t)c] = mostly_on_lines(tab);
+        }
+        tried[(size_t)c] = 1;
     }
     return PARO_OK;
+}
+
+// The tables that a call needs: the pieces for the tensor layout, the tiles for a weight-decay mask
+// applied block by block.
+int ensure_tables(paro_plan_t *pl, int rank, bool pieces, bool tiles) {
+    std::lock_guard<std::mutex> lock(pl->dev_mutex);
+    paro_device_tables &d = pl->dev;
+    int rc = PARO_OK;
+    if (pieces) rc = ensure_table(pl, rank, d.piece_tab, d.piece_tab_tried, list_pieces);
+    if (tiles && rc == PARO_OK) rc = ensure_table(pl, rank, d.tile_tab, d.tile_tab_tried, list_tiles);
+    return rc;
 }
 
 // The map from elements to tensors for a launch whose element 0 is flat index `begin`.  The
@@ -651,6 +774,8 @@ TensorMap map_for(const paro_plan_t *pl, const Scratch &sc, int64_t begin, bool 
         tm.total = pl->total;
         tm.begin = begin;
         tm.tile_tab = nullptr;
+        tm.pieces = nullptr;
+        tm.n_pieces = 0;
         return tm;
     }
     tm.nz_off = pl->dev.nz_off;
@@ -662,7 +787,14 @@ TensorMap map_for(const paro_plan_t *pl, const Scratch &sc, int64_t begin, bool 
     tm.total = pl->total;
     tm.begin = begin;
     tm.tile_tab = nullptr;
-    if (one_chunk && begin % pl->L == 0) tm.tile_tab = pl->dev.tile_tab[(size_t)(begin / pl->L)];
+    tm.pieces = nullptr;
+    tm.n_pieces = 0;
+    if (one_chunk && begin % pl->L == 0) {
+        const size_t c = (size_t)(begin / pl->L);
+        tm.tile_tab = pl->dev.tile_tab[c];
+        tm.pieces = pl->dev.piece_tab[c];
+        tm.n_pieces = pl->dev.n_pieces[c];
+    }
     return tm;
 }
 
@@ -717,6 +849,7 @@ int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
 // chunk's first element inside the update range.
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
+    tab->paced = piece_count(pl->L) >= PARO_PACE_MIN_BLOCKS;
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
     paro::fold_order(pl, chunk, order, &gl);
@@ -731,7 +864,8 @@ void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int
 
 // ... and of a launch over an update range of several chunks: pointers in rank order, the order of
 // each chunk's fold follows from the range map.
-RangeMap range_map(const paro_plan_t *pl, int64_t ob, int own, const void *const *contrib, SrcTable *tab) {
+RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const void *const *contrib, SrcTable *tab) {
+    tab->paced = piece_count(on) >= PARO_PACE_MIN_BLOCKS;
     for (int q = 0; q < pl->P; ++q) tab->p[q] = contrib[q];
     for (int q = pl->P; q < PARO_MAX_RANKS; ++q) tab->p[q] = nullptr;
     const bool ring = pl->sched == PARO_RING;
@@ -752,6 +886,17 @@ RangeMap range_map(const paro_plan_t *pl, int64_t ob, int own, const void *const
             constexpr int DT = PARO_F32;   \
             CALL;                          \
         }                                  \
+    } while (0)
+
+#define PARO_BY_LINES(on_lines, CALL)  \
+    do {                               \
+        if (on_lines) {                \
+            constexpr bool NT = true;  \
+            CALL;                      \
+        } else {                       \
+            constexpr bool NT = false; \
+            CALL;                      \
+        }                              \
     } while (0)
 
 // Whether chunk c is cut into many small pieces of tensors (fewer than PARO_DENSE_BLOCKS_PER_TENSOR
@@ -779,31 +924,27 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         return (int)grid;
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
-    // What decides is the list.  A chunk cut into many small pieces of tensors: its waves wait for their look-ups
-    // with no data in flight, and want more bytes in flight per wave and per compute unit (no throttle; with few
-    // contributions and a launch that fills the GPU many times over, two blocks per wave).  A few large tensors:
-    // the look-ups hit the scalar cache and the launch behaves like the chunk layout's, budget included; only with
-    // 4 contributions or fewer does a wave with one block have too little in flight beside its look-ups.
+    const int64_t pieces = tm.pieces ? tm.n_pieces : piece_count(n);
+    const bool on_lines = pl->dev.on_lines[(size_t)c] != 0;
+    // What decides is the list, see PARO_PAIR_MAX_RANKS.
     const bool small = many_small_tensors(pl, c);
     int64_t pair_min_blocks = PARO_PAIR_MIN_BLOCKS;
-    const char *env = std::getenv("PARO_PAIR_MIN_BLOCKS");                  // for tests: pairs on any list from this size on
-    if (env) pair_min_blocks = std::atoll(env);
-    if (pl->P <= PARO_PAIR_MAX_RANKS && (small || env || 2 * pl->P <= PARO_PAIR_MAX_RANKS) &&
-        (int64_t)piece_grid(n) >= pair_min_blocks) {
-        const unsigned grid = (piece_grid(n, 2) + 7u) & ~7u;
-        const unsigned lds = throttle_lds(
-            sc.lds_per_cu, fold_waves(fold_loads(pl->P, 2), small ? PARO_FOLD_T_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU));
-        hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, group_len, n, g, partials, tm);
+    if (const char *env = std::getenv("PARO_PAIR_MIN_BLOCKS")) pair_min_blocks = std::atoll(env);     // for tests
+    if (pl->P <= PARO_PAIR_MAX_RANKS && piece_count(n) >= pair_min_blocks) {
+        const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
+        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT>), dim3(grid), dim3(WAVE), 0, st,
+                                                   tab, pl->P, group_len, n, g, partials, tm));
         return (int)grid;
     }
-    const unsigned grid = (piece_grid(n) + 7u) & ~7u;
+    const unsigned grid = (unsigned)((pieces + 7) & ~(int64_t)7);
     const unsigned lds =
         throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU));
-    if (pl->P <= PARO_PAIR_MAX_RANKS)                                       // a batch of 8 contributions: fewer registers
-        hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, group_len, n, g, partials, tm);
+    if (pl->P <= 8)                                                         // a batch of 8 contributions: fewer registers
+        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P,
+                                                   group_len, n, g, partials, tm));
     else
-        hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, group_len, n, g,
-                           partials, tm);
+        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT>), dim3(grid), dim3(WAVE), lds, st, tab,
+                                                   pl->P, group_len, n, g, partials, tm));
     return (int)grid;
 }
 
@@ -812,15 +953,16 @@ template <bool MASK>
 void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const SrcTable &tab, int group_len, int64_t c,
                   const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     const int64_t n = pl->L;
-    const bool small = layout == PARO_TENSORS && many_small_tensors(pl, c);
-    const int waves = fold_waves(fold_loads(pl->P) + 3, small ? PARO_FUSED_T_LOADS_PER_CU : PARO_FUSED_LOADS_PER_CU);
+    const bool small = layout == PARO_TENSORS && piece_count(n) < PARO_LARGE_TILES && many_small_tensors(pl, c);
+    const int waves = fold_waves(fold_loads(pl->P) + 3, small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FUSED_LOADS_PER_CU);
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const unsigned grid = piece_grid(n), lds = throttle_lds(sc.lds_per_cu, waves);
     if (layout == PARO_TENSORS)
-        hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASK>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, group_len, n, a, p, m,
-                           v, dst, tm);
+        PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0,
+                      hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASK, NT>), dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE),
+                                         lds, st, tab, pl->P, group_len, n, a, p, m, v, dst, tm));
     else
-        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4<false, DT, MASK>), dim3(grid), dim3(WAVE), lds, st, tab,
+        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4<false, DT, MASK, true>), dim3(grid), dim3(WAVE), lds, st, tab,
                                                        pl->P, group_len, n, a, p, m, v, dst, tm));
 }
 
@@ -828,7 +970,7 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
 int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_t on, const void *const *contrib,
                        const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     SrcTable tab;
-    const RangeMap rm = range_map(pl, ob, -1, contrib, &tab);
+    const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P) + 3, PARO_FUSED_LOADS_PER_CU));
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
@@ -900,7 +1042,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
                     float *grad_out, double *sumsq_out, hipStream_t st, NormSums *rest) {
     int rc;
     SrcTable tab;
-    const RangeMap rm = range_map(pl, ob, own, contrib, &tab);
+    const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), PARO_FOLD_LOADS_PER_CU));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
@@ -1086,7 +1228,7 @@ int paro_reduce_shard(paro_plan_t *pl, int rank, const void *const *contrib, int
     if (sumsq_out && (reinterpret_cast<uintptr_t>(sumsq_out) & 7))
         return fail(PARO_EALIGN, "paro_reduce_shard: sumsq_out is not 8-byte aligned");
     if ((rc = ensure_device(pl))) return rc;
-    if (layout == PARO_TENSORS && (rc = ensure_tile_tables(pl, rank))) return rc;
+    if (layout == PARO_TENSORS && (rc = ensure_tables(pl, rank, true, false))) return rc;
     return do_reduce(pl, plan_scratch(pl), rank, contrib, layout, grad_out, sumsq_out, false, static_cast<hipStream_t>(stream));
 }
 
@@ -1106,7 +1248,7 @@ int paro_adam_shard(paro_plan_t *pl, int rank, const paro_adam_t *hp, const floa
     if (dst_base && (reinterpret_cast<uintptr_t>(dst_base) & 15))
         return fail(PARO_EALIGN, "paro_adam_shard: dst_base is not 16-byte aligned");
     if ((rc = ensure_device(pl))) return rc;
-    if (pl->any_no_decay && (rc = ensure_tile_tables(pl, rank))) return rc;
+    if (pl->any_no_decay && (rc = ensure_tables(pl, rank, false, true))) return rc;
     uint16_t *dst = nullptr;
     if (dst_base) {
         int64_t dl, so, sl;
@@ -1152,7 +1294,8 @@ int paro_step_fused(paro_plan_t *pl, int rank, const void *const *contrib, int l
             return fail(sumsq_scratch ? PARO_EALIGN : PARO_EINVAL, "paro_step_fused: clipping and skip_nonfinite need sumsq_scratch");
     }
     if ((rc = ensure_device(pl))) return rc;
-    if ((layout == PARO_TENSORS || pl->any_no_decay) && (rc = ensure_tile_tables(pl, rank))) return rc;
+    const bool tensors = layout == PARO_TENSORS;          // its single sweep has the mask from the pieces
+    if ((rc = ensure_tables(pl, rank, tensors, pl->any_no_decay && (clip || !tensors)))) return rc;
     return launch_step(pl, plan_scratch(pl), rank, contrib, layout, a, grad_scratch, sumsq_scratch, p, m, v, dst_base,
                        static_cast<hipStream_t>(stream));
 }

@@ -9,9 +9,11 @@
 namespace {
 
 // ------------------------------------------------------------------- loaders
-// A loader hands the fold the 4 values that contribution k (in fold order) holds for the
-// thread's 4 elements: load() issues the memory operations, unpack() turns what came back into
-// fp32.  kBatch contributions are loaded before the first is consumed.
+// A loader hands the fold the 4 values that a contribution (entry k of the pointer table) holds for
+// the thread's 4 elements: source() finds where they lie, load() issues the memory operations,
+// unpack() turns what came back into fp32.  kBatch contributions are loaded before the first is
+// consumed, and all their sources are found before the first load: found one by one, each would wait
+// for its own scalar loads.
 
 // Contributions are arrays in shard coordinates, all of one dtype: an 8-byte load per
 // contribution for the 2-byte dtypes (a wave instruction covers 512 consecutive bytes), a
@@ -20,11 +22,14 @@ template <int DT>
 struct Chunk4Loader {
     static constexpr int kBatch = PARO_BATCH;
     static constexpr int kElems = 4;
+    static constexpr bool kPaced = true;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw = std::conditional_t<DT == PARO_F32, u32x4, u32x2>;
+    using At = const void *;
     int64_t e;                                   // first of the thread's 4 elements
-    __device__ __forceinline__ void load(const SrcTable &src, int k, Raw &r) const {
-        r = ld_nt(reinterpret_cast<const Raw *>(static_cast<const char *>(src.p[k]) + e * ESIZE));
+    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return src.p[k]; }
+    __device__ __forceinline__ void load(At at, Raw &r) const {
+        r = ld_nt(reinterpret_cast<const Raw *>(static_cast<const char *>(at) + e * ESIZE));
     }
     static __device__ __forceinline__ void to_f32(const Raw &r, float x[4]) {
         if constexpr (DT != PARO_F32) {
@@ -172,64 +177,104 @@ __device__ __forceinline__ void locate4(const TensorMap &tm, int seg, int64_t f0
 }
 
 // Contributions are per-tensor gradients (source k is a device array of T pointers) and the
-// block's elements lie in one tensor.  Where a source's first byte for this block is 8-byte
-// (2-byte dtypes) or 16-byte (fp32) aligned, one vector load fetches the thread's 4 values, as
-// in the chunk layout; else element loads.  The test is wave-uniform, source by source.
-template <int DT, int KB = PARO_BATCH>
+// block's elements lie in one tensor: one vector load fetches the thread's 4 values, as in the chunk
+// layout, wherever the tensor's data start (the hardware takes vector loads at any address; a branch
+// on the alignment, source by source, costs more than the misaligned load does).
+template <class V>
+struct Unaligned;
+template <>
+struct Unaligned<u32x2> { typedef u32x2 type __attribute__((aligned(2))); };
+template <>
+struct Unaligned<u32x4> { typedef u32x4 type __attribute__((aligned(4))); };
+
+// Address of the tensor's data in contribution k (wave-uniform).
+__device__ __forceinline__ uintptr_t tensor_base(const SrcTable &src, int k, int tensor) {
+    return global_ptr<uintptr_t>(reinterpret_cast<uintptr_t>(src.p[k]))[tensor];
+}
+
+// NT: streaming loads, for blocks that start on a cache line (a Llama-like list, P = 16, 26 M elements: 313
+// us a clipped step against 325 with plain loads); a line shared with the next block is better kept (160 000
+// ragged tensors, P = 8, single sweep: 922 us against 1055).
+template <int DT, bool NT, int KB = PARO_BATCH>
 struct Tensor4Loader {
     static constexpr int kBatch = (DT == PARO_F32 && KB > 8) ? KB / 2 : KB;     // 32 registers of loads in flight at most
     static constexpr int kElems = 4;
+    static constexpr bool kPaced = false;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw = typename Chunk4Loader<DT>::Raw;
+    using At = uintptr_t;
     int tensor;
     int64_t piece_byte_off;    // of the block's first element inside the tensor
-    __device__ __forceinline__ void load(const SrcTable &src, int k, Raw &r) const {
-        const uintptr_t b0 = static_cast<const uintptr_t *>(src.p[k])[tensor] + (uintptr_t)piece_byte_off;
-        const uintptr_t mine = b0 + (uintptr_t)lane_id() * (4 * ESIZE);
-        if ((b0 & (4 * ESIZE - 1)) == 0) {
-            r = ld_nt(global_ptr<Raw>(mine));
-        } else if constexpr (DT != PARO_F32) {
-            const auto *h = global_ptr<uint16_t>(mine);
-            r.x = (unsigned)h[0] | ((unsigned)h[1] << 16);
-            r.y = (unsigned)h[2] | ((unsigned)h[3] << 16);
-        } else {
-            const auto *w = global_ptr<unsigned int>(mine);
-            r = u32x4{w[0], w[1], w[2], w[3]};
-        }
+    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    __device__ __forceinline__ void load(At at, Raw &r) const {
+        const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
+        r = ld_once<NT>(global_ptr<typename Unaligned<Raw>::type>(mine));
     }
     __device__ __forceinline__ void unpack(const Raw &r, float x[4]) const { Chunk4Loader<DT>::to_f32(r, x); }
 };
 
-// Two consecutive blocks inside one tensor, folded by one wave (sweep 1 with few contributions:
-// the wave then has as many loads in flight as with many, and one look-up serves 512 elements).
-// The thread's elements 0-3 lie in the first block, 4-7 in the second, 256 elements further on.
+// A part of a block: the elements of [lo, hi) lie in one tensor, found like a whole block's; a thread
+// with all of its 4 elements inside loads them as above, at the part's ends element by element.
 template <int DT>
+struct Part4Loader {
+    static constexpr int kBatch = 4;              // more costs every wave of the kernel registers
+    static constexpr int kElems = 4;
+    static constexpr bool kPaced = false;
+    static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
+    struct Raw { unsigned int w[4]; };
+    using At = uintptr_t;
+    int tensor;
+    int64_t piece_byte_off;    // of the block's first element inside the tensor (may be negative: it is not loaded)
+    int a, b;                  // the thread's elements [a, b) of its 4 belong to the part
+    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    __device__ __forceinline__ bool whole() const { return a == 0 && b == 4; }
+    __device__ __forceinline__ void load(At at, Raw &r) const {
+        const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
+        if (whole()) {
+            using V = typename Chunk4Loader<DT>::Raw;
+            const V v = ld_once<false>(global_ptr<typename Unaligned<V>::type>(mine));
+            r.w[0] = v.x; r.w[1] = v.y;
+            if constexpr (DT == PARO_F32) { r.w[2] = v.z; r.w[3] = v.w; }
+        } else {
+            using E = std::conditional_t<DT == PARO_F32, unsigned int, uint16_t>;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (i >= a && i < b) r.w[i] = global_ptr<E>(mine)[i];
+        }
+    }
+    __device__ __forceinline__ void unpack(const Raw &r, float x[4]) const {
+        if constexpr (DT == PARO_F32) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(r.w[i]);
+        } else {
+            const bool pairs = whole();
+            x[0] = cvt_lo<DT>(r.w[0]);
+            x[1] = pairs ? cvt_hi<DT>(r.w[0]) : cvt_lo<DT>(r.w[1]);
+            x[2] = pairs ? cvt_lo<DT>(r.w[1]) : cvt_lo<DT>(r.w[2]);
+            x[3] = pairs ? cvt_hi<DT>(r.w[1]) : cvt_lo<DT>(r.w[3]);
+        }
+    }
+};
+
+// Two consecutive blocks inside one tensor, folded by one wave (sweep 1 with 4 contributions or fewer:
+// the wave then has twice the loads in flight, and one look-up serves 512 elements).
+// The thread's elements 0-3 lie in the first block, 4-7 in the second, 256 elements further on.
+template <int DT, bool NT>
 struct Tensor8Loader {
-    static constexpr int kBatch = DT == PARO_F32 ? 4 : 8;     // 32 registers of loads in flight either way
+    static constexpr int kBatch = PARO_PAIR_MAX_RANKS;
     static constexpr int kElems = 8;
+    static constexpr bool kPaced = false;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw4 = typename Chunk4Loader<DT>::Raw;
     struct Raw { Raw4 a, b; };
+    using At = uintptr_t;
     int tensor;
     int64_t piece_byte_off;    // of the first block's first element inside the tensor
-    __device__ __forceinline__ void load(const SrcTable &src, int k, Raw &r) const {
-        const uintptr_t b0 = static_cast<const uintptr_t *>(src.p[k])[tensor] + (uintptr_t)piece_byte_off;
-        const uintptr_t mine = b0 + (uintptr_t)lane_id() * (4 * ESIZE);
-        constexpr uintptr_t NEXT = (uintptr_t)PIECE * ESIZE;
-        if ((b0 & (4 * ESIZE - 1)) == 0) {
-            r.a = ld_nt(global_ptr<Raw4>(mine));
-            r.b = ld_nt(global_ptr<Raw4>(mine + NEXT));
-        } else if constexpr (DT != PARO_F32) {
-            const auto *h = global_ptr<uint16_t>(mine), *h2 = global_ptr<uint16_t>(mine + NEXT);
-            r.a.x = (unsigned)h[0] | ((unsigned)h[1] << 16);
-            r.a.y = (unsigned)h[2] | ((unsigned)h[3] << 16);
-            r.b.x = (unsigned)h2[0] | ((unsigned)h2[1] << 16);
-            r.b.y = (unsigned)h2[2] | ((unsigned)h2[3] << 16);
-        } else {
-            const auto *w = global_ptr<unsigned int>(mine), *w2 = global_ptr<unsigned int>(mine + NEXT);
-            r.a = u32x4{w[0], w[1], w[2], w[3]};
-            r.b = u32x4{w2[0], w2[1], w2[2], w2[3]};
-        }
+    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    __device__ __forceinline__ void load(At at, Raw &r) const {
+        const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
+        r.a = ld_once<NT>(global_ptr<typename Unaligned<Raw4>::type>(mine));
+        r.b = ld_once<NT>(global_ptr<typename Unaligned<Raw4>::type>(mine + (uintptr_t)PIECE * ESIZE));
     }
     __device__ __forceinline__ void unpack(const Raw &r, float x[8]) const {
         Chunk4Loader<DT>::to_f32(r.a, x);
@@ -238,25 +283,30 @@ struct Tensor8Loader {
 };
 
 // ... and a tensor boundary (or the end of the data) falls inside the block: every element has
-// its own tensor, dtype and offset; element loads.  Padding contributes +0.  A source's base
-// pointer is fetched per element only where the thread's elements lie in different tensors.
+// its own tensor, dtype and offset; element loads.  Padding contributes +0.
 struct Lane4Loader {
     static constexpr int kBatch = PARO_LANE_BATCH;
     static constexpr int kElems = 4;
+    static constexpr bool kPaced = false;
     struct Raw { unsigned int bits[4]; };
+    struct At { uintptr_t base[4]; };
     Located at;
-    __device__ __forceinline__ void load(const SrcTable &src, int k, Raw &r) const {
-        const uintptr_t *ptrs = static_cast<const uintptr_t *>(src.p[k]);
-        uintptr_t b = 0;
+    __device__ __forceinline__ At source(const SrcTable &src, int k) const {
+        const auto *ptrs = global_ptr<uintptr_t>(reinterpret_cast<uintptr_t>(src.p[k]));
+        At a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a.base[i] = ptrs[max(at.tens[i], 0)];      // padding: any entry, never followed
+        return a;
+    }
+    __device__ __forceinline__ void load(const At &a, Raw &r) const {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             r.bits[i] = 0u;
             if (at.tens[i] >= 0) {
-                if (i == 0 || at.tens[i] != at.tens[i - 1]) b = ptrs[at.tens[i]];
                 if (at.dt[i] != PARO_F32)
-                    r.bits[i] = global_ptr<uint16_t>(b)[at.toff[i]];
+                    r.bits[i] = global_ptr<uint16_t>(a.base[i])[at.toff[i]];
                 else
-                    r.bits[i] = global_ptr<unsigned int>(b)[at.toff[i]];
+                    r.bits[i] = global_ptr<unsigned int>(a.base[i])[at.toff[i]];
             }
         }
     }
@@ -277,44 +327,95 @@ struct Lane4Loader {
 struct InOrder {
     __device__ __forceinline__ int next(int k) { return k; }
 };
-template <class Ld, class Order = InOrder>
-__device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, int group_len, float *X,
-                                      Order ord = Order()) {
-    constexpr int NE = Ld::kElems;
+
+template <class Ld>
+struct Folding {
+    static constexpr int NE = Ld::kElems;
     float A[NE];
     int pos = 0;
     bool first_group = true;
-    constexpr int B = Ld::kBatch;
-    for (int k0 = 0; k0 < P; k0 += B) {
-        typename Ld::Raw raw[B];
-        static_for<0, B>([&](auto b) {
-            if (k0 + b < P) ld.load(src, ord.next(k0 + b), raw[b]);
-        });
-        static_for<0, B>([&](auto b) {
-            if (k0 + b < P) {
-                float x[NE];
-                ld.unpack(raw[b], x);
-                if (pos == 0) {
+};
+
+// N contributions, from the k-th on: all sources, then all loads - straight-line code.  A large launch
+// over the chunk layout is paced: with all its loads issued at once a wave touches P DRAM pages in one go;
+// with a pause after each, waves that start together read the same contribution together.  Whole clipped
+// steps unpaced -> paced: P = 64, 105 M elements 2913 -> 2830 us, P = 16, 421 M elements 4340 -> 4268; a
+// small launch is bound by latency (P = 16, 0.5 M elements 13.7 -> 15.9) and is not paced.
+template <int N, class Ld, class Order>
+__device__ __forceinline__ void load_batch(const Ld &ld, const SrcTable &src, int k, Order &ord, typename Ld::Raw *raw) {
+    typename Ld::At at[N];
+    static_for<0, N>([&](auto b) { at[b] = ld.source(src, ord.next(k + b)); });
+    static_for<0, N>([&](auto b) {
+        ld.load(at[b], raw[b]);
+        if constexpr (Ld::kPaced) {
+            if (src.paced) __builtin_amdgcn_s_sleep(PARO_PACE_SLEEP);
+        }
+    });
+}
+template <int N, class Ld>
+__device__ __forceinline__ void add_batch(const Ld &ld, const typename Ld::Raw *raw, int group_len, Folding<Ld> &f, float *X) {
+    constexpr int NE = Ld::kElems;
+    static_for<0, N>([&](auto b) {
+        float x[NE];
+        ld.unpack(raw[b], x);
+        if (f.pos == 0) {
 #pragma unroll
-                    for (int i = 0; i < NE; ++i) A[i] = x[i];
-                } else {
+            for (int i = 0; i < NE; ++i) f.A[i] = x[i];
+        } else {
 #pragma unroll
-                    for (int i = 0; i < NE; ++i) A[i] = A[i] + x[i];
-                }
-                if (++pos == group_len) {
-                    pos = 0;
-                    if (first_group) {
+            for (int i = 0; i < NE; ++i) f.A[i] = f.A[i] + x[i];
+        }
+        if (++f.pos == group_len) {
+            f.pos = 0;
+            if (f.first_group) {
 #pragma unroll
-                        for (int i = 0; i < NE; ++i) X[i] = A[i];
-                        first_group = false;
-                    } else {
+                for (int i = 0; i < NE; ++i) X[i] = f.A[i];
+                f.first_group = false;
+            } else {
 #pragma unroll
-                        for (int i = 0; i < NE; ++i) X[i] = X[i] + A[i];
-                    }
-                }
+                for (int i = 0; i < NE; ++i) X[i] = X[i] + f.A[i];
             }
-        });
+        }
+    });
+}
+
+// Whole batches, then what is left as batches of 8, 4, 2 and 1 (their loads are all issued before the
+// first is consumed).
+template <class Ld, class Order = InOrder>
+__device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, int group_len, float *X,
+                                      Order ord = Order()) {
+    constexpr int B = Ld::kBatch;
+    static_assert(B == 16 || B == 8 || B == 4 || B == 2, "the rest is split into powers of two");
+    Folding<Ld> f;
+    int k = 0;
+    for (; k + B <= P; k += B) {
+        typename Ld::Raw raw[B];
+        load_batch<B>(ld, src, k, ord, raw);
+        add_batch<B>(ld, raw, group_len, f, X);
     }
+    const int rest = P - k;
+    if (rest == 0) return;
+    typename Ld::Raw r8[8], r4[4], r2[2], r1[1];
+    if constexpr (B > 8) {
+        if (rest & 8) load_batch<8>(ld, src, k, ord, r8), k += 8;
+    }
+    if constexpr (B > 4) {
+        if (rest & 4) load_batch<4>(ld, src, k, ord, r4), k += 4;
+    }
+    if constexpr (B > 2) {
+        if (rest & 2) load_batch<2>(ld, src, k, ord, r2), k += 2;
+    }
+    if (rest & 1) load_batch<1>(ld, src, k, ord, r1);
+    if constexpr (B > 8) {
+        if (rest & 8) add_batch<8>(ld, r8, group_len, f, X);
+    }
+    if constexpr (B > 4) {
+        if (rest & 4) add_batch<4>(ld, r4, group_len, f, X);
+    }
+    if constexpr (B > 2) {
+        if (rest & 2) add_batch<2>(ld, r2, group_len, f, X);
+    }
+    if (rest & 1) add_batch<1>(ld, r1, group_len, f, X);
 }
 
 // Fold order of a chunk, walked inside the kernel: the pointer table is in rank order, and the
@@ -392,18 +493,18 @@ __device__ __forceinline__ bool fold_range(const RangeMap &rm, const SrcTable &s
 // not all padding.  loc: from locate4 when the block holds a boundary (pc.tensor == -1).
 // KB: contributions loaded before the first is consumed (a kernel that is only launched for few
 // contributions says so, and saves the registers).
-template <int KB = PARO_BATCH>
+template <bool NT, int KB = PARO_BATCH>
 __device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc, const SrcTable &src, int P,
                                              int group_len, float X[4]) {
     if (pc.tensor >= 0) {
         if (pc.dt == PARO_BF16) {
-            Tensor4Loader<PARO_BF16, KB> ld{pc.tensor, pc.toff * 2};
+            Tensor4Loader<PARO_BF16, NT, KB> ld{pc.tensor, pc.toff * 2};
             fold4(ld, src, P, group_len, X);
         } else if (pc.dt == PARO_F16) {
-            Tensor4Loader<PARO_F16, KB> ld{pc.tensor, pc.toff * 2};
+            Tensor4Loader<PARO_F16, NT, KB> ld{pc.tensor, pc.toff * 2};
             fold4(ld, src, P, group_len, X);
         } else {
-            Tensor4Loader<PARO_F32, KB> ld{pc.tensor, pc.toff * 4};
+            Tensor4Loader<PARO_F32, NT, KB> ld{pc.tensor, pc.toff * 4};
             fold4(ld, src, P, group_len, X);
         }
     } else {
@@ -413,15 +514,84 @@ __device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc
 }
 
 // ... of the thread's 8 elements in two consecutive blocks that lie in one tensor (pc: the first).
+template <bool NT>
 __device__ __forceinline__ void fold_tensor_pair(const Piece &pc, const SrcTable &src, int P, int group_len, float X[8]) {
     if (pc.dt == PARO_BF16) {
-        Tensor8Loader<PARO_BF16> ld{pc.tensor, pc.toff * 2};
+        Tensor8Loader<PARO_BF16, NT> ld{pc.tensor, pc.toff * 2};
         fold4(ld, src, P, group_len, X);
     } else if (pc.dt == PARO_F16) {
-        Tensor8Loader<PARO_F16> ld{pc.tensor, pc.toff * 2};
+        Tensor8Loader<PARO_F16, NT> ld{pc.tensor, pc.toff * 2};
         fold4(ld, src, P, group_len, X);
     } else {
-        Tensor8Loader<PARO_F32> ld{pc.tensor, pc.toff * 4};
+        Tensor8Loader<PARO_F32, NT> ld{pc.tensor, pc.toff * 4};
+        fold4(ld, src, P, group_len, X);
+    }
+}
+
+// One piece of a launch's list, as the wave that takes it sees it.
+struct Cut {
+    Piece pc;
+    int64_t e0;        // first element of the piece's block, in the launch (n or more: nothing to do)
+    int a, b;          // the thread's elements [a, b) of its 4 belong to the piece (ends of the launch apart)
+    bool whole;        // the piece is its whole block
+};
+
+// The i-th piece; without a list the i-th block.  Everything but a and b is wave-uniform.
+__device__ __forceinline__ Cut cut_of(const TensorMap &tm, int64_t i, int64_t n) {
+    Cut c;
+    c.a = 0;
+    c.b = EPT;
+    c.whole = true;
+    c.e0 = i * PIECE;
+    if (!tm.pieces) {
+        if (c.e0 < n) c.pc = piece_of(tm, c.e0, n);
+        return c;
+    }
+    c.e0 = n;
+    if (i >= tm.n_pieces) return c;
+    const paro_piece_info info = tm.pieces[i];                                // one address for the whole wave
+    const int64_t w = uniform(info.where);
+    const int lo = (int)(w & 255), hi = (int)(w >> 8 & 511), x0 = (int)lane_id() * EPT;
+    c.e0 = (int64_t)(unsigned)uniform((int)info.tile) * TILE;
+    c.pc.tensor = uniform(info.tensor);
+    c.pc.dt = (int)(w >> 17 & 3);
+    c.pc.toff = w >> 19;
+    c.pc.seg = (int)(w >> 19);
+    c.whole = lo == 0 && hi == PIECE;
+    if (!c.whole) {
+        c.a = max(lo - x0, 0);
+        c.b = min(hi - x0, EPT);
+    }
+    return c;
+}
+
+// Whether the i-th and the next piece are whole consecutive blocks inside one tensor; *pc: the first.
+// A piece that ends before its block does says so: two whole ones lie inside the launch but for the
+// last block of the chunk, which n tells apart.
+__device__ __forceinline__ bool pair_of(const TensorMap &tm, int64_t i, int64_t n, Piece *pc, int64_t *e0) {
+    if (!tm.pieces || i + 1 >= tm.n_pieces) return false;
+    const paro_piece_info x = tm.pieces[i], y = tm.pieces[i + 1];
+    const int64_t w = uniform(x.where);
+    const unsigned tile = (unsigned)uniform((int)x.tile);
+    constexpr unsigned WHOLE = (unsigned)TILE << 8, ENDS = 0x1FFFF;
+    pc->tensor = uniform(x.tensor);
+    pc->dt = (int)(w >> 17 & 3);
+    pc->toff = w >> 19;
+    *e0 = (int64_t)tile * TILE;
+    return pc->tensor >= 0 && uniform(y.tensor) == pc->tensor && (unsigned)uniform((int)y.tile) == tile + 1 &&
+           ((unsigned)w & ENDS) == WHOLE && ((unsigned)uniform((int)y.where) & ENDS) == WHOLE && *e0 + 2 * PIECE <= n;
+}
+
+// The ordered fold of the thread's elements [a, b) of a piece that is part of its block.
+__device__ __forceinline__ void fold_part(const Cut &c, const SrcTable &src, int P, int group_len, float X[4]) {
+    if (c.pc.dt == PARO_BF16) {
+        Part4Loader<PARO_BF16> ld{c.pc.tensor, c.pc.toff * 2, c.a, c.b};
+        fold4(ld, src, P, group_len, X);
+    } else if (c.pc.dt == PARO_F16) {
+        Part4Loader<PARO_F16> ld{c.pc.tensor, c.pc.toff * 2, c.a, c.b};
+        fold4(ld, src, P, group_len, X);
+    } else {
+        Part4Loader<PARO_F32> ld{c.pc.tensor, c.pc.toff * 4, c.a, c.b};
         fold4(ld, src, P, group_len, X);
     }
 }

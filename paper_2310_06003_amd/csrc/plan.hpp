@@ -24,6 +24,17 @@ struct paro_tile_info {
     int32_t first_seg;
 };
 
+// A piece of a chunk: elements [lo, hi) of a tile (hi == PARO_TILE: to its end), which lie in one
+// tensor.  Pieces are listed in address order (those of cut tiles first, in a small chunk); a tile is one piece, or, where it holds a few tensors,
+// one for each of them (and one for the padding at its end).
+struct paro_piece_info {
+    int64_t where;      // offset in the tensor of the tile's first element (< 0 where the tensor starts
+                        // later) << 19 | gradient dtype << 17 | hi << 8 | lo
+    int32_t tensor;     // -2: padding; -1: a whole tile that holds too many tensors to be cut (or no room for
+                        // more pieces), and the offset is the index of its first non-empty tensor
+    uint32_t tile;
+};
+
 struct paro_device_tables {
     int device = -1;
     int lds_per_cu = 0;             // bytes of LDS a compute unit has (for the occupancy throttle)
@@ -32,11 +43,15 @@ struct paro_device_tables {
     uint8_t *nz_dtype = nullptr;    // [n_nz]     its gradient dtype
     uint8_t *dtype = nullptr;       // [T]
     uint8_t *no_decay = nullptr;    // [T]
-    // per chunk, built at the first call that works on the chunk tensor by tensor (tensor layout,
-    // weight-decay mask):
-    std::vector<paro_tile_info *> tile_tab;   // [P] the chunk's [tiles_per_chunk] table, or null
+    // per chunk, each built at the first call that needs it:
+    std::vector<paro_tile_info *> tile_tab;   // [P] the chunk's [tiles_per_chunk] table, or null (weight-decay mask)
     std::vector<uint8_t> tile_tab_tried;      // [P] the decision for the chunk has been made
+    std::vector<paro_piece_info *> piece_tab; // [P] the chunk's list of pieces, or null (tensor layout)
+    std::vector<uint32_t> n_pieces;           // [P]
+    std::vector<uint8_t> on_lines;            // [P] nearly every piece starts on a multiple of 64 elements of its tensor
+    std::vector<uint8_t> piece_tab_tried;     // [P]
     int64_t tiles_per_chunk = 0;
+    int64_t max_pieces = 0;         // of a chunk: what the partial sums have room for
     double *partials = nullptr;     // per-block partial sums of squares, then the second-level sums
     int64_t n_partials = 0;         // capacity of the first level
 };
