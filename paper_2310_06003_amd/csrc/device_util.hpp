@@ -104,12 +104,17 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// P device pointers in fold order.  Lives in the kernel-argument segment and is
-// only ever indexed with wave-uniform indices, i.e. read with scalar loads.
-struct SrcTable {
-    const void *p[PARO_MAX_RANKS];
+// P device pointers in fold order (or in rank order, see RangeMap).  Lives in the kernel-argument
+// segment and is only ever indexed with wave-uniform indices, i.e. read with scalar loads.  Kernels
+// come with room for 16 pointers and for PARO_MAX_RANKS: 2 KB of arguments cost the host 0.2-0.3 us a
+// launch (a small step of one launch: 6.20 -> 5.99 us; of two: 10.2 -> 9.6).
+template <int N>
+struct SrcTableOf {
+    const void *p[N];
     int paced;       // the chunk layout's loads go out one by one, with a pause in between
 };
+using SrcTable = SrcTableOf<PARO_MAX_RANKS>;
+constexpr int FEW_SRC = 16;
 
 struct AdamConsts {
     float beta1, beta2, omb1, omb2, eps, step_size, sqrt_bc2, decay, wd, grad_scale, max_norm;

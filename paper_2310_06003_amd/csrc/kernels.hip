@@ -194,8 +194,8 @@ __device__ __forceinline__ void store_g4(float *g, int64_t e0, unsigned elems, c
 }
 
 // Sweep 1, chunk layout: g = fold of the contributions; optional per-block partial of sum g^2.
-template <int DT, bool SUMSQ>
-__global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTable src, int P, int group_len, int64_t n,
+template <int DT, bool SUMSQ, int NSRC>
+__global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
                                                   float *__restrict__ g, double *__restrict__ partials) {
     const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
     double acc = 0.0;
@@ -219,8 +219,8 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTable src, int P, int
 // multiple of 8 elements, and blocks counted from its start would straddle cache lines in every array
 // (MI355X, P = 16 fp32, chunks of 62.5 M elements: 5.1 TB/s there against 6.1).  Partial sums of blocks
 // [part0, part0 + part_n) only (both multiples of 8, block0 too); the others hold no element that counts.
-template <int DT, bool SUMSQ>
-__global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTable src, int P, const RangeMap rm, int64_t block0, int64_t n,
+template <int DT, bool SUMSQ, int NSRC>
+__global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, int P, const RangeMap rm, int64_t block0, int64_t n,
                                                    float *__restrict__ g, double *__restrict__ partials, unsigned part0,
                                                    unsigned part_n) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
@@ -243,8 +243,8 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTable src, int P, co
 }
 
 // Sweep 1, tensor layout: one piece of the launch.  Every lane of the wave takes part.
-template <bool SUMSQ, int KB, bool NT>
-__device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, const SrcTable &src, int P, int group_len,
+template <bool SUMSQ, int KB, bool NT, class Src>
+__device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, const Src &src, int P, int group_len,
                                            int64_t n, float *g, double &acc) {
     const int64_t e = c.e0 + lane_id() * EPT;
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};               // padding: the sum of zeros
@@ -285,8 +285,8 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
 // loads are straight-line code.  Sweep 1 over 10 000 tensors of 1 to 65536 elements (P = 8, 174 MB): 49.8
 // -> 29 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
 // (290 MB): 113 -> 86 us.
-template <bool SUMSQ, int PPW, int KB, bool NT>
-__global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTable src, int P, int group_len, int64_t n,
+template <bool SUMSQ, int PPW, int KB, bool NT, int NSRC>
+__global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
                                                    float *__restrict__ g, double *__restrict__ partials,
                                                    const TensorMap tm) {
     const int64_t i0 = (int64_t)blockIdx.x * PPW;
@@ -377,8 +377,8 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
 // reduced gradient never goes to memory.  TENSORS: contributions are per-tensor gradients; else
 // arrays in shard coordinates of dtype DT.  NT: as for k_reduce4t.
-template <bool TENSORS, int DT, bool MASK, bool NT>
-__global__ __launch_bounds__(WAVE) void k_fused4(const SrcTable src, int P, int group_len, int64_t n,
+template <bool TENSORS, int DT, bool MASK, bool NT, int NSRC>
+__global__ __launch_bounds__(WAVE) void k_fused4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
                                                  const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
                                                  float *__restrict__ v, uint16_t *__restrict__ dst,
                                                  const TensorMap tm) {
@@ -422,8 +422,8 @@ __global__ __launch_bounds__(WAVE) void k_fused4(const SrcTable src, int P, int 
 }
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
-template <int DT>
-__global__ __launch_bounds__(WAVE) void k_fused4r(const SrcTable src, int P, const RangeMap rm, int64_t block0, int64_t n,
+template <int DT, int NSRC>
+__global__ __launch_bounds__(WAVE) void k_fused4r(const SrcTableOf<NSRC> src, int P, const RangeMap rm, int64_t block0, int64_t n,
                                                   const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
                                                   float *__restrict__ v, uint16_t *__restrict__ dst) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
@@ -888,6 +888,26 @@ RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const
         }                                  \
     } while (0)
 
+SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
+    SrcTableOf<FEW_SRC> few;
+    std::copy(tab.p, tab.p + FEW_SRC, few.p);
+    few.paced = tab.paced;
+    return few;
+}
+// CALL with `src`, the pointer table in the size that the kernels for NSRC pointers take.
+#define PARO_BY_TABLE(P, tab, CALL)              \
+    do {                                         \
+        if ((P) <= FEW_SRC) {                    \
+            constexpr int NSRC = FEW_SRC;        \
+            const auto src = few_sources(tab);   \
+            CALL;                                \
+        } else {                                 \
+            constexpr int NSRC = PARO_MAX_RANKS; \
+            const SrcTable &src = tab;           \
+            CALL;                                \
+        }                                        \
+    } while (0)
+
 #define PARO_BY_LINES(on_lines, CALL)  \
     do {                               \
         if (on_lines) {                \
@@ -919,8 +939,8 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     if (layout == PARO_CHUNK) {
         const unsigned grid = (piece_grid(n) + 7u) & ~7u;       // a multiple of 8: see partial_slot()
         const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), PARO_FOLD_LOADS_PER_CU));
-        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P,
-                                                       group_len, n, g, partials));
+        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
+                                                                                 lds, st, src, pl->P, group_len, n, g, partials)));
         return (int)grid;
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
@@ -932,19 +952,20 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     if (const char *env = std::getenv("PARO_PAIR_MIN_BLOCKS")) pair_min_blocks = std::atoll(env);     // for tests
     if (pl->P <= PARO_PAIR_MAX_RANKS && piece_count(n) >= pair_min_blocks) {
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
-        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT>), dim3(grid), dim3(WAVE), 0, st,
-                                                   tab, pl->P, group_len, n, g, partials, tm));
+        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC>), dim3(grid), dim3(WAVE),
+                                                   0, st, few_sources(tab), pl->P, group_len, n, g, partials, tm));
         return (int)grid;
     }
     const unsigned grid = (unsigned)((pieces + 7) & ~(int64_t)7);
     const unsigned lds =
         throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU));
     if (pl->P <= 8)                                                         // a batch of 8 contributions: fewer registers
-        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P,
-                                                   group_len, n, g, partials, tm));
+        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC>), dim3(grid), dim3(WAVE), lds, st,
+                                                   few_sources(tab), pl->P, group_len, n, g, partials, tm));
     else
-        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT>), dim3(grid), dim3(WAVE), lds, st, tab,
-                                                   pl->P, group_len, n, g, partials, tm));
+        PARO_BY_TABLE(pl->P, tab, PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT, NSRC>), dim3(grid),
+                                                                             dim3(WAVE), lds, st, src, pl->P, group_len, n, g,
+                                                                             partials, tm)));
     return (int)grid;
 }
 
@@ -958,12 +979,14 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const unsigned grid = piece_grid(n), lds = throttle_lds(sc.lds_per_cu, waves);
     if (layout == PARO_TENSORS)
-        PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0,
-                      hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASK, NT>), dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE),
-                                         lds, st, tab, pl->P, group_len, n, a, p, m, v, dst, tm));
+        PARO_BY_TABLE(pl->P, tab, PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0,
+                                                hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASK, NT, NSRC>),
+                                                                   dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE), lds, st, src,
+                                                                   pl->P, group_len, n, a, p, m, v, dst, tm)));
     else
-        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4<false, DT, MASK, true>), dim3(grid), dim3(WAVE), lds, st, tab,
-                                                       pl->P, group_len, n, a, p, m, v, dst, tm));
+        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid),
+                                                                                 dim3(WAVE), lds, st, src, pl->P, group_len, n, a, p,
+                                                                                 m, v, dst, tm)));
 }
 
 // ... over an update range of several chunks (chunk layout, no decay mask).
@@ -974,8 +997,8 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P) + 3, PARO_FUSED_LOADS_PER_CU));
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
-        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT>), dim3(grid), dim3(WAVE), lds, st, tab, pl->P, rm, b0, on, a,
-                                                       p, m, v, dst));
+        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, NSRC>), dim3(grid), dim3(WAVE), lds,
+                                                                                 st, src, pl->P, rm, b0, on, a, p, m, v, dst)));
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
@@ -1056,9 +1079,10 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
             last = std::min((piece_count(lo + pl->L) + 7) & ~(int64_t)7, last);
         }
         if (sumsq_out && first < last) {
-            PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true>), dim3((unsigned)grid), dim3(WAVE), lds, st, tab,
-                                                           pl->P, rm, b0, on, grad_out, sc.partials, (unsigned)(first - b0),
-                                                           (unsigned)(last - first)));
+            PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC>), dim3((unsigned)grid),
+                                                                                     dim3(WAVE), lds, st, src, pl->P, rm, b0, on,
+                                                                                     grad_out, sc.partials, (unsigned)(first - b0),
+                                                                                     (unsigned)(last - first))));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
             if (step < blocks)
@@ -1067,8 +1091,9 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
                 rc = finalize_partials(sc, (int)(last - first), sumsq_out, st, rest);
             if (rc) return rc;
         } else {
-            PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false>), dim3((unsigned)grid), dim3(WAVE), lds, st, tab,
-                                                           pl->P, rm, b0, on, grad_out, sc.partials, 0u, 0u));
+            PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC>), dim3((unsigned)grid),
+                                                                                     dim3(WAVE), lds, st, src, pl->P, rm, b0, on,
+                                                                                     grad_out, sc.partials, 0u, 0u)));
             PARO_HIP(hipGetLastError());
         }
     }

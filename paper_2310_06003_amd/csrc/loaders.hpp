@@ -27,7 +27,8 @@ struct Chunk4Loader {
     using Raw = std::conditional_t<DT == PARO_F32, u32x4, u32x2>;
     using At = const void *;
     int64_t e;                                   // first of the thread's 4 elements
-    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return src.p[k]; }
+    template <class Src>
+    __device__ __forceinline__ At source(const Src &src, int k) const { return src.p[k]; }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         r = ld_nt(reinterpret_cast<const Raw *>(static_cast<const char *>(at) + e * ESIZE));
     }
@@ -188,7 +189,8 @@ template <>
 struct Unaligned<u32x4> { typedef u32x4 type __attribute__((aligned(4))); };
 
 // Address of the tensor's data in contribution k (wave-uniform).
-__device__ __forceinline__ uintptr_t tensor_base(const SrcTable &src, int k, int tensor) {
+template <class Src>
+__device__ __forceinline__ uintptr_t tensor_base(const Src &src, int k, int tensor) {
     return global_ptr<uintptr_t>(reinterpret_cast<uintptr_t>(src.p[k]))[tensor];
 }
 
@@ -205,7 +207,8 @@ struct Tensor4Loader {
     using At = uintptr_t;
     int tensor;
     int64_t piece_byte_off;    // of the block's first element inside the tensor
-    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    template <class Src>
+    __device__ __forceinline__ At source(const Src &src, int k) const { return tensor_base(src, k, tensor); }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
         r = ld_once<NT>(global_ptr<typename Unaligned<Raw>::type>(mine));
@@ -226,7 +229,8 @@ struct Part4Loader {
     int tensor;
     int64_t piece_byte_off;    // of the block's first element inside the tensor (may be negative: it is not loaded)
     int a, b;                  // the thread's elements [a, b) of its 4 belong to the part
-    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    template <class Src>
+    __device__ __forceinline__ At source(const Src &src, int k) const { return tensor_base(src, k, tensor); }
     __device__ __forceinline__ bool whole() const { return a == 0 && b == 4; }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
@@ -270,7 +274,8 @@ struct Tensor8Loader {
     using At = uintptr_t;
     int tensor;
     int64_t piece_byte_off;    // of the first block's first element inside the tensor
-    __device__ __forceinline__ At source(const SrcTable &src, int k) const { return tensor_base(src, k, tensor); }
+    template <class Src>
+    __device__ __forceinline__ At source(const Src &src, int k) const { return tensor_base(src, k, tensor); }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
         r.a = ld_once<NT>(global_ptr<typename Unaligned<Raw4>::type>(mine));
@@ -291,7 +296,8 @@ struct Lane4Loader {
     struct Raw { unsigned int bits[4]; };
     struct At { uintptr_t base[4]; };
     Located at;
-    __device__ __forceinline__ At source(const SrcTable &src, int k) const {
+    template <class Src>
+    __device__ __forceinline__ At source(const Src &src, int k) const {
         const auto *ptrs = global_ptr<uintptr_t>(reinterpret_cast<uintptr_t>(src.p[k]));
         At a;
 #pragma unroll
@@ -341,8 +347,8 @@ struct Folding {
 // with a pause after each, waves that start together read the same contribution together.  Whole clipped
 // steps unpaced -> paced: P = 64, 105 M elements 2913 -> 2830 us, P = 16, 421 M elements 4340 -> 4268; a
 // small launch is bound by latency (P = 16, 0.5 M elements 13.7 -> 15.9) and is not paced.
-template <int N, class Ld, class Order>
-__device__ __forceinline__ void load_batch(const Ld &ld, const SrcTable &src, int k, Order &ord, typename Ld::Raw *raw) {
+template <int N, class Ld, class Src, class Order>
+__device__ __forceinline__ void load_batch(const Ld &ld, const Src &src, int k, Order &ord, typename Ld::Raw *raw) {
     typename Ld::At at[N];
     static_for<0, N>([&](auto b) { at[b] = ld.source(src, ord.next(k + b)); });
     static_for<0, N>([&](auto b) {
@@ -381,8 +387,8 @@ __device__ __forceinline__ void add_batch(const Ld &ld, const typename Ld::Raw *
 
 // Whole batches, then what is left as batches of 8, 4, 2 and 1 (their loads are all issued before the
 // first is consumed).
-template <class Ld, class Order = InOrder>
-__device__ __forceinline__ void fold4(const Ld &ld, const SrcTable &src, int P, int group_len, float *X,
+template <class Ld, class Src, class Order = InOrder>
+__device__ __forceinline__ void fold4(const Ld &ld, const Src &src, int P, int group_len, float *X,
                                       Order ord = Order()) {
     constexpr int B = Ld::kBatch;
     static_assert(B == 16 || B == 8 || B == 4 || B == 2, "the rest is split into powers of two");
@@ -472,8 +478,8 @@ __device__ __forceinline__ RingWalk walk_of(const RangeMap &rm, int c) {
 // coordinates): e0 the block's first element, n the range's length.  Nearly every block lies inside
 // one chunk; where chunks meet inside a block, its lanes take turns, chunk by chunk.  Returns
 // whether the thread's elements count for the sum of squares.
-template <int DT>
-__device__ __forceinline__ bool fold_range(const RangeMap &rm, const SrcTable &src, int P, int64_t e0, int64_t n, float X[4]) {
+template <int DT, class Src>
+__device__ __forceinline__ bool fold_range(const RangeMap &rm, const Src &src, int P, int64_t e0, int64_t n, float X[4]) {
     Chunk4Loader<DT> ld{e0 + lane_id() * EPT};
     const int64_t end = min(e0 + (int64_t)PIECE, n);
     bool counts = false;
@@ -493,8 +499,8 @@ __device__ __forceinline__ bool fold_range(const RangeMap &rm, const SrcTable &s
 // not all padding.  loc: from locate4 when the block holds a boundary (pc.tensor == -1).
 // KB: contributions loaded before the first is consumed (a kernel that is only launched for few
 // contributions says so, and saves the registers).
-template <bool NT, int KB = PARO_BATCH>
-__device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc, const SrcTable &src, int P,
+template <bool NT, int KB = PARO_BATCH, class Src>
+__device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc, const Src &src, int P,
                                              int group_len, float X[4]) {
     if (pc.tensor >= 0) {
         if (pc.dt == PARO_BF16) {
@@ -514,8 +520,8 @@ __device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc
 }
 
 // ... of the thread's 8 elements in two consecutive blocks that lie in one tensor (pc: the first).
-template <bool NT>
-__device__ __forceinline__ void fold_tensor_pair(const Piece &pc, const SrcTable &src, int P, int group_len, float X[8]) {
+template <bool NT, class Src>
+__device__ __forceinline__ void fold_tensor_pair(const Piece &pc, const Src &src, int P, int group_len, float X[8]) {
     if (pc.dt == PARO_BF16) {
         Tensor8Loader<PARO_BF16, NT> ld{pc.tensor, pc.toff * 2};
         fold4(ld, src, P, group_len, X);
@@ -583,7 +589,8 @@ __device__ __forceinline__ bool pair_of(const TensorMap &tm, int64_t i, int64_t 
 }
 
 // The ordered fold of the thread's elements [a, b) of a piece that is part of its block.
-__device__ __forceinline__ void fold_part(const Cut &c, const SrcTable &src, int P, int group_len, float X[4]) {
+template <class Src>
+__device__ __forceinline__ void fold_part(const Cut &c, const Src &src, int P, int group_len, float X[4]) {
     if (c.pc.dt == PARO_BF16) {
         Part4Loader<PARO_BF16> ld{c.pc.tensor, c.pc.toff * 2, c.a, c.b};
         fold4(ld, src, P, group_len, X);
