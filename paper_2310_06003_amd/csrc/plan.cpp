@@ -47,10 +47,13 @@ void coalesce(std::vector<int> chunks, int64_t L, std::vector<std::pair<int64_t,
     }
 }
 
-void emit_pass(const RingPass &rp, int collective, int64_t L, std::vector<paro_msg_t> *msgs) {
+// only: null, or the one message that is wanted.
+void emit_pass(const RingPass &rp, int collective, int64_t L, const paro::MessageId *only, std::vector<paro_msg_t> *msgs) {
+    if (only && (only->phase != rp.phase || only->ring != rp.ring_id)) return;
     auto mod = [&](int x) { return ((x % rp.n) + rp.n) % rp.n; };
     std::vector<std::pair<int64_t, int64_t>> s, r;
     for (int step = 1; step < rp.n; ++step) {
+        if (only && only->step != step) continue;
         int su = collective == PARO_RS ? mod(rp.idx - step) : mod(rp.idx - step + 1);
         int ru = collective == PARO_RS ? mod(rp.idx - step - 1) : mod(rp.idx - step);
         coalesce(rp.unit(su), L, &s);
@@ -111,6 +114,61 @@ void fold_order(const paro_plan_t *pl, int chunk, int32_t *ranks, int32_t *group
         for (int di = 1; di <= G; ++di) ranks[n++] = grp * G + (oi + di) % G;
     }
     *group_len = G;
+}
+int schedule_messages(const paro_plan_t *pl, int rank, int sched, int collective, const MessageId *only,
+                      std::vector<paro_msg_t> *out) {
+    if (collective != PARO_RS && collective != PARO_AG) return fail(PARO_EINVAL, "paro_schedule: bad collective");
+    if (sched == PARO_SCHED_DEFAULT) sched = pl->sched;
+    if (sched < PARO_RING || sched > PARO_HORING) return fail(PARO_EINVAL, "paro_schedule: bad sched");
+    const int P = pl->P, G = pl->G, g = pl->g;
+    const int j = rank / G, i = rank % G;
+    std::vector<paro_msg_t> &msgs = *out;
+    try {
+        RingPass flat{P, rank, (rank + 1) % P, (rank + P - 1) % P, 0, 1,
+                      [&](int k) { return std::vector<int>{chunk_of_rank(pl, k)}; }};
+        const int ito = j * G + (i + 1) % G, ifrom = j * G + (i + G - 1) % G;
+        const int xto = ((j + 1) % g) * G + i, xfrom = ((j + g - 1) % g) * G + i;
+        // units of the intra-group ring (position = local index b)
+        auto whole_block = [&](int b) {
+            std::vector<int> v;
+            for (int jj = 0; jj < g; ++jj) v.push_back(b * g + jj);
+            return v;
+        };
+        auto own_group_chunk = [&](int b) { return std::vector<int>{b * g + j}; };
+        auto other_groups_chunks = [&](int b) {
+            std::vector<int> v;
+            for (int jj = 0; jj < g; ++jj)
+                if (jj != j) v.push_back(b * g + jj);
+            return v;
+        };
+        // unit of the inter-group ring (position = group index k), inside block i
+        auto group_chunk = [&](int k) { return std::vector<int>{i * g + k}; };
+
+        if (sched == PARO_RING) {
+            emit_pass(flat, collective, pl->L, only, &msgs);
+        } else if (sched == PARO_HRING) {
+            if (collective == PARO_RS) {
+                emit_pass({G, i, ito, ifrom, 0, 1, whole_block}, PARO_RS, pl->L, only, &msgs);
+                emit_pass({g, j, xto, xfrom, 1, 2, group_chunk}, PARO_RS, pl->L, only, &msgs);
+            } else {
+                emit_pass({g, j, xto, xfrom, 1, 1, group_chunk}, PARO_AG, pl->L, only, &msgs);
+                emit_pass({G, i, ito, ifrom, 0, 2, whole_block}, PARO_AG, pl->L, only, &msgs);
+            }
+        } else {  // HO-Ring
+            if (collective == PARO_AG) {
+                emit_pass({G, i, ito, ifrom, 0, 1, own_group_chunk}, PARO_AG, pl->L, only, &msgs);
+                emit_pass({g, j, xto, xfrom, 1, 1, group_chunk}, PARO_AG, pl->L, only, &msgs);
+                if (g > 1) emit_pass({G, i, ito, ifrom, 0, 2, other_groups_chunks}, PARO_AG, pl->L, only, &msgs);
+            } else {
+                if (g > 1) emit_pass({G, i, ito, ifrom, 0, 1, other_groups_chunks}, PARO_RS, pl->L, only, &msgs);
+                emit_pass({G, i, ito, ifrom, 0, 2, own_group_chunk}, PARO_RS, pl->L, only, &msgs);
+                emit_pass({g, j, xto, xfrom, 1, 2, group_chunk}, PARO_RS, pl->L, only, &msgs);
+            }
+        }
+    } catch (const std::bad_alloc &) {
+        return fail(PARO_ENOMEM, "paro_schedule: out of host memory");
+    }
+    return PARO_OK;
 }
 }  // namespace paro
 
@@ -261,57 +319,9 @@ int paro_fold_order(const paro_plan_t *pl, int chunk, int32_t *ranks, int32_t *g
 int64_t paro_schedule(const paro_plan_t *pl, int rank, int sched, int collective, paro_msg_t *out, int64_t cap) {
     if (!rank_ok(pl, rank)) return fail(PARO_ERANGE, "paro_schedule: rank out of range");
     if (cap < 0 || (cap > 0 && !out)) return fail(PARO_EINVAL, "paro_schedule: bad output array");
-    if (collective != PARO_RS && collective != PARO_AG) return fail(PARO_EINVAL, "paro_schedule: bad collective");
-    if (sched == PARO_SCHED_DEFAULT) sched = pl->sched;
-    if (sched < PARO_RING || sched > PARO_HORING) return fail(PARO_EINVAL, "paro_schedule: bad sched");
-    const int P = pl->P, G = pl->G, g = pl->g;
-    const int j = rank / G, i = rank % G;
     std::vector<paro_msg_t> msgs;
-    try {
-        RingPass flat{P, rank, (rank + 1) % P, (rank + P - 1) % P, 0, 1,
-                      [&](int k) { return std::vector<int>{chunk_of_rank(pl, k)}; }};
-        const int ito = j * G + (i + 1) % G, ifrom = j * G + (i + G - 1) % G;
-        const int xto = ((j + 1) % g) * G + i, xfrom = ((j + g - 1) % g) * G + i;
-        // units of the intra-group ring (position = local index b)
-        auto whole_block = [&](int b) {
-            std::vector<int> v;
-            for (int jj = 0; jj < g; ++jj) v.push_back(b * g + jj);
-            return v;
-        };
-        auto own_group_chunk = [&](int b) { return std::vector<int>{b * g + j}; };
-        auto other_groups_chunks = [&](int b) {
-            std::vector<int> v;
-            for (int jj = 0; jj < g; ++jj)
-                if (jj != j) v.push_back(b * g + jj);
-            return v;
-        };
-        // unit of the inter-group ring (position = group index k), inside block i
-        auto group_chunk = [&](int k) { return std::vector<int>{i * g + k}; };
-
-        if (sched == PARO_RING) {
-            emit_pass(flat, collective, pl->L, &msgs);
-        } else if (sched == PARO_HRING) {
-            if (collective == PARO_RS) {
-                emit_pass({G, i, ito, ifrom, 0, 1, whole_block}, PARO_RS, pl->L, &msgs);
-                emit_pass({g, j, xto, xfrom, 1, 2, group_chunk}, PARO_RS, pl->L, &msgs);
-            } else {
-                emit_pass({g, j, xto, xfrom, 1, 1, group_chunk}, PARO_AG, pl->L, &msgs);
-                emit_pass({G, i, ito, ifrom, 0, 2, whole_block}, PARO_AG, pl->L, &msgs);
-            }
-        } else {  // HO-Ring
-            if (collective == PARO_AG) {
-                emit_pass({G, i, ito, ifrom, 0, 1, own_group_chunk}, PARO_AG, pl->L, &msgs);
-                emit_pass({g, j, xto, xfrom, 1, 1, group_chunk}, PARO_AG, pl->L, &msgs);
-                if (g > 1) emit_pass({G, i, ito, ifrom, 0, 2, other_groups_chunks}, PARO_AG, pl->L, &msgs);
-            } else {
-                if (g > 1) emit_pass({G, i, ito, ifrom, 0, 1, other_groups_chunks}, PARO_RS, pl->L, &msgs);
-                emit_pass({G, i, ito, ifrom, 0, 2, own_group_chunk}, PARO_RS, pl->L, &msgs);
-                emit_pass({g, j, xto, xfrom, 1, 2, group_chunk}, PARO_RS, pl->L, &msgs);
-            }
-        }
-    } catch (const std::bad_alloc &) {
-        return fail(PARO_ENOMEM, "paro_schedule: out of host memory");
-    }
+    const int rc = schedule_messages(pl, rank, sched, collective, nullptr, &msgs);
+    if (rc != PARO_OK) return rc;
     for (int64_t n = 0; n < (int64_t)msgs.size() && n < cap; ++n) out[n] = msgs[n];
     return (int64_t)msgs.size();
 }

@@ -92,6 +92,13 @@ inline int owner_of_chunk(const paro_plan_t *pl, int chunk) {
 }
 // [begin, begin+len) of a rank's range for a sharding letter
 void letter_range(const paro_plan_t *pl, int rank, char letter, int64_t *begin, int64_t *len);
+// One rank's messages of a collective, in the order of the public table: all of them, or those of one
+// (phase, ring, step).
+struct MessageId {
+    int phase, ring, step;
+};
+int schedule_messages(const paro_plan_t *pl, int rank, int sched, int collective, const MessageId *only,
+                      std::vector<paro_msg_t> *out);
 // ranks in fold order for a chunk, and the run length of the first-level sums
 void fold_order(const paro_plan_t *pl, int chunk, int32_t *ranks, int32_t *group_len);
 }  // namespace paro
