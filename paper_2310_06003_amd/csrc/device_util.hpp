@@ -39,6 +39,9 @@ namespace {
 #ifndef PARO_FOLD_LOADS_PER_CU
 #define PARO_FOLD_LOADS_PER_CU 224
 #endif
+#ifndef PARO_FOLD_WIDE_LOADS_PER_CU
+#define PARO_FOLD_WIDE_LOADS_PER_CU 192   // more than PARO_BATCH contributions
+#endif
 #ifndef PARO_FUSED_LOADS_PER_CU
 #define PARO_FUSED_LOADS_PER_CU 190
 #endif

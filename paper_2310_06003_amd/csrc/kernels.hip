@@ -17,8 +17,7 @@
 //             run per compute unit: fewer requests outstanding fight less over
 //             DRAM pages (another 3-6 %).  The tensor layout over many small
 //             tensors wants the opposite - its waves wait on look-ups with no
-//             data in flight - and gets two blocks per wave (few contributions)
-//             or every wave the registers allow.
+//             data in flight - and gets every wave the registers allow.
 //   caches    everything is touched once: streaming (non-temporal) loads; stores
 //             through per-wave buffer descriptors, which let the instruction say
 //             "streaming, system scope" (nt sc1: 2 % better than nt alone).
@@ -26,13 +25,13 @@
 //             (never re-associated, never contracted into FMAs) so the result
 //             is bit-identical to a reduce-scatter ring run in that order
 //   norm      squares are exact in fp64; per-thread fp64 sums -> wave shuffles
-//             -> one partial per block -> a small kernel adds the partials in a
-//             fixed order, in two levels.  No atomics: run-to-run identical.
-//   tensors   the tensor layout and the weight-decay mask need the tensor an
-//             element belongs to: a per-block table (built once per chunk) answers
-//             with a single look-up; a block with a tensor boundary inside finds
-//             its elements' tensors with one load per lane and a search across
-//             the lanes' registers.
+//             -> one partial per block -> added in a fixed order, by a small
+//             kernel, by sweep 2's waves, or both.  No atomics: run-to-run identical.
+//   tensors   the tensor layout needs the tensor an element belongs to: a list of
+//             pieces (built once per chunk), each inside one tensor, answers with
+//             a single look-up; a block of very many tensors finds its elements'
+//             tensors with one load per lane and a search across the lanes'
+//             registers.  The weight-decay mask has a per-block table.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -283,7 +282,7 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
 // by one - pointer of the table, pointer of the tensor, a branch on its alignment, the load - the second
 // was P round trips to the scalar cache in a row; now all pointers of a batch are fetched together and the
 // loads are straight-line code.  Sweep 1 over 10 000 tensors of 1 to 65536 elements (P = 8, 174 MB): 49.8
-// -> 29 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
+// -> 35 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
 // (290 MB): 113 -> 86 us.
 template <bool SUMSQ, int PPW, int KB, bool NT, int NSRC>
 __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
@@ -535,6 +534,10 @@ int fold_waves(int per_wave, int loads_per_cu) {
 }
 // Loads a wave of the fold has in flight: a batch of contributions.
 int fold_loads(int P) { return std::min(P, PARO_BATCH); }
+// The chunk layout's budget.  More contributions than one batch are more DRAM pages than the wave's loads in
+// flight say: 12 waves instead of 14 (whole clipped steps: P = 64, 105 M elements 2786 -> 2743 us; P = 32, 77 M
+// 1232 -> 1226; 10 waves: 2735 and 1273).
+int fold_budget(int P) { return P > PARO_BATCH ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU; }
 
 // What a launch needs from the device besides the caller's buffers: the LDS size behind the
 // occupancy throttle and the scratch array of partial sums (per-block sums of a sweep-1 launch,
@@ -938,7 +941,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     double *partials = sc.partials;
     if (layout == PARO_CHUNK) {
         const unsigned grid = (piece_grid(n) + 7u) & ~7u;       // a multiple of 8: see partial_slot()
-        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), PARO_FOLD_LOADS_PER_CU));
+        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl->P)));
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
                                                                                  lds, st, src, pl->P, group_len, n, g, partials)));
         return (int)grid;
@@ -1066,7 +1069,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), PARO_FOLD_LOADS_PER_CU));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl->P)));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;
