@@ -33,3 +33,31 @@ def test_every_chunk_of_the_range_in_its_own_order(paro, P, G, strategy, sched, 
         for max_norm in (0.0, 0.01):                                        # one sweep; two sweeps, clipped
             run_rank(paro, pl, lay, strategy, sched, rank, dev, host, state, hp_dict(P, max_norm=max_norm), 7,
                      check_unfused=max_norm > 0)
+
+
+def test_a_range_that_takes_several_launches_for_its_norm(paro):
+    """The entry point that allocates nothing has room for the partial sums of 2^30 elements: a longer
+    update range is swept in pieces whose sums are added in order.  Same results as the plan's own scratch,
+    which holds them all."""
+    import torch
+    from harness import DEV, hp_struct, stream
+    P, L = 2, (1 << 29) + 264
+    pl = paro.paro_plan(P, 1, "NNN", [P * L])
+    n = P * L
+    contrib = wl.chunk_contribs(P, n, 90, device=DEV)
+    hp = hp_struct(paro, hp_dict(P, max_norm=0.01), 3)
+    got = []
+    for static in (True, False):
+        p, m, v = wl.master_state(n, 91, device=DEV)
+        g = torch.empty(n, dtype=torch.float32, device=DEV)
+        ss = torch.zeros(1, dtype=torch.float64, device=DEV)
+        dst = torch.zeros(n, dtype=torch.bfloat16, device=DEV)
+        ptrs = [t.data_ptr() for t in contrib]
+        tail = (g.data_ptr(), ss.data_ptr(), p.data_ptr(), m.data_ptr(), v.data_ptr(), dst.data_ptr(), stream())
+        if static:
+            paro.paro_step_fused_static(pl, 1, ptrs, hp, *tail)
+        else:
+            paro.paro_step_fused(pl, 1, ptrs, paro.PARO_CHUNK, hp, *tail)
+        got.append((float(ss.item()), g, p, m, v, dst))
+    assert abs(got[0][0] - got[1][0]) <= 1e-12 * got[1][0]
+    assert all(torch.equal(a, b) for a, b in zip(got[0][1:], got[1][1:]))
