@@ -190,10 +190,22 @@ __device__ __forceinline__ V ld_nt(const V *p) { return __builtin_nontemporal_lo
 template <class V>
 __device__ __forceinline__ V ld_nt(const __attribute__((address_space(1))) V *p) { return __builtin_nontemporal_load(p); }
 
-template <bool NT, class Ptr>
-__device__ __forceinline__ auto ld_once(Ptr p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
+// Vector load of 4 elements at any address that suits one element (2 bytes of the 2-byte dtypes, 4 of
+// fp32); NT: streaming.  The alignment is part of the type of the pointer that is dereferenced, so the type is
+// named here and not handed in as a template argument, which would drop it.
+template <class V, bool NT>
+__device__ __forceinline__ V ld_any(uintptr_t a) {
+    typedef u32x2 u32x2_at2 __attribute__((aligned(2)));
+    typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+    if constexpr (std::is_same_v<V, u32x2>) {
+        const auto *p = reinterpret_cast<const __attribute__((address_space(1))) u32x2_at2 *>(a);
+        if constexpr (NT) return __builtin_nontemporal_load(p);
+        else return *p;
+    } else {
+        const auto *p = reinterpret_cast<const __attribute__((address_space(1))) u32x4_at4 *>(a);
+        if constexpr (NT) return __builtin_nontemporal_load(p);
+        else return *p;
+    }
 }
 
 // ---- stores through per-wave buffer descriptors.  A block's stores to one array go through a

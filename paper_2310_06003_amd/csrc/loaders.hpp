@@ -181,12 +181,6 @@ __device__ __forceinline__ void locate4(const TensorMap &tm, int seg, int64_t f0
 // block's elements lie in one tensor: one vector load fetches the thread's 4 values, as in the chunk
 // layout, wherever the tensor's data start (the hardware takes vector loads at any address; a branch
 // on the alignment, source by source, costs more than the misaligned load does).
-template <class V>
-struct Unaligned;
-template <>
-struct Unaligned<u32x2> { typedef u32x2 type __attribute__((aligned(2))); };
-template <>
-struct Unaligned<u32x4> { typedef u32x4 type __attribute__((aligned(4))); };
 
 // Address of the tensor's data in contribution k (wave-uniform).
 template <class Src>
@@ -211,7 +205,7 @@ struct Tensor4Loader {
     __device__ __forceinline__ At source(const Src &src, int k) const { return tensor_base(src, k, tensor); }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
-        r = ld_once<NT>(global_ptr<typename Unaligned<Raw>::type>(mine));
+        r = ld_any<Raw, NT>(mine);
     }
     __device__ __forceinline__ void unpack(const Raw &r, float x[4]) const { Chunk4Loader<DT>::to_f32(r, x); }
 };
@@ -236,7 +230,7 @@ struct Part4Loader {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
         if (whole()) {
             using V = typename Chunk4Loader<DT>::Raw;
-            const V v = ld_once<false>(global_ptr<typename Unaligned<V>::type>(mine));
+            const V v = ld_any<V, false>(mine);
             r.w[0] = v.x; r.w[1] = v.y;
             if constexpr (DT == PARO_F32) { r.w[2] = v.z; r.w[3] = v.w; }
         } else {
@@ -278,8 +272,8 @@ struct Tensor8Loader {
     __device__ __forceinline__ At source(const Src &src, int k) const { return tensor_base(src, k, tensor); }
     __device__ __forceinline__ void load(At at, Raw &r) const {
         const uintptr_t mine = at + (uintptr_t)piece_byte_off + (uintptr_t)lane_id() * (4 * ESIZE);
-        r.a = ld_once<NT>(global_ptr<typename Unaligned<Raw4>::type>(mine));
-        r.b = ld_once<NT>(global_ptr<typename Unaligned<Raw4>::type>(mine + (uintptr_t)PIECE * ESIZE));
+        r.a = ld_any<Raw4, NT>(mine);
+        r.b = ld_any<Raw4, NT>(mine + (uintptr_t)PIECE * ESIZE);
     }
     __device__ __forceinline__ void unpack(const Raw &r, float x[8]) const {
         Chunk4Loader<DT>::to_f32(r.a, x);
