@@ -101,6 +101,7 @@ constexpr int FINALIZE_CHUNK = 8192;  // partials per block in its first level: 
 constexpr int NORM_DIRECT_PARTIALS = 2048;      // partials that every wave of sweep 2 adds up itself
 constexpr int NORM_SLICES = 8;                  // else: slice sums that it does (one scalar load) ...
 constexpr int NORM_SLICES_PARTIALS = 131072;    // ... up to so many partials (33.5 M elements)
+constexpr int NORM_ONE_BLOCK_PARTIALS = 2 * FINALIZE_TPB * NORM_SLICES;     // slices and total by one block up to here
 static_assert(TILE == PIECE, "the per-tile table has one entry per block");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

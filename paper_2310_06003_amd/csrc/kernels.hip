@@ -51,8 +51,23 @@
 namespace {
 
 // ---------------------------------------------------------------------- Adam
+// sums[k0] + sums[k0 + STRIDE] + ... up to sums[n - 1], in that order; U loads in flight at a time.
+template <int STRIDE, int U>
+__device__ __forceinline__ double strided_sum(const double *__restrict__ sums, int k0, int n) {
+    double acc = 0.0;
+    for (; k0 < n; k0 += U * STRIDE) {
+        double x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = (k0 + u * STRIDE < n) ? sums[k0 + u * STRIDE] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += x[u];
+    }
+    return acc;
+}
+
 // The global sum of squares as sweep 2 gets it: n sums to be added up in a fixed order, the same in
 // every wave.  Lanes hold the result.
+template <int U = 8>
 __device__ __forceinline__ double norm_total(const double *__restrict__ sums, int n) {
     if (n == 1) return sums[0];
     if (n == NORM_SLICES) {                                        // one scalar load
@@ -61,14 +76,7 @@ __device__ __forceinline__ double norm_total(const double *__restrict__ sums, in
         for (int k = 1; k < NORM_SLICES; ++k) s += sums[k];
         return s;
     }
-    double acc = 0.0;
-    for (int k0 = lane_id(); k0 < n; k0 += 8 * WAVE) {
-        double x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = (k0 + u * WAVE < n) ? sums[k0 + u * WAVE] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += x[u];
-    }
+    double acc = strided_sum<WAVE, U>(sums, lane_id(), n);
     for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, WAVE);
     return acc;
 }
@@ -319,20 +327,49 @@ __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, i
 
 // Adds partials in a fixed order: block b takes the slice [b*chunk, b*chunk + chunk) of the n
 // values; thread t adds its slice's elements t, t+T, t+2T, ... (eight loads in flight at a time,
-// added in index order); then the fixed block tree.  Launched as many-blocks -> one block.
+// added in index order); then the fixed block tree.
 __global__ __launch_bounds__(FINALIZE_TPB) void k_finalize(const double *__restrict__ partials, int n, int chunk,
                                                            double *out) {
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double acc = 0.0;
-    for (int k0 = lo + threadIdx.x; k0 < hi; k0 += 8 * FINALIZE_TPB) {
-        double x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = (k0 + u * FINALIZE_TPB < hi) ? partials[k0 + u * FINALIZE_TPB] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += x[u];
-    }
-    const double s = block_sum(acc);
+    const double s = block_sum(strided_sum<FINALIZE_TPB, 8>(partials, lo + threadIdx.x, hi));
     if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// What sweep 2's waves do with n sums, for the call that leaves the total itself: the same adds in the
+// same order, so the same value to the last bit.
+__global__ __launch_bounds__(WAVE) void k_norm_total(const double *__restrict__ sums, int n, double *out) {
+    const double total = norm_total<NORM_DIRECT_PARTIALS / WAVE>(sums, n);      // all loads in flight
+    if (lane_id() == 0) *out = total;
+}
+
+// The NORM_SLICES slice sums of k_finalize and their total in one small launch: block_sum() of every slice,
+// then the slices in order.
+__global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double *__restrict__ partials, int n, int chunk,
+                                                                    double *out) {
+    __shared__ double s_wave[NORM_SLICES][FINALIZE_TPB / WAVE];
+    double acc[NORM_SLICES];
+#pragma unroll
+    for (int b = 0; b < NORM_SLICES; ++b)
+        acc[b] = strided_sum<FINALIZE_TPB, NORM_ONE_BLOCK_PARTIALS / NORM_SLICES / FINALIZE_TPB>(
+            partials, b * chunk + (int)threadIdx.x, min(n, (b + 1) * chunk));
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+#pragma unroll
+    for (int b = 0; b < NORM_SLICES; ++b) {
+        const double s = wave_sum(acc[b]);
+        if (lane == 0) s_wave[b][wave] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < NORM_SLICES) {
+        double r = s_wave[threadIdx.x][0];
+        for (int w = 1; w < FINALIZE_TPB / WAVE; ++w) r += s_wave[threadIdx.x][w];
+        s_wave[threadIdx.x][0] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = s_wave[0][0];
+        for (int b = 1; b < NORM_SLICES; ++b) s += s_wave[b][0];
+        *out = s;
+    }
 }
 
 // Sweep 2: Adam on the stored gradient, optionally packing the low-precision parameters.
@@ -1015,8 +1052,16 @@ struct NormSums {
     double *out;
 };
 
+// The total of what is left, in its place: for the call that no sweep 2 follows.
+int total_of(const NormSums &s, hipStream_t st) {
+    hipLaunchKernelGGL(k_norm_total, dim3(1), dim3(WAVE), 0, st, s.sums, s.n, s.out);
+    PARO_HIP(hipGetLastError());
+    return PARO_OK;
+}
+
 // Adds the n_part partial sums a sweep-1 launch left in the scratch array into *out (device) - or, with
-// `rest`, only as far as sweep 2 goes on by itself, and *rest says from where.  Every kernel more in this
+// `rest`, only as far as sweep 2 goes on by itself, and *rest says from where.  Either way the same adds in the
+// same order: the fused step clips by the value that paro_reduce_shard leaves, to the last bit.  Every kernel more in this
 // chain of short dependent ones costs 2-3 us of a step; what a wave of sweep 2 adds up beside its state
 // loads is hidden while it is little.  Whole clipped steps at P = 8, bf16, with the chain of up to two
 // small kernels that ended in one scalar, and now:
@@ -1026,25 +1071,27 @@ struct NormSums {
 //   16.8 M (65536; eight slice sums)                        135.7 -> 133.7
 // Sixteen slice sums fetched one after the other took back all of it at 16 M; eight are one scalar load.
 int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st, NormSums *rest = nullptr) {
-    if (rest && n_part <= NORM_DIRECT_PARTIALS) {
-        *rest = NormSums{sc.partials, n_part, out};
+    if (n_part <= NORM_DIRECT_PARTIALS) {
+        const NormSums all{sc.partials, n_part, out};
+        return rest ? (*rest = all, PARO_OK) : total_of(all, st);
+    }
+    const int chunk = (n_part + NORM_SLICES - 1) / NORM_SLICES;
+    if (!rest && n_part <= NORM_ONE_BLOCK_PARTIALS) {
+        hipLaunchKernelGGL(k_norm_slices_total, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, chunk, out);
+        PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
-    if (rest && n_part <= NORM_SLICES_PARTIALS) {
-        const int chunk = (n_part + NORM_SLICES - 1) / NORM_SLICES;
+    if (n_part <= NORM_SLICES_PARTIALS) {
         hipLaunchKernelGGL(k_finalize, dim3(NORM_SLICES), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, chunk, sc.level2);
         PARO_HIP(hipGetLastError());
-        *rest = NormSums{sc.level2, NORM_SLICES, out};
-        return PARO_OK;
+        const NormSums slices{sc.level2, NORM_SLICES, out};
+        return rest ? (*rest = slices, PARO_OK) : total_of(slices, st);
     }
-    if (n_part > 2 * FINALIZE_CHUNK) {        // two levels: slices of FINALIZE_CHUNK partials, then their sums
-        const int nb = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
-        hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, FINALIZE_CHUNK, sc.level2);
-        PARO_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.level2, nb, nb, out);
-    } else {
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, n_part, out);
-    }
+    // two levels: slices of FINALIZE_CHUNK partials, then their sums
+    const int nb = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
+    hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, FINALIZE_CHUNK, sc.level2);
+    PARO_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.level2, nb, nb, out);
     PARO_HIP(hipGetLastError());
     if (rest) *rest = NormSums{out, 1, nullptr};
     return PARO_OK;
@@ -1052,13 +1099,8 @@ int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st
 
 // ... and the sums of several launches, in sc.chunk_sums.
 int finalize_sums(const Scratch &sc, int n, double *out, hipStream_t st, NormSums *rest) {
-    if (rest) {
-        *rest = NormSums{sc.chunk_sums, n, out};
-        return PARO_OK;
-    }
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.chunk_sums, n, n, out);
-    PARO_HIP(hipGetLastError());
-    return PARO_OK;
+    const NormSums all{sc.chunk_sums, n, out};
+    return rest ? (*rest = all, PARO_OK) : total_of(all, st);
 }
 
 // Sweep 1 over an update range of several chunks, chunk layout: one launch, or, where the norm covers
