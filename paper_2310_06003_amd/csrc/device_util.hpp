@@ -102,6 +102,7 @@ constexpr int NORM_DIRECT_PARTIALS = 2048;      // partials that every wave of s
 constexpr int NORM_SLICES = 8;                  // else: slice sums that it does (one scalar load) ...
 constexpr int NORM_SLICES_PARTIALS = 131072;    // ... up to so many partials (33.5 M elements)
 constexpr int NORM_ONE_BLOCK_PARTIALS = 2 * FINALIZE_TPB * NORM_SLICES;     // slices and total by one block up to here
+constexpr unsigned NORM_GROUP = PARO_STATIC_MAX_CHUNK / PIECE;              // blocks of a range whose partials are added up together
 static_assert(TILE == PIECE, "the per-tile table has one entry per block");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));

@@ -226,6 +226,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, in
 // multiple of 8 elements, and blocks counted from its start would straddle cache lines in every array
 // (MI355X, P = 16 fp32, chunks of 62.5 M elements: 5.1 TB/s there against 6.1).  Partial sums of blocks
 // [part0, part0 + part_n) only (both multiples of 8, block0 too); the others hold no element that counts.
+// The partials are laid out group by group (NORM_GROUP blocks), each like a launch of its own.
 template <int DT, bool SUMSQ, int NSRC>
 __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, int P, const RangeMap rm, int64_t block0, int64_t n,
                                                    float *__restrict__ g, double *__restrict__ partials, unsigned part0,
@@ -244,7 +245,8 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, i
         const unsigned b = blockIdx.x - part0;
         if (b < part_n) {
             const double s = wave_sum(acc);
-            if (lane_id() == 0) partials[(b & 7u) * (part_n >> 3) + (b >> 3)] = s;     // see partial_slot()
+            const unsigned group = b & ~(NORM_GROUP - 1), in_group = min(part_n - group, NORM_GROUP), k = b - group;
+            if (lane_id() == 0) partials[group + (k & 7u) * (in_group >> 3) + (k >> 3)] = s;     // see partial_slot()
         }
     }
 }
@@ -585,7 +587,7 @@ struct Scratch {
     double *partials;
     int64_t n_partials;    // a multiple of 8
     double *level2;
-    double *chunk_sums;    // [PARO_MAX_RANKS] one sum per chunk of an update range of several chunks
+    double *chunk_sums;    // [range_sums()] one sum per chunk, or per group of blocks, of an update range of several chunks
     bool plan_tables;      // the plan's device tables (offset tables, per-tile tables) exist
 };
 
@@ -593,6 +595,13 @@ struct Scratch {
 constexpr int64_t level2_sums(int64_t n_part) {
     const int64_t n = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
     return n < NORM_SLICES ? NORM_SLICES : n;
+}
+
+// Room for the sums of a range with n_part partials: of its chunks, or of its groups, cut once more where a
+// launch ends (MAX_GRID is a multiple of the group) or the own chunk does.
+constexpr int64_t range_sums(int64_t n_part) {
+    const int64_t n = n_part / NORM_GROUP + 3;
+    return n < PARO_MAX_RANKS ? (int64_t)PARO_MAX_RANKS : n;
 }
 
 Scratch plan_scratch(const paro_plan_t *pl) {
@@ -648,7 +657,7 @@ int fill_tables(const paro_plan_t *pl, paro_device_tables &d) {
     if (n_part < PARO_MIN_PARTIALS) n_part = PARO_MIN_PARTIALS;
     d.n_partials = n_part;
     const int64_t n_level2 = level2_sums(n_part);
-    PARO_HIP(hipMalloc(reinterpret_cast<void **>(&d.partials), (n_part + n_level2 + PARO_MAX_RANKS) * sizeof(double)));
+    PARO_HIP(hipMalloc(reinterpret_cast<void **>(&d.partials), (n_part + n_level2 + range_sums(n_part)) * sizeof(double)));
     return PARO_OK;
 }
 
@@ -1070,26 +1079,27 @@ int total_of(const NormSums &s, hipStream_t st) {
 //   1.5 M (5860; eight slice sums)                           21.7 -> 19.6
 //   16.8 M (65536; eight slice sums)                        135.7 -> 133.7
 // Sixteen slice sums fetched one after the other took back all of it at 16 M; eight are one scalar load.
-int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st, NormSums *rest = nullptr) {
+int finalize_partials(const Scratch &sc, const double *partials, int n_part, double *out, hipStream_t st,
+                      NormSums *rest = nullptr) {
     if (n_part <= NORM_DIRECT_PARTIALS) {
-        const NormSums all{sc.partials, n_part, out};
+        const NormSums all{partials, n_part, out};
         return rest ? (*rest = all, PARO_OK) : total_of(all, st);
     }
     const int chunk = (n_part + NORM_SLICES - 1) / NORM_SLICES;
     if (!rest && n_part <= NORM_ONE_BLOCK_PARTIALS) {
-        hipLaunchKernelGGL(k_norm_slices_total, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, chunk, out);
+        hipLaunchKernelGGL(k_norm_slices_total, dim3(1), dim3(FINALIZE_TPB), 0, st, partials, n_part, chunk, out);
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
     if (n_part <= NORM_SLICES_PARTIALS) {
-        hipLaunchKernelGGL(k_finalize, dim3(NORM_SLICES), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, chunk, sc.level2);
+        hipLaunchKernelGGL(k_finalize, dim3(NORM_SLICES), dim3(FINALIZE_TPB), 0, st, partials, n_part, chunk, sc.level2);
         PARO_HIP(hipGetLastError());
         const NormSums slices{sc.level2, NORM_SLICES, out};
         return rest ? (*rest = slices, PARO_OK) : total_of(slices, st);
     }
     // two levels: slices of FINALIZE_CHUNK partials, then their sums
     const int nb = (n_part + FINALIZE_CHUNK - 1) / FINALIZE_CHUNK;
-    hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(FINALIZE_TPB), 0, st, sc.partials, n_part, FINALIZE_CHUNK, sc.level2);
+    hipLaunchKernelGGL(k_finalize, dim3(nb), dim3(FINALIZE_TPB), 0, st, partials, n_part, FINALIZE_CHUNK, sc.level2);
     PARO_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FINALIZE_TPB), 0, st, sc.level2, nb, nb, out);
     PARO_HIP(hipGetLastError());
@@ -1097,7 +1107,7 @@ int finalize_partials(const Scratch &sc, int n_part, double *out, hipStream_t st
     return PARO_OK;
 }
 
-// ... and the sums of several launches, in sc.chunk_sums.
+// ... and the sums of several launches or groups, in sc.chunk_sums.
 int finalize_sums(const Scratch &sc, int n, double *out, hipStream_t st, NormSums *rest) {
     const NormSums all{sc.chunk_sums, n, out};
     return rest ? (*rest = all, PARO_OK) : total_of(all, st);
@@ -1105,6 +1115,8 @@ int finalize_sums(const Scratch &sc, int n, double *out, hipStream_t st, NormSum
 
 // Sweep 1 over an update range of several chunks, chunk layout: one launch, or, where the norm covers
 // the whole range and the scratch array is too small for its partial sums, one for each piece that fits.
+// The norm is formed in groups of NORM_GROUP blocks, as many as the static array holds, whose sums are added
+// in order: the same value from either scratch array, however many launches it takes.
 // own >= 0: the sum of squares of that chunk alone.
 int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_t on, int own, const void *const *contrib,
                     float *grad_out, double *sumsq_out, hipStream_t st, NormSums *rest) {
@@ -1115,6 +1127,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;
+    bool one_sum = false;
     for (int64_t b0 = 0; b0 < blocks; b0 += step) {
         const int64_t grid = std::min(step, blocks - b0);
         int64_t first = b0, last = b0 + grid;                     // the blocks whose squares count
@@ -1130,11 +1143,15 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
                                                                                      (unsigned)(last - first))));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
-            if (step < blocks)
-                rc = finalize_partials(sc, (int)(last - first), sc.chunk_sums + n_sums++, st);
-            else
-                rc = finalize_partials(sc, (int)(last - first), sumsq_out, st, rest);
-            if (rc) return rc;
+            one_sum = step >= blocks && last - first <= NORM_GROUP;
+            for (int64_t k = 0; k < last - first; k += NORM_GROUP) {
+                const int n_part = (int)std::min(last - first - k, (int64_t)NORM_GROUP);
+                if (one_sum)
+                    rc = finalize_partials(sc, sc.partials, n_part, sumsq_out, st, rest);
+                else
+                    rc = finalize_partials(sc, sc.partials + k, n_part, sc.chunk_sums + n_sums++, st);
+                if (rc) return rc;
+            }
         } else {
             PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC>), dim3((unsigned)grid),
                                                                                      dim3(WAVE), lds, st, src, pl->P, rm, b0, on,
@@ -1142,7 +1159,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
             PARO_HIP(hipGetLastError());
         }
     }
-    return sumsq_out && step < blocks ? finalize_sums(sc, n_sums, sumsq_out, st, rest) : PARO_OK;
+    return sumsq_out && !one_sum ? finalize_sums(sc, n_sums, sumsq_out, st, rest) : PARO_OK;
 }
 
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own
@@ -1167,8 +1184,8 @@ int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *co
             const int n_part = launch_reduce<true>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this chunk's partials are added up first
-            rc = per_chunk ? finalize_partials(sc, n_part, sc.chunk_sums + (c - c0), st)
-                           : finalize_partials(sc, n_part, sumsq_out, st, rest);
+            rc = per_chunk ? finalize_partials(sc, sc.partials, n_part, sc.chunk_sums + (c - c0), st)
+                           : finalize_partials(sc, sc.partials, n_part, sumsq_out, st, rest);
             if (rc) return rc;
         } else {
             launch_reduce<false>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
@@ -1243,6 +1260,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
 // runs on holds its own copy of this array, at its own address, until the process ends.
 constexpr int64_t STATIC_PARTIALS = PARO_STATIC_MAX_CHUNK / PIECE;
 constexpr int64_t STATIC_LEVEL2 = level2_sums(STATIC_PARTIALS);
+static_assert(STATIC_PARTIALS == NORM_GROUP, "a launch on the static array is one group of the norm");
 static __device__ __align__(256) double scratch[STATIC_PARTIALS + STATIC_LEVEL2 + PARO_MAX_RANKS];
 
 constexpr int MAX_DEVICES = 64;
