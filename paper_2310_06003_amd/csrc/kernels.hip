@@ -752,14 +752,6 @@ void list_pieces(const paro_plan_t *pl, int64_t c, std::vector<paro_piece_info> 
         std::stable_partition(tab->begin(), tab->end(), [](const paro_piece_info &x) { return (x.where & 0x1FFFF) != TILE << 8 || x.tensor == -1; });
 }
 
-// Whether nearly every piece starts on a multiple of 64 elements inside its tensor: on a cache line, if
-// the tensor does.
-bool mostly_on_lines(const std::vector<paro_piece_info> &tab) {
-    size_t on = 0;
-    for (const paro_piece_info &x : tab) on += x.tensor >= 0 && (x.where >> 19) % 64 == 0;
-    return on >= tab.size() - tab.size() / 8;
-}
-
 // Builds, once per chunk, a table of the chunks of a rank's update range.  Too large a one (chunks of more
 // than 4 Mi tiles, or what the environment variable PARO_TILE_TABLE_MAX_TILES says) is not built; the
 // kernels then search the offset table for every block.
@@ -773,6 +765,7 @@ int ensure_table(paro_plan_t *pl, int rank, std::vector<Info *> &tabs, std::vect
     std::vector<Info> tab;
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {
         if (tried[(size_t)c]) continue;
+        if constexpr (std::is_same_v<Info, paro_piece_info>) pl->dev.on_lines[(size_t)c] = paro::on_cache_lines(pl, c);
         if (d.tiles_per_chunk > max_tiles) {
             tried[(size_t)c] = 1;                    // decided: this chunk works without a table
             continue;
@@ -790,10 +783,7 @@ int ensure_table(paro_plan_t *pl, int rank, std::vector<Info *> &tabs, std::vect
             return rc;
         }
         tabs[(size_t)c] = dev_tab;
-        if constexpr (std::is_same_v<Info, paro_piece_info>) {
-            pl->dev.n_pieces[(size_t)c] = (uint32_t)tab.size();
-            pl->dev.on_lines[(size_t)c] = mostly_on_lines(tab);
-        }
+        if constexpr (std::is_same_v<Info, paro_piece_info>) pl->dev.n_pieces[(size_t)c] = (uint32_t)tab.size();
         tried[(size_t)c] = 1;
     }
     return PARO_OK;

@@ -565,11 +565,17 @@ __device__ __forceinline__ Cut cut_of(const TensorMap &tm, int64_t i, int64_t n)
     return c;
 }
 
-// Whether the i-th and the next piece are whole consecutive blocks inside one tensor; *pc: the first.
-// A piece that ends before its block does says so: two whole ones lie inside the launch but for the
-// last block of the chunk, which n tells apart.
+// Whether the i-th and the next piece (without a list: block) are whole consecutive blocks inside one tensor;
+// *pc: the first.  A piece that ends before its block does says so: two whole ones lie inside the launch but
+// for the last block of the chunk, which n tells apart.
 __device__ __forceinline__ bool pair_of(const TensorMap &tm, int64_t i, int64_t n, Piece *pc, int64_t *e0) {
-    if (!tm.pieces || i + 1 >= tm.n_pieces) return false;
+    if (!tm.pieces) {
+        *e0 = i * PIECE;
+        if (*e0 + 2 * PIECE > n) return false;
+        *pc = piece_of(tm, *e0, n);
+        return pc->tensor >= 0 && piece_of(tm, *e0 + PIECE, n).tensor == pc->tensor;
+    }
+    if (i + 1 >= tm.n_pieces) return false;
     const paro_piece_info x = tm.pieces[i], y = tm.pieces[i + 1];
     const int64_t w = uniform(x.where);
     const unsigned tile = (unsigned)uniform((int)x.tile);

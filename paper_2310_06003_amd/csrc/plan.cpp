@@ -115,6 +115,20 @@ void fold_order(const paro_plan_t *pl, int chunk, int32_t *ranks, int32_t *group
     }
     *group_len = G;
 }
+bool on_cache_lines(const paro_plan_t *pl, int64_t chunk) {
+    const int64_t c0 = chunk * pl->L, c1 = std::min(c0 + pl->L, pl->total), n_nz = (int64_t)pl->nz_tensor.size();
+    if (c0 >= c1) return false;                                                       // all padding
+    int64_t on = 0, all = 0;
+    if (c1 - c0 < pl->L) all = (pl->L + PARO_TILE - 1) / PARO_TILE - (c1 - c0) / PARO_TILE;      // blocks with padding
+    for (int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), c0) - pl->nz_off.begin() - 1;
+         k < n_nz && pl->nz_off[(size_t)k] < c1; ++k) {
+        const int64_t begin = pl->nz_off[(size_t)k], end = std::min(pl->nz_off[(size_t)k + 1], c1);
+        const int64_t pieces = (end - 1 - c0) / PARO_TILE - (std::max(begin, c0) - c0) / PARO_TILE + 1;
+        all += pieces;
+        if ((c0 - begin) % 64 == 0) on += pieces;             // blocks are multiples of 64 elements long
+    }
+    return on >= all - all / 8;
+}
 int schedule_messages(const paro_plan_t *pl, int rank, int sched, int collective, const MessageId *only,
                       std::vector<paro_msg_t> *out) {
     if (collective != PARO_RS && collective != PARO_AG) return fail(PARO_EINVAL, "paro_schedule: bad collective");

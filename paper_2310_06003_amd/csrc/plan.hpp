@@ -48,7 +48,7 @@ struct paro_device_tables {
     std::vector<uint8_t> tile_tab_tried;      // [P] the decision for the chunk has been made
     std::vector<paro_piece_info *> piece_tab; // [P] the chunk's list of pieces, or null (tensor layout)
     std::vector<uint32_t> n_pieces;           // [P]
-    std::vector<uint8_t> on_lines;            // [P] nearly every piece starts on a multiple of 64 elements of its tensor
+    std::vector<uint8_t> on_lines;            // [P] on_cache_lines() of the chunk
     std::vector<uint8_t> piece_tab_tried;     // [P]
     int64_t tiles_per_chunk = 0;
     int64_t max_pieces = 0;         // of a chunk: what the partial sums have room for
@@ -92,6 +92,9 @@ inline int owner_of_chunk(const paro_plan_t *pl, int chunk) {
 }
 // [begin, begin+len) of a rank's range for a sharding letter
 void letter_range(const paro_plan_t *pl, int rank, char letter, int64_t *begin, int64_t *len);
+// Whether nearly every piece of a chunk (the part of a block that lies in one tensor) belongs to a block
+// that starts on a multiple of 64 elements of its tensor: on a cache line, if the tensor does.
+bool on_cache_lines(const paro_plan_t *pl, int64_t chunk);
 // One rank's messages of a collective, in the order of the public table: all of them, or those of one
 // (phase, ring, step).
 struct MessageId {

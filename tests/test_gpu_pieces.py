@@ -64,3 +64,11 @@ def test_cut_blocks(paro, P, pairs, monkeypatch):
                 for k, t in (("p", p), ("m", m), ("v", v)):
                     assert np_of(t).tobytes() == lit[k].tobytes(), what + ": " + k
                 assert np_of(dst)[slot:slot + n].tobytes() == lit["q"].tobytes(), what
+
+
+@pytest.mark.parametrize("pairs", [False, True])
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 8, 17])
+def test_without_a_list(paro, P, pairs, monkeypatch):
+    """The same where no list is built: every block found by a search, two of one tensor still taken together."""
+    monkeypatch.setenv("PARO_TILE_TABLE_MAX_TILES", "0")
+    test_cut_blocks(paro, P, pairs, monkeypatch)
