@@ -646,6 +646,7 @@ int fill_tables(const paro_plan_t *pl, paro_device_tables &d) {
     d.piece_tab.assign((size_t)pl->P, nullptr);
     d.n_pieces.assign((size_t)pl->P, 0);
     d.on_lines.assign((size_t)pl->P, 0);
+    d.f32.assign((size_t)pl->P, 0);
     d.piece_tab_tried.assign((size_t)pl->P, 0);
     d.tile_tab_tried.assign((size_t)pl->P, 0);
     // one partial per block of a sweep-1 launch (which covers a rank's whole update range at most),
@@ -720,11 +721,16 @@ void list_tiles(const paro_plan_t *pl, int64_t c, std::vector<paro_tile_info> *t
 // P times over (P = 64, 1.4 M elements of tensors of 1 to 65536 elements: sweep 1 in 195 us, a handful of
 // such waves keeping the rest waiting; cut, 85 us).  With few contributions that fetching is short, and in a
 // large chunk the cut's partial cache lines of g cost more (P = 2, 59 M elements: whole step 370 us, cut
-// 395; P = 4, 4 M elements, though: 22.6 us, cut 20.2).  A tile of more tensors than PARO_SPLIT_MAX stays whole.
+// 395; P = 4, 4 M elements, though: 22.6 us, cut 20.2).  Nor is a very large chunk of fp32 gradients cut, up to 32
+// ranks: few enough waves have slow lanes among their 16-byte loads, and the partial lines weigh as much as ever
+// (clipped, cut and whole: 80 M elements, P = 8 938 and 916 us, P = 12 1214 and 1166; 40 M, P = 16 716 and 732, P = 64
+// 2273 and 2385; bf16, 80 M, P = 12: 779 and 790).  A tile of more tensors than PARO_SPLIT_MAX stays whole.
 void list_pieces(const paro_plan_t *pl, int64_t c, std::vector<paro_piece_info> *tab) {
     const int64_t n_nz = (int64_t)pl->nz_tensor.size(), most = pl->dev.max_pieces;
     int64_t spare = most - pl->dev.tiles_per_chunk;
-    const bool cut = pl->P > PARO_PAIR_MAX_RANKS || pl->dev.tiles_per_chunk < PARO_LARGE_TILES;
+    const int64_t tiles = pl->dev.tiles_per_chunk;
+    const bool whole_f32 = pl->dev.f32[(size_t)c] && pl->P <= 32 && tiles >= 2 * PARO_LARGE_TILES;
+    const bool cut = tiles < PARO_LARGE_TILES || (pl->P > PARO_PAIR_MAX_RANKS && !whole_f32);
     tab->reserve((size_t)most);
     auto add = [&](int64_t off, int64_t dt, int64_t lo, int64_t hi, int32_t tensor, int64_t i) {
         tab->push_back({off * ((int64_t)1 << 19) + (dt << 17 | hi << 8 | lo), tensor, (uint32_t)i});
@@ -765,7 +771,10 @@ int ensure_table(paro_plan_t *pl, int rank, std::vector<Info *> &tabs, std::vect
     std::vector<Info> tab;
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {
         if (tried[(size_t)c]) continue;
-        if constexpr (std::is_same_v<Info, paro_piece_info>) pl->dev.on_lines[(size_t)c] = paro::on_cache_lines(pl, c);
+        if constexpr (std::is_same_v<Info, paro_piece_info>) {
+            pl->dev.on_lines[(size_t)c] = paro::on_cache_lines(pl, c);
+            pl->dev.f32[(size_t)c] = paro::mostly_f32(pl, c);
+        }
         if (d.tiles_per_chunk > max_tiles) {
             tried[(size_t)c] = 1;                    // decided: this chunk works without a table
             continue;
@@ -984,7 +993,13 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const int64_t pieces = tm.pieces ? tm.n_pieces : piece_count(n);
-    const bool on_lines = pl->dev.on_lines[(size_t)c] != 0;
+    // Streaming loads where the blocks start on cache lines (see Tensor4Loader).  A wave's kilobyte of an fp32 tensor
+    // shares only one line in nine with a neighbour: in a large chunk streaming is better there as well, but with 5 to
+    // 8 contributions (ragged tensors, whole clipped step, plain and streaming: 80 M elements, P = 4 677 and 662 us,
+    // P = 16 1457 and 1441; 40 M, P = 6 394 and 398, P = 64 2289 and 2162; 10 M, P = 4, which fit the caches, 85 and 92).
+    // In the single sweep it is not (P = 8, 80 M: 834 and 872).
+    const bool f32_streams = pl->dev.f32[(size_t)c] && piece_count(n) >= PARO_LARGE_TILES && (pl->P <= PARO_PAIR_MAX_RANKS || pl->P > 8);
+    const bool on_lines = pl->dev.on_lines[(size_t)c] || f32_streams;
     // What decides is the list, see PARO_PAIR_MAX_RANKS.
     const bool small = many_small_tensors(pl, c);
     int64_t pair_min_blocks = PARO_PAIR_MIN_BLOCKS;

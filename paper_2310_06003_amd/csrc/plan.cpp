@@ -129,6 +129,16 @@ bool on_cache_lines(const paro_plan_t *pl, int64_t chunk) {
     }
     return on >= all - all / 8;
 }
+bool mostly_f32(const paro_plan_t *pl, int64_t chunk) {
+    const int64_t c0 = chunk * pl->L, c1 = std::min(c0 + pl->L, pl->total), n_nz = (int64_t)pl->nz_tensor.size();
+    if (c0 >= c1) return false;
+    int64_t f32 = 0;
+    for (int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), c0) - pl->nz_off.begin() - 1;
+         k < n_nz && pl->nz_off[(size_t)k] < c1; ++k)
+        if (pl->dtype[(size_t)pl->nz_tensor[(size_t)k]] == PARO_F32)
+            f32 += std::min(pl->nz_off[(size_t)k + 1], c1) - std::max(pl->nz_off[(size_t)k], c0);
+    return 2 * f32 > c1 - c0;
+}
 int schedule_messages(const paro_plan_t *pl, int rank, int sched, int collective, const MessageId *only,
                       std::vector<paro_msg_t> *out) {
     if (collective != PARO_RS && collective != PARO_AG) return fail(PARO_EINVAL, "paro_schedule: bad collective");

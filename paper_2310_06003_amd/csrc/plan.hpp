@@ -49,6 +49,7 @@ struct paro_device_tables {
     std::vector<paro_piece_info *> piece_tab; // [P] the chunk's list of pieces, or null (tensor layout)
     std::vector<uint32_t> n_pieces;           // [P]
     std::vector<uint8_t> on_lines;            // [P] on_cache_lines() of the chunk
+    std::vector<uint8_t> f32;                 // [P] mostly_f32() of the chunk
     std::vector<uint8_t> piece_tab_tried;     // [P]
     int64_t tiles_per_chunk = 0;
     int64_t max_pieces = 0;         // of a chunk: what the partial sums have room for
@@ -95,6 +96,8 @@ void letter_range(const paro_plan_t *pl, int rank, char letter, int64_t *begin, 
 // Whether nearly every piece of a chunk (the part of a block that lies in one tensor) belongs to a block
 // that starts on a multiple of 64 elements of its tensor: on a cache line, if the tensor does.
 bool on_cache_lines(const paro_plan_t *pl, int64_t chunk);
+// Whether more than half of a chunk's gradient elements are fp32.
+bool mostly_f32(const paro_plan_t *pl, int64_t chunk);
 // One rank's messages of a collective, in the order of the public table: all of them, or those of one
 // (phase, ring, step).
 struct MessageId {

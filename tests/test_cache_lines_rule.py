@@ -1,6 +1,6 @@
-"""Whether a chunk's blocks start on cache lines inside their tensors - what makes the tensor layout stream
-its loads - is known from the tensors' offsets, with or without a list of pieces.  The rule (host code, no GPU)
-against a count over every element."""
+"""Whether a chunk's blocks start on cache lines inside their tensors, and whether its gradients are mostly
+fp32 - what makes the tensor layout stream its loads - is known from the tensors' offsets, with or without a list
+of pieces.  The rules (host code, no GPU) against a count over every element."""
 import os
 import subprocess
 
@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle as orc
+import workloads as wl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BLOCK = 256
@@ -20,10 +21,13 @@ int main() {
     int P; long T, x;
     while (std::scanf("%d %ld", &P, &T) == 2) {
         std::vector<int64_t> sizes;
+        std::vector<uint8_t> dt;
         for (long t = 0; t < T; ++t) { if (std::scanf("%ld", &x) != 1) return 1; sizes.push_back(x); }
+        for (long t = 0; t < T; ++t) { if (std::scanf("%ld", &x) != 1) return 1; dt.push_back((uint8_t)x); }
+        paro_plan_opts_t o = {PARO_SCHED_DEFAULT, 0, dt.data(), nullptr, PARO_BF16, 0};
         paro_plan_t *pl = nullptr;
-        if (paro_plan(P, 1, "GGG", sizes.data(), T, nullptr, &pl) != PARO_OK) return 2;
-        for (int c = 0; c < P; ++c) std::printf("%d", (int)paro::on_cache_lines(pl, c));
+        if (paro_plan(P, 1, "GGG", sizes.data(), T, &o, &pl) != PARO_OK) return 2;
+        for (int c = 0; c < P; ++c) std::printf("%d", (int)paro::on_cache_lines(pl, c) + 2 * paro::mostly_f32(pl, c));
         std::printf("\n");
         paro_plan_destroy(pl);
     }
@@ -42,16 +46,17 @@ def rule(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
 
-    def ask(P, sizes):
-        text = f"{P} {len(sizes)} " + " ".join(map(str, sizes))
+    def ask(P, sizes, dtypes):
+        text = f"{P} {len(sizes)} " + " ".join(map(str, sizes)) + " " + " ".join(map(str, dtypes))
         r = subprocess.run([str(where / "rule")], input=text, capture_output=True, text=True)
         assert r.returncode == 0
-        return [ch == "1" for ch in r.stdout.strip()]
+        return [(int(ch) & 1 == 1, int(ch) & 2 == 2) for ch in r.stdout.strip()]
     return ask
 
 
-def counted(P, sizes):
+def counted(P, sizes, dtypes):
     """Pieces of every chunk, element by element; padding is a tensor that starts nowhere in particular."""
+    f32 = np.array([d == wl.F32 for d in dtypes] + [False])
     L = orc.layout(P, 1, sizes).L
     start = np.concatenate([[0], np.cumsum(sizes)])
     tensor = np.concatenate([np.repeat(np.arange(len(sizes)), sizes), np.full(P * L - start[-1], -1)])
@@ -60,12 +65,13 @@ def counted(P, sizes):
         e = np.arange(L)
         pieces = sorted(set(zip((e // BLOCK).tolist(), tensor[c * L:(c + 1) * L].tolist())))
         on = sum(t >= 0 and (c * L + b * BLOCK - int(start[t])) % 64 == 0 for b, t in pieces)
-        out.append(on > 0 and on >= len(pieces) - len(pieces) // 8)
+        real = tensor[c * L:(c + 1) * L][tensor[c * L:(c + 1) * L] >= 0]
+        out.append((on > 0 and on >= len(pieces) - len(pieces) // 8, 2 * int(f32[real].sum()) > real.size))
     return out
 
 
 @pytest.mark.parametrize("P", [1, 2, 5, 8])
-def test_rule_equals_a_count_over_the_elements(rule, P):
+def test_rules_equal_a_count_over_the_elements(rule, P):
     rng = np.random.default_rng(70 + P)
     lists = [[5], [64], [1 << 14], [256, 256, 256], [255, 257, 512], [0, 64, 0, 128, 0], [1] * 300, [64] * 300,
              [100_000, 1], [100_000, 8, 60_000], [63] + [4096] * 9, [8, 50_000], [50_000, 8]]
@@ -73,7 +79,8 @@ def test_rule_equals_a_count_over_the_elements(rule, P):
         unit = int(rng.choice([1, 8, 64, 64, 256]))
         lists.append([unit * int(x) for x in rng.integers(0, int(rng.choice([20, 200, 4000])) // unit + 2,
                                                           int(rng.integers(1, 30)))] + [int(rng.choice([1, 64, 700, 9000]))])
-    asked = [rule(P, s) for s in lists]
-    want = [counted(P, s) for s in lists]
-    assert asked == want
-    assert any(any(w) for w in want) and any(not all(w) for w in want)
+    dtypes = [[int(x) for x in rng.integers(0, 3, len(s))] for s in lists]
+    want = [counted(P, s, d) for s, d in zip(lists, dtypes)]
+    assert [rule(P, s, d) for s, d in zip(lists, dtypes)] == want
+    for k in (0, 1):
+        assert {w[k] for chunks in want for w in chunks} == {False, True}

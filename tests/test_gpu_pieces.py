@@ -72,3 +72,48 @@ def test_without_a_list(paro, P, pairs, monkeypatch):
     """The same where no list is built: every block found by a search, two of one tensor still taken together."""
     monkeypatch.setenv("PARO_TILE_TABLE_MAX_TILES", "0")
     test_cut_blocks(paro, P, pairs, monkeypatch)
+
+
+@pytest.mark.parametrize("P,dtype,blocks", [(6, wl.BF16, 131072), (9, wl.BF16, 131072), (9, wl.F32, 131072),
+                                            (5, wl.F32, 262144)])
+def test_boundaries_in_a_large_chunk(paro, P, dtype, blocks):
+    """Many small tensors in a chunk of 131 072 blocks and more: with more than 4 ranks blocks are still cut, the list
+    in address order; with fp32 gradients, which stream with up to 4 and more than 8 ranks, not from 262 144 blocks
+    on.  Both sides of 8 ranks: a batch of loads and a launch shape each."""
+    sizes = wl.ragged_sizes(6200 * P * (blocks // 131072), seed=7)
+    no_decay = [int(n % 3 == 0) for n in sizes]
+    lay = orc.layout(P, 1, sizes)
+    assert lay.L // 256 >= blocks
+    sched, rank = orc.default_sched(P, 1), P // 2
+    pl = paro.paro_plan(P, 1, "GGG", sizes, grad_dtype=[dtype] * len(sizes), no_decay=no_decay)
+    ob, ol = orc.state_range(lay, rank, "G")
+    off = np.concatenate([[0], np.cumsum(sizes)])                 # only the tensors that meet the rank's range exist
+    meets = [t for t in range(len(sizes)) if off[t] < ob + ol and off[t + 1] > ob]
+    first, span = int(off[meets[0]]), int(off[meets[-1] + 1] - off[meets[0]])
+    flat = [wl.draw(span, 403 + q, dtype=dtype, device=DEV) for q in range(P)]
+
+    def views(x):
+        some = {t: x[int(off[t]) - first:int(off[t + 1]) - first] for t in meets}
+        return [some.get(t) for t in range(len(sizes))]
+    tables = [PtrTable(views(x)) for x in flat]
+    host = [views(np_of(x)) for x in flat]
+    g_ref, ss_ref = orc.reduce_shard(lay, "GGG", sched, rank, host, "tensors")
+    state = wl.master_state(ol, 404, device=DEV)
+    old = [np_of(t) for t in state]
+    for max_norm in (0.0, 0.01):
+        hp = dict(hp_dict(P, max_norm=max_norm), weight_decay=0.1)
+        lit = oracle_update(lay, "GGG", rank, g_ref, *old, total_sumsq=ss_ref, hp=hp, step=3, no_decay=no_decay,
+                            literal32=True)
+        p, m, v = (t.clone() for t in state)
+        g = torch.empty(ol, dtype=torch.float32, device=DEV)
+        ss = torch.zeros(1, dtype=torch.float64, device=DEV)
+        dst_len, slot, n = orc.pack_slot(lay, rank, "GGG")
+        dst = torch.zeros(dst_len, dtype=torch.bfloat16, device=DEV)
+        paro.paro_step_fused(pl, rank, [t.ptr() for t in tables], paro.PARO_TENSORS, hp_struct(paro, hp, 3), g.data_ptr(),
+                             ss.data_ptr(), p.data_ptr(), m.data_ptr(), v.data_ptr(), dst.data_ptr(), stream())
+        if max_norm:
+            assert np_of(g).tobytes() == g_ref.tobytes()
+            assert abs(float(ss.item()) - ss_ref) <= 1e-12 * ss_ref
+        for k, t in (("p", p), ("m", m), ("v", v)):
+            assert np_of(t).tobytes() == lit[k].tobytes(), f"clip {max_norm}: {k}"
+        assert np_of(dst)[slot:slot + n].tobytes() == lit["q"].tobytes()
