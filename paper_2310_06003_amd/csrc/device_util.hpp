@@ -70,6 +70,9 @@ namespace {
 #ifndef PARO_FOLD_TM_LOADS_PER_CU
 #define PARO_FOLD_TM_LOADS_PER_CU 100000
 #endif
+#ifndef PARO_FUSED_TL_WAVES_PER_CU
+#define PARO_FUSED_TL_WAVES_PER_CU 20    // the single sweep over a large chunk of many small tensors, more than 8 ranks
+#endif
 #ifndef PARO_LARGE_TILES
 #define PARO_LARGE_TILES 131072
 #endif

@@ -1028,8 +1028,13 @@ template <bool MASK>
 void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const SrcTable &tab, int group_len, int64_t c,
                   const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     const int64_t n = pl->L;
-    const bool small = layout == PARO_TENSORS && piece_count(n) < PARO_LARGE_TILES && many_small_tensors(pl, c);
-    const int waves = fold_waves(fold_loads(pl->P) + 3, small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FUSED_LOADS_PER_CU);
+    const bool small = layout == PARO_TENSORS && many_small_tensors(pl, c), large = piece_count(n) >= PARO_LARGE_TILES;
+    int waves = fold_waves(fold_loads(pl->P) + 3, small && !large ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FUSED_LOADS_PER_CU);
+    // A large chunk of many small tensors: the budget's 10 waves at P > 8 are too few to hide the look-ups, all that
+    // fit too many for DRAM (bf16, budget, 20 waves, all: P = 12, 80 M elements 820, 686, 793 us; P = 16, 115 M 1410,
+    // 1197, 1271; P = 64, 80 M 2667, 2408; a quarter fp32, P = 16, 80 M 1021, 935).  fp32 gradients, whose loads are twice
+    // as wide and half as many, want the budget (P = 16, 80 M: 1314, 1443).
+    if (small && large && pl->P > 8 && !pl->dev.f32[(size_t)c]) waves = PARO_FUSED_TL_WAVES_PER_CU;
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const unsigned grid = piece_grid(n), lds = throttle_lds(sc.lds_per_cu, waves);
     if (layout == PARO_TENSORS)
