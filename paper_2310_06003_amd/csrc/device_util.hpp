@@ -57,9 +57,13 @@ namespace {
 // many small pieces has waves that spend part of their life on look-ups with no data in flight: it is
 // launched without the throttle (the single sweep, whose waves load their state as well, only in
 // chunks of fewer than PARO_LARGE_TILES blocks).  With at most PARO_PAIR_MAX_RANKS contributions and at
-// least PARO_PAIR_MIN_BLOCKS blocks a wave takes two consecutive blocks (see k_reduce4t).
+// least PARO_PAIR_MIN_BLOCKS blocks, and with at most PARO_PAIR_SMALL_MAX_RANKS in a large chunk of many
+// small pieces that are not mostly fp32, a wave takes two consecutive blocks (see k_reduce4t).
 #ifndef PARO_PAIR_MAX_RANKS
 #define PARO_PAIR_MAX_RANKS 4
+#endif
+#ifndef PARO_PAIR_SMALL_MAX_RANKS
+#define PARO_PAIR_SMALL_MAX_RANKS 6
 #endif
 #ifndef PARO_PAIR_MIN_BLOCKS
 #define PARO_PAIR_MIN_BLOCKS 16384

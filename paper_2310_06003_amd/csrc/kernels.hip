@@ -281,11 +281,13 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
     }
 }
 
-// A wave takes PPW consecutive pieces.  PPW = 2 is for few contributions (P <= 4): where both are whole
-// blocks that lie inside one tensor - the usual case - the wave folds them as one stream of 512 elements
-// per contribution: one look-up and twice the bytes in flight per wave.  Whole clipped steps, one and two
-// blocks per wave: P = 2, 31 M elements of tensors of 1 to 65536: 216 and 205 us; P = 4, 10 M elements of a
-// Llama-like list 73.4 and 70.0 us; at P = 8 the other way round (69 M elements: 457 and 476 us).
+// A wave takes PPW consecutive pieces.  PPW = 2 is for few contributions (P <= 4; P <= 6 over large chunks of
+// many small tensors): where both are whole blocks that lie inside one tensor - the usual case - the wave folds
+// them as one stream of 512 elements per contribution: one look-up and twice the bytes in flight per wave.
+// Whole clipped steps, one and two blocks per wave: P = 2, 31 M elements of tensors of 1 to 65536: 216 and 205
+// us; P = 4, 10 M elements of a Llama-like list 73.4 and 70.0 us; P = 5, 115 M of tensors of 1 to 65536 878 and
+// 835, P = 6, 80 M 641 and 611, P = 7, 80 M with a quarter fp32 699 and 696; at P = 8 the other way round (69 M
+// elements: 457 and 476 us).  The list must leave its blocks whole: cut ones part the pairs (P = 5, 115 M: 884).
 // KB: contributions loaded before the first is consumed (8 when launched for P <= 8 only: fewer
 // registers, more waves).  NT: the list's blocks start on cache lines.
 // What bounds it: HBM, behind two dependent look-ups per wave (the piece, then the P pointers).  Taken one
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, i
         int64_t e0;
         if (pair_of(tm, i0, n, &pc, &e0)) {                  // two whole blocks inside one tensor
             float X[8];
-            fold_tensor_pair<NT>(pc, src, P, group_len, X);
+            fold_tensor_pair<NT, KB>(pc, src, P, group_len, X);
             const wave_buf out = wave_buffer(g + e0, 2 * PIECE * 4);
             buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), out, lane_id() * 16);
             buf_store16<PARO_POL_G_ST>(as_u32x4(X[4], X[5], X[6], X[7]), out, PIECE * 4 + lane_id() * 16);
@@ -729,8 +731,9 @@ void list_pieces(const paro_plan_t *pl, int64_t c, std::vector<paro_piece_info> 
     const int64_t n_nz = (int64_t)pl->nz_tensor.size(), most = pl->dev.max_pieces;
     int64_t spare = most - pl->dev.tiles_per_chunk;
     const int64_t tiles = pl->dev.tiles_per_chunk;
-    const bool whole_f32 = pl->dev.f32[(size_t)c] && pl->P <= 32 && tiles >= 2 * PARO_LARGE_TILES;
-    const bool cut = tiles < PARO_LARGE_TILES || (pl->P > PARO_PAIR_MAX_RANKS && !whole_f32);
+    const bool f32 = pl->dev.f32[(size_t)c] != 0;
+    const bool few = pl->P <= (f32 ? PARO_PAIR_MAX_RANKS : PARO_PAIR_SMALL_MAX_RANKS);
+    const bool cut = tiles < PARO_LARGE_TILES || !(few || (f32 && pl->P <= 32 && tiles >= 2 * PARO_LARGE_TILES));
     tab->reserve((size_t)most);
     auto add = [&](int64_t off, int64_t dt, int64_t lo, int64_t hi, int32_t tensor, int64_t i) {
         tab->push_back({off * ((int64_t)1 << 19) + (dt << 17 | hi << 8 | lo), tensor, (uint32_t)i});
@@ -1002,12 +1005,18 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const bool on_lines = pl->dev.on_lines[(size_t)c] || f32_streams;
     // What decides is the list, see PARO_PAIR_MAX_RANKS.
     const bool small = many_small_tensors(pl, c);
-    int64_t pair_min_blocks = PARO_PAIR_MIN_BLOCKS;
+    const bool few = pl->P <= PARO_PAIR_MAX_RANKS;
+    int64_t pair_min_blocks = few ? PARO_PAIR_MIN_BLOCKS : PARO_LARGE_TILES;
     if (const char *env = std::getenv("PARO_PAIR_MIN_BLOCKS")) pair_min_blocks = std::atoll(env);     // for tests
-    if (pl->P <= PARO_PAIR_MAX_RANKS && piece_count(n) >= pair_min_blocks) {
+    const bool pairs = few || (pl->P <= PARO_PAIR_SMALL_MAX_RANKS && small && !pl->dev.f32[(size_t)c]);
+    if (pairs && piece_count(n) >= pair_min_blocks) {
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
-        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC>), dim3(grid), dim3(WAVE),
-                                                   0, st, few_sources(tab), pl->P, group_len, n, g, partials, tm));
+        if (few)
+            PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC>), dim3(grid), dim3(WAVE),
+                                                       0, st, few_sources(tab), pl->P, group_len, n, g, partials, tm));
+        else
+            PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC>), dim3(grid), dim3(WAVE), 0, st,
+                                                       few_sources(tab), pl->P, group_len, n, g, partials, tm));
         return (int)grid;
     }
     const unsigned grid = (unsigned)((pieces + 7) & ~(int64_t)7);

@@ -254,12 +254,12 @@ struct Part4Loader {
     }
 };
 
-// Two consecutive blocks inside one tensor, folded by one wave (sweep 1 with 4 contributions or fewer:
-// the wave then has twice the loads in flight, and one look-up serves 512 elements).
+// Two consecutive blocks inside one tensor, folded by one wave (sweep 1 with few contributions: the wave
+// then has twice the loads in flight, and one look-up serves 512 elements).
 // The thread's elements 0-3 lie in the first block, 4-7 in the second, 256 elements further on.
-template <int DT, bool NT>
+template <int DT, bool NT, int KB>
 struct Tensor8Loader {
-    static constexpr int kBatch = PARO_PAIR_MAX_RANKS;
+    static constexpr int kBatch = KB;
     static constexpr int kElems = 8;
     static constexpr bool kPaced = false;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
@@ -514,16 +514,16 @@ __device__ __forceinline__ void fold_tensors(const Piece &pc, const Located &loc
 }
 
 // ... of the thread's 8 elements in two consecutive blocks that lie in one tensor (pc: the first).
-template <bool NT, class Src>
+template <bool NT, int KB, class Src>
 __device__ __forceinline__ void fold_tensor_pair(const Piece &pc, const Src &src, int P, int group_len, float X[8]) {
     if (pc.dt == PARO_BF16) {
-        Tensor8Loader<PARO_BF16, NT> ld{pc.tensor, pc.toff * 2};
+        Tensor8Loader<PARO_BF16, NT, KB> ld{pc.tensor, pc.toff * 2};
         fold4(ld, src, P, group_len, X);
     } else if (pc.dt == PARO_F16) {
-        Tensor8Loader<PARO_F16, NT> ld{pc.tensor, pc.toff * 2};
+        Tensor8Loader<PARO_F16, NT, KB> ld{pc.tensor, pc.toff * 2};
         fold4(ld, src, P, group_len, X);
     } else {
-        Tensor8Loader<PARO_F32, NT> ld{pc.tensor, pc.toff * 4};
+        Tensor8Loader<PARO_F32, NT, KB> ld{pc.tensor, pc.toff * 4};
         fold4(ld, src, P, group_len, X);
     }
 }

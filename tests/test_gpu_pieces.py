@@ -74,12 +74,12 @@ def test_without_a_list(paro, P, pairs, monkeypatch):
     test_cut_blocks(paro, P, pairs, monkeypatch)
 
 
-@pytest.mark.parametrize("P,dtype,blocks", [(6, wl.BF16, 131072), (9, wl.BF16, 131072), (9, wl.F32, 131072),
-                                            (5, wl.F32, 262144)])
+@pytest.mark.parametrize("P,dtype,blocks", [(6, wl.BF16, 131072), (7, wl.BF16, 131072), (9, wl.BF16, 131072),
+                                            (6, wl.F32, 131072), (9, wl.F32, 131072), (5, wl.F32, 262144)])
 def test_boundaries_in_a_large_chunk(paro, P, dtype, blocks):
-    """Many small tensors in a chunk of 131 072 blocks and more: with more than 4 ranks blocks are still cut, the list
-    in address order; with fp32 gradients, which stream with up to 4 and more than 8 ranks, not from 262 144 blocks
-    on.  Both sides of 8 ranks: a batch of loads and a launch shape each."""
+    """Many small tensors in a chunk of 131 072 blocks and more: with up to 6 ranks two blocks per wave and no cuts,
+    with more blocks are cut, the list in address order; with fp32 gradients, which stream with up to 4 and more than 8
+    ranks, cut with more than 4, but not from 262 144 blocks on."""
     sizes = wl.ragged_sizes(6200 * P * (blocks // 131072), seed=7)
     no_decay = [int(n % 3 == 0) for n in sizes]
     lay = orc.layout(P, 1, sizes)

@@ -12,8 +12,8 @@ DTYPES = {"bf16": ("PARO_BF16", 2, "dwordx2"), "f16": ("PARO_F16", 2, "dwordx2")
 LOADERS = {                                     # name: type, its members, vector loads, streaming
     "whole_nt": ("Tensor4Loader<{dt}, true>", "0, 0", 1, True),
     "whole": ("Tensor4Loader<{dt}, false>", "0, 0", 1, False),
-    "pair_nt": ("Tensor8Loader<{dt}, true>", "0, 0", 2, True),
-    "pair": ("Tensor8Loader<{dt}, false>", "0, 0", 2, False),
+    "pair_nt": ("Tensor8Loader<{dt}, true, 4>", "0, 0", 2, True),
+    "pair": ("Tensor8Loader<{dt}, false, 8>", "0, 0", 2, False),
     "part": ("Part4Loader<{dt}>", "0, 0, a, b", 1, False),
 }
 
