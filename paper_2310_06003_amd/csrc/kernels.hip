@@ -70,10 +70,13 @@ __device__ __forceinline__ double strided_sum(const double *__restrict__ sums, i
 template <int U = 8>
 __device__ __forceinline__ double norm_total(const double *__restrict__ sums, int n) {
     if (n == 1) return sums[0];
-    if (n == NORM_SLICES) {                                        // one scalar load
-        double s = sums[0];
+    if (n <= NORM_SLICES) {                                        // one scalar load; there is room for as many
+        double x[NORM_SLICES];
 #pragma unroll
-        for (int k = 1; k < NORM_SLICES; ++k) s += sums[k];
+        for (int k = 0; k < NORM_SLICES; ++k) x[k] = sums[k];
+        double s = x[0];
+#pragma unroll
+        for (int k = 1; k < NORM_SLICES; ++k) s += k < n ? x[k] : 0.0;
         return s;
     }
     double acc = strided_sum<WAVE, U>(sums, lane_id(), n);
@@ -1126,10 +1129,13 @@ int finalize_partials(const Scratch &sc, const double *partials, int n_part, dou
     return PARO_OK;
 }
 
-// ... and the sums of several launches or groups, in sc.chunk_sums.
+// ... and the sums of several chunks, launches or groups, in sc.chunk_sums.  Up to eight of them are left to
+// sweep 2's scalar loads; adding more across the lanes would cost every wave of a large sweep more than one small
+// kernel (two sums, 100 M elements: sweep 2 505 us, 470 from one scalar).
 int finalize_sums(const Scratch &sc, int n, double *out, hipStream_t st, NormSums *rest) {
     const NormSums all{sc.chunk_sums, n, out};
-    return rest ? (*rest = all, PARO_OK) : total_of(all, st);
+    if (rest) *rest = n <= NORM_SLICES ? all : NormSums{out, 1, nullptr};
+    return rest && n <= NORM_SLICES ? PARO_OK : total_of(all, st);
 }
 
 // Sweep 1 over an update range of several chunks, chunk layout: one launch, or, where the norm covers
