@@ -349,33 +349,52 @@ __global__ __launch_bounds__(WAVE) void k_norm_total(const double *__restrict__ 
     if (lane_id() == 0) *out = total;
 }
 
-// The NORM_SLICES slice sums of k_finalize and their total in one small launch: block_sum() of every slice,
-// then the slices in order.
+// The NORM_SLICES slice sums of k_finalize and their total in one small launch: block_sum() of every slice -
+// the same pairs of lanes at every step, the same order of waves - then the slices in order.  Eight separate
+// sums across the lanes would be 48 shuffles a wave, 16 waves on one compute unit, and eight loops as many round
+// trips to memory (together 4 us); here each of the first three steps also halves the slices that a lane carries: ten.
 __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double *__restrict__ partials, int n, int chunk,
                                                                     double *out) {
+    static_assert(NORM_SLICES == 8, "three halvings leave one slice to a lane");
     __shared__ double s_wave[NORM_SLICES][FINALIZE_TPB / WAVE];
-    double acc[NORM_SLICES];
-#pragma unroll
-    for (int b = 0; b < NORM_SLICES; ++b)
-        acc[b] = strided_sum<FINALIZE_TPB, NORM_ONE_BLOCK_PARTIALS / NORM_SLICES / FINALIZE_TPB>(
-            partials, b * chunk + (int)threadIdx.x, min(n, (b + 1) * chunk));
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    constexpr int U = NORM_ONE_BLOCK_PARTIALS / NORM_SLICES / FINALIZE_TPB;
+    double x[NORM_SLICES][U], acc[NORM_SLICES];
+#pragma unroll
+    for (int b = 0; b < NORM_SLICES; ++b)                   // all in flight
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = (int)threadIdx.x + u * FINALIZE_TPB;
+            x[b][u] = k < chunk && b * chunk + k < n ? partials[b * chunk + k] : 0.0;
+        }
 #pragma unroll
     for (int b = 0; b < NORM_SLICES; ++b) {
-        const double s = wave_sum(acc[b]);
-        if (lane == 0) s_wave[b][wave] = s;
+        acc[b] = x[b][0];
+#pragma unroll
+        for (int u = 1; u < U; ++u) acc[b] += x[b][u];
     }
+    static_for<0, 3>([&](auto step) {
+        constexpr int HALF = NORM_SLICES >> (step + 1), FAR = WAVE / 2 >> step;
+        const bool upper = lane & FAR;                      // keeps the upper half of the slices, hands over the lower
+#pragma unroll
+        for (int b = 0; b < HALF; ++b) {
+            const double keep = upper ? acc[b + HALF] : acc[b], give = upper ? acc[b] : acc[b + HALF];
+            acc[b] = keep + __shfl_xor(give, FAR, WAVE);
+        }
+    });
+    double s = acc[0];                                      // of slice lane / 8
+    for (int d = WAVE / 16; d >= 1; d >>= 1) s += __shfl_xor(s, d, WAVE);
+    if (lane % 8 == 0) s_wave[lane / 8][wave] = s;
     __syncthreads();
-    if (threadIdx.x < NORM_SLICES) {
-        double r = s_wave[threadIdx.x][0];
-        for (int w = 1; w < FINALIZE_TPB / WAVE; ++w) r += s_wave[threadIdx.x][w];
-        s_wave[threadIdx.x][0] = r;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = s_wave[0][0];
-        for (int b = 1; b < NORM_SLICES; ++b) s += s_wave[b][0];
-        *out = s;
+    if (wave == 0) {
+        const double *of_slice = s_wave[lane & (NORM_SLICES - 1)];
+        double r = of_slice[0];
+#pragma unroll
+        for (int w = 1; w < FINALIZE_TPB / WAVE; ++w) r += of_slice[w];
+        double total = __shfl(r, 0, WAVE);
+#pragma unroll
+        for (int b = 1; b < NORM_SLICES; ++b) total += __shfl(r, b, WAVE);
+        if (lane == 0) *out = total;
     }
 }
 
