@@ -92,6 +92,9 @@ namespace {
 #ifndef PARO_SPLIT_MAX
 #define PARO_SPLIT_MAX 16           // a tile with up to so many tensors inside is cut into pieces
 #endif
+#ifndef PARO_RANGE_MAX_BLOCKS
+#define PARO_RANGE_MAX_BLOCKS 65536   // chunks of so many blocks are launched one by one (see chunk_by_chunk)
+#endif
 #ifndef PARO_HOP_WAVES_PER_CU
 #define PARO_HOP_WAVES_PER_CU 0
 #endif

@@ -203,14 +203,16 @@ __device__ __forceinline__ void store_g4(float *g, int64_t e0, unsigned elems, c
     buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), wave_buffer(g + e0, elems * 4), lane_id() * 16);
 }
 
-// Sweep 1, chunk layout: g = fold of the contributions; optional per-block partial of sum g^2.
+// Sweep 1, chunk layout: g = fold of the contributions; optional per-block partial of sum g^2.  The chunk is
+// elements [lo, hi) of the update range; blocks are counted from the start of the range (see k_reduce4r), and
+// one that two chunks share is launched for both.
 template <int DT, bool SUMSQ, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
+__global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t lo, int64_t hi,
                                                   float *__restrict__ g, double *__restrict__ partials) {
-    const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
+    const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
     double acc = 0.0;
-    if (e < n) {
-        const unsigned elems = piece_elems(e0, n);
+    if (e >= lo && e < hi) {
+        const unsigned elems = piece_elems(e0, hi);
         Chunk4Loader<DT> ld{e};
         float X[4];
         fold4(ld, src, P, group_len, X);
@@ -1003,17 +1005,23 @@ bool many_small_tensors(const paro_plan_t *pl, int64_t c) {
     return (int64_t)piece_grid(pl->L) < pieces * PARO_DENSE_BLOCKS_PER_TENSOR;
 }
 
-// Launches sweep 1 over chunk c; returns the number of per-block partial sums it writes.
+// Blocks, counted from the start of the update range, that hold elements of the chunk that starts at lo.
+int64_t chunk_blocks(const paro_plan_t *pl, int64_t lo) { return piece_count(lo % PIECE + pl->L); }
+
+// Launches sweep 1 over chunk c, which starts at element lo of the update range (and of the arrays that it
+// gets); returns the number of per-block partial sums it writes.
 template <bool SUMSQ>
 int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const SrcTable &tab, int group_len, int64_t c,
-                  float *g, hipStream_t st) {
+                  int64_t lo, float *g_range, hipStream_t st) {
     const int64_t n = pl->L;
+    float *g = g_range + lo;
     double *partials = sc.partials;
     if (layout == PARO_CHUNK) {
-        const unsigned grid = (piece_grid(n) + 7u) & ~7u;       // a multiple of 8: see partial_slot()
+        const unsigned grid = (unsigned)((chunk_blocks(pl, lo) + 7) & ~(int64_t)7);       // a multiple of 8: see partial_slot()
         const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl->P)));
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
-                                                                                 lds, st, src, pl->P, group_len, n, g, partials)));
+                                                                                 lds, st, src, pl->P, group_len, lo, lo + n,
+                                                                                 g_range, partials)));
         return (int)grid;
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
@@ -1206,6 +1214,19 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     return sumsq_out && !one_sum ? finalize_sums(sc, n_sums, sumsq_out, st, rest) : PARO_OK;
 }
 
+// Whether sweep 1 over an update range of several chunks in the chunk layout goes chunk by chunk.  A wave of the
+// one launch over the range works out its chunk and the order of its ranks before its first load; with few
+// contributions of two bytes that is as much work as the fold (P = 2, two chunks of 50 M: 200 us against 2 x 66), and
+// large chunks repay a launch each.  Whole clipped steps, one launch and one per chunk: P = 2, 2 x 24 M 310 and 294
+// us, 2 x 120 M 1517 and 1400; P = 4, 2 x 50 M 664 and 643; but 4 x 12 M 321 and 331, fp32 at P = 4, 2 x 50 M 770 and
+// 783, P = 8, 2 x 50 M 758 and 767.
+bool chunk_by_chunk(const paro_plan_t *pl) {
+    if (pl->P > PARO_PAIR_MAX_RANKS || pl->dtype[0] == PARO_F32) return false;
+    const int64_t blocks = (chunk_blocks(pl, PIECE - 1) + 7) & ~(int64_t)7;       // at most
+    // (no more than a group of the norm, so that the scratch array does not matter)
+    return blocks >= PARO_RANGE_MAX_BLOCKS && blocks <= (pl->L > PARO_STATIC_MAX_CHUNK ? MAX_GRID : (int64_t)NORM_GROUP);
+}
+
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own
 // chunk only (so that the ranks' values add up to the model's) - or, with norm_over_range, every
 // chunk of the update range: one sum per chunk, added in chunk order.  rest: sweep 2 finishes the norm.
@@ -1216,23 +1237,23 @@ int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *co
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     const int own = paro::chunk_of_rank(pl, rank);
     const int64_t c0 = ob / pl->L, c1 = (ob + on) / pl->L;
-    if (layout == PARO_CHUNK && c1 - c0 > 1)
+    if (layout == PARO_CHUNK && c1 - c0 > 1 && !chunk_by_chunk(pl))
         return do_reduce_range(pl, sc, ob, on, norm_over_range ? -1 : own, contrib, grad_out, sumsq_out, st, rest);
     const bool per_chunk = sumsq_out && norm_over_range && c1 - c0 > 1;
     for (int64_t c = c0; c < c1; ++c) {
         SrcTable tab;
         int gl;
         const int64_t lo = c * pl->L - ob;
-        src_table(pl, (int)c, contrib, layout, lo, &tab, &gl);
+        src_table(pl, (int)c, contrib, layout, 0, &tab, &gl);
         if (sumsq_out && (per_chunk || c == own)) {
-            const int n_part = launch_reduce<true>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
+            const int n_part = launch_reduce<true>(pl, sc, layout, tab, gl, c, lo, grad_out, st);
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this chunk's partials are added up first
             rc = per_chunk ? finalize_partials(sc, sc.partials, n_part, sc.chunk_sums + (c - c0), st)
                            : finalize_partials(sc, sc.partials, n_part, sumsq_out, st, rest);
             if (rc) return rc;
         } else {
-            launch_reduce<false>(pl, sc, layout, tab, gl, c, grad_out + lo, st);
+            launch_reduce<false>(pl, sc, layout, tab, gl, c, lo, grad_out, st);
             PARO_HIP(hipGetLastError());
         }
     }

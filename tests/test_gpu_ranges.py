@@ -1,13 +1,14 @@
 """Update ranges of several chunks (optimizer state sharded inside the group, or not at all), chunk
-layout: one launch covers the whole range, blocks are counted from the range's start, and every chunk
-is folded in its own owner's order.  Sizes where that can go wrong: chunks shorter than a block (many
+layout: one launch covers the whole range (large chunks of few ranks: one launch each), blocks are counted
+from the range's start, and every chunk is folded in its own owner's order.  Sizes where that can go wrong: chunks shorter than a block (many
 chunks in one block), a block more or less than a chunk, chunk ends inside a block, padding."""
 import numpy as np
 import pytest
+import torch
 
 import oracle as orc
 import workloads as wl
-from harness import flat_inputs, hp_dict, np_of, run_rank
+from harness import DEV, flat_inputs, hp_dict, hp_struct, np_of, oracle_update, run_rank, stream
 
 pytestmark = pytest.mark.gpu
 
@@ -35,13 +36,57 @@ def test_every_chunk_of_the_range_in_its_own_order(paro, P, G, strategy, sched, 
                      check_unfused=max_norm > 0)
 
 
+@pytest.mark.parametrize("P,G,strategy,sched,dtype", [
+    (2, 1, "NNN", orc.RING, wl.BF16), (4, 2, "III", orc.HORING, wl.F16), (4, 4, "NNN", orc.RING, wl.BF16),
+    (4, 2, "III", orc.HORING, wl.F32), (6, 3, "III", orc.HRING, wl.BF16)])
+@pytest.mark.parametrize("L", [65528 * 256, 65529 * 256 + 8])
+def test_large_chunks_with_few_ranks_are_launched_one_by_one(paro, P, G, strategy, sched, dtype, L):
+    """Chunks of 65 536 blocks, counted with the one more that they may straddle and in eights, with up to 4 ranks and
+    two-byte gradients; the others of that size are not.  The second size ends inside a block that two launches share."""
+    total = P * L - 3
+    lay = orc.layout(P, G, [total])
+    assert lay.L == L
+    pl = paro.paro_plan(P, G, strategy, [total], sched=sched, grad_dtype=[dtype])
+    rank = P - 1
+    ob, ol = orc.state_range(lay, rank, strategy[2])
+    dev, host = flat_inputs(P, ol, 44, dtype=dtype)
+    for t, h in zip(dev, host):
+        t[total - ob:] = 0
+        h[total - ob:] = 0
+    state = [np_of(t) for t in wl.master_state(ol, 45)]
+    g_ref, own_ref = orc.reduce_shard(lay, strategy, sched, rank, host, "chunk")
+    ss_ref = orc.range_sumsq(lay, strategy, rank, g_ref)
+    ptrs = [t.data_ptr() for t in dev]
+    g = torch.empty(ol, dtype=torch.float32, device=DEV)
+    ss, own = (torch.full((1,), -1.0, dtype=torch.float64, device=DEV) for _ in range(2))
+    paro.paro_reduce_shard(pl, rank, ptrs, paro.PARO_CHUNK, g.data_ptr(), own.data_ptr(), stream())
+    assert np_of(g).tobytes() == g_ref.tobytes()
+    assert abs(float(own.item()) - own_ref) <= 1e-12 * own_ref
+    hp = hp_dict(P, max_norm=0.01)
+    lit = oracle_update(lay, strategy, rank, g_ref, *state, total_sumsq=ss_ref, hp=hp, step=3, literal32=True)
+    dst_len, slot, n = orc.pack_slot(lay, rank, strategy)
+    for static in (False, True):
+        p, m, v = (torch.from_numpy(a.copy()).to(DEV) for a in state)
+        g.zero_()
+        dst = torch.zeros(dst_len, dtype=torch.bfloat16, device=DEV)
+        tail = (hp_struct(paro, hp, 3), g.data_ptr(), ss.data_ptr(), p.data_ptr(), m.data_ptr(), v.data_ptr(), dst.data_ptr(),
+                stream())
+        if static:
+            paro.paro_step_fused_static(pl, rank, ptrs, *tail)
+        else:
+            paro.paro_step_fused(pl, rank, ptrs, paro.PARO_CHUNK, *tail)
+        assert np_of(g).tobytes() == g_ref.tobytes()
+        assert abs(float(ss.item()) - ss_ref) <= 1e-12 * ss_ref
+        for k, t in (("p", p), ("m", m), ("v", v)):
+            assert np_of(t).tobytes() == lit[k].tobytes(), k
+        assert np_of(dst)[slot:slot + n].tobytes() == lit["q"].tobytes()
+
+
 @pytest.mark.parametrize("L", [(1 << 29) + 264, (1 << 29) + 30_000_008, (1 << 29) + 70_001_000])
 def test_a_range_that_takes_several_launches_for_its_norm(paro, L):
     """The entry point that allocates nothing has room for the partial sums of 2^30 elements: a longer
     update range is swept in pieces whose sums are added in order.  Same results, the norm to the last bit, as with
     the plan's own scratch, which holds them all."""
-    import torch
-    from harness import DEV, hp_struct, stream
     P = 2
     pl = paro.paro_plan(P, 1, "NNN", [P * L], grad_dtype=[wl.F32])
     n = P * L
