@@ -40,7 +40,7 @@ namespace {
 #define PARO_FOLD_LOADS_PER_CU 224
 #endif
 #ifndef PARO_FOLD_WIDE_LOADS_PER_CU
-#define PARO_FOLD_WIDE_LOADS_PER_CU 192   // more than PARO_BATCH contributions
+#define PARO_FOLD_WIDE_LOADS_PER_CU 192   // many contributions (see fold_budget)
 #endif
 #ifndef PARO_FUSED_LOADS_PER_CU
 #define PARO_FUSED_LOADS_PER_CU 190

@@ -600,9 +600,14 @@ int fold_waves(int per_wave, int loads_per_cu) {
 // Loads a wave of the fold has in flight: a batch of contributions.
 int fold_loads(int P) { return std::min(P, PARO_BATCH); }
 // The chunk layout's budget.  More contributions than one batch are more DRAM pages than the wave's loads in
-// flight say: 12 waves instead of 14 (whole clipped steps: P = 64, 105 M elements 2786 -> 2743 us; P = 32, 77 M
-// 1232 -> 1226; 10 waves: 2735 and 1273).
-int fold_budget(int P) { return P > PARO_BATCH ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU; }
+// flight say: 12 waves instead of 14.  Not where a large part of a wave's life belongs to a short last batch of
+// two-byte contributions, with few bytes in flight.  Whole clipped steps on the same buffers, 14 and 12 waves: P = 64,
+// 105 M elements 2783 and 2753 us; P = 32, 105 M 1664 and 1638; P = 40, 36 M 666 and 659; fp32, P = 20, 36 M 654 and 642;
+// but bf16, P = 17, 105 M 1151 and 1219, P = 24, 77 M 1009 and 1025, P = 36, 77 M 1339 and 1350.
+int fold_budget(const paro_plan_t *pl) {
+    const bool short_batch = pl->dtype[0] != PARO_F32 && pl->P % PARO_BATCH != 0 && pl->P < 5 * PARO_BATCH / 2;
+    return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
+}
 
 // What a launch needs from the device besides the caller's buffers: the LDS size behind the
 // occupancy throttle and the scratch array of partial sums (per-block sums of a sweep-1 launch,
@@ -1021,7 +1026,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     double *partials = sc.partials;
     if (layout == PARO_CHUNK) {
         const unsigned grid = (unsigned)((chunk_blocks(pl, lo) + 7) & ~(int64_t)7);       // a multiple of 8: see partial_slot()
-        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl->P)));
+        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl)));
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
                                                                                  lds, st, src, pl->P, group_len, lo, lo + n,
                                                                                  g_range, partials)));
@@ -1178,7 +1183,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl->P)));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl)));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;
