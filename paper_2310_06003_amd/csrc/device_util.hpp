@@ -87,7 +87,7 @@ namespace {
 #define PARO_PACE_SLEEP 4           // units of 64 clocks between two loads of a paced fold
 #endif
 #ifndef PARO_PACE_MIN_BLOCKS
-#define PARO_PACE_MIN_BLOCKS 131072 // blocks of a launch from which on it is paced
+#define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)
 #endif
 #ifndef PARO_SPLIT_MAX
 #define PARO_SPLIT_MAX 16           // a tile with up to so many tensors inside is cut into pieces

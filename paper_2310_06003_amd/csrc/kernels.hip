@@ -929,7 +929,7 @@ int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
 // chunk's first element inside the update range.
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
-    tab->paced = piece_count(pl->L) >= PARO_PACE_MIN_BLOCKS;
+    tab->paced = piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
     paro::fold_order(pl, chunk, order, &gl);
@@ -948,7 +948,7 @@ RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const
     // not with two-byte contributions of 16 ranks and more, where the pauses only delay (paced and not, 90 M elements in
     // all: P = 16, 2 chunks, clipped 969 and 947 us, single sweep 841 and 832; 8 chunks 957 and 930; P = 32, 4 chunks 1533
     // and 1452; P = 64, 8 chunks 2526 and 2493; but P = 8, 8 chunks 687 and 695, fp32 at P = 16 1426 and 1440)
-    tab->paced = piece_count(on) >= PARO_PACE_MIN_BLOCKS && (pl->P < PARO_BATCH || pl->dtype[0] == PARO_F32);
+    tab->paced = piece_count(on) >= 2 * PARO_PACE_MIN_BLOCKS && (pl->P < PARO_BATCH || pl->dtype[0] == PARO_F32);
     for (int q = 0; q < pl->P; ++q) tab->p[q] = contrib[q];
     for (int q = pl->P; q < PARO_MAX_RANKS; ++q) tab->p[q] = nullptr;
     const bool ring = pl->sched == PARO_RING;

@@ -339,8 +339,9 @@ struct Folding {
 // N contributions, from the k-th on: all sources, then all loads - straight-line code.  A large launch
 // over the chunk layout is paced: with all its loads issued at once a wave touches P DRAM pages in one go;
 // with a pause after each, waves that start together read the same contribution together.  Whole clipped
-// steps unpaced -> paced: P = 64, 105 M elements 2913 -> 2830 us, P = 16, 421 M elements 4340 -> 4268; a
-// small launch is bound by latency (P = 16, 0.5 M elements 13.7 -> 15.9) and is not paced.
+// steps unpaced -> paced, on the same buffers: P = 64, 90 M elements 2446 -> 2373 us, P = 16, 150 M 1544 -> 1521,
+// P = 4, 150 M as they were; single sweep, P = 64, 16 M 418 -> 409, P = 16, 24 M 224 -> 223, P = 8, 16 M 109 -> 109.  A
+// small launch is bound by latency (P = 16, 2 M 26.5 -> 28.5; P = 32, 2 M, single sweep 29 -> 32) and is not paced.
 template <int N, class Ld, class Src, class Order>
 __device__ __forceinline__ void load_batch(const Ld &ld, const Src &src, int k, Order &ord, typename Ld::Raw *raw) {
     typename Ld::At at[N];
