@@ -18,9 +18,18 @@ pytestmark = pytest.mark.gpu
     (8, 2, "III", orc.HORING, wl.BF16), (6, 3, "NNN", orc.HRING, wl.F32), (8, 4, "NNI", orc.RING, wl.F16),
     (5, 5, "NNN", orc.RING, wl.BF16), (24, 2, "III", orc.HORING, wl.BF16), (4, 1, "III", orc.RING, wl.BF16)])
 def test_every_chunk_of_the_range_in_its_own_order(paro, P, G, strategy, sched, dtype, L):
-    total = P * L - (L + 3 if L > 8 and strategy == "NNN" else 3)           # the last chunk(s) end in padding
+    _three_ranks(paro, P, G, strategy, sched, dtype, L, P * L - 3)           # the last chunk ends in padding
+
+
+@pytest.mark.parametrize("L", [8, 24, 136])
+@pytest.mark.parametrize("strategy,G,sched,dtype", [("III", 2, orc.HORING, wl.BF16), ("NNN", 6, orc.HRING, wl.F32)])
+def test_chunks_that_are_all_padding(paro, strategy, G, sched, dtype, L):
+    _three_ranks(paro, 24, G, strategy, sched, dtype, L, 24 * (L - 7))       # 7 elements a chunk short: whole chunks in the end
+
+
+def _three_ranks(paro, P, G, strategy, sched, dtype, L, total):
     lay = orc.layout(P, G, [total])
-    assert lay.L == (L if total > P * (L - 8) else lay.L)
+    assert lay.L == L
     pl = paro.paro_plan(P, G, strategy, [total], sched=sched, grad_dtype=[dtype])
     n = P * lay.L
     dev, host = flat_inputs(P, n, 40 + L, dtype=dtype)
