@@ -56,12 +56,12 @@
  * elements each, the list up to twice that; built when the chunk has at most
  * 4 Mi tiles, or at most PARO_TILE_TABLE_MAX_TILES when that environment
  * variable is set; without them the kernels search; PARO_PAIR_MIN_BLOCKS, also
- * read at every call, makes sweep 1 of the tensor layout with up to 4 ranks give
- * a wave two blocks from that many blocks on instead of from the built-in size
- * on - both exist for tests).  Those first calls allocate and copy
- * synchronously - make them outside any stream capture; every later call only
- * enqueues kernels and can be captured.  Device
- * functions only enqueue work on `stream` (a hipStream_t passed as void*; NULL =
+ * read at every call, makes sweep 1 of the tensor layout with up to 4 ranks, or
+ * up to 6 over many small tensors, give a wave two blocks from that many blocks on
+ * instead of from the built-in size on - both exist for tests).  Those first calls
+ * allocate and copy synchronously - make them outside any stream capture; every
+ * later call only enqueues kernels and can be captured.  Device functions only
+ * enqueue work on `stream` (a hipStream_t passed as void*; NULL =
  * the default stream) and never synchronise; a launch error is reported by the
  * call that launched.  Calls that run concurrently on ONE plan (different
  * streams) race on the plan's scratch array; use one plan per stream.  Host
@@ -206,10 +206,8 @@ int paro_pack_slot(const paro_plan_t *plan, int rank, int64_t *dst_len, int64_t 
  *                 the same grad_dtype).
  *   PARO_TENSORS: contrib[q] -> DEVICE array of n_tensors DEVICE pointers, the
  *                 q-th rank's full gradient of each tensor (dtype per tensor as
- *                 planned; each naturally aligned - 8-byte (2-byte dtypes) or
- *                 16-byte (fp32) alignment of the data a rank contributes to
- *                 the range lets the kernels use vector loads, anything less
- *                 costs element loads; empty tensors may be NULL).
+ *                 planned; each aligned to its elements, which is enough for
+ *                 the kernels' vector loads; empty tensors may be NULL).
  * grad_out, p, m, v: DEVICE fp32 arrays over the update range, 16-byte aligned.
  * PARO_EALIGN for a misaligned pointer, PARO_EINVAL for a NULL one. */
 
@@ -242,9 +240,9 @@ int paro_pack_params(paro_plan_t *plan, int rank, const float *p, uint16_t *dst_
  * here): over the rank's whole UPDATE RANGE - its own chunk when the optimizer
  * state is sharded over all ranks ('G': the same value paro_reduce_shard gives);
  * every chunk of its block or of the model when it is sharded inside the group
- * only or not at all ('I', 'N': one sum per chunk, added in chunk order), so that
- * every replica of a range clips, or skips an overflowed step, alike - and with
- * 'N' it is the model's true norm.  With neither clipping nor skipping one sweep
+ * only or not at all ('I', 'N': added up in an order that depends only on the plan
+ * and the layout), so that every replica of a range clips, or skips an overflowed
+ * step, alike - and with 'N' it is the model's true norm.  With neither clipping nor skipping one sweep
  * does everything, the gradient is never stored, and both scratch pointers may
  * be NULL. */
 int paro_step_fused(paro_plan_t *plan, int rank, const void *const *contrib, int layout,
@@ -256,7 +254,7 @@ int paro_step_fused(paro_plan_t *plan, int rank, const void *const *contrib, int
  * serving or training loops and harnesses that forbid hipMalloc.  Same work, same
  * results, same buffer arguments as paro_step_fused with layout PARO_CHUNK, but the
  * per-block partial sums of the norm go to a static device array inside the library
- * (32 MiB + 16 KiB, held by every GPU the library runs on until the process ends)
+ * (32 MiB + 6 KiB, held by every GPU the library runs on until the process ends)
  * instead of the plan's device allocation: this call never allocates or frees
  * device memory, never synchronises, and does not touch the plan's device tables
  * (the plan may never have seen a device call).  Limits: chunk layout only; no

@@ -250,6 +250,11 @@ __device__ __forceinline__ int64_t uniform(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// One lane's value, for the whole wave.
+__device__ __forceinline__ double of_lane(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // Sum over the wave, valid in lane 0.  Fixed shape (shuffles by 32, 16, ... 1).
 __device__ __forceinline__ double wave_sum(double v) {
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_down(v, d, 64);

@@ -75,8 +75,13 @@ __device__ __forceinline__ double norm_total(const double *__restrict__ sums, in
 #pragma unroll
         for (int k = 0; k < NORM_SLICES; ++k) x[k] = sums[k];
         double s = x[0];
+        if (n == NORM_SLICES) {
 #pragma unroll
-        for (int k = 1; k < NORM_SLICES; ++k) s += k < n ? x[k] : 0.0;
+            for (int k = 1; k < NORM_SLICES; ++k) s += x[k];
+        } else {
+#pragma unroll
+            for (int k = 1; k < NORM_SLICES; ++k) s += k < n ? x[k] : 0.0;
+        }
         return s;
     }
     double acc = strided_sum<WAVE, U>(sums, lane_id(), n);
@@ -358,7 +363,7 @@ __global__ __launch_bounds__(WAVE) void k_norm_total(const double *__restrict__ 
 __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double *__restrict__ partials, int n, int chunk,
                                                                     double *out) {
     static_assert(NORM_SLICES == 8, "three halvings leave one slice to a lane");
-    __shared__ double s_wave[NORM_SLICES][FINALIZE_TPB / WAVE];
+    __shared__ double s_wave[NORM_SLICES][FINALIZE_TPB / WAVE + 1];     // + 1: the slices' rows start in different banks
     const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
     constexpr int U = NORM_ONE_BLOCK_PARTIALS / NORM_SLICES / FINALIZE_TPB;
     double x[NORM_SLICES][U], acc[NORM_SLICES];
@@ -393,9 +398,9 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
         double r = of_slice[0];
 #pragma unroll
         for (int w = 1; w < FINALIZE_TPB / WAVE; ++w) r += of_slice[w];
-        double total = __shfl(r, 0, WAVE);
+        double total = of_lane(r, 0);
 #pragma unroll
-        for (int b = 1; b < NORM_SLICES; ++b) total += __shfl(r, b, WAVE);
+        for (int b = 1; b < NORM_SLICES; ++b) total += of_lane(r, b);
         if (lane == 0) *out = total;
     }
 }
@@ -1126,10 +1131,10 @@ int total_of(const NormSums &s, hipStream_t st) {
 }
 
 // Adds the n_part partial sums a sweep-1 launch left in the scratch array into *out (device) - or, with
-// `rest`, only as far as sweep 2 goes on by itself, and *rest says from where.  Either way the same adds in the
-// same order: the fused step clips by the value that paro_reduce_shard leaves, to the last bit.  Every kernel more in this
-// chain of short dependent ones costs 2-3 us of a step; what a wave of sweep 2 adds up beside its state
-// loads is hidden while it is little.  Whole clipped steps at P = 8, bf16, with the chain of up to two
+// `rest`, only as far as sweep 2 goes on by itself, and *rest says from where.  Either way the same adds in
+// the same order: the fused step clips by the value that paro_reduce_shard leaves, to the last bit.  Every
+// kernel more in this chain of short dependent ones costs 2-3 us of a step; what a wave of sweep 2 adds up
+// beside its state loads is hidden while it is little.  Whole clipped steps at P = 8, bf16, with the chain of up to two
 // small kernels that ended in one scalar, and now:
 //   0.5 M elements (1954 partials, added up by every wave)   12.9 -> 10.4 us
 //   0.75 M (2930; eight slice sums)                          13.7 -> 13.3; added up by every wave 16.5
@@ -1237,7 +1242,7 @@ bool chunk_by_chunk(const paro_plan_t *pl) {
 
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own
 // chunk only (so that the ranks' values add up to the model's) - or, with norm_over_range, every
-// chunk of the update range: one sum per chunk, added in chunk order.  rest: sweep 2 finishes the norm.
+// chunk of the update range, in a fixed order.  rest: sweep 2 finishes the norm.
 int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *const *contrib, int layout, float *grad_out,
               double *sumsq_out, bool norm_over_range, hipStream_t st, NormSums *rest = nullptr) {
     int rc;

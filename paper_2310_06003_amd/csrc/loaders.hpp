@@ -1,5 +1,5 @@
 // How the fold gets its operands - the chunk layout (arrays in shard coordinates) and the tensor
-// layout (per-tensor gradients, found through the plan's per-tile table or by searching its offset
+// layout (per-tensor gradients, found through the plan's list of pieces or by searching its offset
 // table) - and the ordered fold itself.  Every sweep kernel runs in one-wave blocks of 256
 // elements, 4 per thread.  Included by kernels.hip only.
 #pragma once

@@ -25,8 +25,8 @@ struct paro_tile_info {
 };
 
 // A piece of a chunk: elements [lo, hi) of a tile (hi == PARO_TILE: to its end), which lie in one
-// tensor.  Pieces are listed in address order (those of cut tiles first, in a small chunk); a tile is one piece, or, where it holds a few tensors,
-// one for each of them (and one for the padding at its end).
+// tensor.  Pieces are listed in address order (those of cut tiles first, in a small chunk); a tile is
+// one piece, or, where it is cut, one for each tensor in it (and one for the padding at its end).
 struct paro_piece_info {
     int64_t where;      // offset in the tensor of the tile's first element (< 0 where the tensor starts
                         // later) << 19 | gradient dtype << 17 | hi << 8 | lo

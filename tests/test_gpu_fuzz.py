@@ -2,7 +2,8 @@
 list (empty, tiny, tile-sized and large tensors), gradient dtypes, weight-decay mask, layout,
 alignment of the per-tensor gradients, clipping, decay style, with and without the per-tile
 table, with sweep 1's two-blocks-per-wave shape forced on where there are at most 4 ranks, or 6
-and many small tensors (it is otherwise kept for large launches).  Every rank of every configuration, fused entry point, full parity."""
+and many small tensors (it is otherwise kept for large launches).  Every rank of every
+configuration, fused entry point, full parity."""
 import numpy as np
 import pytest
 import torch
