@@ -13,17 +13,41 @@
 namespace {
 
 // Cache-policy and occupancy knobs (the defaults are the measured best on MI355X).
-// Everything is touched once: loads are streaming (nt) loads.  Cache policy of the stores, as the
+// Nearly everything is touched once: loads are streaming (nt) loads.  Cache policy of the stores, as the
 // instruction's bits: 1 = sc0, 2 = nt, 16 = sc1 (0 = default policy): streaming at system scope
-// (nt sc1), which the mixed read/write sweeps like 2 % better than nt alone.
-#ifndef PARO_POL_G_ST
-#define PARO_POL_G_ST 18            // the reduced gradient out of sweep 1
+// (nt sc1), which the large mixed read/write sweeps like 2 % better than nt alone - and without the
+// streaming hint (sc1) for what the 256 MB memory-side cache holds until it is read again, see the
+// PARO_KEEP_ limits.
+#ifndef PARO_POL_STREAM_ST
+#define PARO_POL_STREAM_ST 18
 #endif
-#ifndef PARO_POL_STATE_ST
-#define PARO_POL_STATE_ST 18        // p, m, v and the packed parameters out of them
+#ifndef PARO_POL_KEEP_ST
+#define PARO_POL_KEEP_ST 16
 #endif
-#ifndef PARO_POL_LIGHT_ST
-#define PARO_POL_LIGHT_ST 18
+// Largest results that are stored without the streaming hint.
+// The reduced gradient, which sweep 2 reads again (with plain loads: a streaming load gives the line up), where the
+// contributions that pass through the cache meanwhile are no more than it holds.  Whole clipped steps, bf16, streaming and
+// kept, one process on three states in turn: P = 2, 12 M elements 77.6 and 72.9 us; P = 4, 16 M 107.3 and 100.6; P = 8,
+// 3 M 31.6 and 30.0, 16 M 127.9 and 120.2; P = 16, 6 M 69.1 and 66.3; on ten states in turn (each with a gradient array of its
+// own) P = 8, 2 to 16 M, 2 to 6 % ahead.  After a kernel that leaves the cache full of its own results, P = 2 to 8 gain 1 to 4 %,
+// P = 16 loses 0 to 1 % to 8 M and 2 % at 16 M, P = 32 and 64 2 to 4 % from 2 M on: hence the limit on the contributions, and
+// more than 16 ranks keep only what is small enough to keep its state as well.
+#ifndef PARO_KEEP_G_ELEMS
+#define PARO_KEEP_G_ELEMS (16 << 20)
+#endif
+#ifndef PARO_KEEP_G_READ_BYTES
+#define PARO_KEEP_G_READ_BYTES (256 << 20)
+#endif
+// p, m, v and the packed parameters, which the next step reads: with 1 M elements (18 MB with the gradient)
+// 15.3 -> 14.1 us (P = 8, clipped) and 9.6 -> 8.5 (one sweep), on ten states as on three; 4 M on ten states 37.5 -> 40.0.
+#ifndef PARO_KEEP_STATE_ELEMS
+#define PARO_KEEP_STATE_ELEMS (1 << 20)
+#endif
+// A message of an all-gather or the result of a hop, which the next step of the ring reads: 8 buffers, messages of
+// 15 MB (56 of them) 375 -> 341 us, 31 MB 641 -> 607, 62 MB 1256 -> 1312; hop, 8 M elements 13.6 -> 12.9 us, 30 M 45.1
+// -> 45.6.
+#ifndef PARO_KEEP_MESSAGE_BYTES
+#define PARO_KEEP_MESSAGE_BYTES (48 << 20)
 #endif
 #ifndef PARO_BATCH
 #define PARO_BATCH 16               // contributions loaded before the first is consumed
@@ -47,6 +71,9 @@ namespace {
 #endif
 #ifndef PARO_ADAM_WAVES_PER_CU
 #define PARO_ADAM_WAVES_PER_CU 12
+#endif
+#ifndef PARO_ADAM_SMALL_ELEMS
+#define PARO_ADAM_SMALL_ELEMS (4 << 20)  // a small sweep 2 runs in as many waves as the masked one (12 waves: 2 M elements 22.7 us, 16: 22.5)
 #endif
 #ifndef PARO_ADAM_MASK_WAVES_PER_CU
 #define PARO_ADAM_MASK_WAVES_PER_CU 16   // with a decay mask: a table look-up per wave to hide as well
@@ -127,6 +154,7 @@ template <int N>
 struct SrcTableOf {
     const void *p[N];
     int paced;       // the chunk layout's loads go out one by one, with a pause in between
+    int keep_g;      // the reduced gradient is stored to stay in the memory-side cache
 };
 using SrcTable = SrcTableOf<PARO_MAX_RANKS>;
 constexpr int FEW_SRC = 16;
@@ -134,6 +162,7 @@ constexpr int FEW_SRC = 16;
 struct AdamConsts {
     float beta1, beta2, omb1, omb2, eps, step_size, sqrt_bc2, decay, wd, grad_scale, max_norm;
     int adamw, skip_nonfinite, pack_dtype;
+    int keep_state;     // p, m, v and the packed parameters are stored to stay in the memory-side cache
 };
 
 // What a launch needs to map its elements to tensors.
@@ -236,6 +265,11 @@ __device__ __forceinline__ void buf_store8(u32x2 v, wave_buf b, unsigned off) {
 template <int POL>
 __device__ __forceinline__ void buf_store16(u32x4 v, wave_buf b, unsigned off) {
     __builtin_amdgcn_raw_buffer_store_b128(v, b, (int)off, 0, POL);
+}
+// ... with the streaming hint or, where the memory-side cache is to keep the data, without.
+__device__ __forceinline__ void buf_store16_as(bool keep, u32x4 v, wave_buf b, unsigned off) {
+    if (keep) buf_store16<PARO_POL_KEEP_ST>(v, b, off);
+    else buf_store16<PARO_POL_STREAM_ST>(v, b, off);
 }
 __device__ __forceinline__ u32x4 as_u32x4(float a, float b, float c, float d) {
     return u32x4{__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};

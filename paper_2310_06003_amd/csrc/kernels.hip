@@ -18,7 +18,7 @@
 //             DRAM pages (another 3-6 %).  The tensor layout over many small
 //             tensors wants the opposite - its waves wait on look-ups with no
 //             data in flight - and gets every wave the registers allow.
-//   caches    everything is touched once: streaming (non-temporal) loads; stores
+//   caches    nearly everything is touched once: streaming (non-temporal) loads; stores
 //             through per-wave buffer descriptors, which let the instruction say
 //             "streaming, system scope" (nt sc1: 2 % better than nt alone).
 //   fold      the P contributions of an element are added in a fixed order
@@ -162,14 +162,18 @@ __device__ __forceinline__ void update4(const AdamConsts &a, float sc, const boo
         }
         return;
     }
-    constexpr int ST = PARO_POL_STATE_ST;
-    buf_store16<ST>(as_u32x4(pp[0], pp[1], pp[2], pp[3]), wave_buffer(p + e0, elems * 4), lane_id() * 16);
-    buf_store16<ST>(as_u32x4(mm[0], mm[1], mm[2], mm[3]), wave_buffer(m + e0, elems * 4), lane_id() * 16);
-    buf_store16<ST>(as_u32x4(vv[0], vv[1], vv[2], vv[3]), wave_buffer(v + e0, elems * 4), lane_id() * 16);
-    if (PACK) {
-        const u32x2 w = {pack2_lowp(pp[0], pp[1], a.pack_dtype), pack2_lowp(pp[2], pp[3], a.pack_dtype)};
-        buf_store8<ST>(w, wave_buffer(dst + e0, elems * 2), lane_id() * 8);
-    }
+    const auto store = [&](auto pol) {
+        constexpr int ST = decltype(pol)::value;
+        buf_store16<ST>(as_u32x4(pp[0], pp[1], pp[2], pp[3]), wave_buffer(p + e0, elems * 4), lane_id() * 16);
+        buf_store16<ST>(as_u32x4(mm[0], mm[1], mm[2], mm[3]), wave_buffer(m + e0, elems * 4), lane_id() * 16);
+        buf_store16<ST>(as_u32x4(vv[0], vv[1], vv[2], vv[3]), wave_buffer(v + e0, elems * 4), lane_id() * 16);
+        if (PACK) {
+            const u32x2 w = {pack2_lowp(pp[0], pp[1], a.pack_dtype), pack2_lowp(pp[2], pp[3], a.pack_dtype)};
+            buf_store8<ST>(w, wave_buffer(dst + e0, elems * 2), lane_id() * 8);
+        }
+    };
+    if (a.keep_state) store(std::integral_constant<int, PARO_POL_KEEP_ST>{});
+    else store(std::integral_constant<int, PARO_POL_STREAM_ST>{});
 }
 
 // Which of the thread's 4 elements take weight decay (padding does, and stays 0).  loc: from
@@ -204,8 +208,8 @@ __device__ __forceinline__ double sumsq4(const float X[4]) {
 
 // --------------------------------------------------------------------- kernels
 
-__device__ __forceinline__ void store_g4(float *g, int64_t e0, unsigned elems, const float X[4]) {
-    buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), wave_buffer(g + e0, elems * 4), lane_id() * 16);
+__device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsigned elems, const float X[4]) {
+    buf_store16_as(keep, as_u32x4(X[0], X[1], X[2], X[3]), wave_buffer(g + e0, elems * 4), lane_id() * 16);
 }
 
 // Sweep 1, chunk layout: g = fold of the contributions; optional per-block partial of sum g^2.  The chunk is
@@ -221,7 +225,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, in
         Chunk4Loader<DT> ld{e};
         float X[4];
         fold4(ld, src, P, group_len, X);
-        store_g4(g, e0, elems, X);
+        store_g4(src.keep_g, g, e0, elems, X);
         if (SUMSQ) acc = sumsq4(X);
     }
     if (SUMSQ) {
@@ -247,7 +251,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, i
         float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         const bool counts = fold_range<DT>(rm, src, P, e0, n, X);
         if (e < n) {
-            store_g4(g, e0, piece_elems(e0, n), X);
+            store_g4(src.keep_g, g, e0, piece_elems(e0, n), X);
             if (SUMSQ && counts) acc = sumsq4(X);
         }
     }
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, i
 }
 
 // Sweep 1, tensor layout: one piece of the launch.  Every lane of the wave takes part.
-template <bool SUMSQ, int KB, bool NT, class Src>
+template <bool SUMSQ, int KB, bool NT, bool KEEP, class Src>
 __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, const Src &src, int P, int group_len,
                                            int64_t n, float *g, double &acc) {
     const int64_t e = c.e0 + lane_id() * EPT;
@@ -272,12 +276,12 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
         if (c.pc.tensor == -1) locate4(tm, c.pc.seg, tm.begin + c.e0, lane_id() * EPT, loc);     // the whole wave
         if (e >= n) return;
         if (c.pc.tensor != -2) fold_tensors<NT, KB>(c.pc, loc, src, P, group_len, X);
-        store_g4(g, c.e0, piece_elems(c.e0, n), X);
+        store_g4(KEEP, g, c.e0, piece_elems(c.e0, n), X);
         if (SUMSQ) acc += sumsq4(X);
     } else if (c.a < c.b) {
         if (c.pc.tensor != -2) fold_part(c, src, P, group_len, X);
         if (c.a == 0 && c.b == EPT) {
-            store_g4(g, c.e0, piece_elems(c.e0, n), X);
+            store_g4(KEEP, g, c.e0, piece_elems(c.e0, n), X);
             if (SUMSQ) acc += sumsq4(X);
         } else {
 #pragma unroll
@@ -299,14 +303,15 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
 // 835, P = 6, 80 M 641 and 611, P = 7, 80 M with a quarter fp32 699 and 696; at P = 8 the other way round (69 M
 // elements: 457 and 476 us).  The list must leave its blocks whole: cut ones part the pairs (P = 5, 115 M: 884).
 // KB: contributions loaded before the first is consumed (8 when launched for P <= 8 only: fewer
-// registers, more waves).  NT: the list's blocks start on cache lines.
+// registers, more waves).  NT: the list's blocks start on cache lines.  KEEP: g is stored to stay in the memory-side
+// cache (a branch on it in the kernel cost 12 scalar registers and, in a launch that streams or not, 2 % of a step).
 // What bounds it: HBM, behind two dependent look-ups per wave (the piece, then the P pointers).  Taken one
 // by one - pointer of the table, pointer of the tensor, a branch on its alignment, the load - the second
 // was P round trips to the scalar cache in a row; now all pointers of a batch are fetched together and the
 // loads are straight-line code.  Sweep 1 over 10 000 tensors of 1 to 65536 elements (P = 8, 174 MB): 49.8
 // -> 35 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
 // (290 MB): 113 -> 86 us.
-template <bool SUMSQ, int PPW, int KB, bool NT, int NSRC>
+template <bool SUMSQ, int PPW, int KB, bool NT, int NSRC, bool KEEP>
 __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
                                                    float *__restrict__ g, double *__restrict__ partials,
                                                    const TensorMap tm) {
@@ -320,8 +325,8 @@ __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, i
             float X[8];
             fold_tensor_pair<NT, KB>(pc, src, P, group_len, X);
             const wave_buf out = wave_buffer(g + e0, 2 * PIECE * 4);
-            buf_store16<PARO_POL_G_ST>(as_u32x4(X[0], X[1], X[2], X[3]), out, lane_id() * 16);
-            buf_store16<PARO_POL_G_ST>(as_u32x4(X[4], X[5], X[6], X[7]), out, PIECE * 4 + lane_id() * 16);
+            buf_store16_as(KEEP, as_u32x4(X[0], X[1], X[2], X[3]), out, lane_id() * 16);
+            buf_store16_as(KEEP, as_u32x4(X[4], X[5], X[6], X[7]), out, PIECE * 4 + lane_id() * 16);
             if (SUMSQ) acc = sumsq4(X) + sumsq4(X + 4);
             done = true;
         }
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, i
 #pragma unroll 1
         for (int j = 0; j < PPW; ++j) {
             const Cut c = cut_of(tm, i0 + j, n);
-            if (c.e0 < n) reduce_cut<SUMSQ, KB, NT>(tm, c, src, P, group_len, n, g, acc);
+            if (c.e0 < n) reduce_cut<SUMSQ, KB, NT, KEEP>(tm, c, src, P, group_len, n, g, acc);
         }
     }
     if (SUMSQ) {
@@ -409,7 +414,8 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // MASK: some tensors are exempt from weight decay.  The global sum of squares comes as n_sums sums
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
-template <bool PACK, bool MASK>
+// KEPT: sweep 1 stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
+template <bool PACK, bool MASK, bool KEPT>
 __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double *__restrict__ sums, int n_sums,
                                                 double *__restrict__ sumsq_out, const float *__restrict__ g, float *__restrict__ p,
                                                 float *__restrict__ m, float *__restrict__ v,
@@ -426,7 +432,7 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
     u32x4 G;
     State4 s;
     if (e < n) {
-        G = ld_nt(reinterpret_cast<const u32x4 *>(g + e));
+        G = KEPT ? *reinterpret_cast<const u32x4 *>(g + e) : ld_nt(reinterpret_cast<const u32x4 *>(g + e));
         s = load_state4(p, m, v, e);
     }
     float sc = a.grad_scale;
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(WAVE) void k_pack(const float *__restrict__ p, uint
     const u32x4 P = ld_nt(reinterpret_cast<const u32x4 *>(p + e));
     const u32x2 w = {pack2_lowp(__uint_as_float(P.x), __uint_as_float(P.y), pack_dtype),
                      pack2_lowp(__uint_as_float(P.z), __uint_as_float(P.w), pack_dtype)};
-    buf_store8<PARO_POL_LIGHT_ST>(w, wave_buffer(dst + e0, elems * 2), lane_id() * 8);
+    buf_store8<PARO_POL_STREAM_ST>(w, wave_buffer(dst + e0, elems * 2), lane_id() * 8);
 }
 
 // One ring hop / one accumulation: out = a + b, element by element in fp32.  n may be any
@@ -533,27 +539,27 @@ __device__ __forceinline__ float hop_load1(const void *a, int64_t i) {
 }
 
 template <int DA, int DB>
-__global__ __launch_bounds__(WAVE) void k_hop(const void *a, const void *b, float *out, int64_t n) {
+__global__ __launch_bounds__(WAVE) void k_hop(const void *a, const void *b, float *out, int64_t n, int keep) {
     const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
     const unsigned whole = piece_elems(e0, n) & ~3u;       // elements of the block in whole groups of 4
     if (e + EPT <= n) {
         float x[4], y[4];
         hop_load4<DA>(a, e, x);
         hop_load4<DB>(b, e, y);
-        buf_store16<PARO_POL_LIGHT_ST>(as_u32x4(x[0] + y[0], x[1] + y[1], x[2] + y[2], x[3] + y[3]),
-                                       wave_buffer(out + e0, whole * 4), lane_id() * 16);
+        buf_store16_as(keep, as_u32x4(x[0] + y[0], x[1] + y[1], x[2] + y[2], x[3] + y[3]), wave_buffer(out + e0, whole * 4),
+                       lane_id() * 16);
     } else {
         for (int64_t i = e; i < n; ++i) out[i] = hop_load1<DA>(a, i) + hop_load1<DB>(b, i);
     }
 }
 
 // Plain copy of n 16-byte units (an all-gather message landing in the parameter buffer).
-__global__ __launch_bounds__(WAVE) void k_copy16(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int64_t n) {
+__global__ __launch_bounds__(WAVE) void k_copy16(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int64_t n, int keep) {
     const int64_t i0 = (int64_t)blockIdx.x * WAVE;
     if (i0 + threadIdx.x >= n) return;
     const unsigned bytes = (unsigned)min((int64_t)WAVE, n - i0) * 16;
     const u32x4 v = ld_nt(src + i0 + threadIdx.x);
-    buf_store16<PARO_POL_LIGHT_ST>(v, wave_buffer(dst + i0, bytes), lane_id() * 16);
+    buf_store16_as(keep, v, wave_buffer(dst + i0, bytes), lane_id() * 16);
 }
 
 }  // namespace
@@ -904,6 +910,18 @@ int check_contrib(const paro_plan_t *pl, const void *const *contrib, int layout,
     return PARO_OK;
 }
 
+// Elements of a rank's update range: the length of its state arrays and of the reduced gradient.
+int64_t update_elems(const paro_plan_t *pl) {
+    int64_t ob, on;
+    paro::letter_range(pl, 0, pl->letters[2], &ob, &on);
+    return on;
+}
+bool keeps_g(const paro_plan_t *pl) {
+    const int64_t n = update_elems(pl), esize = pl->uniform_dtype && pl->dtype[0] == PARO_F32 ? 4 : 2;
+    if (pl->P > PARO_BATCH && n > PARO_KEEP_STATE_ELEMS) return false;
+    return n <= PARO_KEEP_G_ELEMS && n * pl->P * esize <= PARO_KEEP_G_READ_BYTES;
+}
+
 int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
     if (!hp) return fail(PARO_EINVAL, std::string(fn) + ": hp is NULL");
     if (hp->step < 1) return fail(PARO_EINVAL, std::string(fn) + ": step must be >= 1");
@@ -926,14 +944,20 @@ int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
     a->max_norm = hp->max_norm;
     a->adamw = hp->adamw ? 1 : 0;
     a->skip_nonfinite = hp->skip_nonfinite ? 1 : 0;
-    a->pack_dtype = PARO_BF16;         // the entry points overwrite it with the plan's
     return PARO_OK;
+}
+
+// ... and what the plan says.
+void plan_consts(const paro_plan_t *pl, AdamConsts *a) {
+    a->pack_dtype = pl->pack_dtype;
+    a->keep_state = update_elems(pl) <= PARO_KEEP_STATE_ELEMS;
 }
 
 // Pointer table of a chunk in fold order.  Chunk layout: pointers advanced to the
 // chunk's first element inside the update range.
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
+    tab->keep_g = keeps_g(pl);
     tab->paced = piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
@@ -950,6 +974,7 @@ void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int
 // ... and of a launch over an update range of several chunks: pointers in rank order, the order of
 // each chunk's fold follows from the range map.
 RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const void *const *contrib, SrcTable *tab) {
+    tab->keep_g = keeps_g(pl);
     // not with two-byte contributions of 16 ranks and more, where the pauses only delay (paced and not, 90 M elements in
     // all: P = 16, 2 chunks, clipped 969 and 947 us, single sweep 841 and 832; 8 chunks 957 and 930; P = 32, 4 chunks 1533
     // and 1452; P = 64, 8 chunks 2526 and 2493; but P = 8, 8 chunks 687 and 695, fp32 at P = 16 1426 and 1440)
@@ -980,6 +1005,7 @@ SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
     SrcTableOf<FEW_SRC> few;
     std::copy(tab.p, tab.p + FEW_SRC, few.p);
     few.paced = tab.paced;
+    few.keep_g = tab.keep_g;
     return few;
 }
 // CALL with `src`, the pointer table in the size that the kernels for NSRC pointers take.
@@ -996,16 +1022,17 @@ SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
         }                                        \
     } while (0)
 
-#define PARO_BY_LINES(on_lines, CALL)  \
-    do {                               \
-        if (on_lines) {                \
-            constexpr bool NT = true;  \
-            CALL;                      \
-        } else {                       \
-            constexpr bool NT = false; \
-            CALL;                      \
-        }                              \
+#define PARO_BY_FLAG(value, FLAG, ...)   \
+    do {                                 \
+        if (value) {                     \
+            constexpr bool FLAG = true;  \
+            __VA_ARGS__;                 \
+        } else {                         \
+            constexpr bool FLAG = false; \
+            __VA_ARGS__;                 \
+        }                                \
     } while (0)
+#define PARO_BY_LINES(on_lines, CALL) PARO_BY_FLAG(on_lines, NT, CALL)
 
 // Whether chunk c is cut into many small pieces of tensors (fewer than PARO_DENSE_BLOCKS_PER_TENSOR
 // blocks per piece on average) rather than a few large ones.
@@ -1054,24 +1081,27 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const bool pairs = few || (pl->P <= PARO_PAIR_SMALL_MAX_RANKS && small && !pl->dev.f32[(size_t)c]);
     if (pairs && piece_count(n) >= pair_min_blocks) {
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
-        if (few)
-            PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC>), dim3(grid), dim3(WAVE),
-                                                       0, st, few_sources(tab), pl->P, group_len, n, g, partials, tm));
-        else
-            PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC>), dim3(grid), dim3(WAVE), 0, st,
-                                                       few_sources(tab), pl->P, group_len, n, g, partials, tm));
+        PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
+            if (few)
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st,
+                                   few_sources(tab), pl->P, group_len, n, g, partials, tm);
+            else
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, few_sources(tab),
+                                   pl->P, group_len, n, g, partials, tm);
+        }));
         return (int)grid;
     }
     const unsigned grid = (unsigned)((pieces + 7) & ~(int64_t)7);
     const unsigned lds =
         throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU));
-    if (pl->P <= 8)                                                         // a batch of 8 contributions: fewer registers
-        PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC>), dim3(grid), dim3(WAVE), lds, st,
-                                                   few_sources(tab), pl->P, group_len, n, g, partials, tm));
-    else
-        PARO_BY_TABLE(pl->P, tab, PARO_BY_LINES(on_lines, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT, NSRC>), dim3(grid),
-                                                                             dim3(WAVE), lds, st, src, pl->P, group_len, n, g,
-                                                                             partials, tm)));
+    PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
+        if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
+            hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, few_sources(tab), pl->P,
+                               group_len, n, g, partials, tm);
+        else
+            PARO_BY_TABLE(pl->P, tab, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT, NSRC, KEEP>), dim3(grid), dim3(WAVE), lds,
+                                                         st, src, pl->P, group_len, n, g, partials, tm));
+    }));
     return (int)grid;
 }
 
@@ -1279,17 +1309,18 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     if (!pl->any_no_decay) {
-        const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_WAVES_PER_CU);
-        hipLaunchKernelGGL((k_adam4<PACK, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out, grad, p, m, v,
-                           dst, on, map_for(pl, sc, ob, false));
+        const unsigned lds = throttle_lds(sc.lds_per_cu, on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU : PARO_ADAM_WAVES_PER_CU);
+        PARO_BY_FLAG(keeps_g(pl), KEPT, hipLaunchKernelGGL((k_adam4<PACK, false, KEPT>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a,
+                                                           norm.sums, norm.n, norm.out, grad, p, m, v, dst, on, map_for(pl, sc, ob, false)));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {      // chunk by chunk: each has its own per-tile table
         const int64_t lo = c * pl->L - ob;
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_MASK_WAVES_PER_CU);
-        hipLaunchKernelGGL((k_adam4<PACK, true>), dim3(piece_grid(pl->L)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out, grad + lo,
-                           p + lo, m + lo, v + lo, dst ? dst + lo : nullptr, pl->L, map_for(pl, sc, c * pl->L, true));
+        PARO_BY_FLAG(keeps_g(pl), KEPT, hipLaunchKernelGGL((k_adam4<PACK, true, KEPT>), dim3(piece_grid(pl->L)), dim3(WAVE), lds, st, a,
+                                                           norm.sums, norm.n, norm.out, grad + lo, p + lo, m + lo, v + lo,
+                                                           dst ? dst + lo : nullptr, pl->L, map_for(pl, sc, c * pl->L, true)));
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
@@ -1410,7 +1441,7 @@ int paro_adam_shard(paro_plan_t *pl, int rank, const paro_adam_t *hp, const floa
     if ((rc = check_ptr(v, "paro_adam_shard: v"))) return rc;
     if ((a.max_norm > 0.0f || a.skip_nonfinite) && !total_sumsq)
         return fail(PARO_EINVAL, "paro_adam_shard: clipping and skip_nonfinite need total_sumsq");
-    a.pack_dtype = pl->pack_dtype;
+    plan_consts(pl, &a);
     if (dst_base && (reinterpret_cast<uintptr_t>(dst_base) & 15))
         return fail(PARO_EALIGN, "paro_adam_shard: dst_base is not 16-byte aligned");
     if ((rc = ensure_device(pl))) return rc;
@@ -1452,7 +1483,7 @@ int paro_step_fused(paro_plan_t *pl, int rank, const void *const *contrib, int l
     if ((rc = check_ptr(m, "paro_step_fused: m"))) return rc;
     if ((rc = check_ptr(v, "paro_step_fused: v"))) return rc;
     if ((rc = check_ptr(dst_base, "paro_step_fused: dst_base"))) return rc;
-    a.pack_dtype = pl->pack_dtype;
+    plan_consts(pl, &a);
     const bool clip = a.max_norm > 0.0f || a.skip_nonfinite;       // both need the norm before the update
     if (clip) {
         if ((rc = check_ptr(grad_scratch, "paro_step_fused: grad_scratch"))) return rc;
@@ -1485,7 +1516,7 @@ int paro_step_fused_static(const paro_plan_t *pl, int rank, const void *const *c
     if ((rc = check_ptr(m, "paro_step_fused_static: m"))) return rc;
     if ((rc = check_ptr(v, "paro_step_fused_static: v"))) return rc;
     if ((rc = check_ptr(dst_base, "paro_step_fused_static: dst_base"))) return rc;
-    a.pack_dtype = pl->pack_dtype;
+    plan_consts(pl, &a);
     if (a.max_norm > 0.0f || a.skip_nonfinite) {
         if ((rc = check_ptr(grad_scratch, "paro_step_fused_static: grad_scratch"))) return rc;
         if (!sumsq_scratch || (reinterpret_cast<uintptr_t>(sumsq_scratch) & 7))
@@ -1508,8 +1539,9 @@ int launch_hop(const paro_plan_t *pl, const void *a, int da, const void *b, int 
     if (n <= 0) return PARO_OK;
     const unsigned grid = piece_grid(n);
     const unsigned lds = throttle_lds(pl->dev.lds_per_cu, PARO_HOP_WAVES_PER_CU);
+    const int keep = n * 4 <= PARO_KEEP_MESSAGE_BYTES;
 #define PARO_HOP_CASE(A, B)                                                                                   \
-    if (da == A && db == B) hipLaunchKernelGGL((k_hop<A, B>), dim3(grid), dim3(WAVE), lds, st, a, b, out, n)
+    if (da == A && db == B) hipLaunchKernelGGL((k_hop<A, B>), dim3(grid), dim3(WAVE), lds, st, a, b, out, n, keep)
     PARO_HOP_CASE(PARO_BF16, PARO_BF16); PARO_HOP_CASE(PARO_BF16, PARO_F32); PARO_HOP_CASE(PARO_BF16, PARO_F16);
     PARO_HOP_CASE(PARO_F32, PARO_BF16);  PARO_HOP_CASE(PARO_F32, PARO_F32);  PARO_HOP_CASE(PARO_F32, PARO_F16);
     PARO_HOP_CASE(PARO_F16, PARO_BF16);  PARO_HOP_CASE(PARO_F16, PARO_F32);  PARO_HOP_CASE(PARO_F16, PARO_F16);
@@ -1565,7 +1597,8 @@ int64_t paro_collective_step(paro_plan_t *pl, int rank, int sched, int collectiv
             const unsigned grid = (unsigned)((n16 + WAVE - 1) / WAVE);
             if (n16 > 0) {
                 hipLaunchKernelGGL(k_copy16, dim3(grid), dim3(WAVE), throttle_lds(pl->dev.lds_per_cu, PARO_COPY_WAVES_PER_CU), st,
-                                   reinterpret_cast<const u32x4 *>(from), reinterpret_cast<u32x4 *>(mine), n16);
+                                   reinterpret_cast<const u32x4 *>(from), reinterpret_cast<u32x4 *>(mine), n16,
+                                   (int)(n16 * 16 <= PARO_KEEP_MESSAGE_BYTES));
                 PARO_HIP(hipGetLastError());
             }
         }
