@@ -2,7 +2,8 @@
 
 Every step of the path runs inside the HIP library; there is no Python or CPU
 fallback - if ``libparo.so`` has not been built, importing this package raises.
-Functions carry the C names.  Device buffers are passed as integer addresses
+Functions carry the C names.  The device calls are read by a small extension
+(``csrc/marshal.cpp``), everything else through ctypes.  Device buffers are passed as integer addresses
 (``tensor.data_ptr()``), streams as ``torch.cuda.current_stream().cuda_stream``.
 """
 from __future__ import annotations
@@ -30,10 +31,11 @@ PARO_RS, PARO_AG = 0, 1
 PARO_MAX_RANKS = 256
 PARO_STATIC_MAX_CHUNK = 1 << 30
 
-if not os.path.exists(_SO):
-    raise ImportError(
-        f"{_SO} is missing: build it first (python paper_2310_06003_amd/build.py, or __graft_entry__.build()). "
-        "There is no fallback path.")
+for _f in (_SO, os.path.join(_HERE, "_marshal.so")):
+    if not os.path.exists(_f):
+        raise ImportError(
+            f"{_f} is missing: build it first (python paper_2310_06003_amd/build.py, or __graft_entry__.build()). "
+            "There is no fallback path.")
 _lib = ctypes.CDLL(_SO)
 
 
@@ -275,3 +277,14 @@ def paro_cost(strategy: str, psi: float, psi_trainable: float, N: int, M: int, s
 
 def paro_two_step_saving(psi: float, N: int, M: int, s: int) -> float:
     return float(_lib.paro_two_step_saving(psi, N, M, s))
+
+
+# The device calls and make_adam, which a training program makes every step, take their usual arguments through
+# an extension; what it does not know it hands to the functions above.
+import sys  # noqa: E402
+
+from . import _marshal  # noqa: E402
+
+_usual = _marshal.setup(sys.modules[__name__], _lib._handle)
+_through_ctypes = {_name: globals()[_name] for _name in _usual}
+globals().update(_usual)

@@ -1,14 +1,17 @@
-"""Builds libparo.so (host plan + gfx950 kernels) in-tree with hipcc."""
+"""Builds libparo.so (host plan + gfx950 kernels) in-tree with hipcc, and the binding's extension with g++."""
 from __future__ import annotations
 
 import hashlib
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SO = os.path.join(HERE, "libparo.so")
 SOURCES = [os.path.join(HERE, "csrc", "plan.cpp"), os.path.join(HERE, "csrc", "kernels.hip")]
+MARSHAL_SO = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(HERE, "csrc", "marshal.cpp")
 HEADERS = [os.path.join(HERE, "csrc", h) for h in ("plan.hpp", "device_util.hpp", "loaders.hpp")] + \
           [os.path.join(ROOT, "include", "paro.h")]
 
@@ -18,15 +21,16 @@ HEADERS = [os.path.join(HERE, "csrc", h) for h in ("plan.hpp", "device_util.hpp"
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall",
          "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(HERE, "csrc")]
-
+MARSHAL_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+                 "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"]]
 
 STAMP = SO + ".srchash"        # hash of what the library in the tree was built from
 
 
 def source_hash() -> str:
     """sha256 over the compiler flags and the text of every source and header."""
-    h = hashlib.sha256(" ".join(FLAGS[:-2]).encode())          # without the two -I paths (they differ per checkout)
-    for f in SOURCES + HEADERS:
+    h = hashlib.sha256(" ".join(FLAGS[:-2] + MARSHAL_FLAGS[:-2]).encode())     # without the -I paths (they differ per checkout)
+    for f in SOURCES + [MARSHAL_SOURCE] + HEADERS:
         h.update(os.path.basename(f).encode())
         with open(f, "rb") as fh:
             h.update(fh.read())
@@ -44,17 +48,18 @@ def built_hash() -> str:
 
 def stale() -> bool:
     """True when there is no library, or it was built from other sources than the tree holds."""
-    return not os.path.exists(SO) or built_hash() != source_hash()
+    return not (os.path.exists(SO) and os.path.exists(MARSHAL_SO)) or built_hash() != source_hash()
 
 
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + SOURCES + ["-o", SO]
-    if verbose:
-        print(" ".join(cmd))
     if os.path.exists(STAMP):
         os.remove(STAMP)
-    subprocess.run(cmd, check=True)
+    for cmd in ([hipcc] + FLAGS + SOURCES + ["-o", SO],
+                [os.environ.get("CXX", "g++")] + MARSHAL_FLAGS + [MARSHAL_SOURCE, "-o", MARSHAL_SO]):
+        if verbose:
+            print(" ".join(cmd))
+        subprocess.run(cmd, check=True)
     with open(STAMP, "w") as fh:
         fh.write(source_hash() + "\n")
     return SO
