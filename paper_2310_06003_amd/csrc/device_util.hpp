@@ -59,7 +59,7 @@ namespace {
 // run faster with fewer requests outstanding than the registers would allow.  For the fold the
 // budget is in loads: a wave has min(P, PARO_BATCH) of them in flight, so with P = 16 the numbers
 // below mean 14 waves per compute unit for sweep 1 and 10 for the single sweep (whose waves also
-// load 3 state vectors); with fewer contributions per wave, more waves.
+// load 3 state vectors); with fewer contributions per wave, more waves.  Where other numbers hold: fold_budget, fused_waves.
 #ifndef PARO_FOLD_LOADS_PER_CU
 #define PARO_FOLD_LOADS_PER_CU 224
 #endif
@@ -68,6 +68,9 @@ namespace {
 #endif
 #ifndef PARO_FUSED_LOADS_PER_CU
 #define PARO_FUSED_LOADS_PER_CU 190
+#endif
+#ifndef PARO_FUSED_MIN_BLOCKS
+#define PARO_FUSED_MIN_BLOCKS 8192  // blocks of a single sweep from which on fused_waves thins out its waves
 #endif
 #ifndef PARO_ADAM_WAVES_PER_CU
 #define PARO_ADAM_WAVES_PER_CU 12

@@ -620,6 +620,27 @@ int fold_budget(const paro_plan_t *pl) {
     return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
 }
 
+// Waves per compute unit of a single sweep over `blocks` blocks.  The budget, which was found at P = 16, lets too many
+// waves with few loads each run beside one another: a wave also loads and stores its state, and what counts is the bytes that
+// a compute unit has in flight, 60 to 100 KB.  So no more than 13 waves of two-byte contributions with up to 7 ranks, 12 beyond,
+// and 13 (P = 2) to 8 (P >= 8) of fp32.  Whole steps on the same buffers, by the budget and with these: P = 2, 200 M elements
+// 965 -> 916 us; P = 4, 150 M 833 -> 787; P = 6, 80 M 486 -> 467; P = 8, 200 M 1365 -> 1287, 6 M 42.2 -> 40.2; P = 10, 60 M 432 ->
+// 425; fp32: P = 4, 100 M 685 -> 642; P = 6, 80 M 659 -> 622; P = 8, 20 M 194 -> 181; P = 12, 60 M 714 -> 693; a range of 8 chunks of
+// 7.5 M, P = 8, 394 -> 381.  Not in launches that run in one round of waves (P = 8, 1 M: 6.3 -> 7.5).
+// A list of few large fp32 tensors whose blocks start on cache lines has look-ups to hide as well and wants a few more: 13 waves, 10 from 7
+// ranks on (Llama-like lists, P = 4, 572 -> 539; P = 6, 2144 -> 2046; P = 8, 2725 -> 2610).  Two-byte ones keep the budget (P = 4 2596, 15
+// waves 2591; P = 3 597, 16 waves 626), and so do blocks that share cache lines with their neighbours, which want them close in time,
+// and many small tensors (fp32, ragged, P = 6, 13 waves 420 -> 391, but P = 7 463 -> 531; Llama-like, P = 7 1901 -> 2032).
+enum class Sweep { CHUNK, TENSORS_ON_LINES, OTHER_TENSORS };
+int fused_waves(int P, bool f32, Sweep over, int64_t blocks) {
+    const int waves = fold_waves(fold_loads(P) + 3, PARO_FUSED_LOADS_PER_CU);
+    if (blocks < PARO_FUSED_MIN_BLOCKS || P >= PARO_BATCH || over == Sweep::OTHER_TENSORS) return waves;
+    int most;
+    if (over == Sweep::TENSORS_ON_LINES) most = !f32 ? waves : P < 7 ? 13 : 10;
+    else most = f32 ? std::max(14 - 5 * P / 6, 8) : P < 8 ? 13 : 12;
+    return waves == 0 ? most : std::min(waves, most);
+}
+
 // What a launch needs from the device besides the caller's buffers: the LDS size behind the
 // occupancy throttle and the scratch array of partial sums (per-block sums of a sweep-1 launch,
 // then `level2`, the second-level sums).  Either the plan's own allocation or the library's
@@ -1111,7 +1132,11 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
                   const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     const int64_t n = pl->L;
     const bool small = layout == PARO_TENSORS && many_small_tensors(pl, c), large = piece_count(n) >= PARO_LARGE_TILES;
-    int waves = fold_waves(fold_loads(pl->P) + 3, small && !large ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FUSED_LOADS_PER_CU);
+    const bool f32 = layout == PARO_TENSORS ? pl->dev.f32[(size_t)c] != 0 : pl->dtype[0] == PARO_F32;
+    const Sweep over = layout == PARO_CHUNK ? Sweep::CHUNK
+                       : !small && pl->dev.on_lines[(size_t)c] ? Sweep::TENSORS_ON_LINES : Sweep::OTHER_TENSORS;
+    int waves = small && !large ? fold_waves(fold_loads(pl->P) + 3, PARO_FOLD_TM_LOADS_PER_CU)
+                                : fused_waves(pl->P, f32, over, piece_count(n));
     // A large chunk of many small tensors: the budget's 10 waves at P > 8 are too few to hide the look-ups, all that
     // fit too many for DRAM (bf16, budget, 20 waves, all: P = 12, 80 M elements 820, 686, 793 us; P = 16, 115 M 1410,
     // 1197, 1271; P = 64, 80 M 2667, 2408; a quarter fp32, P = 16, 80 M 1021, 935).  fp32 gradients, whose loads are twice
@@ -1135,7 +1160,7 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
                        const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P) + 3, PARO_FUSED_LOADS_PER_CU));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::CHUNK, piece_count(on)));
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, NSRC>), dim3(grid), dim3(WAVE), lds,
