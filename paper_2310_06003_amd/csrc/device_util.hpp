@@ -66,6 +66,9 @@ namespace {
 #ifndef PARO_FOLD_WIDE_LOADS_PER_CU
 #define PARO_FOLD_WIDE_LOADS_PER_CU 192   // many contributions (see fold_budget)
 #endif
+#ifndef PARO_FOLD_F32_LIST_LOADS_PER_CU
+#define PARO_FOLD_F32_LIST_LOADS_PER_CU 160   // sweep 1 over large chunks of fp32 gradients, tensor layout
+#endif
 #ifndef PARO_FUSED_LOADS_PER_CU
 #define PARO_FUSED_LOADS_PER_CU 190
 #endif
@@ -115,6 +118,12 @@ namespace {
 #endif
 #ifndef PARO_PACE_SLEEP
 #define PARO_PACE_SLEEP 4           // units of 64 clocks between two loads of a paced fold
+#endif
+#ifndef PARO_PACE_WIDE_SLEEP
+#define PARO_PACE_WIDE_SLEEP 10     // ... in sweep 1 over one chunk with more than 16 ranks
+#endif
+#ifndef PARO_PACE_WIDE_F32_SLEEP
+#define PARO_PACE_WIDE_F32_SLEEP 6  // ... of fp32 gradients
 #endif
 #ifndef PARO_PACE_MIN_BLOCKS
 #define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)

@@ -222,7 +222,8 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, in
     double acc = 0.0;
     if (e >= lo && e < hi) {
         const unsigned elems = piece_elems(e0, hi);
-        Chunk4Loader<DT> ld{e};
+        constexpr int WIDE = DT == PARO_F32 ? PARO_PACE_WIDE_F32_SLEEP : PARO_PACE_WIDE_SLEEP;
+        Chunk4Loader<DT, (NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
         float X[4];
         fold4(ld, src, P, group_len, X);
         store_g4(src.keep_g, g, e0, elems, X);
@@ -610,13 +611,22 @@ int fold_waves(int per_wave, int loads_per_cu) {
 }
 // Loads a wave of the fold has in flight: a batch of contributions.
 int fold_loads(int P) { return std::min(P, PARO_BATCH); }
-// The chunk layout's budget.  More contributions than one batch are more DRAM pages than the wave's loads in
-// flight say: 12 waves instead of 14.  Not where a large part of a wave's life belongs to a short last batch of
-// two-byte contributions, with few bytes in flight.  Whole clipped steps on the same buffers, 14 and 12 waves: P = 64,
-// 105 M elements 2783 and 2753 us; P = 32, 105 M 1664 and 1638; P = 40, 36 M 666 and 659; fp32, P = 20, 36 M 654 and 642;
-// but bf16, P = 17, 105 M 1151 and 1219, P = 24, 77 M 1009 and 1025, P = 36, 77 M 1339 and 1350.
-int fold_budget(const paro_plan_t *pl) {
-    const bool short_batch = pl->dtype[0] != PARO_F32 && pl->P % PARO_BATCH != 0 && pl->P < 5 * PARO_BATCH / 2;
+// The budget of sweep 1 over the chunk layout; paced: a large launch over one chunk (see paces).
+// More contributions than one batch are more DRAM pages than the wave's loads in flight say: 12 waves instead of 14, but
+// where a large part of a wave's life belongs to a short last batch of two-byte contributions, with few bytes in flight.
+// A paced launch is told apart further - whole clipped steps on the same buffers, with the numbers of the line before
+// (224 loads, 192 for more than 16 ranks, a pause of 4) and with these:
+//   more than 16 ranks, a pause of 10 and more waves, so that waves side by side read the same page for longer: P = 64, 105 M
+//     elements 2696 -> 2673 us, 40 M 1068 -> 1029; P = 48, 40 M 826 -> 793; P = 32, 30 M 479 -> 469; P = 17, 60 M 638 -> 631
+//   fp32, whose loads are twice as wide, half as many waves: P = 64, 20 M 924 -> 895; P = 16, 100 M 1568 -> 1520; P = 12, 60 M
+//     781 -> 747; P = 8, 150 M 1576 -> 1531; P = 6, 100 M 895 -> 872 (P = 4 774 -> 766, P = 3 as it was)
+//   5 to 10 ranks, 20 waves instead of 28 (P = 8): P = 8, 200 M 1525 -> 1499; P = 7, 80 M 589 -> 579; P = 10, 60 M 494 -> 489
+int fold_budget(const paro_plan_t *pl, bool paced) {
+    const bool f32 = pl->dtype[0] == PARO_F32;
+    if (paced && f32) return pl->P <= 8 ? 80 : 112;
+    if (paced && pl->P > PARO_BATCH) return pl->P >= 2 * PARO_BATCH ? 288 : 352;
+    if (paced && pl->P > PARO_PAIR_MAX_RANKS && pl->P <= 10) return 160;
+    const bool short_batch = !f32 && pl->P % PARO_BATCH != 0 && pl->P < 5 * PARO_BATCH / 2;
     return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
 }
 
@@ -937,6 +947,10 @@ int64_t update_elems(const paro_plan_t *pl) {
     paro::letter_range(pl, 0, pl->letters[2], &ob, &on);
     return on;
 }
+// Whether the loads of a launch over one chunk of the chunk layout are paced (see load_batch).
+bool paces(const paro_plan_t *pl) {
+    return piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
+}
 bool keeps_g(const paro_plan_t *pl) {
     const int64_t n = update_elems(pl), esize = pl->uniform_dtype && pl->dtype[0] == PARO_F32 ? 4 : 2;
     if (pl->P > PARO_BATCH && n > PARO_KEEP_STATE_ELEMS) return false;
@@ -979,7 +993,7 @@ void plan_consts(const paro_plan_t *pl, AdamConsts *a) {
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
     tab->keep_g = keeps_g(pl);
-    tab->paced = piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
+    tab->paced = paces(pl);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
     paro::fold_order(pl, chunk, order, &gl);
@@ -1079,7 +1093,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     double *partials = sc.partials;
     if (layout == PARO_CHUNK) {
         const unsigned grid = (unsigned)((chunk_blocks(pl, lo) + 7) & ~(int64_t)7);       // a multiple of 8: see partial_slot()
-        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl)));
+        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl, paces(pl))));
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
                                                                                  lds, st, src, pl->P, group_len, lo, lo + n,
                                                                                  g_range, partials)));
@@ -1113,8 +1127,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         return (int)grid;
     }
     const unsigned grid = (unsigned)((pieces + 7) & ~(int64_t)7);
-    const unsigned lds =
-        throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU));
+    // fp32 gradients in a large chunk want a budget whatever the list (whole clipped steps, before and now: ragged tensors,
+    // P = 8, 59 M elements 672 and 634 us, P = 16 652 and 620, P = 32 544 and 526; a Llama-like list, P = 8 2977 and 2942, P = 32 2970 and 2847)
+    const bool f32_large = pl->dev.f32[(size_t)c] && piece_count(n) >= PARO_LARGE_TILES;
+    const int budget = f32_large ? PARO_FOLD_F32_LIST_LOADS_PER_CU : small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), budget));
     PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
             hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, few_sources(tab), pl->P,
@@ -1243,7 +1260,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl)));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl, false)));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;

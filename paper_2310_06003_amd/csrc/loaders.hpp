@@ -18,11 +18,12 @@ namespace {
 // Contributions are arrays in shard coordinates, all of one dtype: an 8-byte load per
 // contribution for the 2-byte dtypes (a wave instruction covers 512 consecutive bytes), a
 // 16-byte load for fp32.
-template <int DT>
+// PACE: the pause between two loads of a paced launch, see load_batch.
+template <int DT, int PACE = PARO_PACE_SLEEP>
 struct Chunk4Loader {
     static constexpr int kBatch = PARO_BATCH;
     static constexpr int kElems = 4;
-    static constexpr bool kPaced = true;
+    static constexpr int kPace = PACE;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw = std::conditional_t<DT == PARO_F32, u32x4, u32x2>;
     using At = const void *;
@@ -195,7 +196,7 @@ template <int DT, bool NT, int KB = PARO_BATCH>
 struct Tensor4Loader {
     static constexpr int kBatch = (DT == PARO_F32 && KB > 8) ? KB / 2 : KB;     // 32 registers of loads in flight at most
     static constexpr int kElems = 4;
-    static constexpr bool kPaced = false;
+    static constexpr int kPace = 0;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw = typename Chunk4Loader<DT>::Raw;
     using At = uintptr_t;
@@ -216,7 +217,7 @@ template <int DT>
 struct Part4Loader {
     static constexpr int kBatch = 4;              // more costs every wave of the kernel registers
     static constexpr int kElems = 4;
-    static constexpr bool kPaced = false;
+    static constexpr int kPace = 0;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     struct Raw { unsigned int w[4]; };
     using At = uintptr_t;
@@ -261,7 +262,7 @@ template <int DT, bool NT, int KB>
 struct Tensor8Loader {
     static constexpr int kBatch = KB;
     static constexpr int kElems = 8;
-    static constexpr bool kPaced = false;
+    static constexpr int kPace = 0;
     static constexpr int ESIZE = DT == PARO_F32 ? 4 : 2;
     using Raw4 = typename Chunk4Loader<DT>::Raw;
     struct Raw { Raw4 a, b; };
@@ -286,7 +287,7 @@ struct Tensor8Loader {
 struct Lane4Loader {
     static constexpr int kBatch = PARO_LANE_BATCH;
     static constexpr int kElems = 4;
-    static constexpr bool kPaced = false;
+    static constexpr int kPace = 0;
     struct Raw { unsigned int bits[4]; };
     struct At { uintptr_t base[4]; };
     Located at;
@@ -342,14 +343,17 @@ struct Folding {
 // steps unpaced -> paced, on the same buffers: P = 64, 90 M elements 2446 -> 2373 us, P = 16, 150 M 1544 -> 1521,
 // P = 4, 150 M as they were; single sweep, P = 64, 16 M 418 -> 409, P = 16, 24 M 224 -> 223, P = 8, 16 M 109 -> 109.  A
 // small launch is bound by latency (P = 16, 2 M 26.5 -> 28.5; P = 32, 2 M, single sweep 29 -> 32) and is not paced.
+// How long a pause goes with how many waves is in fold_budget.  The pause is a constant of the kernel and the branch is
+// taken load by load: a pause that the launch chooses (a loop of short ones, two or three tests, copies of the code behind one
+// branch) costs the scalar work of choosing after every load and was 2 to 12 % slower at the same length.
 template <int N, class Ld, class Src, class Order>
 __device__ __forceinline__ void load_batch(const Ld &ld, const Src &src, int k, Order &ord, typename Ld::Raw *raw) {
     typename Ld::At at[N];
     static_for<0, N>([&](auto b) { at[b] = ld.source(src, ord.next(k + b)); });
     static_for<0, N>([&](auto b) {
         ld.load(at[b], raw[b]);
-        if constexpr (Ld::kPaced) {
-            if (src.paced) __builtin_amdgcn_s_sleep(PARO_PACE_SLEEP);
+        if constexpr (Ld::kPace > 0) {
+            if (src.paced) __builtin_amdgcn_s_sleep(Ld::kPace);
         }
     });
 }
