@@ -1302,14 +1302,26 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
 // Whether sweep 1 over an update range of several chunks in the chunk layout goes chunk by chunk.  A wave of the
 // one launch over the range works out its chunk and the order of its ranks before its first load; with few
 // contributions of two bytes that is as much work as the fold (P = 2, two chunks of 50 M: 200 us against 2 x 66), and
-// large chunks repay a launch each.  Whole clipped steps, one launch and one per chunk: P = 2, 2 x 24 M 310 and 294
-// us, 2 x 120 M 1517 and 1400; P = 4, 2 x 50 M 664 and 643; but 4 x 12 M 321 and 331, fp32 at P = 4, 2 x 50 M 770 and
-// 783, P = 8, 2 x 50 M 758 and 767.
+// large chunks repay a launch each; with many, only launches over one chunk are paced to advantage.  Whole clipped steps, one
+// launch and one per chunk, from how many blocks on:
+//   up to 4 ranks, two bytes, 65 536    P = 2, 2 x 24 M 310 and 294 us, 2 x 120 M 1517 and 1400; P = 4, 2 x 50 M 664 and 643; but 4 x 12 M
+//                                       321 and 331, fp32 2 x 60 M 906 and 918
+//   two bytes, 12 ranks, 131 072        P = 12, 2 x 40 M 731 and 720; P = 16, 2 x 60 M 1251 and 1235; but 4 x 20 M 833 and 841; P = 8, 2 x 60 M
+//                                       920 and 919, 8 x 17 M 1029 and 1083
+//              32 ranks, 65 536         P = 32, 4 x 45 M 2895 and 2751; 4 x 17 M 1075 and 1067; but 4 x 9 M 571 and 578
+//              64 ranks, 32 768         P = 64, 8 x 9 M 2003 and 1862
+//   fp32, 8 ranks, 131 072              P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277
+//         16 ranks, 65 536              P = 16, 2 x 20 M 630 and 611; but 2 x 5 M 164 and 170; P = 32, 4 x 20 M 2116 and 2058
 bool chunk_by_chunk(const paro_plan_t *pl) {
-    if (pl->P > PARO_PAIR_MAX_RANKS || pl->dtype[0] == PARO_F32) return false;
+    const int P = pl->P;
+    int64_t from;
+    if (pl->dtype[0] == PARO_F32) from = P < 8 ? 0 : P < 16 ? PARO_RANGE_MAX_BLOCKS * 2 : PARO_RANGE_MAX_BLOCKS;
+    else from = P <= PARO_PAIR_MAX_RANKS ? PARO_RANGE_MAX_BLOCKS : P < 12 ? 0 : P < 32 ? PARO_RANGE_MAX_BLOCKS * 2
+                : P < 64 ? PARO_RANGE_MAX_BLOCKS : PARO_RANGE_MAX_BLOCKS / 2;
+    if (!from) return false;
     const int64_t blocks = (chunk_blocks(pl, PIECE - 1) + 7) & ~(int64_t)7;       // at most
     // (no more than a group of the norm, so that the scratch array does not matter)
-    return blocks >= PARO_RANGE_MAX_BLOCKS && blocks <= (pl->L > PARO_STATIC_MAX_CHUNK ? MAX_GRID : (int64_t)NORM_GROUP);
+    return blocks >= from && blocks <= (pl->L > PARO_STATIC_MAX_CHUNK ? MAX_GRID : (int64_t)NORM_GROUP);
 }
 
 // Sweep 1 over the whole update range, chunk by chunk.  The sum of squares covers the rank's own

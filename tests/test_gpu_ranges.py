@@ -91,6 +91,16 @@ def test_large_chunks_with_few_ranks_are_launched_one_by_one(paro, P, G, strateg
         assert np_of(dst)[slot:slot + n].tobytes() == lit["q"].tobytes()
 
 
+@pytest.mark.parametrize("P,G,dtype,first", [
+    (12, 6, wl.BF16, 131072), (32, 16, wl.F16, 65536), (64, 32, wl.BF16, 32768), (8, 4, wl.F32, 131072), (16, 8, wl.F32, 65536)])
+@pytest.mark.parametrize("short", [16, 8, 7])
+def test_more_ranks_where_chunks_begin_to_be_launched_one_by_one(paro, P, G, dtype, first, short):
+    """`first`: the blocks of a chunk, counted with the one more that it may straddle and in eights, from which on each is
+    launched by itself.  16 blocks short of it the range is one launch."""
+    L = (first - short) * 256 + (8 if short == 7 else 0)
+    test_large_chunks_with_few_ranks_are_launched_one_by_one(paro, P, G, "III", orc.HORING, dtype, L)
+
+
 @pytest.mark.parametrize("L", [(1 << 29) + 264, (1 << 29) + 30_000_008, (1 << 29) + 70_001_000])
 def test_a_range_that_takes_several_launches_for_its_norm(paro, L):
     """The entry point that allocates nothing has room for the partial sums of 2^30 elements: a longer
