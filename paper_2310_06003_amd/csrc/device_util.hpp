@@ -152,7 +152,7 @@ constexpr int NORM_SLICES = 8;                  // else: slice sums that it does
 constexpr int NORM_SLICES_PARTIALS = 131072;    // ... up to so many partials (33.5 M elements)
 constexpr int NORM_ONE_BLOCK_PARTIALS = 2 * FINALIZE_TPB * NORM_SLICES;     // slices and total by one block up to here
 constexpr unsigned NORM_GROUP = PARO_STATIC_MAX_CHUNK / PIECE;              // blocks of a range whose partials are added up together
-static_assert(TILE == PIECE, "the per-tile table has one entry per block");
+static_assert(TILE == PIECE, "the per-tile tables have one entry per block");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -177,6 +177,10 @@ struct AdamConsts {
     int keep_state;     // p, m, v and the packed parameters are stored to stay in the memory-side cache
 };
 
+// An entry of a chunk's weight-decay table: all elements of the tile take weight decay, none does, or DECAY_BITS + the index,
+// in the table, of the first of eight words with a bit for each element (set: it does).
+constexpr uint32_t DECAY_ALL = 0, DECAY_NONE = 1, DECAY_BITS = 2;
+
 // What a launch needs to map its elements to tensors.
 struct TensorMap {
     const int64_t *nz_off;      // [n_nz + 1] flat start of every non-empty tensor, then Psi
@@ -187,7 +191,7 @@ struct TensorMap {
     int n_nz;
     int64_t total;              // Psi
     int64_t begin;              // flat index of the launch's element 0
-    const paro_tile_info *tile_tab;   // the per-tile table of the launch's chunk, or null
+    const uint32_t *decay_tab;        // the weight-decay table of the launch's chunk, or null
     const paro_piece_info *pieces;    // [n_pieces] the chunk's pieces, or null
     unsigned n_pieces;
 };

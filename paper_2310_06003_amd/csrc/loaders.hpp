@@ -69,10 +69,8 @@ struct Piece {
                        // holds the block's first element
 };
 
-// e0: the block's first element (< n, the launch's length).  With the per-tile table a block
-// inside a single-tensor or all-padding tile needs one look-up; otherwise the wave searches the
-// offset table (below the tile's first segment when the table gives it, else from the start).
-// Everything returned is wave-uniform.
+// e0: the block's first element (< n, the launch's length).  The wave searches the offset table; where the
+// plan has made a list or a table, nobody comes here.  Everything returned is wave-uniform.
 __device__ __forceinline__ Piece piece_of(const TensorMap &tm, int64_t e0, int64_t n) {
     Piece pc;
     pc.tensor = -2;
@@ -80,22 +78,8 @@ __device__ __forceinline__ Piece piece_of(const TensorMap &tm, int64_t e0, int64
     pc.toff = 0;
     pc.seg = 0;
     const int64_t f0 = tm.begin + e0;
-    int k_lo = 0, k_hi = tm.n_nz + 1;
-    if (tm.tile_tab) {
-        const paro_tile_info info = tm.tile_tab[e0 / TILE];                 // one address for the whole wave
-        const int t = uniform(info.tensor);
-        if (t != -1) {
-            pc.tensor = t;
-            pc.dt = uniform(info.first_seg);
-            pc.toff = uniform(info.toff);
-            return pc;
-        }
-        pc.tensor = -1;                                               // a boundary inside: the table names the first segment
-        pc.seg = uniform(info.first_seg);
-        return pc;
-    }
     if (f0 >= tm.total) return pc;                                    // padding
-    const int k = uniform(k_lo + wave_search(tm.nz_off + k_lo, k_hi - k_lo, f0, (int)lane_id()));
+    const int k = uniform(wave_search(tm.nz_off, tm.n_nz + 1, f0, (int)lane_id()));
     const int64_t piece_end = tm.begin + min(e0 + (int64_t)PIECE, n);
     if (tm.nz_off[k + 1] >= piece_end) {
         pc.tensor = tm.nz_tensor[k];

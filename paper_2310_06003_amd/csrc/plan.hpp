@@ -11,18 +11,7 @@
 #ifndef PARO_TILE_ELEMS
 #define PARO_TILE_ELEMS 256
 #endif
-constexpr int PARO_TILE = PARO_TILE_ELEMS;      // elements per tile of the per-tile table (a multiple of 256)
-
-// What a tile (PARO_TILE consecutive elements: by default one block's 256) of a chunk looks like,
-// precomputed so that the kernels do not have to search: tensor >= 0: the whole tile lies inside that tensor, its first element at
-// offset toff, first_seg = the tensor's gradient dtype; tensor == -1: the tile holds a tensor
-// boundary (or ends in padding), first_seg = index of its first non-empty tensor; tensor == -2:
-// the tile is all padding.
-struct paro_tile_info {
-    int64_t toff;
-    int32_t tensor;
-    int32_t first_seg;
-};
+constexpr int PARO_TILE = PARO_TILE_ELEMS;      // elements per tile of the per-tile tables: a block's
 
 // A piece of a chunk: elements [lo, hi) of a tile (hi == PARO_TILE: to its end), which lie in one
 // tensor.  Pieces are listed in address order (those of cut tiles first, in a small chunk); a tile is
@@ -44,8 +33,8 @@ struct paro_device_tables {
     uint8_t *dtype = nullptr;       // [T]
     uint8_t *no_decay = nullptr;    // [T]
     // per chunk, each built at the first call that needs it:
-    std::vector<paro_tile_info *> tile_tab;   // [P] the chunk's [tiles_per_chunk] table, or null (weight-decay mask)
-    std::vector<uint8_t> tile_tab_tried;      // [P] the decision for the chunk has been made
+    std::vector<uint32_t *> decay_tab;        // [P] the chunk's weight-decay table (see list_decays), or null
+    std::vector<uint8_t> decay_tab_tried;     // [P] the decision for the chunk has been made
     std::vector<paro_piece_info *> piece_tab; // [P] the chunk's list of pieces, or null (tensor layout)
     std::vector<uint32_t> n_pieces;           // [P]
     std::vector<uint8_t> on_lines;            // [P] on_cache_lines() of the chunk
