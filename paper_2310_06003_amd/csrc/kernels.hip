@@ -66,29 +66,55 @@ __device__ __forceinline__ double strided_sum(const double *__restrict__ sums, i
     return acc;
 }
 
-// The global sum of squares as sweep 2 gets it: n sums to be added up in a fixed order, the same in
-// every wave.  Lanes hold the result.
-template <int U = 8>
-__device__ __forceinline__ double norm_total(const double *__restrict__ sums, int n) {
-    if (n == 1) return sums[0];
-    if (n <= NORM_SLICES) {                                        // one scalar load; there is room for as many
-        double x[NORM_SLICES];
+// The global sum of squares as sweep 2 gets it: n sums to be added up in a fixed order, the same in every wave.
+// Lanes hold the result.  MANY: more than NORM_SLICES, up to NORM_DIRECT_PARTIALS of them.  fetch() issues the vector loads of
+// many: before a wave's state, because loads return in the order of their issue, and sums behind the state would be waited for
+// together with it, with their adds to come (whole clipped steps, same buffers: P = 8, 0.5 M elements 10.0 -> 9.4 us, 0.375 M 8.4 -> 8.1;
+// P = 4, 0.5 M 9.5 -> 9.0).  Their registers cost a sweep 2 with few 1 to 2 %: a kernel of its own.  Few are one scalar load, on a
+// way of its own (there is room for as many).
+template <bool MANY>
+struct NormTotal {
+    static constexpr int U = MANY ? NORM_DIRECT_PARTIALS / WAVE : 1, ROUND = 8;
+    double x[U];
+    __device__ __forceinline__ void fetch(const double *__restrict__ sums, int n) {
+        if constexpr (MANY) {
 #pragma unroll
-        for (int k = 0; k < NORM_SLICES; ++k) x[k] = sums[k];
-        double s = x[0];
+            for (int u0 = 0; u0 < U; u0 += ROUND) {
+                if (u0 * WAVE >= n) break;
+#pragma unroll
+                for (int u = u0; u < u0 + ROUND; ++u) {
+                    const int k = (int)lane_id() + u * WAVE;
+                    x[u] = k < n ? sums[k] : 0.0;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ double total(const double *__restrict__ sums, int n) const {
+        if constexpr (MANY) {
+            double acc = 0.0;
+#pragma unroll
+            for (int u0 = 0; u0 < U; u0 += ROUND) {
+                if (u0 * WAVE >= n) break;
+#pragma unroll
+                for (int u = u0; u < u0 + ROUND; ++u) acc += x[u];
+            }
+            return wave_sum(acc);
+        }
+        if (n == 1) return sums[0];
+        double y[NORM_SLICES];
+#pragma unroll
+        for (int k = 0; k < NORM_SLICES; ++k) y[k] = sums[k];
+        double s = y[0];
         if (n == NORM_SLICES) {
 #pragma unroll
-            for (int k = 1; k < NORM_SLICES; ++k) s += x[k];
+            for (int k = 1; k < NORM_SLICES; ++k) s += y[k];
         } else {
 #pragma unroll
-            for (int k = 1; k < NORM_SLICES; ++k) s += k < n ? x[k] : 0.0;
+            for (int k = 1; k < NORM_SLICES; ++k) s += k < n ? y[k] : 0.0;
         }
         return s;
     }
-    double acc = strided_sum<WAVE, U>(sums, lane_id(), n);
-    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, WAVE);
-    return acc;
-}
+};
 
 // sc = grad_scale * clip coefficient, from the global sum of squares.
 __device__ __forceinline__ float scale_from_norm(const AdamConsts &a, double total_sumsq) {
@@ -369,8 +395,11 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_finalize(const double *__restr
 
 // What sweep 2's waves do with n sums, for the call that leaves the total itself: the same adds in the
 // same order, so the same value to the last bit.
+template <bool MANY>
 __global__ __launch_bounds__(WAVE) void k_norm_total(const double *__restrict__ sums, int n, double *out) {
-    const double total = norm_total<NORM_DIRECT_PARTIALS / WAVE>(sums, n);      // all loads in flight
+    NormTotal<MANY> norm;
+    norm.fetch(sums, n);
+    const double total = norm.total(sums, n);
     if (lane_id() == 0) *out = total;
 }
 
@@ -428,7 +457,7 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
 // KEPT: sweep 1 stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
-template <bool PACK, int MASK, bool KEPT>
+template <bool PACK, int MASK, bool KEPT, bool MANY>
 __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double *__restrict__ sums, int n_sums,
                                                 double *__restrict__ sumsq_out, const float *__restrict__ g, float *__restrict__ p,
                                                 float *__restrict__ m, float *__restrict__ v,
@@ -444,6 +473,8 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
         pc = piece_of(tm, e0, n);
         if (pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
     }
+    NormTotal<MANY> norm;
+    norm.fetch(sums, n_sums);
     u32x4 G;
     State4 s;
     if (e < n) {
@@ -453,7 +484,7 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
     if (MASK == MASK_TABLE) decay_flags(tm.decay_tab, (uint32_t)uniform((int)entry), decays);
     float sc = a.grad_scale;
     if (n_sums > 0) {                                                                      // the whole wave
-        const double total = norm_total(sums, n_sums);
+        const double total = norm.total(sums, n_sums);
         if (sumsq_out && blockIdx.x == 0 && lane_id() == 0) *sumsq_out = total;
         // an overflowed (non-finite) gradient makes its sum of squares non-finite: the whole step is skipped
         if (a.skip_nonfinite && !isfinite(total)) return;
@@ -1249,7 +1280,7 @@ struct NormSums {
 
 // The total of what is left, in its place: for the call that no sweep 2 follows.
 int total_of(const NormSums &s, hipStream_t st) {
-    hipLaunchKernelGGL(k_norm_total, dim3(1), dim3(WAVE), 0, st, s.sums, s.n, s.out);
+    PARO_BY_FLAG(s.n > NORM_SLICES, MANY, hipLaunchKernelGGL(k_norm_total<MANY>, dim3(1), dim3(WAVE), 0, st, s.sums, s.n, s.out));
     PARO_HIP(hipGetLastError());
     return PARO_OK;
 }
@@ -1414,10 +1445,13 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
                 const NormSums &norm, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
+    const bool many = norm.n > NORM_SLICES;
     if (!pl->any_no_decay) {
         const unsigned lds = throttle_lds(sc.lds_per_cu, on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU : PARO_ADAM_WAVES_PER_CU);
-        PARO_BY_FLAG(keeps_g(pl), KEPT, hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a,
-                                                           norm.sums, norm.n, norm.out, grad, p, m, v, dst, on, map_for(pl, sc, ob, false)));
+        PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
+            hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
+                               grad, p, m, v, dst, on, map_for(pl, sc, ob, false));
+        }));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
@@ -1427,11 +1461,15 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         const TensorMap tm = map_for(pl, sc, c * pl->L, true);
         uint16_t *dst_c = dst ? dst + lo : nullptr;
         if (tm.decay_tab)
-            PARO_BY_FLAG(keeps_g(pl), KEPT, hipLaunchKernelGGL((k_adam4<PACK, MASK_TABLE, KEPT>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums,
-                                                               norm.n, norm.out, grad + lo, p + lo, m + lo, v + lo, dst_c, pl->L, tm));
+            PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
+                hipLaunchKernelGGL((k_adam4<PACK, MASK_TABLE, KEPT, MANY>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
+                                   grad + lo, p + lo, m + lo, v + lo, dst_c, pl->L, tm);
+            }));
         else
-            hipLaunchKernelGGL((k_adam4<PACK, MASK_TENSORS, false>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out, grad + lo,
-                               p + lo, m + lo, v + lo, dst_c, pl->L, tm);
+            PARO_BY_FLAG(many, MANY, {
+                hipLaunchKernelGGL((k_adam4<PACK, MASK_TENSORS, false, MANY>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
+                                   grad + lo, p + lo, m + lo, v + lo, dst_c, pl->L, tm);
+            });
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
