@@ -18,8 +18,10 @@ HEADERS = [os.path.join(HERE, "csrc", h) for h in ("plan.hpp", "device_util.hpp"
 # -ffp-contract=off: every fp32 operation of the fold and of Adam is rounded on its own, so
 #   results do not depend on which multiply-adds the compiler could fuse.
 # -packed-fp32-ops off: scalar fp32 arithmetic only.
+# -amdgpu-kernarg-preload-count: the first 14 words of a kernel's arguments are in scalar registers when a wave starts (as many as there
+# are), where it would begin with one or two trips to the scalar cache; the kernels take what their first loads need first.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-ffp-contract=off",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=14", "-Wall",
          "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(HERE, "csrc")]
 MARSHAL_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
                  "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"]]

@@ -245,6 +245,11 @@ __device__ __forceinline__ double sumsq4(const float X[4]) {
 }
 
 // --------------------------------------------------------------------- kernels
+// Order of their arguments: the first 14 words are in scalar registers when a wave starts (a flag of the build), as long
+// as they are plain values and pointers; a structure ends the row.  So what the first loads need comes first, tables and constants
+// behind it.  A wave used to begin with two or three trips to the scalar cache, one after the other, with no data in flight:
+// whole steps on the same buffers, P = 8, clipped, 0.5 M elements 9.2 -> 8.9 us, 1.5 M 17.7 -> 17.0, 7.5 M 61.4 -> 60.4; 10 000 ragged
+// tensors 68.0 -> 67.1; GPT-2 tensors, P = 64, 64.8 -> 63.8; all-gather of GPT-2 608 -> 592; from 100 M elements on as before.
 
 __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsigned elems, const float X[4]) {
     buf_store16_as(keep, as_u32x4(X[0], X[1], X[2], X[3]), wave_buffer(g + e0, elems * 4), lane_id() * 16);
@@ -254,8 +259,8 @@ __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsign
 // elements [lo, hi) of the update range; blocks are counted from the start of the range (see k_reduce4r), and
 // one that two chunks share is launched for both.
 template <int DT, bool SUMSQ, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t lo, int64_t hi,
-                                                  float *__restrict__ g, double *__restrict__ partials) {
+__global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P, int group_len, float *__restrict__ g,
+                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src) {
     const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
     double acc = 0.0;
     if (e >= lo && e < hi) {
@@ -281,9 +286,9 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(const SrcTableOf<NSRC> src, in
 // [part0, part0 + part_n) only (both multiples of 8, block0 too); the others hold no element that counts.
 // The partials are laid out group by group (NORM_GROUP blocks), each like a launch of its own.
 template <int DT, bool SUMSQ, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_reduce4r(const SrcTableOf<NSRC> src, int P, const RangeMap rm, int64_t block0, int64_t n,
-                                                   float *__restrict__ g, double *__restrict__ partials, unsigned part0,
-                                                   unsigned part_n) {
+__global__ __launch_bounds__(WAVE) void k_reduce4r(int64_t block0, int64_t n, int P, unsigned part0, unsigned part_n,
+                                                   float *__restrict__ g, double *__restrict__ partials, const RangeMap rm,
+                                                   const SrcTableOf<NSRC> src) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
     double acc = 0.0;
     if (e0 < n) {
@@ -351,9 +356,11 @@ __device__ __forceinline__ void reduce_cut(const TensorMap &tm, const Cut &c, co
 // -> 35 us; GPT-2's 100 tensors (P = 8, 310 MB) 70 -> 57 us; the single sweep over 5 tensors at P = 32
 // (290 MB): 113 -> 86 us.
 template <bool SUMSQ, int PPW, int KB, bool NT, int NSRC, bool KEEP>
-__global__ __launch_bounds__(WAVE) void k_reduce4t(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
+__global__ __launch_bounds__(WAVE) void k_reduce4t(int64_t n, const paro_piece_info *pieces, unsigned n_pieces, int P, int group_len,
                                                    float *__restrict__ g, double *__restrict__ partials,
-                                                   const TensorMap tm) {
+                                                   const SrcTableOf<NSRC> src, TensorMap tm) {
+    tm.pieces = pieces;
+    tm.n_pieces = n_pieces;
     const int64_t i0 = (int64_t)blockIdx.x * PPW;
     double acc = 0.0;
     bool done = false;
@@ -458,10 +465,9 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // the total to sumsq_out unless that is null.
 // KEPT: sweep 1 stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
-__global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double *__restrict__ sums, int n_sums,
-                                                double *__restrict__ sumsq_out, const float *__restrict__ g, float *__restrict__ p,
-                                                float *__restrict__ m, float *__restrict__ v,
-                                                uint16_t *__restrict__ dst, int64_t n, const TensorMap tm) {
+__global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
+                                                float *__restrict__ v, const double *__restrict__ sums, int n_sums, const AdamConsts a,
+                                                uint16_t *__restrict__ dst, double *__restrict__ sumsq_out, const TensorMap tm) {
     const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
     if (e0 >= n) return;
     bool decays[4] = {true, true, true, true};
@@ -500,10 +506,11 @@ __global__ __launch_bounds__(WAVE) void k_adam4(const AdamConsts a, const double
 // reduced gradient never goes to memory.  TENSORS: contributions are per-tensor gradients; else
 // arrays in shard coordinates of dtype DT.  NT: as for k_reduce4t.
 template <bool TENSORS, int DT, int MASK, bool NT, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_fused4(const SrcTableOf<NSRC> src, int P, int group_len, int64_t n,
-                                                 const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
-                                                 float *__restrict__ v, uint16_t *__restrict__ dst,
-                                                 const TensorMap tm) {
+__global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
+                                                 const paro_piece_info *pieces, unsigned n_pieces, int P, int group_len,
+                                                 const SrcTableOf<NSRC> src, const AdamConsts a, uint16_t *__restrict__ dst, TensorMap tm) {
+    tm.pieces = pieces;
+    tm.n_pieces = n_pieces;
     Piece pc;
     Located loc;
     int64_t e0 = block_first();
@@ -548,9 +555,9 @@ __global__ __launch_bounds__(WAVE) void k_fused4(const SrcTableOf<NSRC> src, int
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
 template <int DT, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_fused4r(const SrcTableOf<NSRC> src, int P, const RangeMap rm, int64_t block0, int64_t n,
-                                                  const AdamConsts a, float *__restrict__ p, float *__restrict__ m,
-                                                  float *__restrict__ v, uint16_t *__restrict__ dst) {
+__global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v, int P,
+                                                  const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
+                                                  uint16_t *__restrict__ dst) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
     if (e0 >= n) return;
     State4 s;
@@ -1177,8 +1184,8 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         const unsigned grid = (unsigned)((chunk_blocks(pl, lo) + 7) & ~(int64_t)7);       // a multiple of 8: see partial_slot()
         const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl, paces(pl))));
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
-                                                                                 lds, st, src, pl->P, group_len, lo, lo + n,
-                                                                                 g_range, partials)));
+                                                                                 lds, st, lo, lo + n, pl->P, group_len,
+                                                                                 g_range, partials, src)));
         return (int)grid;
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
@@ -1200,11 +1207,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
         PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
             if (few)
-                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st,
-                                   few_sources(tab), pl->P, group_len, n, g, partials, tm);
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
+                                   partials, few_sources(tab), tm);
             else
-                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, few_sources(tab),
-                                   pl->P, group_len, n, g, partials, tm);
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
+                                   partials, few_sources(tab), tm);
         }));
         return (int)grid;
     }
@@ -1216,11 +1223,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), budget));
     PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
-            hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, few_sources(tab), pl->P,
-                               group_len, n, g, partials, tm);
+            hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
+                                   partials, few_sources(tab), tm);
         else
             PARO_BY_TABLE(pl->P, tab, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT, NSRC, KEEP>), dim3(grid), dim3(WAVE), lds,
-                                                         st, src, pl->P, group_len, n, g, partials, tm));
+                                                         st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g, partials, src, tm));
     }));
     return (int)grid;
 }
@@ -1246,12 +1253,13 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     if (layout == PARO_TENSORS)
         PARO_BY_TABLE(pl->P, tab, PARO_BY_FLAG(mask != MASK_NONE, MASKED, PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0, {
             hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC>), dim3(tm.pieces ? tm.n_pieces : grid),
-                               dim3(WAVE), lds, st, src, pl->P, group_len, n, a, p, m, v, dst, tm);
+                               dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P, group_len, src, a,
+                               dst, tm);
         })));
     else
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, src, pl->P, group_len, n, a, p,
-                               m, v, dst, tm);
+            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P, group_len, src, a,
+                               dst, tm);
         })));
 }
 
@@ -1264,7 +1272,7 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, NSRC>), dim3(grid), dim3(WAVE), lds,
-                                                                                 st, src, pl->P, rm, b0, on, a, p, m, v, dst)));
+                                                                                 st, b0, on, p, m, v, pl->P, rm, src, a, dst)));
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
@@ -1358,9 +1366,8 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
         }
         if (sumsq_out && first < last) {
             PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC>), dim3((unsigned)grid),
-                                                                                     dim3(WAVE), lds, st, src, pl->P, rm, b0, on,
-                                                                                     grad_out, sc.partials, (unsigned)(first - b0),
-                                                                                     (unsigned)(last - first))));
+                                                                                     dim3(WAVE), lds, st, b0, on, pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out,
+                                                                                     sc.partials, rm, src)));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
             one_sum = step >= blocks && last - first <= NORM_GROUP;
@@ -1374,8 +1381,8 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
             }
         } else {
             PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC>), dim3((unsigned)grid),
-                                                                                     dim3(WAVE), lds, st, src, pl->P, rm, b0, on,
-                                                                                     grad_out, sc.partials, 0u, 0u)));
+                                                                                     dim3(WAVE), lds, st, b0, on, pl->P, 0u, 0u, grad_out,
+                                                                                     sc.partials, rm, src)));
             PARO_HIP(hipGetLastError());
         }
     }
@@ -1449,8 +1456,8 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
     if (!pl->any_no_decay) {
         const unsigned lds = throttle_lds(sc.lds_per_cu, on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU : PARO_ADAM_WAVES_PER_CU);
         PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
-            hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
-                               grad, p, m, v, dst, on, map_for(pl, sc, ob, false));
+            hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, on, grad, p, m, v, norm.sums, norm.n, a, dst,
+                               norm.out, map_for(pl, sc, ob, false));
         }));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
@@ -1462,13 +1469,13 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         uint16_t *dst_c = dst ? dst + lo : nullptr;
         if (tm.decay_tab)
             PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
-                hipLaunchKernelGGL((k_adam4<PACK, MASK_TABLE, KEPT, MANY>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
-                                   grad + lo, p + lo, m + lo, v + lo, dst_c, pl->L, tm);
+                hipLaunchKernelGGL((k_adam4<PACK, MASK_TABLE, KEPT, MANY>), dim3(grid), dim3(WAVE), lds, st, pl->L, grad + lo, p + lo, m + lo, v + lo,
+                                   norm.sums, norm.n, a, dst_c, norm.out, tm);
             }));
         else
             PARO_BY_FLAG(many, MANY, {
-                hipLaunchKernelGGL((k_adam4<PACK, MASK_TENSORS, false, MANY>), dim3(grid), dim3(WAVE), lds, st, a, norm.sums, norm.n, norm.out,
-                                   grad + lo, p + lo, m + lo, v + lo, dst_c, pl->L, tm);
+                hipLaunchKernelGGL((k_adam4<PACK, MASK_TENSORS, false, MANY>), dim3(grid), dim3(WAVE), lds, st, pl->L, grad + lo, p + lo, m + lo, v + lo,
+                                   norm.sums, norm.n, a, dst_c, norm.out, tm);
             });
         PARO_HIP(hipGetLastError());
     }
