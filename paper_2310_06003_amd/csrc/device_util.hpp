@@ -78,6 +78,12 @@ namespace {
 #ifndef PARO_ADAM_WAVES_PER_CU
 #define PARO_ADAM_WAVES_PER_CU 12
 #endif
+// A large sweep 2, from PARO_LARGE_TILES blocks on, wants one wave less since its waves start at once (whole clipped steps, same buffers, 12,
+// 11 and 10 waves: fp16, P = 8, 124 M elements 955, 946 and 948 us; P = 16, 421 M 4244, 4227 and 4242; P = 8, 62 M 481, 476 and 477; P = 2, 80 M
+// 462, 462 and 467; but 16 M 121.4 and 122.1).
+#ifndef PARO_ADAM_LARGE_WAVES_PER_CU
+#define PARO_ADAM_LARGE_WAVES_PER_CU 11
+#endif
 #ifndef PARO_ADAM_SMALL_ELEMS
 #define PARO_ADAM_SMALL_ELEMS (4 << 20)  // a small sweep 2 runs in as many waves as the masked one (12 waves: 2 M elements 22.7 us, 16: 22.5)
 #endif

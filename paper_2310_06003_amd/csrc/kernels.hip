@@ -1454,7 +1454,9 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     const bool many = norm.n > NORM_SLICES;
     if (!pl->any_no_decay) {
-        const unsigned lds = throttle_lds(sc.lds_per_cu, on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU : PARO_ADAM_WAVES_PER_CU);
+        const int waves = on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU
+                          : piece_count(on) < PARO_LARGE_TILES ? PARO_ADAM_WAVES_PER_CU : PARO_ADAM_LARGE_WAVES_PER_CU;
+        const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
         PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
             hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, on, grad, p, m, v, norm.sums, norm.n, a, dst,
                                norm.out, map_for(pl, sc, ob, false));
