@@ -183,10 +183,6 @@ struct AdamConsts {
     int keep_state;     // p, m, v and the packed parameters are stored to stay in the memory-side cache
 };
 
-// An entry of a chunk's weight-decay table: all elements of the tile take weight decay, none does, or DECAY_BITS + the index,
-// in the table, of the first of eight words with a bit for each element (set: it does).
-constexpr uint32_t DECAY_ALL = 0, DECAY_NONE = 1, DECAY_BITS = 2;
-
 // What a launch needs to map its elements to tensors.
 struct TensorMap {
     const int64_t *nz_off;      // [n_nz + 1] flat start of every non-empty tensor, then Psi

@@ -35,7 +35,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <bitset>
 #include <cmath>
 #include <new>
 #include <cstdlib>
@@ -818,53 +817,6 @@ int ensure_device(paro_plan_t *pl) {
     return PARO_OK;
 }
 
-// Walks the tiles of chunk c in address order: fn(i, f0, f1, k), tile i holding the flat indices
-// [f0, f1) and k the segment (non-empty tensor) that f0 lies in, or their number where f0 is padding.
-template <class F>
-void for_each_tile(const paro_plan_t *pl, int64_t c, F fn) {
-    const int64_t tiles = pl->dev.tiles_per_chunk, n_nz = (int64_t)pl->nz_tensor.size();
-    int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), c * pl->L) - pl->nz_off.begin() - 1;
-    for (int64_t i = 0; i < tiles; ++i) {
-        const int64_t f0 = c * pl->L + i * TILE, f1 = std::min(f0 + (int64_t)TILE, (c + 1) * pl->L);
-        while (k < n_nz && pl->nz_off[(size_t)k + 1] <= f0) ++k;
-        fn(i, f0, f1, k);
-    }
-}
-
-// The weight-decay table of a chunk: one entry per tile, then a bit for each element of the tiles in which some elements
-// take weight decay and some do not (padding does, and stays 0).
-// A wave of the masked sweep 2 used to look up its tile's tensor, then - with its data on the way - the tensor's flag, and in a
-// tile with a boundary the tensor of every element; the first look-up also held back its loads.  Now one scalar load that
-// nothing waits for, one vector load more in a mixed tile.  Clipped steps on the same buffers: 100 GPT-2 tensors, P = 8, 15.5 M
-// elements 130.5 -> 128.6 us; tensors of 1 to 65536 elements, P = 8, 0.7 M 16.0 -> 14.4, 2.2 M 30.3 -> 28.4, 14.5 M 127.8 -> 126.1,
-// 66 M 573 -> 565; few large tensors, P = 16, 105 M 878 as before.
-void list_decays(const paro_plan_t *pl, int64_t c, std::vector<uint32_t> *tab) {
-    tab->assign((size_t)pl->dev.tiles_per_chunk, DECAY_ALL);
-    for_each_tile(pl, c, [&](int64_t i, int64_t f0, int64_t f1, int64_t k) {
-        std::bitset<TILE> exempt;
-        for (; k < (int64_t)pl->nz_tensor.size() && pl->nz_off[(size_t)k] < f1; ++k) {
-            if (!pl->no_decay[(size_t)pl->nz_tensor[(size_t)k]]) continue;
-            const int64_t lo = std::max(pl->nz_off[(size_t)k], f0), hi = std::min(pl->nz_off[(size_t)k + 1], f1);
-            if (hi - lo == f1 - f0) {
-                (*tab)[(size_t)i] = DECAY_NONE;
-                return;
-            }
-            for (int64_t x = lo; x < hi; ++x) exempt.set((size_t)(x - f0));
-        }
-        if (exempt.none()) return;
-        if ((int64_t)exempt.count() == f1 - f0) {
-            (*tab)[(size_t)i] = DECAY_NONE;
-            return;
-        }
-        (*tab)[(size_t)i] = (uint32_t)tab->size() + DECAY_BITS;
-        for (int w = 0; w < TILE / 32; ++w) {
-            uint32_t bits = 0;
-            for (int b = 0; b < 32; ++b) bits |= (uint32_t)!exempt[(size_t)(w * 32 + b)] << b;
-            tab->push_back(bits);
-        }
-    });
-}
-
 // The chunk's pieces, for the tensor layout.  A tile with a boundary inside is cut where the tensors
 // meet: taken by one wave, its lanes would each have pointers of their own to fetch, element by element,
 // P times over (P = 64, 1.4 M elements of tensors of 1 to 65536 elements: sweep 1 in 195 us, a handful of
@@ -885,7 +837,7 @@ void list_pieces(const paro_plan_t *pl, int64_t c, std::vector<paro_piece_info> 
     auto add = [&](int64_t off, int64_t dt, int64_t lo, int64_t hi, int32_t tensor, int64_t i) {
         tab->push_back({off * ((int64_t)1 << 19) + (dt << 17 | hi << 8 | lo), tensor, (uint32_t)i});
     };
-    for_each_tile(pl, c, [&](int64_t i, int64_t f0, int64_t f1, int64_t k) {
+    paro::for_each_tile(pl, c, [&](int64_t i, int64_t f0, int64_t f1, int64_t k) {
         if (k == n_nz) return add(0, 0, 0, TILE, -2, i);
         const int32_t t = pl->nz_tensor[(size_t)k];
         if (f1 <= pl->nz_off[(size_t)k + 1]) return add(f0 - pl->nz_off[(size_t)k], pl->dtype[(size_t)t], 0, TILE, t, i);
@@ -955,7 +907,7 @@ int ensure_tables(paro_plan_t *pl, int rank, bool pieces, bool decays) {
     paro_device_tables &d = pl->dev;
     int rc = PARO_OK;
     if (pieces) rc = ensure_table(pl, rank, d.piece_tab, d.piece_tab_tried, list_pieces);
-    if (decays && rc == PARO_OK) rc = ensure_table(pl, rank, d.decay_tab, d.decay_tab_tried, list_decays);
+    if (decays && rc == PARO_OK) rc = ensure_table(pl, rank, d.decay_tab, d.decay_tab_tried, paro::list_decays);
     return rc;
 }
 

@@ -1,6 +1,7 @@
 // Internal definition of the plan object (host side) shared by plan.cpp and the
 // device entry points.  Not part of the public interface.
 #pragma once
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <string>
@@ -23,6 +24,10 @@ struct paro_piece_info {
                         // more pieces), and the offset is the index of its first non-empty tensor
     uint32_t tile;
 };
+
+// An entry of a chunk's weight-decay table: all elements of the tile take weight decay, none does, or DECAY_BITS + the index,
+// in the table, of the first of eight words with a bit for each element (set: it does).
+constexpr uint32_t DECAY_ALL = 0, DECAY_NONE = 1, DECAY_BITS = 2;
 
 struct paro_device_tables {
     int device = -1;
@@ -87,6 +92,20 @@ void letter_range(const paro_plan_t *pl, int rank, char letter, int64_t *begin, 
 bool on_cache_lines(const paro_plan_t *pl, int64_t chunk);
 // Whether more than half of a chunk's gradient elements are fp32.
 bool mostly_f32(const paro_plan_t *pl, int64_t chunk);
+// Walks the tiles of a chunk in address order: fn(i, f0, f1, k), tile i holding the flat indices
+// [f0, f1) and k the segment (non-empty tensor) that f0 lies in, or their number where f0 is padding.
+template <class F>
+void for_each_tile(const paro_plan_t *pl, int64_t chunk, F fn) {
+    const int64_t c0 = chunk * pl->L, c1 = c0 + pl->L, n_nz = (int64_t)pl->nz_tensor.size();
+    int64_t k = std::upper_bound(pl->nz_off.begin(), pl->nz_off.end(), c0) - pl->nz_off.begin() - 1;
+    for (int64_t f0 = c0, i = 0; f0 < c1; f0 += PARO_TILE, ++i) {
+        while (k < n_nz && pl->nz_off[(size_t)k + 1] <= f0) ++k;
+        fn(i, f0, std::min(f0 + PARO_TILE, c1), k);
+    }
+}
+// The weight-decay table of a chunk: one entry per tile, then the words of the tiles in which some elements take weight
+// decay and some do not (padding does, and stays 0).
+void list_decays(const paro_plan_t *pl, int64_t chunk, std::vector<uint32_t> *tab);
 // One rank's messages of a collective, in the order of the public table: all of them, or those of one
 // (phase, ring, step).
 struct MessageId {
