@@ -462,7 +462,7 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // MASK: how it finds the elements exempt from weight decay.  The global sum of squares comes as n_sums sums
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
-// KEPT: sweep 1 stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
+// KEPT: the launch before this one stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
 __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
                                                 float *__restrict__ v, const double *__restrict__ sums, int n_sums, const AdamConsts a,
@@ -1399,7 +1399,7 @@ int do_reduce(const paro_plan_t *pl, const Scratch &sc, int rank, const void *co
     return per_chunk ? finalize_sums(sc, (int)(c1 - c0), sumsq_out, st, rest) : PARO_OK;
 }
 
-template <bool PACK>
+template <bool PACK, bool KEPT>
 int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad,
                 const NormSums &norm, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     int64_t ob, on;
@@ -1409,10 +1409,10 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         const int waves = on <= PARO_ADAM_SMALL_ELEMS ? PARO_ADAM_MASK_WAVES_PER_CU
                           : piece_count(on) < PARO_LARGE_TILES ? PARO_ADAM_WAVES_PER_CU : PARO_ADAM_LARGE_WAVES_PER_CU;
         const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
-        PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
-            hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, on, grad, p, m, v, norm.sums, norm.n, a, dst,
-                               norm.out, map_for(pl, sc, ob, false));
-        }));
+        PARO_BY_FLAG(many, MANY, {
+            hipLaunchKernelGGL((k_adam4<PACK, MASK_NONE, KEPT, MANY>), dim3(piece_grid(on)), dim3(WAVE), lds, st, on, grad, p, m, v,
+                               norm.sums, norm.n, a, dst, norm.out, map_for(pl, sc, ob, false));
+        });
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
@@ -1421,25 +1421,24 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_MASK_WAVES_PER_CU), grid = piece_grid(pl->L);
         const TensorMap tm = map_for(pl, sc, c * pl->L, true);
         uint16_t *dst_c = dst ? dst + lo : nullptr;
-        if (tm.decay_tab)
-            PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(keeps_g(pl), KEPT, {
-                hipLaunchKernelGGL((k_adam4<PACK, MASK_TABLE, KEPT, MANY>), dim3(grid), dim3(WAVE), lds, st, pl->L, grad + lo, p + lo, m + lo, v + lo,
-                                   norm.sums, norm.n, a, dst_c, norm.out, tm);
-            }));
-        else
-            PARO_BY_FLAG(many, MANY, {
-                hipLaunchKernelGGL((k_adam4<PACK, MASK_TENSORS, false, MANY>), dim3(grid), dim3(WAVE), lds, st, pl->L, grad + lo, p + lo, m + lo, v + lo,
-                                   norm.sums, norm.n, a, dst_c, norm.out, tm);
-            });
+        PARO_BY_FLAG(many, MANY, PARO_BY_FLAG(tm.decay_tab != nullptr, TABLE, {
+            hipLaunchKernelGGL((k_adam4<PACK, TABLE ? MASK_TABLE : MASK_TENSORS, TABLE && KEPT, MANY>), dim3(grid), dim3(WAVE), lds, st,
+                               pl->L, grad + lo, p + lo, m + lo, v + lo, norm.sums, norm.n, a, dst_c, norm.out, tm);
+        }));
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
 }
 
-int do_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad,
+// Sweep 2 behind sweep 1, whose gradient may be in the memory-side cache (kept), or with a gradient that another call, or
+// another program's kernel, left anywhere: that is read as it always was.  Plain loads of a gradient that is no longer in the
+// cache drive out of it what other kernels wrote there (paro_adam_shard after 512 MB of something else, P = 8, streaming and
+// plain: 4 M elements 25.0 and 27.6 us, 12 M 58.4 and 65.7; of one just written 24.3 and 23.3, 55.8 and 54.4).
+int do_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad, bool kept,
             const NormSums &norm, float *p, float *m, float *v, uint16_t *dst /* nullable: no pack */, hipStream_t st) {
-    return dst ? launch_adam<true>(pl, sc, rank, a, grad, norm, p, m, v, dst, st)
-               : launch_adam<false>(pl, sc, rank, a, grad, norm, p, m, v, dst, st);
+    return !dst ? launch_adam<false, false>(pl, sc, rank, a, grad, norm, p, m, v, dst, st)
+           : kept ? launch_adam<true, true>(pl, sc, rank, a, grad, norm, p, m, v, dst, st)
+                  : launch_adam<true, false>(pl, sc, rank, a, grad, norm, p, m, v, dst, st);
 }
 
 // The launches of the fused step, arguments already checked: two sweeps when the update waits for
@@ -1455,7 +1454,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
         // the norm this rank can form on its own: over everything it updates (its update range)
         NormSums norm{nullptr, 0, nullptr};
         if ((rc = do_reduce(pl, sc, rank, contrib, layout, grad_scratch, sumsq_scratch, true, st, &norm))) return rc;
-        return do_adam(pl, sc, rank, a, grad_scratch, norm, p, m, v, dst, st);
+        return do_adam(pl, sc, rank, a, grad_scratch, keeps_g(pl), norm, p, m, v, dst, st);
     }
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     if (layout == PARO_CHUNK && !pl->any_no_decay && on > pl->L) return launch_fused_range(pl, sc, ob, on, contrib, a, p, m, v, dst, st);
@@ -1560,7 +1559,7 @@ int paro_adam_shard(paro_plan_t *pl, int rank, const paro_adam_t *hp, const floa
         dst = dst_base + so;
     }
     const bool needs_norm = a.max_norm > 0.0f || a.skip_nonfinite;
-    return do_adam(pl, plan_scratch(pl), rank, a, grad, NormSums{total_sumsq, needs_norm ? 1 : 0, nullptr}, p, m, v, dst,
+    return do_adam(pl, plan_scratch(pl), rank, a, grad, false, NormSums{total_sumsq, needs_norm ? 1 : 0, nullptr}, p, m, v, dst,
                    static_cast<hipStream_t>(stream));
 }
 
