@@ -25,18 +25,30 @@ namespace {
 #define PARO_POL_KEEP_ST 16
 #endif
 // Largest results that are stored without the streaming hint.
-// The reduced gradient, which sweep 2 reads again (with plain loads: a streaming load gives the line up), where the
-// contributions that pass through the cache meanwhile are no more than it holds.  Whole clipped steps, bf16, streaming and
-// kept, one process on three states in turn: P = 2, 12 M elements 77.6 and 72.9 us; P = 4, 16 M 107.3 and 100.6; P = 8,
-// 3 M 31.6 and 30.0, 16 M 127.9 and 120.2; P = 16, 6 M 69.1 and 66.3; on ten states in turn (each with a gradient array of its
-// own) P = 8, 2 to 16 M, 2 to 6 % ahead.  After a kernel that leaves the cache full of its own results, P = 2 to 8 gain 1 to 4 %,
-// P = 16 loses 0 to 1 % to 8 M and 2 % at 16 M, P = 32 and 64 2 to 4 % from 2 M on: hence the limit on the contributions, and
-// more than 16 ranks keep only what is small enough to keep its state as well.
+// The reduced gradient, which sweep 2 reads again (in the fused step with plain loads: a streaming load gives the line up), where the
+// contributions that pass through the cache meanwhile are no more than it holds.  Whole clipped steps, bf16, on the same buffers, streaming
+// and kept: P = 2, 12 M elements 75.7 and 71.5 us; P = 4, 16 M 111.0 and 103.9; P = 8, 3 M 29.9 and 28.9, 8 M 71.1 and 67.0, 16 M 129.9 and
+// 121.8; P = 16, 6 M 70.7 and 67.6.  With other work on the GPU between the steps:
+//   contributions just written, or copied in: up to 200 MB of them P = 2 to 16 are ahead by 1 to 5 %, up to 13 %.  Copied ones of 205 to 260 MB
+//   fill the cache by themselves and are behind by 3 to 13 % in places (P = 15, 8 M elements 77.5 and 89.0 us, P = 16, 7 M 71.7 and 80.7, P = 12,
+//   10 M 90.2 and 98.8, P = 8, 13 M 100.3 and 105.5), ahead by as much in others (P = 8, 16 M 131.6 and 120.0); written ones there are 2 to 4 %
+//   ahead, from 256 MB on 1 to 5 % behind (P = 16, 8 M 87.7 and 89.4; P = 8, 16 M 123.0 and 125.4).  Hence the limit on the contributions, and
+//   a lower one for arrays in shard coordinates of more than 8 ranks, for which what is lost there weighs more than what is won.  Lists of
+//   tensors do not mind (GPT-2, P = 16, 249 MB: 3 to 5 % ahead in all but one)
+//   512 MB of something else: P = 2 to 8 ahead by 1 to 4 %, P = 12 by 1 % to behind by 1, P = 16 behind by 0 to 3; P = 32 and 64 were behind by
+//   2 to 4 % from 2 M on, so more than 16 ranks keep only what is small enough to keep its state as well.
+// 20 to 32 M elements with P = 2 and 4 would still gain 2 to 6 %; they are not kept.
 #ifndef PARO_KEEP_G_ELEMS
 #define PARO_KEEP_G_ELEMS (16 << 20)
 #endif
 #ifndef PARO_KEEP_G_READ_BYTES
 #define PARO_KEEP_G_READ_BYTES (256 << 20)
+#endif
+#ifndef PARO_KEEP_G_FEW_RANKS
+#define PARO_KEEP_G_FEW_RANKS 8
+#endif
+#ifndef PARO_KEEP_G_WIDE_READ_BYTES
+#define PARO_KEEP_G_WIDE_READ_BYTES (192 << 20)   // ... chunk layout, more ranks than that
 #endif
 // p, m, v and the packed parameters, which the next step reads: with 1 M elements (18 MB with the gradient)
 // 15.3 -> 14.1 us (P = 8, clipped) and 9.6 -> 8.5 (one sweep), on ten states as on three; 4 M on ten states 37.5 -> 40.0.

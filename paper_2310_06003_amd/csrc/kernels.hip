@@ -979,10 +979,13 @@ int64_t update_elems(const paro_plan_t *pl) {
 bool paces(const paro_plan_t *pl) {
     return piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
 }
-bool keeps_g(const paro_plan_t *pl) {
+// Whether sweep 1 stores the reduced gradient to stay in the memory-side cache, where sweep 2 finds it.  Contributions of a
+// list with both types are counted as two-byte ones.
+bool keeps_g(const paro_plan_t *pl, int layout) {
     const int64_t n = update_elems(pl), esize = pl->uniform_dtype && pl->dtype[0] == PARO_F32 ? 4 : 2;
     if (pl->P > PARO_BATCH && n > PARO_KEEP_STATE_ELEMS) return false;
-    return n <= PARO_KEEP_G_ELEMS && n * pl->P * esize <= PARO_KEEP_G_READ_BYTES;
+    const int64_t most = layout == PARO_CHUNK && pl->P > PARO_KEEP_G_FEW_RANKS ? PARO_KEEP_G_WIDE_READ_BYTES : PARO_KEEP_G_READ_BYTES;
+    return n <= PARO_KEEP_G_ELEMS && n * pl->P * esize <= most;
 }
 
 int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
@@ -1020,7 +1023,7 @@ void plan_consts(const paro_plan_t *pl, AdamConsts *a) {
 // chunk's first element inside the update range.
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
-    tab->keep_g = keeps_g(pl);
+    tab->keep_g = keeps_g(pl, layout);
     tab->paced = paces(pl);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
@@ -1037,7 +1040,7 @@ void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int
 // ... and of a launch over an update range of several chunks: pointers in rank order, the order of
 // each chunk's fold follows from the range map.
 RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const void *const *contrib, SrcTable *tab) {
-    tab->keep_g = keeps_g(pl);
+    tab->keep_g = keeps_g(pl, PARO_CHUNK);
     // not with two-byte contributions of 16 ranks and more, where the pauses only delay (paced and not, 90 M elements in
     // all: P = 16, 2 chunks, clipped 969 and 947 us, single sweep 841 and 832; 8 chunks 957 and 930; P = 32, 4 chunks 1533
     // and 1452; P = 64, 8 chunks 2526 and 2493; but P = 8, 8 chunks 687 and 695, fp32 at P = 16 1426 and 1440)
@@ -1454,7 +1457,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
         // the norm this rank can form on its own: over everything it updates (its update range)
         NormSums norm{nullptr, 0, nullptr};
         if ((rc = do_reduce(pl, sc, rank, contrib, layout, grad_scratch, sumsq_scratch, true, st, &norm))) return rc;
-        return do_adam(pl, sc, rank, a, grad_scratch, keeps_g(pl), norm, p, m, v, dst, st);
+        return do_adam(pl, sc, rank, a, grad_scratch, keeps_g(pl, layout), norm, p, m, v, dst, st);
     }
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
     if (layout == PARO_CHUNK && !pl->any_no_decay && on > pl->L) return launch_fused_range(pl, sc, ob, on, contrib, a, p, m, v, dst, st);

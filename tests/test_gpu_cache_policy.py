@@ -15,7 +15,8 @@ M = 1 << 20
 @pytest.mark.parametrize("P,strategy,L,dtype", [
     (2, "NNG", M, wl.BF16), (2, "NNG", M + 8, wl.BF16), (2, "NNG", 4 * M, wl.F16), (2, "NNG", 4 * M + 8, wl.BF16),
     (2, "NNG", 16 * M, wl.BF16), (2, "NNG", 16 * M + 8, wl.BF16), (2, "NNN", 8 * M, wl.BF16), (2, "NNN", 8 * M + 8, wl.BF16),
-    (24, "NNG", M, wl.BF16), (24, "NNG", M + 8, wl.BF16), (8, "NNG", 8 * M, wl.F32), (8, "NNG", 8 * M + 8, wl.F32)])
+    (16, "NNG", 6 * M, wl.BF16), (16, "NNG", 6 * M + 8, wl.BF16), (24, "NNG", M, wl.BF16), (24, "NNG", M + 8, wl.BF16),
+    (8, "NNG", 8 * M, wl.F32), (8, "NNG", 8 * M + 8, wl.F32)])
 def test_steps_at_the_limits(paro, P, strategy, L, dtype):
     lay = orc.layout(P, 1, [P * L])
     pl = paro.paro_plan(P, 1, strategy, [P * L], sched=orc.RING, grad_dtype=[dtype])
