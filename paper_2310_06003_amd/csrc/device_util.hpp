@@ -96,8 +96,11 @@ namespace {
 #ifndef PARO_ADAM_LARGE_WAVES_PER_CU
 #define PARO_ADAM_LARGE_WAVES_PER_CU 11
 #endif
+// A small sweep 2 runs in as many waves as the masked one where all of it fits the chip at once, and not beyond (whole clipped steps, same
+// buffers, 12 and 16 waves: 1 M elements, P = 2, 11.0 and 10.1 us, P = 16 14.3 and 13.8; 1.5 M, P = 8, 16.8 and 17.0; 2 M, P = 2, 17.0 and 17.2;
+// 3 M, P = 8, 28.1 and 28.4; 4 M, P = 16, 46.5 and 47.0; 0.4 M no difference).
 #ifndef PARO_ADAM_SMALL_ELEMS
-#define PARO_ADAM_SMALL_ELEMS (4 << 20)  // a small sweep 2 runs in as many waves as the masked one (12 waves: 2 M elements 22.7 us, 16: 22.5)
+#define PARO_ADAM_SMALL_ELEMS (1 << 20)
 #endif
 #ifndef PARO_ADAM_MASK_WAVES_PER_CU
 #define PARO_ADAM_MASK_WAVES_PER_CU 16   // with a decay mask: a table look-up per wave to hide as well
