@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 from ctypes import (POINTER, Structure, byref, c_char, c_char_p, c_double, c_float, c_int, c_int32, c_int64, c_uint8,
                     c_void_p)
 from typing import List, Optional, Sequence, Tuple
@@ -31,7 +32,7 @@ PARO_RS, PARO_AG = 0, 1
 PARO_MAX_RANKS = 256
 PARO_STATIC_MAX_CHUNK = 1 << 30
 
-for _f in (_SO, os.path.join(_HERE, "_marshal.so")):
+for _f in (_SO, os.path.join(_HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))):
     if not os.path.exists(_f):
         raise ImportError(
             f"{_f} is missing: build it first (python paper_2310_06003_amd/build.py, or __graft_entry__.build()). "

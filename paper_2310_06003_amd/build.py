@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SO = os.path.join(HERE, "libparo.so")
 SOURCES = [os.path.join(HERE, "csrc", "plan.cpp"), os.path.join(HERE, "csrc", "kernels.hip")]
-MARSHAL_SO = os.path.join(HERE, "_marshal.so")
+# the extension reads CPython's own structures: its name carries the interpreter that it was built for, so that no other loads it
+MARSHAL_SO = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 MARSHAL_SOURCE = os.path.join(HERE, "csrc", "marshal.cpp")
 HEADERS = [os.path.join(HERE, "csrc", h) for h in ("plan.hpp", "device_util.hpp", "loaders.hpp")] + \
           [os.path.join(ROOT, "include", "paro.h")]
@@ -30,8 +31,9 @@ STAMP = SO + ".srchash"        # hash of what the library in the tree was built 
 
 
 def source_hash() -> str:
-    """sha256 over the compiler flags and the text of every source and header."""
-    h = hashlib.sha256(" ".join(FLAGS[:-2] + MARSHAL_FLAGS[:-2]).encode())     # without the -I paths (they differ per checkout)
+    """sha256 over the compiler flags, the interpreter's ABI and the text of every source and header."""
+    flags = FLAGS[:-2] + MARSHAL_FLAGS[:-2]                         # without the -I paths (they differ per checkout)
+    h = hashlib.sha256(" ".join(flags + [sysconfig.get_config_var("EXT_SUFFIX")]).encode())
     for f in SOURCES + [MARSHAL_SOURCE] + HEADERS:
         h.update(os.path.basename(f).encode())
         with open(f, "rb") as fh:

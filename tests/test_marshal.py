@@ -3,6 +3,7 @@ functions do.  Without a GPU every call ends in a refusal: which one tells what 
 import ctypes
 import inspect
 import itertools
+import os
 
 import numpy as np
 import pytest
@@ -109,3 +110,23 @@ def test_a_closed_plan_is_refused():
     with pytest.raises(paro.ParoError) as e:
         paro.paro_pack_params(plan, 1, 16, 16)
     assert e.value.code == paro.PARO_EINVAL
+
+
+def test_another_interpreter_neither_trusts_nor_loads_this_ones_extension(monkeypatch):
+    """The extension is compiled against one CPython's structures: in a tree built by this interpreter another one finds the
+    build stale and the package refuses to import, until it is built again."""
+    import __graft_entry__ as entry
+    import importlib.util
+    import sysconfig
+    entry.ensure_built()
+    assert not entry._lib_build_module().stale()
+    here = sysconfig.get_config_var("EXT_SUFFIX")
+    assert entry._lib_build_module().MARSHAL_SO == paro._marshal.__file__ and paro._marshal.__file__.endswith("_marshal" + here)
+    real = sysconfig.get_config_var
+    monkeypatch.setattr(sysconfig, "get_config_var", lambda k: ".cpython-399-other.so" if k == "EXT_SUFFIX" else real(k))
+    other = entry._lib_build_module()
+    assert other.stale() and other.source_hash() != other.built_hash()
+    spec = importlib.util.spec_from_file_location("another_interpreters_package", paro.__file__,
+                                                  submodule_search_locations=[os.path.dirname(paro.__file__)])
+    with pytest.raises(ImportError, match="cpython-399-other"):
+        spec.loader.exec_module(importlib.util.module_from_spec(spec))
