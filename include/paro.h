@@ -52,8 +52,9 @@
  * of an update range; up to twice that for many small tensors); the first call
  * for a rank that uses the tensor layout adds a list of pieces, the first that
  * needs a weight-decay mask block by block (sweep 2, or the chunk layout) a
- * per-tile table, for each chunk of that rank's update range (16 bytes per 256
- * elements each, the list up to twice that; built when the chunk has at most
+ * per-tile table, for each chunk of that rank's update range (the list 16 to 32
+ * bytes per 256 elements, the table 4, and 32 more where some of them are exempt
+ * and some are not; each built when the chunk has at most
  * 4 Mi tiles, or at most PARO_TILE_TABLE_MAX_TILES when that environment
  * variable is set; without them the kernels search; PARO_PAIR_MIN_BLOCKS, also
  * read at every call, makes sweep 1 of the tensor layout with up to 4 ranks, or

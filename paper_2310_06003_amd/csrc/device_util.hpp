@@ -51,13 +51,14 @@ namespace {
 #define PARO_KEEP_G_WIDE_READ_BYTES (192 << 20)   // ... chunk layout, more ranks than that
 #endif
 // p, m, v and the packed parameters, which the next step reads: with 1 M elements (18 MB with the gradient)
-// 15.3 -> 14.1 us (P = 8, clipped) and 9.6 -> 8.5 (one sweep), on ten states as on three; 4 M on ten states 37.5 -> 40.0.
+// 15.3 -> 14.1 us (P = 8, clipped) and 9.6 -> 8.5 (one sweep), on ten states as on three; 4 M on ten states 37.5 -> 40.0.  With contributions
+// just written 16.8 -> 15.9 (clipped) and 11.8 -> 10.4; after 512 MB of something else 0 to 3 % behind (17.1 and 17.6; 12.0 and 12.1).
 #ifndef PARO_KEEP_STATE_ELEMS
 #define PARO_KEEP_STATE_ELEMS (1 << 20)
 #endif
 // A message of an all-gather or the result of a hop, which the next step of the ring reads: 8 buffers, messages of
 // 15 MB (56 of them) 375 -> 341 us, 31 MB 641 -> 607, 62 MB 1256 -> 1312; hop, 8 M elements 13.6 -> 12.9 us, 30 M 45.1
-// -> 45.6.
+// -> 45.6; with its addend just written 15.7 -> 14.2, after 512 MB of something else 15.9 -> 16.2.
 #ifndef PARO_KEEP_MESSAGE_BYTES
 #define PARO_KEEP_MESSAGE_BYTES (48 << 20)
 #endif
@@ -72,6 +73,7 @@ namespace {
 // budget is in loads: a wave has min(P, PARO_BATCH) of them in flight, so with P = 16 the numbers
 // below mean 14 waves per compute unit for sweep 1 and 10 for the single sweep (whose waves also
 // load 3 state vectors); with fewer contributions per wave, more waves.  Where other numbers hold: fold_budget, fused_waves.
+// Wave counts here and there are counts asked for; throttle_lds says what fits.
 #ifndef PARO_FOLD_LOADS_PER_CU
 #define PARO_FOLD_LOADS_PER_CU 224
 #endif
@@ -92,7 +94,8 @@ namespace {
 #endif
 // A large sweep 2, from PARO_LARGE_TILES blocks on, wants one wave less since its waves start at once (whole clipped steps, same buffers, 12,
 // 11 and 10 waves: fp16, P = 8, 124 M elements 955, 946 and 948 us; P = 16, 421 M 4244, 4227 and 4242; P = 8, 62 M 481, 476 and 477; P = 2, 80 M
-// 462, 462 and 467; but 16 M 121.4 and 122.1).
+// 462, 462 and 467; but 16 M 121.4 and 122.1.  12 and 11 on another box: 949 and 943; 4288 and 4273; 474 and 470; 459 and 457; P = 8, 40 M 304.6 and
+// 304.2).
 #ifndef PARO_ADAM_LARGE_WAVES_PER_CU
 #define PARO_ADAM_LARGE_WAVES_PER_CU 11
 #endif
@@ -351,7 +354,7 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Sum over a block of FINALIZE_TPB threads, valid in thread 0: lanes by shuffles, then the waves in order.
+// Sum over a block of FINALIZE_TPB threads, valid in thread 0: the lanes of each wave, then the waves in order.
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double s_wave[FINALIZE_TPB / 64];
     v = wave_sum(v);

@@ -13,9 +13,9 @@
 //             address order, interleave reads and writes finely.  On MI355X this
 //             beat 256-thread blocks of 8-element threads by 8-11 %, and those had
 //             beaten persistent grid-stride blocks by 8-15 %.
-//   occupancy the heavy sweeps ask for unused dynamic LDS so that only 10-14 waves
-//             run per compute unit: fewer requests outstanding fight less over
-//             DRAM pages (another 3-6 %).  The tensor layout over many small
+//   occupancy the heavy sweeps ask for unused dynamic LDS so that only 8 to 25 waves
+//             run per compute unit, by kernel and number of ranks: fewer requests
+//             outstanding fight less over DRAM pages (another 3-6 %).  The tensor layout over many small
 //             tensors wants the opposite - its waves wait on look-ups with no
 //             data in flight - and gets every wave the registers allow.
 //   caches    nearly everything is touched once: streaming (non-temporal) loads; stores
@@ -24,8 +24,8 @@
 //   fold      the P contributions of an element are added in a fixed order
 //             (never re-associated, never contracted into FMAs) so the result
 //             is bit-identical to a reduce-scatter ring run in that order
-//   norm      squares are exact in fp64; per-thread fp64 sums -> wave shuffles
-//             -> one partial per block -> added in a fixed order, by a small
+//   norm      squares are exact in fp64; per-thread fp64 sums -> sum over the
+//             wave -> one partial per block -> added in a fixed order, by a small
 //             kernel, by sweep 2's waves, or both.  No atomics: run-to-run identical.
 //   tensors   the tensor layout needs the tensor an element belongs to: a list of
 //             pieces (built once per chunk), each inside one tensor, answers with
@@ -69,8 +69,9 @@ __device__ __forceinline__ double strided_sum(const double *__restrict__ sums, i
 // Lanes hold the result.  MANY: more than NORM_SLICES, up to NORM_DIRECT_PARTIALS of them.  fetch() issues the vector loads of
 // many: before a wave's state, because loads return in the order of their issue, and sums behind the state would be waited for
 // together with it, with their adds to come (whole clipped steps, same buffers: P = 8, 0.5 M elements 10.0 -> 9.4 us, 0.375 M 8.4 -> 8.1;
-// P = 4, 0.5 M 9.5 -> 9.0).  Their registers cost a sweep 2 with few 1 to 2 %: a kernel of its own.  Few are one scalar load, on a
-// way of its own (there is room for as many).
+// P = 4, 0.5 M 9.5 -> 9.0).  Their registers (82 against 32) cost a sweep 2 with few 1 to 2 %: a kernel of its own.  Few are one scalar load, on
+// a way of its own (there is room for as many).  One kernel for both took 39; why GPT-2's tensors at P = 16, which leave few sums,
+// went from 85.8 to 82.0 us when it was parted is not known.
 template <bool MANY>
 struct NormTotal {
     static constexpr int U = MANY ? NORM_DIRECT_PARTIALS / WAVE : 1, ROUND = 8;
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(WAVE) void k_norm_total(const double *__restrict__ 
 
 // The NORM_SLICES slice sums of k_finalize and their total in one small launch: block_sum() of every slice -
 // the same pairs of lanes at every step, the same order of waves - then the slices in order.  Eight separate
-// sums across the lanes would be 48 shuffles a wave, 16 waves on one compute unit, and eight loops as many round
+// sums across the lanes would be 48 steps a wave, 16 waves on one compute unit, and eight loops as many round
 // trips to memory (together 4 us); here each of the first three steps also halves the slices that a lane carries: ten.
 __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double *__restrict__ partials, int n, int chunk,
                                                                     double *out) {
@@ -554,8 +555,8 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
 template <int DT, int NSRC>
-__global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v, int P,
-                                                  const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
+__global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m,
+                                                  float *__restrict__ v, int P, const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
                                                   uint16_t *__restrict__ dst) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
     if (e0 >= n) return;
@@ -649,9 +650,14 @@ unsigned piece_grid(int64_t n, int ppw = 1) { return (unsigned)piece_count(n, pp
 constexpr int64_t MAX_GRID = (int64_t)1 << 25;
 
 // Occupancy throttle for the one-wave-block sweeps: on this part the mixed read/write sweeps run
-// faster with 10-14 waves per compute unit in flight than with the 32 the registers would allow
+// faster with 8 to 25 waves per compute unit in flight than with the 32 the registers would allow
 // (fewer requests fighting over DRAM pages).  The launch asks for dynamic LDS it never touches,
-// sized so that only `waves_per_cu` blocks fit on a compute unit.
+// a share of the compute unit's 160 KB for each of `waves_per_cu` blocks.
+// That is the count asked for, and so are all wave counts in knobs, rules and comments here: LDS is handed out in units of 1280 bytes,
+// to which the share is not rounded down, so that one or two waves fewer may fit (counted by the time that blocks of sleeping waves take;
+// the occupancy query answers with the count asked for):
+//   asked 8 or 9: 8   10: 9   11: 10   12: 11   13: 12   14, 15: 14   16, 17: 16   18 to 20: 18   21 to 24: 21   25 to 30: 25
+// The rules were measured as they stand, with what fits; rounding the share would change launches and not only names.
 unsigned throttle_lds(int lds_per_cu, int waves_per_cu) {
     if (waves_per_cu <= 0) return 0;
     unsigned bytes = (unsigned)(lds_per_cu / waves_per_cu) / 256u * 256u;
@@ -672,10 +678,13 @@ int fold_loads(int P) { return std::min(P, PARO_BATCH); }
 // A paced launch is told apart further - whole clipped steps on the same buffers, with the numbers of the line before
 // (224 loads, 192 for more than 16 ranks, a pause of 4) and with these:
 //   more than 16 ranks, a pause of 10 and more waves, so that waves side by side read the same page for longer: P = 64, 105 M
-//     elements 2696 -> 2673 us, 40 M 1068 -> 1029; P = 48, 40 M 826 -> 793; P = 32, 30 M 479 -> 469; P = 17, 60 M 638 -> 631
-//   fp32, whose loads are twice as wide, half as many waves: P = 64, 20 M 924 -> 895; P = 16, 100 M 1568 -> 1520; P = 12, 60 M
-//     781 -> 747; P = 8, 150 M 1576 -> 1531; P = 6, 100 M 895 -> 872 (P = 4 774 -> 766, P = 3 as it was)
-//   5 to 10 ranks, 20 waves instead of 28 (P = 8): P = 8, 200 M 1525 -> 1499; P = 7, 80 M 589 -> 579; P = 10, 60 M 494 -> 489
+//     elements 2794 -> 2787 us, 40 M 1069 -> 1034; P = 48, 40 M 856 -> 829; P = 32, 30 M 474 -> 464; P = 31, 60 M 924 -> 917; P = 24
+//     776 -> 775; P = 20 685 -> 683; P = 17 648 -> 639
+//   fp32, whose loads are twice as wide, half as many waves: P = 64, 20 M 954 -> 920; P = 16, 100 M 1572 -> 1528; P = 12, 60 M
+//     787 -> 760; P = 11 749 -> 718; P = 9 673 -> 646; P = 8, 150 M 1603 -> 1527; P = 6, 100 M 909 -> 884; P = 4 771 -> 766; P = 3 702
+//     -> 703; P = 2 637 -> 636
+//   5 to 10 ranks, 20 waves instead of 28 (P = 8): P = 8, 200 M 1523 -> 1500; P = 5, 80 M 533 -> 532; P = 7 589 -> 581; P = 10, 60 M
+//     500 -> 496
 int fold_budget(const paro_plan_t *pl, bool paced) {
     const bool f32 = pl->dtype[0] == PARO_F32;
     if (paced && f32) return pl->P <= 8 ? 80 : 112;
@@ -685,17 +694,20 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
     return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
 }
 
-// Waves per compute unit of a single sweep over `blocks` blocks.  The budget, which was found at P = 16, lets too many
-// waves with few loads each run beside one another: a wave also loads and stores its state, and what counts is the bytes that
-// a compute unit has in flight, 60 to 100 KB.  So no more than 13 waves of two-byte contributions with up to 7 ranks, 12 beyond,
-// and 13 (P = 2) to 8 (P >= 8) of fp32.  Whole steps on the same buffers, by the budget and with these: P = 2, 200 M elements
-// 965 -> 916 us; P = 4, 150 M 833 -> 787; P = 6, 80 M 486 -> 467; P = 8, 200 M 1365 -> 1287, 6 M 42.2 -> 40.2; P = 10, 60 M 432 ->
-// 425; fp32: P = 4, 100 M 685 -> 642; P = 6, 80 M 659 -> 622; P = 8, 20 M 194 -> 181; P = 12, 60 M 714 -> 693; a range of 8 chunks of
-// 7.5 M, P = 8, 394 -> 381.  Not in launches that run in one round of waves (P = 8, 1 M: 6.3 -> 7.5).
-// A list of few large fp32 tensors whose blocks start on cache lines has look-ups to hide as well and wants a few more: 13 waves, 10 from 7
-// ranks on (Llama-like lists, P = 4, 572 -> 539; P = 6, 2144 -> 2046; P = 8, 2725 -> 2610).  Two-byte ones keep the budget (P = 4 2596, 15
-// waves 2591; P = 3 597, 16 waves 626), and so do blocks that share cache lines with their neighbours, which want them close in time,
-// and many small tensors (fp32, ragged, P = 6, 13 waves 420 -> 391, but P = 7 463 -> 531; Llama-like, P = 7 1901 -> 2032).
+// Waves per compute unit of a single sweep over `blocks` blocks.  The budget, which was found at P = 16, lets too many waves
+// with few loads each run beside one another: a wave also loads and stores its state, and what counts is the bytes that a
+// compute unit has in flight: 50 KB (P = 2) to 100 (P = 12) with two-byte contributions, 60 to 150 with fp32 ones.  So no
+// more than 13 waves of two-byte contributions with up to 7 ranks, 12 beyond, and 13 (P = 2) to 8 (P >= 8) of fp32.  Whole
+// steps on the same buffers, by the budget and with these: P = 2, 200 M elements 971 -> 897 us; P = 3, 100 M 538 -> 495;
+// P = 4, 150 M 836 -> 775; P = 6, 80 M 487 -> 465; P = 8, 200 M 1333 -> 1272, 6 M 42.8 -> 41.0; P = 10, 60 M 440 -> 425; P = 12 to
+// 15 as they were; fp32: P = 2, 100 M 566 -> 527; P = 4 687 -> 644; P = 6, 80 M 686 -> 617; P = 8, 20 M 194 -> 183; P = 12, 60
+// M 729 -> 707; P = 15, 40 M 559 -> 554; a range of 8 chunks of 7.5 M, P = 8, 405 -> 386.  Not in launches that run in one
+// round of waves (P = 8, 1 M: 6.3 -> 7.5).
+// A list of few large fp32 tensors whose blocks start on cache lines has look-ups to
+// hide as well and wants a few more: 13 waves, 10 from 7 ranks on (Llama-like lists, P = 4, 572 -> 539; P = 6, 2144 -> 2046; P
+// = 8, 2725 -> 2610).  Two-byte ones keep the budget (P = 4 2596, 15 waves 2591; P = 3 597, 16 waves 626), and so do blocks
+// that share cache lines with their neighbours, which want them close in time, and many small tensors (fp32, ragged, P = 6, 13
+// waves 420 -> 391, but P = 7 463 -> 531; Llama-like, P = 7 1901 -> 2032).
 enum class Sweep { CHUNK, TENSORS_ON_LINES, OTHER_TENSORS };
 int fused_waves(int P, bool f32, Sweep over, int64_t blocks) {
     const int waves = fold_waves(fold_loads(P) + 3, PARO_FUSED_LOADS_PER_CU);
@@ -868,7 +880,7 @@ int ensure_table(paro_plan_t *pl, int rank, std::vector<Info *> &tabs, std::vect
     const paro_device_tables &d = pl->dev;
     int64_t ob, on;
     paro::letter_range(pl, rank, pl->letters[2], &ob, &on);
-    int64_t max_tiles = (int64_t)4 << 20;                   // 64 MB of table
+    int64_t max_tiles = (int64_t)4 << 20;                   // up to 128 MB of pieces, up to 151 MB of weight-decay table
     if (const char *env = std::getenv("PARO_TILE_TABLE_MAX_TILES")) max_tiles = std::atoll(env);
     std::vector<Info> tab;
     for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {
@@ -1162,11 +1174,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
         PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
             if (few)
-                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
-                                   partials, few_sources(tab), tm);
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n,
+                                   tm.pieces, tm.n_pieces, pl->P, group_len, g, partials, few_sources(tab), tm);
             else
-                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
-                                   partials, few_sources(tab), tm);
+                hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n,
+                                   tm.pieces, tm.n_pieces, pl->P, group_len, g, partials, few_sources(tab), tm);
         }));
         return (int)grid;
     }
@@ -1178,8 +1190,8 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), budget));
     PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
-            hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g,
-                                   partials, few_sources(tab), tm);
+            hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, n, tm.pieces,
+                               tm.n_pieces, pl->P, group_len, g, partials, few_sources(tab), tm);
         else
             PARO_BY_TABLE(pl->P, tab, hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, PARO_BATCH, NT, NSRC, KEEP>), dim3(grid), dim3(WAVE), lds,
                                                          st, n, tm.pieces, tm.n_pieces, pl->P, group_len, g, partials, src, tm));
@@ -1207,14 +1219,14 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const int mask = !pl->any_no_decay ? MASK_NONE : layout == PARO_CHUNK && tm.decay_tab ? MASK_TABLE : MASK_TENSORS;
     if (layout == PARO_TENSORS)
         PARO_BY_TABLE(pl->P, tab, PARO_BY_FLAG(mask != MASK_NONE, MASKED, PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0, {
-            hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC>), dim3(tm.pieces ? tm.n_pieces : grid),
-                               dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P, group_len, src, a,
-                               dst, tm);
+            hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC>),
+                               dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P,
+                               group_len, src, a, dst, tm);
         })));
     else
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P, group_len, src, a,
-                               dst, tm);
+            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
+                               tm.n_pieces, pl->P, group_len, src, a, dst, tm);
         })));
 }
 
@@ -1321,8 +1333,9 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
         }
         if (sumsq_out && first < last) {
             PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC>), dim3((unsigned)grid),
-                                                                                     dim3(WAVE), lds, st, b0, on, pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out,
-                                                                                     sc.partials, rm, src)));
+                                                                                     dim3(WAVE), lds, st, b0, on, pl->P,
+                                                                                     (unsigned)(first - b0), (unsigned)(last - first),
+                                                                                     grad_out, sc.partials, rm, src)));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
             one_sum = step >= blocks && last - first <= NORM_GROUP;

@@ -1,6 +1,6 @@
 // CPython extension: argument marshalling for the device calls, which a training program makes every step.
 //
-// What bounds a small step is the host (one launch over 2^18 elements: the GPU works 3.3 us).  ctypes makes an array object
+// What bounds a small step is the host (one launch over 2^18 elements: the GPU works 3.4 us).  ctypes makes an array object
 // per call for the contribution pointers and a conversion object per argument: a step of one launch 5.9 us, of two 9.7; with
 // this extension 4.9 and 8.9.  Here the usual call - positional arguments, plain ints, a list or tuple of addresses - is read straight into C
 // variables.  Anything else (keywords, None, numpy integers, ctypes objects, wrong types, a closed plan) goes to the
@@ -113,34 +113,42 @@ bool parse(const char *kinds, PyObject *const *args, Py_ssize_t n, Args *out) {
 }
 
 // The calls.  fn: the function's address in the library that the binding has loaded.
+template <class T>
+T *at(const Arg &a) {
+    return static_cast<T *>(a.ptr);
+}
 int64_t call_reduce(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_reduce_shard)>(fn)((paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, x.contrib, (int)x.a[3].num, (float *)x.a[4].ptr,
-                             (double *)x.a[5].ptr, x.a[6].ptr);
+    return reinterpret_cast<decltype(&paro_reduce_shard)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, x.contrib, (int)x.a[3].num,
+                                                              at<float>(x.a[4]), at<double>(x.a[5]), x.a[6].ptr);
 }
 int64_t call_adam(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_adam_shard)>(fn)((paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, &x.hp, (const float *)x.a[3].ptr, (const double *)x.a[4].ptr,
-                           (float *)x.a[5].ptr, (float *)x.a[6].ptr, (float *)x.a[7].ptr, (uint16_t *)x.a[8].ptr, x.a[9].ptr);
+    return reinterpret_cast<decltype(&paro_adam_shard)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, &x.hp, at<float>(x.a[3]),
+                                                            at<double>(x.a[4]), at<float>(x.a[5]), at<float>(x.a[6]),
+                                                            at<float>(x.a[7]), at<uint16_t>(x.a[8]), x.a[9].ptr);
 }
 int64_t call_pack(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_pack_params)>(fn)((paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, (const float *)x.a[2].ptr, (uint16_t *)x.a[3].ptr, x.a[4].ptr);
+    return reinterpret_cast<decltype(&paro_pack_params)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, at<float>(x.a[2]),
+                                                             at<uint16_t>(x.a[3]), x.a[4].ptr);
 }
 int64_t call_step(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_step_fused)>(fn)((paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, x.contrib, (int)x.a[3].num, &x.hp, (float *)x.a[5].ptr,
-                           (double *)x.a[6].ptr, (float *)x.a[7].ptr, (float *)x.a[8].ptr, (float *)x.a[9].ptr,
-                           (uint16_t *)x.a[10].ptr, x.a[11].ptr);
+    return reinterpret_cast<decltype(&paro_step_fused)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, x.contrib, (int)x.a[3].num, &x.hp,
+                                                            at<float>(x.a[5]), at<double>(x.a[6]), at<float>(x.a[7]),
+                                                            at<float>(x.a[8]), at<float>(x.a[9]), at<uint16_t>(x.a[10]), x.a[11].ptr);
 }
 int64_t call_static(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_step_fused_static)>(fn)((const paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, x.contrib, &x.hp, (float *)x.a[4].ptr,
-                                  (double *)x.a[5].ptr, (float *)x.a[6].ptr, (float *)x.a[7].ptr, (float *)x.a[8].ptr,
-                                  (uint16_t *)x.a[9].ptr, x.a[10].ptr);
+    return reinterpret_cast<decltype(&paro_step_fused_static)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, x.contrib, &x.hp,
+                                                                   at<float>(x.a[4]), at<double>(x.a[5]), at<float>(x.a[6]),
+                                                                   at<float>(x.a[7]), at<float>(x.a[8]), at<uint16_t>(x.a[9]),
+                                                                   x.a[10].ptr);
 }
 int64_t call_hop(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_ring_hop)>(fn)((paro_plan_t *)x.a[0].ptr, x.a[1].ptr, (int)x.a[2].num, x.a[3].ptr, (int)x.a[4].num, (float *)x.a[5].ptr,
-                         x.a[6].num, x.a[7].ptr);
+    return reinterpret_cast<decltype(&paro_ring_hop)>(fn)(at<paro_plan_t>(x.a[0]), x.a[1].ptr, (int)x.a[2].num, x.a[3].ptr,
+                                                          (int)x.a[4].num, at<float>(x.a[5]), x.a[6].num, x.a[7].ptr);
 }
 int64_t call_collective(void *fn, Args &x) {
-    return reinterpret_cast<decltype(&paro_collective_step)>(fn)((paro_plan_t *)x.a[0].ptr, (int)x.a[1].num, (int)x.a[2].num, (int)x.a[3].num, (int)x.a[4].num,
-                                (int)x.a[5].num, (int)x.a[6].num, const_cast<void *const *>(x.contrib), x.a[8].ptr);
+    return reinterpret_cast<decltype(&paro_collective_step)>(fn)(at<paro_plan_t>(x.a[0]), (int)x.a[1].num, (int)x.a[2].num,
+                                                                 (int)x.a[3].num, (int)x.a[4].num, (int)x.a[5].num, (int)x.a[6].num,
+                                                                 const_cast<void *const *>(x.contrib), x.a[8].ptr);
 }
 
 struct Call {
@@ -150,8 +158,10 @@ struct Call {
     bool counts;                      // returns a number
 };
 constexpr Call CALLS[] = {
-    {"paro_reduce_shard", "Picippp", "paro_reduce_shard(plan, rank, contrib, layout, grad_out, sumsq_out, stream=0)\n--\n\n", 6, call_reduce, false},
-    {"paro_adam_shard", "Pihppppppp", "paro_adam_shard(plan, rank, hp, grad, total_sumsq, p, m, v, dst_base=0, stream=0)\n--\n\n", 8, call_adam, false},
+    {"paro_reduce_shard", "Picippp",
+     "paro_reduce_shard(plan, rank, contrib, layout, grad_out, sumsq_out, stream=0)\n--\n\n", 6, call_reduce, false},
+    {"paro_adam_shard", "Pihppppppp",
+     "paro_adam_shard(plan, rank, hp, grad, total_sumsq, p, m, v, dst_base=0, stream=0)\n--\n\n", 8, call_adam, false},
     {"paro_pack_params", "Pippp", "paro_pack_params(plan, rank, p, dst_base, stream=0)\n--\n\n", 4, call_pack, false},
     {"paro_step_fused", "Picihppppppp",
      "paro_step_fused(plan, rank, contrib, layout, hp, grad_scratch, sumsq_scratch, p, m, v, dst_base, stream=0)\n--\n\n", 11, call_step, false},
