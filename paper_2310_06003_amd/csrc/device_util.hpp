@@ -149,6 +149,18 @@ namespace {
 #ifndef PARO_PACE_WIDE_F32_SLEEP
 #define PARO_PACE_WIDE_F32_SLEEP 6  // ... of fp32 gradients
 #endif
+#ifndef PARO_PACE_SINGLE_SLEEP
+#define PARO_PACE_SINGLE_SLEEP 16   // ... in a small single sweep (see paces_single; 10: up to 6 % slower at 25 MB, 20: 3 % at 22 MB)
+#endif
+#ifndef PARO_PACE_SINGLE_MAX_RANKS
+#define PARO_PACE_SINGLE_MAX_RANKS 3
+#endif
+#ifndef PARO_PACE_SINGLE_MIN_BYTES
+#define PARO_PACE_SINGLE_MIN_BYTES 21000000   // bytes read, from here on ...
+#endif
+#ifndef PARO_PACE_SINGLE_MAX_BYTES
+#define PARO_PACE_SINGLE_MAX_BYTES 30500000   // ... and up to here
+#endif
 #ifndef PARO_PACE_MIN_BLOCKS
 #define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)
 #endif
