@@ -149,20 +149,24 @@ namespace {
 #ifndef PARO_PACE_WIDE_F32_SLEEP
 #define PARO_PACE_WIDE_F32_SLEEP 6  // ... of fp32 gradients
 #endif
-#ifndef PARO_PACE_SINGLE_SLEEP
-#define PARO_PACE_SINGLE_SLEEP 16   // ... in a small single sweep (see paces_single; 10: up to 6 % slower at 25 MB, 20: 3 % at 22 MB)
-#endif
-#ifndef PARO_PACE_SINGLE_MAX_RANKS
-#define PARO_PACE_SINGLE_MAX_RANKS 3
-#endif
-#ifndef PARO_PACE_SINGLE_MIN_BYTES
-#define PARO_PACE_SINGLE_MIN_BYTES 21000000   // bytes read, from here on ...
-#endif
-#ifndef PARO_PACE_SINGLE_MAX_BYTES
-#define PARO_PACE_SINGLE_MAX_BYTES 30500000   // ... and up to here
-#endif
 #ifndef PARO_PACE_MIN_BLOCKS
 #define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)
+#endif
+// A small single sweep over one chunk whose waves pause (see pauses_single): how long, and the bytes that the launch reads.
+#ifndef PARO_PAUSE_SLEEP
+#define PARO_PAUSE_SLEEP 26         // units of 64 clocks (20 and 40: 3 to 7 % slower at 25 to 27 MB with P = 1, and with P = 3 or 2)
+#endif
+#ifndef PARO_PAUSE_MAX_RANKS
+#define PARO_PAUSE_MAX_RANKS 3
+#endif
+#ifndef PARO_PAUSE_MIN_BYTES
+#define PARO_PAUSE_MIN_BYTES 21000000       // P = 3, 20.5 MB: 7 % ahead without
+#endif
+#ifndef PARO_PAUSE_MIN_BYTES_ONE
+#define PARO_PAUSE_MIN_BYTES_ONE 20000000   // one rank
+#endif
+#ifndef PARO_PAUSE_MAX_BYTES
+#define PARO_PAUSE_MAX_BYTES 30500000
 #endif
 #ifndef PARO_SPLIT_MAX
 #define PARO_SPLIT_MAX 16           // a tile with up to so many tensors inside is cut into pieces

@@ -505,7 +505,7 @@ __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restri
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
 // reduced gradient never goes to memory.  TENSORS: contributions are per-tensor gradients; else
 // arrays in shard coordinates of dtype DT.  NT: as for k_reduce4t.
-template <bool TENSORS, int DT, int MASK, bool NT, int NSRC, int PACE = PARO_PACE_SLEEP>
+template <bool TENSORS, int DT, int MASK, bool NT, int NSRC, int PAUSE = 0>
 __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
                                                  const paro_piece_info *pieces, unsigned n_pieces, int P, int group_len,
                                                  const SrcTableOf<NSRC> src, const AdamConsts a, uint16_t *__restrict__ dst, TensorMap tm) {
@@ -544,7 +544,8 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
     if constexpr (TENSORS) {
         if (pc.tensor != -2) fold_tensors<NT>(pc, loc, src, P, group_len, X);
     } else {
-        Chunk4Loader<DT, PACE> ld{e};
+        if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);         // see pauses_single
+        Chunk4Loader<DT, PAUSE ? 0 : PARO_PACE_SLEEP> ld{e};
         fold4(ld, src, P, group_len, X);
     }
     bool decays[4] = {true, true, true, true};
@@ -991,16 +992,19 @@ int64_t update_elems(const paro_plan_t *pl) {
 bool paces(const paro_plan_t *pl) {
     return piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
 }
-// Whether the loads of a single sweep over one chunk of n elements are paced.  Its waves start with their arguments in registers, and where
-// the launch reads 21 to 30 MB - all of it runs at once, or nearly - few contributions ask for too much at the same moment.  A pause
-// between the loads of one contribution and the next spreads that (three states in turn; without preloaded arguments, with them, with
-// this pause as well): P = 2, bf16, 1.4 M elements 7.3, 8.3 and 6.9 us, 1.5 M 7.8, 8.9 and 7.4, 1.7 M 10.0, 10.4 and 9.9; P = 3,
-// 1.33 M 7.5, 8.5 and 7.5, 1.5 M 8.8, 9.7 and 8.8; fp32, P = 2, 1.2 M 7.2, 8.2 and 6.9; contributions just written, P = 2, 1.5 M
-// 13.9, 12.6 and 11.2, after 512 MB of something else 11.0, 12.6 and 11.2.  Below 21 MB it delays (P = 3, 1.16 M 6.5 and 7.2), above
-// 30 MB it makes no difference, and 4 ranks pace themselves (1.2 M 6.9 and 7.2).  One rank has no second contribution to wait for.
-bool paces_single(const paro_plan_t *pl, int64_t n) {
-    const int64_t bytes = n * (12 + pl->P * (pl->dtype[0] == PARO_F32 ? 4 : 2));
-    return pl->P > 1 && pl->P <= PARO_PACE_SINGLE_MAX_RANKS && bytes >= PARO_PACE_SINGLE_MIN_BYTES && bytes < PARO_PACE_SINGLE_MAX_BYTES;
+// Whether the waves of a single sweep over one chunk of n elements pause between the loads of their state and those of the
+// contributions.  They start with their arguments in registers, and where the launch reads 21 to 30 MB - all of it runs at once, or
+// nearly - with up to 3 ranks they ask for too much at the same moment.  Three states in turn, without preloaded arguments, with
+// them, and with this pause as well: P = 1, bf16, 1.57 M elements 7.6, 8.4 and 7.2 us, 1.71 M 8.3, 9.3 and 8.0; P = 2, 1.44 M 7.4, 8.4
+// and 7.5, 1.5 M 7.8, 8.9 and 7.7, 1.69 M 10.1, 10.4 and 8.9; P = 3, 1.33 M 7.4, 8.4 and 7.3, 1.5 M 8.9, 9.7 and 8.3; fp32, P = 2,
+// 1.2 M 7.3, 8.2 and 6.9.  Contributions just written, P = 2, 1.5 M: 13.9, 12.6 and 11.3; after 512 MB of something else 11.0, 12.6
+// and 11.0.  A pause after each contribution's load: 6 % ahead of this one at P = 2, 1.4 M, 8 to 15 % behind it at 1.7 M, nothing for P = 1.
+// One fp32 contribution does without (1.4 M 9.0 and 8.3; paused 9.1), and so do 4 ranks.
+bool pauses_single(const paro_plan_t *pl, int64_t n) {
+    const bool f32 = pl->dtype[0] == PARO_F32;
+    const int64_t bytes = n * (12 + pl->P * (f32 ? 4 : 2));
+    if (pl->P > PARO_PAUSE_MAX_RANKS || (pl->P == 1 && f32)) return false;
+    return bytes >= (pl->P == 1 ? PARO_PAUSE_MIN_BYTES_ONE : PARO_PAUSE_MIN_BYTES) && bytes < PARO_PAUSE_MAX_BYTES;
 }
 // Whether sweep 1 stores the reduced gradient to stay in the memory-side cache, where sweep 2 finds it.  Contributions of a
 // list with both types are counted as two-byte ones.
@@ -1234,14 +1238,12 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
                                dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P,
                                group_len, src, a, dst, tm);
         })));
-    else if (paces_single(pl, n)) {
-        SrcTableOf<FEW_SRC> src = few_sources(tab);
-        src.paced = 1;
+    else if (pauses_single(pl, n))
         PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, FEW_SRC, PARO_PACE_SINGLE_SLEEP>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v,
-                               tm.pieces, tm.n_pieces, pl->P, group_len, src, a, dst, tm);
+            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, FEW_SRC, PARO_PAUSE_SLEEP>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v,
+                               tm.pieces, tm.n_pieces, pl->P, group_len, few_sources(tab), a, dst, tm);
         }));
-    } else
+    else
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
             hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
                                tm.n_pieces, pl->P, group_len, src, a, dst, tm);

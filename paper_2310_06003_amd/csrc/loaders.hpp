@@ -326,8 +326,7 @@ struct Folding {
 // with a pause after each, waves that start together read the same contribution together.  Whole clipped
 // steps unpaced -> paced, on the same buffers: P = 64, 90 M elements 2446 -> 2373 us, P = 16, 150 M 1544 -> 1521,
 // P = 4, 150 M as they were; single sweep, P = 64, 16 M 418 -> 409, P = 16, 24 M 224 -> 223, P = 8, 16 M 109 -> 109.  A
-// small launch is bound by latency (P = 16, 2 M 26.5 -> 28.5; P = 32, 2 M, single sweep 29 -> 32) and is not paced, but for
-// the one that paces_single tells.
+// small launch is bound by latency (P = 16, 2 M 26.5 -> 28.5; P = 32, 2 M, single sweep 29 -> 32) and is not paced.
 // How long a pause goes with how many waves is in fold_budget.  The pause is a constant of the kernel and the branch is
 // taken load by load: a pause that the launch chooses (a loop of short ones, two or three tests, copies of the code behind one
 // branch) costs the scalar work of choosing after every load and was 2 to 12 % slower at the same length.

@@ -10,11 +10,12 @@ from test_gpu_cache_policy import _Shifted
 pytestmark = pytest.mark.gpu
 
 
-# A chunk is paced where the launch reads 21 to 30.5 MB and has 2 or 3 ranks: 16, 18, 20 and 24 bytes an element here.
+# Over one chunk, waves pause where the launch reads 21 (one rank: 20) to 30.5 MB with 1 to 3 ranks: 14, 16, 18, 20 and 24 bytes an
+# element here.
 @pytest.mark.parametrize("P,dtype,L", [
     (2, wl.BF16, 1312496), (2, wl.BF16, 1312504), (2, wl.F16, 1906248), (2, wl.BF16, 1906256), (3, wl.BF16, 1166664),
     (3, wl.BF16, 1166672), (2, wl.F32, 1049992), (2, wl.F32, 1050000), (3, wl.F32, 1270832), (3, wl.F32, 1270840),
-    (1, wl.BF16, 1600008), (4, wl.BF16, 1200008)])
+    (1, wl.BF16, 1428568), (1, wl.F16, 1428576), (1, wl.BF16, 2178568), (1, wl.BF16, 2178576), (1, wl.F32, 1600008), (4, wl.BF16, 1200008)])
 def test_one_chunk(paro, P, dtype, L):
     lay = orc.layout(P, 1, [P * L])
     plan = paro.paro_plan(P, 1, "IIG", [P * L], sched=orc.RING, grad_dtype=[dtype])
@@ -33,7 +34,7 @@ def _last_rank(paro, plan, lay, P, dtype, sched, strategy):
 
 @pytest.mark.parametrize("route", ["table", "tensors"])
 def test_one_chunk_with_exempt_tensors(paro, route, monkeypatch):
-    """Where a tensor is exempt a paced step gives what it gives without weight decay, elsewhere what it gives without the mask."""
+    """Where a tensor is exempt a step with pauses gives what it gives without weight decay, elsewhere what it gives without the mask."""
     if route == "tensors":
         monkeypatch.setenv("PARO_TILE_TABLE_MAX_TILES", "0")
     P, L, sizes = 2, 1500000, [700001, 999999, 3, 1299997]
