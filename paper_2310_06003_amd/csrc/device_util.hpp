@@ -152,7 +152,7 @@ namespace {
 #ifndef PARO_PACE_MIN_BLOCKS
 #define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)
 #endif
-// A small single sweep over one chunk whose waves pause (see pauses_single): how long, and the bytes that the launch reads.
+// A small single sweep whose waves pause (see pauses_single, pauses_range): how long, and the bytes that the launch reads.
 #ifndef PARO_PAUSE_SLEEP
 #define PARO_PAUSE_SLEEP 26         // units of 64 clocks (20 and 40: 3 to 7 % slower at 25 to 27 MB with P = 1, and with P = 3 or 2)
 #endif
@@ -167,6 +167,15 @@ namespace {
 #endif
 #ifndef PARO_PAUSE_MAX_BYTES
 #define PARO_PAUSE_MAX_BYTES 30500000
+#endif
+#ifndef PARO_PAUSE_RANGE_MIN_BYTES
+#define PARO_PAUSE_RANGE_MIN_BYTES 19500000   // over a range of several chunks
+#endif
+#ifndef PARO_PAUSE_RANGE_MAX_BYTES
+#define PARO_PAUSE_RANGE_MAX_BYTES 31000000
+#endif
+#ifndef PARO_PAUSE_RANGE_MAX_BYTES_TWO
+#define PARO_PAUSE_RANGE_MAX_BYTES_TWO 27000000   // ... of two ranks
 #endif
 #ifndef PARO_SPLIT_MAX
 #define PARO_SPLIT_MAX 16           // a tile with up to so many tensors inside is cut into pieces

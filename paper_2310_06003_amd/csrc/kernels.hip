@@ -555,7 +555,7 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
 }
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
-template <int DT, int NSRC>
+template <int DT, int NSRC, int PAUSE = 0>
 __global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m,
                                                   float *__restrict__ v, int P, const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
                                                   uint16_t *__restrict__ dst) {
@@ -564,7 +564,8 @@ __global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, flo
     State4 s;
     if (e < n) s = load_state4(p, m, v, e);
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    fold_range<DT>(rm, src, P, e0, n, X);
+    if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);             // see pauses_range
+    fold_range<DT, PAUSE ? 0 : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
     if (e >= n) return;
     const bool decays[4] = {true, true, true, true};
     update4<true>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n));
@@ -1006,6 +1007,16 @@ bool pauses_single(const paro_plan_t *pl, int64_t n) {
     if (pl->P > PARO_PAUSE_MAX_RANKS || (pl->P == 1 && f32)) return false;
     return bytes >= (pl->P == 1 ? PARO_PAUSE_MIN_BYTES_ONE : PARO_PAUSE_MIN_BYTES) && bytes < PARO_PAUSE_MAX_BYTES;
 }
+// ... and over an update range of several chunks: up to 8 ranks with two-byte contributions, 4 with fp32 ones, and 19.5 to 31 MB, with 2
+// ranks 27.  Measured alike: bf16, P = 2, 1.41 M elements 8.2, 8.6 and 7.9 us; P = 3, 1.33 M 8.1, 8.8 and 7.5; P = 4, 1.13 M 7.3, 8.0 and 6.7,
+// 1.3 M 8.2, 9.3 and 7.8; P = 5, 1.27 M 9.0, 10.0 and 8.2; P = 6, 1.25 M 9.2, 9.0 and 8.2; P = 8, 0.8 M 7.3, 7.5 and 7.3; fp32, P = 2, 1.3 M
+// 7.9, 8.1 and 7.4, P = 4, 1 M 8.0, 8.3 and 7.9.  Contributions just written, P = 4, 1.3 M: 14.8, 12.2 and 11.6; after 512 MB of something
+// else 11.4, 12.4 and 10.9.  With fp32 and 8 ranks a pause costs 3 % below 0.55 M, with P = 2 3 % at 28 MB.
+bool pauses_range(const paro_plan_t *pl, int64_t n) {
+    const int64_t esize = pl->dtype[0] == PARO_F32 ? 4 : 2, bytes = n * (12 + pl->P * esize);
+    return pl->P * esize <= 16 && bytes >= PARO_PAUSE_RANGE_MIN_BYTES &&
+           bytes < (pl->P == 2 ? PARO_PAUSE_RANGE_MAX_BYTES_TWO : PARO_PAUSE_RANGE_MAX_BYTES);
+}
 // Whether sweep 1 stores the reduced gradient to stay in the memory-side cache, where sweep 2 finds it.  Contributions of a
 // list with both types are counted as two-byte ones.
 bool keeps_g(const paro_plan_t *pl, int layout) {
@@ -1256,6 +1267,12 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
     const unsigned lds = throttle_lds(sc.lds_per_cu, fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::CHUNK, piece_count(on)));
+    if (pauses_range(pl, on)) {                                 // (one grid holds what pauses)
+        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
+                                                       (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst));
+        PARO_HIP(hipGetLastError());
+        return PARO_OK;
+    }
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, NSRC>), dim3(grid), dim3(WAVE), lds,

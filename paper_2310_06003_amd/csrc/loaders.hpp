@@ -461,9 +461,9 @@ __device__ __forceinline__ RingWalk walk_of(const RangeMap &rm, int c) {
 // coordinates): e0 the block's first element, n the range's length.  Nearly every block lies inside
 // one chunk; where chunks meet inside a block, its lanes take turns, chunk by chunk.  Returns
 // whether the thread's elements count for the sum of squares.
-template <int DT, class Src>
+template <int DT, int PACE = PARO_PACE_SLEEP, class Src>
 __device__ __forceinline__ bool fold_range(const RangeMap &rm, const Src &src, int P, int64_t e0, int64_t n, float X[4]) {
-    Chunk4Loader<DT> ld{e0 + lane_id() * EPT};
+    Chunk4Loader<DT, PACE> ld{e0 + lane_id() * EPT};
     const int64_t end = min(e0 + (int64_t)PIECE, n);
     bool counts = false;
     int c = chunk_at(rm, e0);

@@ -32,6 +32,20 @@ def _last_rank(paro, plan, lay, P, dtype, sched, strategy):
     run_rank(paro, plan, lay, strategy, sched, rank, padded, host, state, hp_dict(P, max_norm=0.0), 5, check_unfused=False)
 
 
+# A range of g chunks: waves pause where the launch reads 19.5 to 31 MB (two ranks: 27), with up to 8 two-byte or 4 fp32 contributions.
+@pytest.mark.parametrize("P,G,sched,dtype,ol", [
+    (2, 1, orc.RING, wl.BF16, 1218736), (2, 1, orc.RING, wl.BF16, 1218752), (2, 1, orc.RING, wl.F16, 1687488),
+    (2, 1, orc.RING, wl.BF16, 1687504), (3, 1, orc.RING, wl.BF16, 1722216), (3, 1, orc.RING, wl.BF16, 1722240),
+    (8, 2, orc.HORING, wl.BF16, 696416), (8, 2, orc.HORING, wl.BF16, 696448), (8, 4, orc.HRING, wl.F16, 1107120), (8, 1, orc.RING, wl.BF16, 1107200),
+    (4, 2, orc.HORING, wl.F32, 696416), (4, 2, orc.HORING, wl.F32, 696432), (5, 1, orc.RING, wl.F32, 700000), (9, 1, orc.RING, wl.BF16, 720000)])
+def test_a_range(paro, P, G, sched, dtype, ol):
+    n = ol * G
+    lay = orc.layout(P, G, [n])
+    plan = paro.paro_plan(P, G, "III", [n], sched=sched, grad_dtype=[dtype])
+    assert orc.state_range(lay, P - 1, "I")[1] == ol
+    _last_rank(paro, plan, lay, P, dtype, sched, "III")
+
+
 @pytest.mark.parametrize("route", ["table", "tensors"])
 def test_one_chunk_with_exempt_tensors(paro, route, monkeypatch):
     """Where a tensor is exempt a step with pauses gives what it gives without weight decay, elsewhere what it gives without the mask."""
