@@ -89,6 +89,9 @@ namespace {
 #ifndef PARO_FUSED_MIN_BLOCKS
 #define PARO_FUSED_MIN_BLOCKS 8192  // blocks of a single sweep from which on fused_waves thins out its waves
 #endif
+#ifndef PARO_FUSED_RANGE_MIN_READS
+#define PARO_FUSED_RANGE_MIN_READS 81920   // ... and blocks times ranks of one over several chunks of two-byte contributions
+#endif
 #ifndef PARO_ADAM_WAVES_PER_CU
 #define PARO_ADAM_WAVES_PER_CU 12
 #endif

@@ -710,10 +710,15 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
 // = 8, 2725 -> 2610).  Two-byte ones keep the budget (P = 4 2596, 15 waves 2591; P = 3 597, 16 waves 626), and so do blocks
 // that share cache lines with their neighbours, which want them close in time, and many small tensors (fp32, ragged, P = 6, 13
 // waves 420 -> 391, but P = 7 463 -> 531; Llama-like, P = 7 1901 -> 2032).
-enum class Sweep { CHUNK, TENSORS_ON_LINES, OTHER_TENSORS };
+// A range of several chunks with two-byte contributions wants that only where its blocks read 81 920 contributions between them, 20 M
+// elements: with fewer, the waves of few ranks that were thinned out were too few (three states in turn, by the budget and thinned out: P = 2,
+// 2.4 M elements 13.7 and 14.7 us, 4 M 22.9 and 23.2; P = 3, 2.8 M 17.5 and 17.9; P = 4, 3 M with contributions just written 21.6 and 22.7;
+// but P = 4, 7 M 41.3 and 40.4, P = 3, 7.8 M 43.1 and 42.6).
+enum class Sweep { CHUNK, RANGE, TENSORS_ON_LINES, OTHER_TENSORS };
 int fused_waves(int P, bool f32, Sweep over, int64_t blocks) {
     const int waves = fold_waves(fold_loads(P) + 3, PARO_FUSED_LOADS_PER_CU);
     if (blocks < PARO_FUSED_MIN_BLOCKS || P >= PARO_BATCH || over == Sweep::OTHER_TENSORS) return waves;
+    if (over == Sweep::RANGE && !f32 && blocks * P < PARO_FUSED_RANGE_MIN_READS) return waves;
     int most;
     if (over == Sweep::TENSORS_ON_LINES) most = !f32 ? waves : P < 7 ? 13 : 10;
     else most = f32 ? std::max(14 - 5 * P / 6, 8) : P < 8 ? 13 : 12;
@@ -1266,7 +1271,7 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
                        const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::CHUNK, piece_count(on)));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::RANGE, piece_count(on)));
     if (pauses_range(pl, on)) {                                 // (one grid holds what pauses)
         PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
                                                        (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst));
