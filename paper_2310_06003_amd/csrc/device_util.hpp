@@ -155,6 +155,37 @@ namespace {
 #ifndef PARO_PACE_MIN_BLOCKS
 #define PARO_PACE_MIN_BLOCKS 65536  // blocks of a launch over one chunk from which on it is paced (32 ranks: half)
 #endif
+// Write windows of sweep 1: which launches have them (see holds_back), and their times in ticks of 10 ns.
+#ifndef PARO_WINDOW_MIN_RANKS
+#define PARO_WINDOW_MIN_RANKS 12
+#endif
+#ifndef PARO_WINDOW_MANY_RANKS
+#define PARO_WINDOW_MANY_RANKS 48
+#endif
+#ifndef PARO_WINDOW_MIN_BLOCKS
+#define PARO_WINDOW_MIN_BLOCKS 98304     // two-byte contributions; 24 to 47 ranks: half
+#endif
+#ifndef PARO_WINDOW_F32_MIN_BLOCKS
+#define PARO_WINDOW_F32_MIN_BLOCKS 16384
+#endif
+#ifndef PARO_WINDOW_TICKS
+#define PARO_WINDOW_TICKS 50             // how long a window is open to waves that arrive
+#endif
+#ifndef PARO_WINDOW_REST_TICKS
+#define PARO_WINDOW_REST_TICKS 60        // how long new waves leave the memory to it
+#endif
+#ifndef PARO_WINDOW_TICKS_PER_RANK
+#define PARO_WINDOW_TICKS_PER_RANK 36    // from one window to the next
+#endif
+#ifndef PARO_WINDOW_MAX_PERIOD
+#define PARO_WINDOW_MAX_PERIOD 1600
+#endif
+#ifndef PARO_WINDOW_PACE_SLEEP
+#define PARO_WINDOW_PACE_SLEEP 5         // pause between two loads of a launch with windows
+#endif
+#ifndef PARO_WINDOW_F32_WAVES_PER_CU
+#define PARO_WINDOW_F32_WAVES_PER_CU 18  // of a launch with windows over fp32 contributions
+#endif
 // A small single sweep whose waves pause (see pauses_single, pauses_range): how long, and the bytes that the launch reads.
 #ifndef PARO_PAUSE_SLEEP
 #define PARO_PAUSE_SLEEP 26         // units of 64 clocks (20 and 40: 3 to 7 % slower at 25 to 27 MB with P = 1, and with P = 3 or 2)
@@ -195,6 +226,8 @@ namespace {
 
 constexpr int WAVE = 64;              // threads of a block: every sweep kernel runs in one-wave blocks
 constexpr int EPT = 4;                // elements per thread
+constexpr int COMPUTE_UNITS = 256;
+constexpr int MAX_WAVES_PER_CU = 32;
 constexpr int PIECE = WAVE * EPT;     // elements per block
 constexpr int TILE = PARO_TILE;       // granularity of the plan's per-block table
 constexpr int FINALIZE_TPB = 1024;    // threads of the kernel that adds the partial sums
@@ -214,11 +247,18 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // segment and is only ever indexed with wave-uniform indices, i.e. read with scalar loads.  Kernels
 // come with room for 16 pointers and for PARO_MAX_RANKS: 2 KB of arguments cost the host 0.2-0.3 us a
 // launch (a small step of one launch: 6.20 -> 5.99 us; of two: 10.2 -> 9.6).
+// Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip
+// shares: one begins at every multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last `last` blocks do not wait.
+struct WriteWindow {
+    unsigned period, inverse, last;
+};
+
 template <int N>
 struct SrcTableOf {
     const void *p[N];
     int paced;       // the chunk layout's loads go out one by one, with a pause in between
     int keep_g;      // the reduced gradient is stored to stay in the memory-side cache
+    WriteWindow window;     // of a launch that holds its results back
 };
 using SrcTable = SrcTableOf<PARO_MAX_RANKS>;
 constexpr int FEW_SRC = 16;
@@ -359,6 +399,24 @@ __device__ __forceinline__ double from_lane(double v) {
     return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false),
                             __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false));
 }
+// Ticks since the last write window began.
+__device__ __forceinline__ unsigned window_phase(const WriteWindow &w) {
+    const unsigned now = (unsigned)__builtin_amdgcn_s_memrealtime();
+    const unsigned phase = now - __umulhi(now, w.inverse) * w.period;       // the quotient may be one too small
+    return phase >= w.period ? phase - w.period : phase;
+}
+// What a wave does before its first load: while a window is open it leaves the memory to the stores.
+__device__ __forceinline__ void leave_window(const WriteWindow &w) {
+    for (int i = 0; i < 32 && window_phase(w) < PARO_WINDOW_REST_TICKS; ++i) __builtin_amdgcn_s_sleep(2);
+}
+// ... and before its stores, with everything in registers (X) that they need.  Both waits are bounded by counts: the clock
+// decides when data go out and never whether.
+__device__ __forceinline__ void wait_for_window(const WriteWindow &w, const float X[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(X[i]));
+    for (int i = 0; i < 256 && window_phase(w) >= PARO_WINDOW_TICKS; ++i) __builtin_amdgcn_s_sleep(3);
+}
+
 // Sum over the wave, in every lane; all 64 take part.  Fixed shape: lanes 32 apart, then 16, 8, 4, 2, 1 - after each step they
 // hold the same sums, so a rotation by 8 or 4 within a row brings the partner's value.  Swaps of half-waves and rows and DPP
 // moves stay in the vector unit; as shuffles the six steps were twelve trips to the LDS unit in a row, some 800 clocks at

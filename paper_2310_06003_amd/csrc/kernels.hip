@@ -257,25 +257,28 @@ __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsign
 
 // Sweep 1, chunk layout: g = fold of the contributions; optional per-block partial of sum g^2.  The chunk is
 // elements [lo, hi) of the update range; blocks are counted from the start of the range (see k_reduce4r), and
-// one that two chunks share is launched for both.
-template <int DT, bool SUMSQ, int NSRC>
+// one that two chunks share is launched for both.  HELD: results wait for the chip's next write window (see holds_back).
+template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P, int group_len, float *__restrict__ g,
                                                   double *__restrict__ partials, const SrcTableOf<NSRC> src) {
     const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
+    const bool inside = e >= lo && e < hi;
+    float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double acc = 0.0;
-    if (e >= lo && e < hi) {
-        const unsigned elems = piece_elems(e0, hi);
+    if (HELD) leave_window(src.window);
+    if (inside) {
         constexpr int WIDE = DT == PARO_F32 ? PARO_PACE_WIDE_F32_SLEEP : PARO_PACE_WIDE_SLEEP;
-        Chunk4Loader<DT, (NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
-        float X[4];
+        Chunk4Loader<DT, (HELD ? PARO_WINDOW_PACE_SLEEP : NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
         fold4(ld, src, P, group_len, X);
-        store_g4(src.keep_g, g, e0, elems, X);
+        if (!HELD) store_g4(src.keep_g, g, e0, piece_elems(e0, hi), X);
         if (SUMSQ) acc = sumsq4(X);
     }
-    if (SUMSQ) {
-        const double s = wave_sum(acc);
-        if (lane_id() == 0) partials[partial_slot()] = s;
+    if (SUMSQ) acc = wave_sum(acc);
+    if (HELD) {
+        if (blockIdx.x + src.window.last < gridDim.x) wait_for_window(src.window, X);
+        if (inside) store_g4(src.keep_g, g, e0, piece_elems(e0, hi), X);
     }
+    if (SUMSQ && lane_id() == 0) partials[partial_slot()] = acc;
 }
 
 // Sweep 1, chunk layout, over blocks [block0, block0 + gridDim) of an update range of several chunks
@@ -998,6 +1001,35 @@ int64_t update_elems(const paro_plan_t *pl) {
 bool paces(const paro_plan_t *pl) {
     return piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
 }
+// Whether sweep 1 over one chunk holds its results back for write windows that the whole chip shares.  A trickle of stores among P
+// streams of loads costs the memory far more than its bytes: the fold of 16 ranks reads at 7.1 TB/s while nothing is stored and at 6.4 with
+// its 11 % of stores, that of 64 at 6.9 and 6.0 with 3 %.  So a wave that has its sums waits (asleep, with four registers of results a
+// lane) until the chip's next window, all stores go out within half a microsecond, and waves that start then leave the memory to them.
+// It takes waves to spare: while about half of them wait the others have to keep the memory busy, so they are not thinned out - as many as
+// fit of two-byte contributions, 18 per compute unit of fp32 ones - and a window comes after 0.55 of the time that all their loads
+// take at 7.1 TB/s: 0.36 us a rank for either type, 16 us at most.  Those that have nobody behind them do not wait.
+// Whole clipped steps on the same buffers, without and with windows: P = 64, 100 M elements 2518 -> 2385 us, 35 M 899 -> 869; P = 128, 30 M 1389 ->
+// 1341; P = 100, 40 M 1516 -> 1455; P = 48, 60 M 1222 -> 1187; P = 32, 100 M 1495 -> 1440, 12 M 192.1 -> 189.6; P = 24, 60 M 780 -> 755; P = 16,
+// 100 M 1028 -> 1008, 25 M 257.9 -> 256.7; P = 12, 100 M 889 -> 876; but P = 16, 17 M 175.9 -> 176.2, 8 M 88.4 -> 88.9; P = 20, 12 M 143 -> 144; P = 64, 15 M 378
+// -> 383; P = 10, 60 M 495 -> 497; P = 8, 100 M 747 -> 759.  fp32: P = 64, 30 M 1341 -> 1309; P = 48, 30 M 1047 -> 1016, 8 M 296 -> 289; P = 32, 40 M
+// 1000 -> 960, 6 M 160 -> 154; P = 24, 10 M 216 -> 210; P = 16, 60 M 895 -> 879, 10 M 166 -> 159; P = 12, 10 M 136 -> 133; but P = 16, 17 M 257 -> 262, 30 M 455 -> 457, 2 M
+// 37.0 -> 37.9; P = 10, 60 M 695 -> 700.  Sweep 2 and the single sweep of 16 ranks, half and a quarter of whose bytes are stores, are 9 and 0 to 3 % slower with windows of
+// any length; a wave that folds 2 to 8 blocks before it waits gains no more than one that folds one.
+bool holds_back(const paro_plan_t *pl) {
+    const int64_t blocks = piece_count(pl->L);
+    if (pl->P < PARO_WINDOW_MIN_RANKS) return false;
+    if (pl->dtype[0] == PARO_F32)
+        return blocks >= PARO_WINDOW_F32_MIN_BLOCKS &&
+               (pl->P >= PARO_WINDOW_MANY_RANKS || blocks < PARO_PACE_MIN_BLOCKS || blocks >= PARO_LARGE_TILES);
+    const bool middle = pl->P >= PARO_BATCH * 3 / 2 && pl->P < PARO_WINDOW_MANY_RANKS;
+    return blocks >= (middle ? PARO_WINDOW_MIN_BLOCKS / 2 : PARO_WINDOW_MIN_BLOCKS);
+}
+int window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_WINDOW_F32_WAVES_PER_CU : 0; }
+WriteWindow window_of(const paro_plan_t *pl) {
+    const unsigned period = std::min((unsigned)(PARO_WINDOW_TICKS_PER_RANK * pl->P), (unsigned)PARO_WINDOW_MAX_PERIOD);
+    const int waves = window_waves(pl);
+    return WriteWindow{period, (unsigned)(((uint64_t)1 << 32) / period), (unsigned)(COMPUTE_UNITS * (waves ? waves : MAX_WAVES_PER_CU))};
+}
 // Whether the waves of a single sweep over one chunk of n elements pause between the loads of their state and those of the
 // contributions.  They start with their arguments in registers, and where the launch reads 21 to 30 MB - all of it runs at once, or
 // nearly - with up to 3 ranks they ask for too much at the same moment.  Three states in turn, without preloaded arguments, with
@@ -1067,7 +1099,8 @@ void plan_consts(const paro_plan_t *pl, AdamConsts *a) {
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
     tab->keep_g = keeps_g(pl, layout);
-    tab->paced = paces(pl);
+    tab->paced = paces(pl) || holds_back(pl);
+    tab->window = window_of(pl);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
     paro::fold_order(pl, chunk, order, &gl);
@@ -1087,6 +1120,7 @@ RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const
     // not with two-byte contributions of 16 ranks and more, where the pauses only delay (paced and not, 90 M elements in
     // all: P = 16, 2 chunks, clipped 969 and 947 us, single sweep 841 and 832; 8 chunks 957 and 930; P = 32, 4 chunks 1533
     // and 1452; P = 64, 8 chunks 2526 and 2493; but P = 8, 8 chunks 687 and 695, fp32 at P = 16 1426 and 1440)
+    tab->window = window_of(pl);
     tab->paced = piece_count(on) >= 2 * PARO_PACE_MIN_BLOCKS && (pl->P < PARO_BATCH || pl->dtype[0] == PARO_F32);
     for (int q = 0; q < pl->P; ++q) tab->p[q] = contrib[q];
     for (int q = pl->P; q < PARO_MAX_RANKS; ++q) tab->p[q] = nullptr;
@@ -1115,6 +1149,7 @@ SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
     std::copy(tab.p, tab.p + FEW_SRC, few.p);
     few.paced = tab.paced;
     few.keep_g = tab.keep_g;
+    few.window = tab.window;
     return few;
 }
 // CALL with `src`, the pointer table in the size that the kernels for NSRC pointers take.
@@ -1180,10 +1215,13 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     double *partials = sc.partials;
     if (layout == PARO_CHUNK) {
         const unsigned grid = (unsigned)((chunk_blocks(pl, lo) + 7) & ~(int64_t)7);       // a multiple of 8: see partial_slot()
-        const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl, paces(pl))));
-        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC>), dim3(grid), dim3(WAVE),
-                                                                                 lds, st, lo, lo + n, pl->P, group_len,
-                                                                                 g_range, partials, src)));
+        const bool held = holds_back(pl);
+        const int waves = held ? window_waves(pl) : fold_waves(fold_loads(pl->P), fold_budget(pl, paces(pl)));
+        const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
+        PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
+            hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC, HELD>), dim3(grid), dim3(WAVE), lds, st, lo, lo + n, pl->P, group_len, g_range,
+                               partials, src);
+        })));
         return (int)grid;
     }
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);

@@ -1,0 +1,57 @@
+"""Sweep 1 whose waves hold their results back for the chip's write windows, at both sides of the sizes where launches begin to:
+the reduced gradient to the last bit, and its sum of squares, against the same adds in torch."""
+import pytest
+import torch
+
+import oracle as orc
+import workloads as wl
+from harness import DEV, hp_dict, hp_struct, stream
+
+pytestmark = pytest.mark.gpu
+TORCH = {wl.BF16: torch.bfloat16, wl.F16: torch.float16, wl.F32: torch.float32}
+
+
+def _fold(paro, plan, contrib, chunk, lo, hi):
+    order, group = paro.paro_fold_order(plan, chunk)
+    total = None
+    for k in range(0, len(order), group):
+        part = contrib[order[k]][lo:hi].to(torch.float32, copy=True)
+        for q in order[k + 1:k + group]:
+            part += contrib[q][lo:hi]
+        total = part if total is None else total + part
+    return total
+
+
+# Two-byte contributions of 12 ranks and more from 98 304 blocks on, 24 to 47 ranks from 49 152; fp32 ones from 16 384 on, with fewer
+# than 48 ranks not from 65 536 to 131 071.  The last sizes end inside a block; in a range of two chunks, each a launch of its
+# own, the second begins inside one.
+@pytest.mark.parametrize("P,G,strategy,dtype,blocks,more", [
+    (12, 4, "IGG", wl.BF16, 98304, 0), (12, 12, "IGG", wl.BF16, 98303, 8), (11, 11, "IGG", wl.BF16, 98304, 8),
+    (16, 8, "IGG", wl.F16, 98303, 0), (24, 8, "IGG", wl.F16, 49151, 248), (24, 6, "IGG", wl.BF16, 49151, 0),
+    (47, 47, "IGG", wl.BF16, 49152, 8), (100, 10, "IGG", wl.BF16, 98304, 8), (12, 4, "IGG", wl.F32, 16383, 8),
+    (13, 13, "IGG", wl.F32, 16383, 0), (48, 8, "IGG", wl.F32, 65536, 8), (20, 4, "IGG", wl.F32, 65535, 0),
+    (20, 4, "IGG", wl.F32, 65536, 0), (12, 6, "III", wl.F32, 131072, 8), (32, 16, "III", wl.BF16, 65536, 8)])
+def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more):
+    L = blocks * 256 + more
+    total = P * L - 5
+    plan = paro.paro_plan(P, G, strategy, [total], grad_dtype=[dtype])
+    lay, rank = orc.layout(P, G, [total]), P - 1
+    ob, ol = orc.state_range(lay, rank, strategy[2])
+    gen = torch.Generator(device=DEV).manual_seed(P * 1000 + blocks)
+    contrib = []
+    for q in range(P):
+        x = torch.randn(ol, generator=gen, device=DEV).mul_(0.01).to(TORCH[dtype])
+        x[max(total - ob, 0):] = 0
+        contrib.append(x)
+    g, ss = torch.full((ol,), -1.0, device=DEV), torch.full((1,), -1.0, dtype=torch.float64, device=DEV)
+    p, m, v = (torch.rand(ol, generator=gen, device=DEV) for _ in range(3))
+    dst = torch.zeros(orc.pack_slot(lay, rank, strategy)[0], dtype=torch.bfloat16, device=DEV)
+    hp = hp_struct(paro, hp_dict(P, max_norm=0.1), 3)
+    want = torch.cat([_fold(paro, plan, contrib, (ob + lo) // L, lo, lo + L) for lo in range(0, ol, L)])
+    norm = sum(float(want[lo:lo + (1 << 24)].double().square().sum()) for lo in range(0, ol, 1 << 24))
+    for _ in range(2):
+        g.fill_(-1.0)
+        paro.paro_step_fused(plan, rank, [x.data_ptr() for x in contrib], paro.PARO_CHUNK, hp, g.data_ptr(), ss.data_ptr(), p.data_ptr(),
+                             m.data_ptr(), v.data_ptr(), dst.data_ptr(), stream())
+        assert torch.equal(g.view(torch.int32), want.view(torch.int32))
+        assert abs(float(ss) - norm) <= 1e-11 * norm
