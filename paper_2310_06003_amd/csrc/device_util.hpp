@@ -37,7 +37,7 @@ namespace {
 //   tensors do not mind (GPT-2, P = 16, 249 MB: 3 to 5 % ahead in all but one)
 //   512 MB of something else: P = 2 to 8 ahead by 1 to 4 %, P = 12 by 1 % to behind by 1, P = 16 behind by 0 to 3; P = 32 and 64 were behind by
 //   2 to 4 % from 2 M on, so more than 16 ranks keep only what is small enough to keep its state as well.
-// 20 to 32 M elements with P = 2 and 4 would still gain 2 to 6 %; they are not kept.
+// Beyond these limits the last PARO_KEEP_G_TAIL_ELEMS are kept, 224 MB, and sweep 2 begins at the end.
 #ifndef PARO_KEEP_G_ELEMS
 #define PARO_KEEP_G_ELEMS (16 << 20)
 #endif
@@ -49,6 +49,18 @@ namespace {
 #endif
 #ifndef PARO_KEEP_G_WIDE_READ_BYTES
 #define PARO_KEEP_G_WIDE_READ_BYTES (192 << 20)   // ... chunk layout, more ranks than that
+#endif
+// Of a larger gradient the end, which sweep 2, begun there, reads before anything else has passed through the cache (streaming loads and
+// plain ones are alike then).  Whole clipped steps, bf16, same buffers, without and with 128 and 224 MB of it:
+//   P = 2, 40 M elements 236 us, -3.1 %, -2.7 %, 60 M 343, -1.4, -3.3, 150 M 853, -0.5, -1.1; P = 4, 17 M 113, -6.2, -6.4, 100 M 632, -1.1, -2.1; P = 6, 70 M
+//   491, -2.0, -4.4; P = 8, 17 M 135, -4.7, -4.7, 60 M 457, -0.9, -1.3, 200 M 1502, -0.4, -0.1; fp16, 124 M 953, -1.5, -2.3; P = 16, 9 M 100.6, -4.5, -5.2, 30 M
+//   300, -3.7, -3.6, 100 M 998, -0.8, -1.6, 420 M 4141, -0.3, -0.5; P = 32, 8 M 135, -1.5, -1.5, 20 M 304, -2.7, -2.8; P = 64, 5 M 143, -1.7, -1.9, 105 M 2583, 0, -0.3;
+//   fp32, P = 4, 30 M 238, -6.7, -5.9, P = 16, 20 M 311, -3.8, -3.9.  256 MB: as 224; more: P = 2, 60 M -4.0, but P = 8, 200 M up to +1.5, P = 16, 200 M up to +1.9
+//   contributions just written, or copied in: -1 to -7 % in all of these; after 512 MB of something else -2 to -12 %
+//   the split calls: P = 8, 20 M -4.6 %, 60 M -1.2, P = 16, 12 M -5.4; fp32, 2 chunks of 62.5 M, P = 16, 1875 us -1.2 to -1.7
+// Kept whole and read from the start, what is below the limits above is as fast (P = 8, 10 M 77.8 and 77.9 us) or up to 1 % faster (4 M and less).
+#ifndef PARO_KEEP_G_TAIL_ELEMS
+#define PARO_KEEP_G_TAIL_ELEMS ((int64_t)56 << 20)
 #endif
 // p, m, v and the packed parameters, which the next step reads: with 1 M elements (18 MB with the gradient)
 // 15.3 -> 14.1 us (P = 8, clipped) and 9.6 -> 8.5 (one sweep), on ten states as on three; 4 M on ten states 37.5 -> 40.0.  With contributions
@@ -247,21 +259,22 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // segment and is only ever indexed with wave-uniform indices, i.e. read with scalar loads.  Kernels
 // come with room for 16 pointers and for PARO_MAX_RANKS: 2 KB of arguments cost the host 0.2-0.3 us a
 // launch (a small step of one launch: 6.20 -> 5.99 us; of two: 10.2 -> 9.6).
-// Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip
-// shares: one begins at every multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last `last` blocks do not wait.
-struct WriteWindow {
-    unsigned period, inverse, last;
-};
-
 template <int N>
 struct SrcTableOf {
     const void *p[N];
-    int paced;       // the chunk layout's loads go out one by one, with a pause in between
-    int keep_g;      // the reduced gradient is stored to stay in the memory-side cache
-    WriteWindow window;     // of a launch that holds its results back
+    int paced;               // the chunk layout's loads go out one by one, with a pause in between
+    unsigned keep_from;      // block of the update range from which on the reduced gradient is stored to stay in the memory-side cache
 };
 using SrcTable = SrcTableOf<PARO_MAX_RANKS>;
 constexpr int FEW_SRC = 16;
+
+// Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip
+// shares: one begins at every multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last blocks, as many as run at
+// once with `waves` per compute unit, do not wait.
+struct WriteWindow {
+    unsigned inverse;
+    unsigned short period, waves;
+};
 
 struct AdamConsts {
     float beta1, beta2, omb1, omb2, eps, step_size, sqrt_bc2, decay, wd, grad_scale, max_norm;
@@ -408,6 +421,10 @@ __device__ __forceinline__ unsigned window_phase(const WriteWindow &w) {
 // What a wave does before its first load: while a window is open it leaves the memory to the stores.
 __device__ __forceinline__ void leave_window(const WriteWindow &w) {
     for (int i = 0; i < 32 && window_phase(w) < PARO_WINDOW_REST_TICKS; ++i) __builtin_amdgcn_s_sleep(2);
+}
+// Whether a block has others behind it that wait for its place.
+__device__ __forceinline__ bool has_followers(const WriteWindow &w) {
+    return blockIdx.x + (unsigned)w.waves * COMPUTE_UNITS < gridDim.x;
 }
 // ... and before its stores, with everything in registers (X) that they need.  Both waits are bounded by counts: the clock
 // decides when data go out and never whether.

@@ -260,23 +260,23 @@ __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsign
 // one that two chunks share is launched for both.  HELD: results wait for the chip's next write window (see holds_back).
 template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P, int group_len, float *__restrict__ g,
-                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src) {
+                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src, const WriteWindow window) {
     const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
     const bool inside = e >= lo && e < hi;
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double acc = 0.0;
-    if (HELD) leave_window(src.window);
+    if (HELD) leave_window(window);
     if (inside) {
         constexpr int WIDE = DT == PARO_F32 ? PARO_PACE_WIDE_F32_SLEEP : PARO_PACE_WIDE_SLEEP;
         Chunk4Loader<DT, (HELD ? PARO_WINDOW_PACE_SLEEP : NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
         fold4(ld, src, P, group_len, X);
-        if (!HELD) store_g4(src.keep_g, g, e0, piece_elems(e0, hi), X);
+        if (!HELD) store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, hi), X);
         if (SUMSQ) acc = sumsq4(X);
     }
     if (SUMSQ) acc = wave_sum(acc);
     if (HELD) {
-        if (blockIdx.x + src.window.last < gridDim.x) wait_for_window(src.window, X);
-        if (inside) store_g4(src.keep_g, g, e0, piece_elems(e0, hi), X);
+        if (has_followers(window)) wait_for_window(window, X);
+        if (inside) store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, hi), X);
     }
     if (SUMSQ && lane_id() == 0) partials[partial_slot()] = acc;
 }
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4r(int64_t block0, int64_t n, in
         float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         const bool counts = fold_range<DT>(rm, src, P, e0, n, X);
         if (e < n) {
-            store_g4(src.keep_g, g, e0, piece_elems(e0, n), X);
+            store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, n), X);
             if (SUMSQ && counts) acc = sumsq4(X);
         }
     }
@@ -466,18 +466,19 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // MASK: how it finds the elements exempt from weight decay.  The global sum of squares comes as n_sums sums
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
-// KEPT: the launch before this one stored the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS).
+// KEPT: the launch before this one stored all of the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS): plain loads.
+// Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
 __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
                                                 float *__restrict__ v, const double *__restrict__ sums, int n_sums, const AdamConsts a,
                                                 uint16_t *__restrict__ dst, double *__restrict__ sumsq_out, const TensorMap tm) {
-    const int64_t e0 = block_first(), e = e0 + lane_id() * EPT;
-    if (e0 >= n) return;
+    const unsigned block = KEPT ? blockIdx.x : (unsigned)((n - 1) / PIECE) - blockIdx.x;
+    const int64_t e0 = (int64_t)block * PIECE, e = e0 + lane_id() * EPT;
     bool decays[4] = {true, true, true, true};
     Piece pc;
     Located loc;
     uint32_t entry = DECAY_ALL;
-    if (MASK == MASK_TABLE) entry = tm.decay_tab[blockIdx.x];
+    if (MASK == MASK_TABLE) entry = tm.decay_tab[block];
     if (MASK == MASK_TENSORS) {
         pc = piece_of(tm, e0, n);
         if (pc.tensor == -1) locate4(tm, pc.seg, tm.begin + e0, lane_id() * EPT, loc);     // the whole wave
@@ -1026,9 +1027,8 @@ bool holds_back(const paro_plan_t *pl) {
 }
 int window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_WINDOW_F32_WAVES_PER_CU : 0; }
 WriteWindow window_of(const paro_plan_t *pl) {
-    const unsigned period = std::min((unsigned)(PARO_WINDOW_TICKS_PER_RANK * pl->P), (unsigned)PARO_WINDOW_MAX_PERIOD);
-    const int waves = window_waves(pl);
-    return WriteWindow{period, (unsigned)(((uint64_t)1 << 32) / period), (unsigned)(COMPUTE_UNITS * (waves ? waves : MAX_WAVES_PER_CU))};
+    const int period = std::min(PARO_WINDOW_TICKS_PER_RANK * pl->P, PARO_WINDOW_MAX_PERIOD), waves = window_waves(pl);
+    return WriteWindow{(unsigned)(((uint64_t)1 << 32) / period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU)};
 }
 // Whether the waves of a single sweep over one chunk of n elements pause between the loads of their state and those of the
 // contributions.  They start with their arguments in registers, and where the launch reads 21 to 30 MB - all of it runs at once, or
@@ -1054,13 +1054,19 @@ bool pauses_range(const paro_plan_t *pl, int64_t n) {
     return pl->P * esize <= 16 && bytes >= PARO_PAUSE_RANGE_MIN_BYTES &&
            bytes < (pl->P == 2 ? PARO_PAUSE_RANGE_MAX_BYTES_TWO : PARO_PAUSE_RANGE_MAX_BYTES);
 }
-// Whether sweep 1 stores the reduced gradient to stay in the memory-side cache, where sweep 2 finds it.  Contributions of a
+// Whether sweep 1 stores all of the reduced gradient to stay in the memory-side cache, where sweep 2 finds it.  Contributions of a
 // list with both types are counted as two-byte ones.
 bool keeps_g(const paro_plan_t *pl, int layout) {
     const int64_t n = update_elems(pl), esize = pl->uniform_dtype && pl->dtype[0] == PARO_F32 ? 4 : 2;
     if (pl->P > PARO_BATCH && n > PARO_KEEP_STATE_ELEMS) return false;
     const int64_t most = layout == PARO_CHUNK && pl->P > PARO_KEEP_G_FEW_RANKS ? PARO_KEEP_G_WIDE_READ_BYTES : PARO_KEEP_G_READ_BYTES;
     return n <= PARO_KEEP_G_ELEMS && n * pl->P * esize <= most;
+}
+// ... and the block from which on it does (of a range of more than 2^32 blocks none does).
+unsigned keeps_g_from(const paro_plan_t *pl, int layout) {
+    if (keeps_g(pl, layout)) return 0;
+    const int64_t block = std::max(update_elems(pl) - PARO_KEEP_G_TAIL_ELEMS, (int64_t)0) / PIECE;
+    return (unsigned)std::min(block, (int64_t)UINT32_MAX);
 }
 
 int adam_consts(const paro_adam_t *hp, AdamConsts *a, const char *fn) {
@@ -1098,9 +1104,8 @@ void plan_consts(const paro_plan_t *pl, AdamConsts *a) {
 // chunk's first element inside the update range.
 void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int layout, int64_t chunk_off_in_range,
                SrcTable *tab, int *group_len) {
-    tab->keep_g = keeps_g(pl, layout);
+    tab->keep_from = keeps_g_from(pl, layout);
     tab->paced = paces(pl) || holds_back(pl);
-    tab->window = window_of(pl);
     int32_t order[PARO_MAX_RANKS];
     int32_t gl = 0;
     paro::fold_order(pl, chunk, order, &gl);
@@ -1116,11 +1121,10 @@ void src_table(const paro_plan_t *pl, int chunk, const void *const *contrib, int
 // ... and of a launch over an update range of several chunks: pointers in rank order, the order of
 // each chunk's fold follows from the range map.
 RangeMap range_map(const paro_plan_t *pl, int64_t ob, int64_t on, int own, const void *const *contrib, SrcTable *tab) {
-    tab->keep_g = keeps_g(pl, PARO_CHUNK);
+    tab->keep_from = keeps_g_from(pl, PARO_CHUNK);
     // not with two-byte contributions of 16 ranks and more, where the pauses only delay (paced and not, 90 M elements in
     // all: P = 16, 2 chunks, clipped 969 and 947 us, single sweep 841 and 832; 8 chunks 957 and 930; P = 32, 4 chunks 1533
     // and 1452; P = 64, 8 chunks 2526 and 2493; but P = 8, 8 chunks 687 and 695, fp32 at P = 16 1426 and 1440)
-    tab->window = window_of(pl);
     tab->paced = piece_count(on) >= 2 * PARO_PACE_MIN_BLOCKS && (pl->P < PARO_BATCH || pl->dtype[0] == PARO_F32);
     for (int q = 0; q < pl->P; ++q) tab->p[q] = contrib[q];
     for (int q = pl->P; q < PARO_MAX_RANKS; ++q) tab->p[q] = nullptr;
@@ -1148,8 +1152,7 @@ SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
     SrcTableOf<FEW_SRC> few;
     std::copy(tab.p, tab.p + FEW_SRC, few.p);
     few.paced = tab.paced;
-    few.keep_g = tab.keep_g;
-    few.window = tab.window;
+    few.keep_from = tab.keep_from;
     return few;
 }
 // CALL with `src`, the pointer table in the size that the kernels for NSRC pointers take.
@@ -1220,7 +1223,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
             hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC, HELD>), dim3(grid), dim3(WAVE), lds, st, lo, lo + n, pl->P, group_len, g_range,
-                               partials, src);
+                               partials, src, window_of(pl));
         })));
         return (int)grid;
     }
@@ -1233,6 +1236,10 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     // In the single sweep it is not (P = 8, 80 M: 834 and 872).
     const bool f32_streams = pl->dev.f32[(size_t)c] && piece_count(n) >= PARO_LARGE_TILES && (pl->P <= PARO_PAIR_MAX_RANKS || pl->P > 8);
     const bool on_lines = pl->dev.on_lines[(size_t)c] || f32_streams;
+    // The end of a large gradient is kept chunk by chunk, and only beside streaming loads of blocks on cache lines: plain ones fill the cache
+    // themselves (whole clipped steps, neither kept nor, and kept: Llama-like lists, P = 8, 28 M elements 371 -> 350 us, P = 4, 57 M 615 -> 600, P = 12, 19 M
+    // 291 -> 276; not on lines, P = 16, 14 M 265 -> 267; ragged tensors, P = 8, 66 M 588 -> 600, P = 16, 33 M 430 -> 436).
+    const bool keep = keeps_g(pl, layout) || (pl->dev.on_lines[(size_t)c] && lo >= (int64_t)tab.keep_from * PIECE);
     // What decides is the list, see PARO_PAIR_MAX_RANKS.
     const bool small = many_small_tensors(pl, c);
     const bool few = pl->P <= PARO_PAIR_MAX_RANKS;
@@ -1241,7 +1248,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const bool pairs = few || (pl->P <= PARO_PAIR_SMALL_MAX_RANKS && small && !pl->dev.f32[(size_t)c]);
     if (pairs && piece_count(n) >= pair_min_blocks) {
         const unsigned grid = (unsigned)(((pieces + 1) / 2 + 7) & ~(int64_t)7);
-        PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
+        PARO_BY_FLAG(keep, KEEP, PARO_BY_FLAG(on_lines, NT, {
             if (few)
                 hipLaunchKernelGGL((k_reduce4t<SUMSQ, 2, PARO_PAIR_MAX_RANKS, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), 0, st, n,
                                    tm.pieces, tm.n_pieces, pl->P, group_len, g, partials, few_sources(tab), tm);
@@ -1257,7 +1264,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const bool f32_large = pl->dev.f32[(size_t)c] && piece_count(n) >= PARO_LARGE_TILES;
     const int budget = f32_large ? PARO_FOLD_F32_LIST_LOADS_PER_CU : small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
     const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), budget));
-    PARO_BY_FLAG(tab.keep_g, KEEP, PARO_BY_FLAG(on_lines, NT, {
+    PARO_BY_FLAG(keep, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
             hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, n, tm.pieces,
                                tm.n_pieces, pl->P, group_len, g, partials, few_sources(tab), tm);
@@ -1512,7 +1519,7 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
-    for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {      // chunk by chunk: each has its own weight-decay table
+    for (int64_t c = (ob + on) / pl->L - 1; c >= ob / pl->L; --c) {      // chunk by chunk: each has its own weight-decay table
         const int64_t lo = c * pl->L - ob;
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_MASK_WAVES_PER_CU), grid = piece_grid(pl->L);
         const TensorMap tm = map_for(pl, sc, c * pl->L, true);
