@@ -68,11 +68,20 @@ namespace {
 #ifndef PARO_KEEP_STATE_ELEMS
 #define PARO_KEEP_STATE_ELEMS (1 << 20)
 #endif
-// A message of an all-gather or the result of a hop, which the next step of the ring reads: 8 buffers, messages of
-// 15 MB (56 of them) 375 -> 341 us, 31 MB 641 -> 607, 62 MB 1256 -> 1312; hop, 8 M elements 13.6 -> 12.9 us, 30 M 45.1
-// -> 45.6; with its addend just written 15.7 -> 14.2, after 512 MB of something else 15.9 -> 16.2.
+// The result of a hop, which the next one reads: 8 M elements 13.6 -> 12.9 us, 30 M 45.1 -> 45.6; with its addend just written 15.7
+// -> 14.2, after 512 MB of something else 15.9 -> 16.2.
 #ifndef PARO_KEEP_MESSAGE_BYTES
 #define PARO_KEEP_MESSAGE_BYTES (48 << 20)
+#endif
+// The messages of one step of an all-gather, over all its ranks: the next step reads them, and of each as much is kept, from its start, as
+// the cache holds of all.  Streamed, messages up to 48 MB whole, and these: 8 ranks, 16 MB 361, 313, 313 us, 31 MB 631, 594, 590, 62 MB 1112, 1112,
+// 1070, 125 MB 2247, 2247, 2215; 16 ranks, 31 MB 2558, 2545, 2520; 4 ranks, 62 MB 236.5, 236.5, 232.9, 120 MB 438, 438, 425; 3 ranks, 60 MB 114.9, 114.9, 109.7; 2
+// ranks, 100 MB 61.1, 61.1, 57.7; but 6 ranks, 40 MB 400, 376.5, 378.
+#ifndef PARO_KEEP_MESSAGES_BYTES
+#define PARO_KEEP_MESSAGES_BYTES (224 << 20)
+#endif
+#ifndef PARO_KEEP_OF_MESSAGE_BYTES
+#define PARO_KEEP_OF_MESSAGE_BYTES (64 << 20)
 #endif
 #ifndef PARO_BATCH
 #define PARO_BATCH 16               // contributions loaded before the first is consumed

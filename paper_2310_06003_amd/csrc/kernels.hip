@@ -616,13 +616,14 @@ __global__ __launch_bounds__(WAVE) void k_hop(const void *a, const void *b, floa
     }
 }
 
-// Plain copy of n 16-byte units (an all-gather message landing in the parameter buffer).
-__global__ __launch_bounds__(WAVE) void k_copy16(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int64_t n, int keep) {
+// Plain copy of n 16-byte units (an all-gather message landing in the parameter buffer); the first `keep` blocks are
+// stored to stay in the memory-side cache.
+__global__ __launch_bounds__(WAVE) void k_copy16(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int64_t n, unsigned keep) {
     const int64_t i0 = (int64_t)blockIdx.x * WAVE;
     if (i0 + threadIdx.x >= n) return;
     const unsigned bytes = (unsigned)min((int64_t)WAVE, n - i0) * 16;
     const u32x4 v = ld_nt(src + i0 + threadIdx.x);
-    buf_store16_as(keep, v, wave_buffer(dst + i0, bytes), lane_id() * 16);
+    buf_store16_as(blockIdx.x < keep, v, wave_buffer(dst + i0, bytes), lane_id() * 16);
 }
 
 }  // namespace
@@ -1743,6 +1744,10 @@ int paro_step_fused_static(const paro_plan_t *pl, int rank, const void *const *c
 
 // ---- ring hops and scheduled transfers ----------------------------------------
 namespace {
+// Bytes from the start of an all-gather's message that are stored to stay in the memory-side cache (see PARO_KEEP_MESSAGES_BYTES).
+int64_t keeps_of_message(const paro_plan_t *pl) {
+    return std::min((int64_t)PARO_KEEP_MESSAGES_BYTES / pl->P, (int64_t)PARO_KEEP_OF_MESSAGE_BYTES);
+}
 int launch_hop(const paro_plan_t *pl, const void *a, int da, const void *b, int db, float *out, int64_t n,
                hipStream_t st) {
     if (n <= 0) return PARO_OK;
@@ -1807,7 +1812,7 @@ int64_t paro_collective_step(paro_plan_t *pl, int rank, int sched, int collectiv
             if (n16 > 0) {
                 hipLaunchKernelGGL(k_copy16, dim3(grid), dim3(WAVE), throttle_lds(pl->dev.lds_per_cu, PARO_COPY_WAVES_PER_CU), st,
                                    reinterpret_cast<const u32x4 *>(from), reinterpret_cast<u32x4 *>(mine), n16,
-                                   (int)(n16 * 16 <= PARO_KEEP_MESSAGE_BYTES));
+                                   (unsigned)(keeps_of_message(pl) / (16 * WAVE)));
                 PARO_HIP(hipGetLastError());
             }
         }

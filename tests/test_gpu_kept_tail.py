@@ -48,3 +48,15 @@ def test_exempt_tensors_and_both_layouts_give_the_same(paro, strategy, sizes):
     assert torch.equal(results[0][0], want[ob:ob + ol])
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("P,G,L", [(2, 1, 32 * M), (2, 1, 32 * M + 8), (8, 4, 14 * M), (8, 4, 14 * M + 8)])
+def test_all_gather_messages_of_which_the_start_is_kept(paro, P, G, L):
+    plan = paro.paro_plan(P, G, "IIG", [P * L])
+    bufs = [torch.randint(-30000, 30000, (P * L,), dtype=torch.int16, device=DEV) for _ in range(P)]
+    want = torch.cat([bufs[paro.paro_owner_of_chunk(plan, c)][c * L:(c + 1) * L] for c in range(P)])
+    steps = sorted({(m.phase, m.ring, m.step) for q in range(P) for m in paro.paro_schedule(plan, q, paro.PARO_AG)})
+    for phase, ring, step in steps:
+        for q in range(P):
+            paro.paro_collective_step(plan, q, paro.PARO_SCHED_DEFAULT, paro.PARO_AG, phase, ring, step, [b.data_ptr() for b in bufs], stream())
+    assert all(torch.equal(b, want) for b in bufs)
