@@ -207,6 +207,31 @@ namespace {
 #ifndef PARO_WINDOW_F32_WAVES_PER_CU
 #define PARO_WINDOW_F32_WAVES_PER_CU 18  // of a launch with windows over fp32 contributions
 #endif
+// ... and of the single sweep (see fused_holds_back).
+#ifndef PARO_FUSED_WINDOW_RANK_BYTES
+#define PARO_FUSED_WINDOW_RANK_BYTES 64          // bytes of contributions for an element from which on it has windows ...
+#endif
+#ifndef PARO_FUSED_WINDOW_MIN_BYTES
+#define PARO_FUSED_WINDOW_MIN_BYTES (512 << 20)  // ... and of all; more than 64 ranks: for each 64
+#endif
+#ifndef PARO_FUSED_WINDOW_MANY_BYTES
+#define PARO_FUSED_WINDOW_MANY_BYTES 80          // with fewer bytes for an element half as many again of all
+#endif
+#ifndef PARO_FUSED_WINDOW_TICKS_PER_BYTE
+#define PARO_FUSED_WINDOW_TICKS_PER_BYTE 26      // from one window to the next, for each of the element's bytes
+#endif
+#ifndef PARO_FUSED_WINDOW_MAX_PERIOD
+#define PARO_FUSED_WINDOW_MAX_PERIOD 2800
+#endif
+#ifndef PARO_FUSED_WINDOW_F32_MAX_PERIOD
+#define PARO_FUSED_WINDOW_F32_MAX_PERIOD 2300
+#endif
+#ifndef PARO_FUSED_WINDOW_PACE_SLEEP
+#define PARO_FUSED_WINDOW_PACE_SLEEP 3
+#endif
+#ifndef PARO_FUSED_WINDOW_F32_WAVES_PER_CU
+#define PARO_FUSED_WINDOW_F32_WAVES_PER_CU 21
+#endif
 // A small single sweep whose waves pause (see pauses_single, pauses_range): how long, and the bytes that the launch reads.
 #ifndef PARO_PAUSE_SLEEP
 #define PARO_PAUSE_SLEEP 26         // units of 64 clocks (20 and 40: 3 to 7 % slower at 25 to 27 MB with P = 1, and with P = 3 or 2)
@@ -279,10 +304,20 @@ constexpr int FEW_SRC = 16;
 
 // Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip
 // shares: one begins at every multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last blocks, as many as run at
-// once with `waves` per compute unit, do not wait.
+// once with `waves` per compute unit, do not wait.  Waves that arrive within `open` of a window's start store at once, and new ones
+// begin to read after `rest`.
 struct WriteWindow {
     unsigned inverse;
-    unsigned short period, waves;
+    unsigned short period, waves, open, rest;
+};
+// ... as an argument of the kernels that come with and without.
+template <bool HELD>
+struct WindowArg : WriteWindow {
+    __host__ __device__ WindowArg(const WriteWindow &w) : WriteWindow(w) {}
+};
+template <>
+struct WindowArg<false> {
+    __host__ __device__ WindowArg(const WriteWindow &) {}
 };
 
 struct AdamConsts {
@@ -429,18 +464,20 @@ __device__ __forceinline__ unsigned window_phase(const WriteWindow &w) {
 }
 // What a wave does before its first load: while a window is open it leaves the memory to the stores.
 __device__ __forceinline__ void leave_window(const WriteWindow &w) {
-    for (int i = 0; i < 32 && window_phase(w) < PARO_WINDOW_REST_TICKS; ++i) __builtin_amdgcn_s_sleep(2);
+    for (int i = 0; i < 128 && window_phase(w) < w.rest; ++i) __builtin_amdgcn_s_sleep(2);
 }
 // Whether a block has others behind it that wait for its place.
 __device__ __forceinline__ bool has_followers(const WriteWindow &w) {
     return blockIdx.x + (unsigned)w.waves * COMPUTE_UNITS < gridDim.x;
 }
-// ... and before its stores, with everything in registers (X) that they need.  Both waits are bounded by counts: the clock
-// decides when data go out and never whether.
-__device__ __forceinline__ void wait_for_window(const WriteWindow &w, const float X[4]) {
+// ... and before its stores, with everything in registers that they need: is_formed() says so, of each four values.  Both waits are
+// bounded by counts: the clock decides when data go out and never whether.
+__device__ __forceinline__ void is_formed(const float X[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(X[i]));
-    for (int i = 0; i < 256 && window_phase(w) >= PARO_WINDOW_TICKS; ++i) __builtin_amdgcn_s_sleep(3);
+}
+__device__ __forceinline__ void wait_for_window(const WriteWindow &w) {
+    for (int i = 0; i < 512 && window_phase(w) >= w.open; ++i) __builtin_amdgcn_s_sleep(3);
 }
 
 // Sum over the wave, in every lane; all 64 take part.  Fixed shape: lanes 32 apart, then 16, 8, 4, 2, 1 - after each step they

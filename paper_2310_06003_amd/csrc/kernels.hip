@@ -167,15 +167,22 @@ __device__ __forceinline__ State4 load_state4(const float *p, const float *m, co
 
 // Adam on the thread's 4 elements; state and (optionally) the low-precision copy written back.
 // PART: only elements [lo, hi) of the 4 are the thread's (the others are some other wave's).
-template <bool PACK, bool PART = false>
+// HELD: the results wait for the chip's next write window (see holds_back).
+template <bool PACK, bool PART, bool HELD>
 __device__ __forceinline__ void update4(const AdamConsts &a, float sc, const bool decays[4], const float gg[4],
                                         const State4 &s, float *p, float *m, float *v, uint16_t *dst, int64_t e0,
-                                        unsigned elems, int lo = 0, int hi = 4) {
+                                        unsigned elems, int lo, int hi, const WindowArg<HELD> &window) {
     float pp[4] = {__uint_as_float(s.p.x), __uint_as_float(s.p.y), __uint_as_float(s.p.z), __uint_as_float(s.p.w)},
           mm[4] = {__uint_as_float(s.m.x), __uint_as_float(s.m.y), __uint_as_float(s.m.z), __uint_as_float(s.m.w)},
           vv[4] = {__uint_as_float(s.v.x), __uint_as_float(s.v.y), __uint_as_float(s.v.z), __uint_as_float(s.v.w)};
 #pragma unroll
     for (int i = 0; i < 4; ++i) adam1(a, sc, decays[i], gg[i], pp[i], mm[i], vv[i]);
+    if constexpr (HELD) {
+        is_formed(pp);
+        is_formed(mm);
+        is_formed(vv);
+        if (has_followers(window)) wait_for_window(window);
+    }
     if (PART && (lo > 0 || hi < 4)) {
         const int64_t e = e0 + lane_id() * EPT;
 #pragma unroll
@@ -260,12 +267,12 @@ __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsign
 // one that two chunks share is launched for both.  HELD: results wait for the chip's next write window (see holds_back).
 template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P, int group_len, float *__restrict__ g,
-                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src, const WriteWindow window) {
+                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src, const WindowArg<HELD> window) {
     const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
     const bool inside = e >= lo && e < hi;
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double acc = 0.0;
-    if (HELD) leave_window(window);
+    if constexpr (HELD) leave_window(window);
     if (inside) {
         constexpr int WIDE = DT == PARO_F32 ? PARO_PACE_WIDE_F32_SLEEP : PARO_PACE_WIDE_SLEEP;
         Chunk4Loader<DT, (HELD ? PARO_WINDOW_PACE_SLEEP : NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
@@ -274,8 +281,9 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P,
         if (SUMSQ) acc = sumsq4(X);
     }
     if (SUMSQ) acc = wave_sum(acc);
-    if (HELD) {
-        if (has_followers(window)) wait_for_window(window, X);
+    if constexpr (HELD) {
+        is_formed(X);
+        if (has_followers(window)) wait_for_window(window);
         if (inside) store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, hi), X);
     }
     if (SUMSQ && lane_id() == 0) partials[partial_slot()] = acc;
@@ -503,21 +511,23 @@ __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restri
     if (e >= n) return;
     if (MASK == MASK_TENSORS) decay_flags(tm, pc, loc, decays);
     const float gg[4] = {__uint_as_float(G.x), __uint_as_float(G.y), __uint_as_float(G.z), __uint_as_float(G.w)};
-    update4<PACK>(a, sc, decays, gg, s, p, m, v, dst, e0, piece_elems(e0, n));
+    update4<PACK, false, false>(a, sc, decays, gg, s, p, m, v, dst, e0, piece_elems(e0, n), 0, EPT, WindowArg<false>(WriteWindow()));
 }
 
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
 // reduced gradient never goes to memory.  TENSORS: contributions are per-tensor gradients; else
 // arrays in shard coordinates of dtype DT.  NT: as for k_reduce4t.
-template <bool TENSORS, int DT, int MASK, bool NT, int NSRC, int PAUSE = 0>
+template <bool TENSORS, int DT, int MASK, bool NT, int NSRC, int PAUSE, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
                                                  const paro_piece_info *pieces, unsigned n_pieces, int P, int group_len,
-                                                 const SrcTableOf<NSRC> src, const AdamConsts a, uint16_t *__restrict__ dst, TensorMap tm) {
+                                                 const SrcTableOf<NSRC> src, const AdamConsts a, uint16_t *__restrict__ dst, TensorMap tm,
+                                                 const WindowArg<HELD> window) {
     tm.pieces = pieces;
     tm.n_pieces = n_pieces;
     Piece pc;
     Located loc;
     int64_t e0 = block_first();
+    if constexpr (HELD) leave_window(window);
     if constexpr (TENSORS) {
         const Cut c = cut_of(tm, blockIdx.x, n);
         if (c.e0 >= n) return;
@@ -528,7 +538,8 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
             if (c.pc.tensor != -2) fold_part(c, src, P, group_len, X);
             const bool d = MASK == MASK_NONE || c.pc.tensor < 0 || tm.no_decay[c.pc.tensor] == 0;
             const bool decays[4] = {d, d, d, d};
-            update4<true, true>(a, a.grad_scale, decays, X, s, p, m, v, dst, c.e0, piece_elems(c.e0, n), c.a, c.b);
+            update4<true, true, false>(a, a.grad_scale, decays, X, s, p, m, v, dst, c.e0, piece_elems(c.e0, n), c.a, c.b,
+                                       WindowArg<false>(WriteWindow()));
             return;
         }
         e0 = c.e0;
@@ -549,30 +560,31 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
         if (pc.tensor != -2) fold_tensors<NT>(pc, loc, src, P, group_len, X);
     } else {
         if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);         // see pauses_single
-        Chunk4Loader<DT, PAUSE ? 0 : PARO_PACE_SLEEP> ld{e};
+        Chunk4Loader<DT, PAUSE ? 0 : HELD ? PARO_FUSED_WINDOW_PACE_SLEEP : PARO_PACE_SLEEP> ld{e};
         fold4(ld, src, P, group_len, X);
     }
     bool decays[4] = {true, true, true, true};
     if (MASK == MASK_TABLE) decay_flags(tm.decay_tab, (uint32_t)uniform((int)entry), decays);
     if (MASK == MASK_TENSORS) decay_flags(tm, pc, loc, decays);
-    update4<true>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, elems);
+    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, elems, 0, EPT, window);
 }
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
-template <int DT, int NSRC, int PAUSE = 0>
+template <int DT, int NSRC, int PAUSE, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m,
                                                   float *__restrict__ v, int P, const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
-                                                  uint16_t *__restrict__ dst) {
+                                                  uint16_t *__restrict__ dst, const WindowArg<HELD> window) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
+    if constexpr (HELD) leave_window(window);
     if (e0 >= n) return;
     State4 s;
     if (e < n) s = load_state4(p, m, v, e);
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (PAUSE > 0) __builtin_amdgcn_s_sleep(PAUSE);             // see pauses_range
-    fold_range<DT, PAUSE ? 0 : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
+    fold_range<DT, PAUSE ? 0 : HELD ? PARO_FUSED_WINDOW_PACE_SLEEP : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
     if (e >= n) return;
     const bool decays[4] = {true, true, true, true};
-    update4<true>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n));
+    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n), 0, EPT, window);
 }
 
 // Low-precision pack alone.
@@ -1027,9 +1039,32 @@ bool holds_back(const paro_plan_t *pl) {
     return blocks >= (middle ? PARO_WINDOW_MIN_BLOCKS / 2 : PARO_WINDOW_MIN_BLOCKS);
 }
 int window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_WINDOW_F32_WAVES_PER_CU : 0; }
+WriteWindow window_for(int period, int waves, int open, int rest) {
+    return WriteWindow{(unsigned)(((uint64_t)1 << 32) / (unsigned)period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU),
+                       (unsigned short)open, (unsigned short)rest};
+}
 WriteWindow window_of(const paro_plan_t *pl) {
-    const int period = std::min(PARO_WINDOW_TICKS_PER_RANK * pl->P, PARO_WINDOW_MAX_PERIOD), waves = window_waves(pl);
-    return WriteWindow{(unsigned)(((uint64_t)1 << 32) / period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU)};
+    return window_for(std::min(PARO_WINDOW_TICKS_PER_RANK * pl->P, PARO_WINDOW_MAX_PERIOD), window_waves(pl), PARO_WINDOW_TICKS, PARO_WINDOW_REST_TICKS);
+}
+// ... and whether the single sweep over n elements does (chunk layout), whose waves store their state as well: a window takes 0.16 of a
+// period that is twice as long.  Whole steps on the same buffers, without and with windows: P = 64, 100 M elements 2632 -> 2314 us, 30 M 774 -> 690, 8 M 217.5
+// -> 203.5; P = 128, 20 M 957 -> 894; P = 256, 6 M 586 -> 539; P = 48, 40 M 811 -> 731; P = 40, 60 M 1037 -> 975, 30 M 518 -> 499; P = 32, 100 M 1458 -> 1451 and on another
+// box 1455 -> 1408, 40 M 572 -> 556, 10 M 149.5 -> 153.2 and 146.3 -> 144.1; a range of 4 x 30 M, P = 32, 1805 -> 1741, 8 x 10 M, P = 64, 2176 -> 1948; but P = 28, 60 M
+// 775 -> 772, P = 24, 100 M 1150 -> 1170, P = 16, 200 M 1796 -> 1870; P = 32, 3 M 46.6 -> 49.0, P = 64, 3 M 79.1 -> 82.8, P = 128, 2 M 94.8 -> 98.2, P = 256, 2 M 184 -> 187.
+// fp32: P = 64, 20 M 992 -> 886; P = 32, 15 M 403 -> 371, 4 M 111.0 -> 107.0; P = 24, 50 M 1028 -> 961; P = 20, 40 M 686 -> 698 and 725 -> 692; P = 16, 80 M 1204 -> 1170, 15 M
+// 228 -> 222, 8 M 122.6 -> 121.8; but P = 14, 60 M 788 -> 799, P = 16, 5 M 80.0 -> 80.6.  Per-tensor gradients of two bytes, whose waves
+// look up their pointers first: P = 32, Llama-like list, 555 -> 618; ragged, 335 -> 366.
+bool fused_holds_back(const paro_plan_t *pl, int64_t n) {
+    const int bytes = pl->P * (pl->dtype[0] == PARO_F32 ? 4 : 2);
+    const int64_t least = (int64_t)PARO_FUSED_WINDOW_MIN_BYTES / 64 * std::max(pl->P, 64);
+    return bytes >= PARO_FUSED_WINDOW_RANK_BYTES && n * bytes >= (bytes < PARO_FUSED_WINDOW_MANY_BYTES ? least * 3 / 2 : least);
+}
+int fused_window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_FUSED_WINDOW_F32_WAVES_PER_CU : 0; }
+WriteWindow fused_window(const paro_plan_t *pl) {
+    const bool f32 = pl->dtype[0] == PARO_F32;
+    const int most = f32 ? PARO_FUSED_WINDOW_F32_MAX_PERIOD : PARO_FUSED_WINDOW_MAX_PERIOD;
+    const int period = std::min(PARO_FUSED_WINDOW_TICKS_PER_BYTE * pl->P * (f32 ? 4 : 2), most), open = period * 4 / 25;
+    return window_for(period, fused_window_waves(pl), open, open);
 }
 // Whether the waves of a single sweep over one chunk of n elements pause between the loads of their state and those of the
 // contributions.  They start with their arguments in registers, and where the launch reads 21 to 30 MB - all of it runs at once, or
@@ -1291,25 +1326,28 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     // 1197, 1271; P = 64, 80 M 2667, 2408; a quarter fp32, P = 16, 80 M 1021, 935).  fp32 gradients, whose loads are twice
     // as wide and half as many, want the budget (P = 16, 80 M: 1314, 1443).
     if (small && large && pl->P > 8 && !pl->dev.f32[(size_t)c]) waves = PARO_FUSED_TL_WAVES_PER_CU;
+    const bool held = layout == PARO_CHUNK && fused_holds_back(pl, n);
+    if (held) waves = fused_window_waves(pl);
+    const WriteWindow window = fused_window(pl);
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const unsigned grid = piece_grid(n), lds = throttle_lds(sc.lds_per_cu, waves);
     const int mask = !pl->any_no_decay ? MASK_NONE : layout == PARO_CHUNK && tm.decay_tab ? MASK_TABLE : MASK_TENSORS;
     if (layout == PARO_TENSORS)
         PARO_BY_TABLE(pl->P, tab, PARO_BY_FLAG(mask != MASK_NONE, MASKED, PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0, {
-            hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC>),
+            hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC, 0, false>),
                                dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P,
-                               group_len, src, a, dst, tm);
+                               group_len, src, a, dst, tm, window);
         })));
     else if (pauses_single(pl, n))
         PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, FEW_SRC, PARO_PAUSE_SLEEP>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v,
-                               tm.pieces, tm.n_pieces, pl->P, group_len, few_sources(tab), a, dst, tm);
+            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, FEW_SRC, PARO_PAUSE_SLEEP, false>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v,
+                               tm.pieces, tm.n_pieces, pl->P, group_len, few_sources(tab), a, dst, tm, window);
         }));
     else
-        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
-                               tm.n_pieces, pl->P, group_len, src, a, dst, tm);
-        })));
+        PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
+            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
+                               tm.n_pieces, pl->P, group_len, src, a, dst, tm, window);
+        }))));
 }
 
 // ... over an update range of several chunks (chunk layout, no decay mask).
@@ -1317,17 +1355,22 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
                        const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::RANGE, piece_count(on)));
+    const bool held = fused_holds_back(pl, on);
+    const int waves = held ? fused_window_waves(pl) : fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::RANGE, piece_count(on));
+    const WriteWindow window = fused_window(pl);
+    const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
     if (pauses_range(pl, on)) {                                 // (one grid holds what pauses)
-        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
-                                                       (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst));
+        PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
+                                                       (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst, window));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
+    if (held) tab.paced = 1;
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
-        PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, NSRC>), dim3(grid), dim3(WAVE), lds,
-                                                                                 st, b0, on, p, m, v, pl->P, rm, src, a, dst)));
+        PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
+            hipLaunchKernelGGL((k_fused4r<DT, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, b0, on, p, m, v, pl->P, rm, src, a, dst, window);
+        })));
         PARO_HIP(hipGetLastError());
     }
     return PARO_OK;
@@ -1567,6 +1610,7 @@ int launch_step(const paro_plan_t *pl, const Scratch &sc, int rank, const void *
         int gl;
         const int64_t lo = c * pl->L - ob;
         src_table(pl, (int)c, contrib, layout, lo, &tab, &gl);
+        tab.paced = paces(pl) || fused_holds_back(pl, pl->L);
         launch_fused(pl, sc, layout, tab, gl, c, a, p + lo, m + lo, v + lo, dst + lo, st);
         PARO_HIP(hipGetLastError());
     }

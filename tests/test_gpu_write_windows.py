@@ -55,3 +55,41 @@ def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more
                              m.data_ptr(), v.data_ptr(), dst.data_ptr(), stream())
         assert torch.equal(g.view(torch.int32), want.view(torch.int32))
         assert abs(float(ss) - norm) <= 1e-11 * norm
+
+
+# The single sweep: 32 two-byte contributions or 16 fp32 ones and more, from 768 MB of them on, 40 and 20 from 512 MB, with more than 64 ranks 8 MB a
+# rank.  It gives what the two calls give whose sweeps it joins.
+@pytest.mark.parametrize("P,G,strategy,dtype,L", [
+    (32, 8, "IGG", wl.BF16, 3 << 22), (32, 8, "IGG", wl.BF16, (3 << 22) - 8), (31, 31, "IGG", wl.BF16, (3 << 22) + 264),
+    (64, 16, "IGG", wl.F16, (1 << 22) + 8), (100, 10, "IGG", wl.BF16, 1 << 22), (100, 10, "IGG", wl.BF16, (1 << 22) - 8),
+    (16, 4, "IGG", wl.F32, (3 << 22) + 200), (16, 4, "IGG", wl.F32, (3 << 22) - 8), (15, 5, "IGG", wl.F32, 3 << 22),
+    (32, 8, "III", wl.BF16, (3 << 20) + 8), (32, 8, "III", wl.BF16, (3 << 20) - 8), (40, 40, "NNN", wl.BF16, 168 << 10),
+    (24, 24, "NNN", wl.F32, (233 << 10) + 8)])
+@pytest.mark.parametrize("exempt", [False, True])
+def test_single_sweep(paro, P, G, strategy, dtype, L, exempt):
+    sizes = [P * L // 2 + 3, 1000, P * L - P * L // 2 - 1008]                # the last 5 elements are padding
+    plan = paro.paro_plan(P, G, strategy, sizes, grad_dtype=[dtype] * 3, no_decay=[0, 1, 1] if exempt else None)
+    lay, rank = orc.layout(P, G, sizes), P - 1
+    assert lay.L == L
+    ob, ol = orc.state_range(lay, rank, strategy[2])
+    gen = torch.Generator(device=DEV).manual_seed(P * 7 + exempt)
+    contrib = [torch.randn(ol, generator=gen, device=DEV).mul_(0.01).to(TORCH[dtype]) for _ in range(P)]
+    start = [torch.rand(ol, generator=gen, device=DEV) for _ in range(3)]
+    ptrs = [x.data_ptr() for x in contrib]
+    hp = hp_struct(paro, hp_dict(P, max_norm=0.0), 3)
+    results = []
+    for joined in (False, True, True):
+        p, m, v = (t.clone() for t in start)
+        g = torch.empty(ol, device=DEV)
+        dst = torch.zeros(orc.pack_slot(lay, rank, strategy)[0], dtype=torch.bfloat16, device=DEV)
+        tail = (p.data_ptr(), m.data_ptr(), v.data_ptr(), dst.data_ptr(), stream())
+        if joined:
+            paro.paro_step_fused(plan, rank, ptrs, paro.PARO_CHUNK, hp, 0, 0, *tail)
+        else:
+            paro.paro_reduce_shard(plan, rank, ptrs, paro.PARO_CHUNK, g.data_ptr(), 0, stream())
+            paro.paro_adam_shard(plan, rank, hp, g.data_ptr(), 0, *tail)
+            want = torch.cat([_fold(paro, plan, contrib, (ob + lo) // L, lo, lo + L) for lo in range(0, ol, L)])
+            assert torch.equal(g.view(torch.int32), want.view(torch.int32))
+        results.append((p, m, v, dst))
+    for other in results[1:]:
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(results[0], other))
