@@ -296,15 +296,20 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P,
 // (MI355X, P = 16 fp32, chunks of 62.5 M elements: 5.1 TB/s there against 6.1).  Partial sums of blocks
 // [part0, part0 + part_n) only (both multiples of 8, block0 too); the others hold no element that counts.
 // The partials are laid out group by group (NORM_GROUP blocks), each like a launch of its own.
-template <int DT, bool SUMSQ, int NSRC>
+template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4r(int64_t block0, int64_t n, int P, unsigned part0, unsigned part_n,
                                                    float *__restrict__ g, double *__restrict__ partials, const RangeMap rm,
-                                                   const SrcTableOf<NSRC> src) {
+                                                   const SrcTableOf<NSRC> src, const WindowArg<HELD> window) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
+    if constexpr (HELD) leave_window(window);
     double acc = 0.0;
     if (e0 < n) {
         float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        const bool counts = fold_range<DT>(rm, src, P, e0, n, X);
+        const bool counts = fold_range<DT, HELD ? PARO_WINDOW_PACE_SLEEP : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
+        if constexpr (HELD) {
+            is_formed(X);
+            if (has_followers(window)) wait_for_window(window);
+        }
         if (e < n) {
             store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, n), X);
             if (SUMSQ && counts) acc = sumsq4(X);
@@ -1038,6 +1043,13 @@ bool holds_back(const paro_plan_t *pl) {
     const bool middle = pl->P >= PARO_BATCH * 3 / 2 && pl->P < PARO_WINDOW_MANY_RANKS;
     return blocks >= (middle ? PARO_WINDOW_MIN_BLOCKS / 2 : PARO_WINDOW_MIN_BLOCKS);
 }
+// ... and over a range of several chunks: fp32 contributions.  Whole clipped steps alike: P = 64, 8 x 4 M elements 1495 -> 1400 us, 2 x 15 M 1369 -> 1324; P = 48, 4 x 5 M
+// 733 -> 687; P = 32, 4 x 12 M 1232 -> 1164; P = 16, 8 x 10 M 1230 -> 1174, 2 x 30 M 894 -> 867; P = 12, 6 x 3 M 235 -> 224, 4 M in all 57.2 -> 57.2; but P = 16, 3 M 54.1 -> 54.5, P = 64,
+// 2.4 M 121.1 -> 124.3.  Waves over two-byte contributions, which find their order of ranks all at the same time after a window: P = 16, 2 x 25 M 498 ->
+// 575, P = 32, 8 x 2 M 252 -> 262, 8 x 12 M 1538 -> 1552, P = 64, 4 x 12 M 1199 -> 1201, 8 x 4 M 876 -> 811.
+bool range_holds_back(const paro_plan_t *pl) {
+    return pl->dtype[0] == PARO_F32 && pl->P >= PARO_WINDOW_MIN_RANKS && piece_count(update_elems(pl)) >= PARO_WINDOW_F32_MIN_BLOCKS;
+}
 int window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_WINDOW_F32_WAVES_PER_CU : 0; }
 WriteWindow window_for(int period, int waves, int open, int rest) {
     return WriteWindow{(unsigned)(((uint64_t)1 << 32) / (unsigned)period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU),
@@ -1449,7 +1461,10 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), fold_budget(pl, false)));
+    const bool held = range_holds_back(pl);
+    tab.paced = tab.paced || held;
+    const WriteWindow window = window_of(pl);
+    const unsigned lds = throttle_lds(sc.lds_per_cu, held ? window_waves(pl) : fold_waves(fold_loads(pl->P), fold_budget(pl, false)));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;
@@ -1463,10 +1478,10 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
             last = std::min((piece_count(lo + pl->L) + 7) & ~(int64_t)7, last);
         }
         if (sumsq_out && first < last) {
-            PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC>), dim3((unsigned)grid),
-                                                                                     dim3(WAVE), lds, st, b0, on, pl->P,
-                                                                                     (unsigned)(first - b0), (unsigned)(last - first),
-                                                                                     grad_out, sc.partials, rm, src)));
+            PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
+                hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC, HELD && DT == PARO_F32>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
+                                   pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out, sc.partials, rm, src, window);
+            })));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
             one_sum = step >= blocks && last - first <= NORM_GROUP;
@@ -1479,9 +1494,10 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
                 if (rc) return rc;
             }
         } else {
-            PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC>), dim3((unsigned)grid),
-                                                                                     dim3(WAVE), lds, st, b0, on, pl->P, 0u, 0u, grad_out,
-                                                                                     sc.partials, rm, src)));
+            PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
+                hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC, HELD && DT == PARO_F32>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
+                                   pl->P, 0u, 0u, grad_out, sc.partials, rm, src, window);
+            })));
             PARO_HIP(hipGetLastError());
         }
     }
@@ -1499,12 +1515,12 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
 //                                       920 and 919, 8 x 17 M 1029 and 1083
 //              32 ranks, 65 536         P = 32, 4 x 45 M 2895 and 2751; 4 x 17 M 1075 and 1067; but 4 x 9 M 571 and 578
 //              64 ranks, 32 768         P = 64, 8 x 9 M 2003 and 1862
-//   fp32, 8 ranks, 131 072              P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277
-//         16 ranks, 65 536              P = 16, 2 x 20 M 630 and 611; but 2 x 5 M 164 and 170; P = 32, 4 x 20 M 2116 and 2058
+//   fp32, 8 to 11 ranks, 131 072        P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277; with 12 and more, where the one launch has write
+//                                       windows, P = 24, 3 x 20 M 1172 and 1202, P = 16, 2 x 60 M 1785 and 1787
 bool chunk_by_chunk(const paro_plan_t *pl) {
     const int P = pl->P;
     int64_t from;
-    if (pl->dtype[0] == PARO_F32) from = P < 8 ? 0 : P < 16 ? PARO_RANGE_MAX_BLOCKS * 2 : PARO_RANGE_MAX_BLOCKS;
+    if (pl->dtype[0] == PARO_F32) from = P < 8 || P >= PARO_WINDOW_MIN_RANKS ? 0 : PARO_RANGE_MAX_BLOCKS * 2;
     else from = P <= PARO_PAIR_MAX_RANKS ? PARO_RANGE_MAX_BLOCKS : P < 12 ? 0 : P < 32 ? PARO_RANGE_MAX_BLOCKS * 2
                 : P < 64 ? PARO_RANGE_MAX_BLOCKS : PARO_RANGE_MAX_BLOCKS / 2;
     if (!from) return false;
