@@ -201,6 +201,19 @@ namespace {
 #ifndef PARO_WINDOW_MAX_PERIOD
 #define PARO_WINDOW_MAX_PERIOD 1600
 #endif
+// ... over a range of several chunks (see range_holds_back).
+#ifndef PARO_RANGE_WINDOW_MIN_BLOCKS
+#define PARO_RANGE_WINDOW_MIN_BLOCKS 16384       // two-byte contributions of up to 16 ranks: four times as many
+#endif
+#ifndef PARO_RANGE_WINDOW_TICKS_PER_RANK
+#define PARO_RANGE_WINDOW_TICKS_PER_RANK 24      // two-byte contributions: from one window to the next
+#endif
+#ifndef PARO_RANGE_WINDOW_MAX_PERIOD
+#define PARO_RANGE_WINDOW_MAX_PERIOD 1300
+#endif
+#ifndef PARO_RANGE_ALWAYS_RANKS
+#define PARO_RANGE_ALWAYS_RANKS 100              // two-byte contributions, from here on one launch whatever the chunks' size
+#endif
 #ifndef PARO_WINDOW_PACE_SLEEP
 #define PARO_WINDOW_PACE_SLEEP 5         // pause between two loads of a launch with windows
 #endif

@@ -1043,20 +1043,29 @@ bool holds_back(const paro_plan_t *pl) {
     const bool middle = pl->P >= PARO_BATCH * 3 / 2 && pl->P < PARO_WINDOW_MANY_RANKS;
     return blocks >= (middle ? PARO_WINDOW_MIN_BLOCKS / 2 : PARO_WINDOW_MIN_BLOCKS);
 }
-// ... and over a range of several chunks: fp32 contributions.  Whole clipped steps alike: P = 64, 8 x 4 M elements 1495 -> 1400 us, 2 x 15 M 1369 -> 1324; P = 48, 4 x 5 M
+// ... and over a range of several chunks.  fp32 contributions, whole clipped steps alike: P = 64, 8 x 4 M elements 1495 -> 1400 us, 2 x 15 M 1369 -> 1324; P = 48, 4 x 5 M
 // 733 -> 687; P = 32, 4 x 12 M 1232 -> 1164; P = 16, 8 x 10 M 1230 -> 1174, 2 x 30 M 894 -> 867; P = 12, 6 x 3 M 235 -> 224, 4 M in all 57.2 -> 57.2; but P = 16, 3 M 54.1 -> 54.5, P = 64,
-// 2.4 M 121.1 -> 124.3.  Waves over two-byte contributions, which find their order of ranks all at the same time after a window: P = 16, 2 x 25 M 498 ->
-// 575, P = 32, 8 x 2 M 252 -> 262, 8 x 12 M 1538 -> 1552, P = 64, 4 x 12 M 1199 -> 1201, 8 x 4 M 876 -> 811.
+// 2.4 M 121.1 -> 124.3.
+// Over two-byte ones the loads are not paced, as without windows, and a window comes after 0.24 us a rank, 13 us at most (P = 24, 3 x 20 M with 0.21, 0.29, 0.38 and 0.46 us
+// 725, 730, 758, 785; paced, with 0.36, 830 where it is 763 without windows; P = 64, 8 x 4 M with 0.08, 0.14, 0.20 us 779, 766, 761): P = 12, 2 x 20 M 356 -> 346; P = 14, 2 x 20 M
+// 389 -> 367; P = 16, 2 x 25 M 495 -> 485, 4 x 6 M 246 -> 239; P = 17, 17 x 0.3 M 63.1 -> 61.4; P = 20, 2 x 2.2 M 58.3 -> 57.7; P = 24, 3 x 20 M 758 -> 713; P = 32, 4 x 12 M 749 -> 681, 2 x
+// 2.2 M 75.0 -> 73.5; P = 48, 4 x 10 M 860 -> 776; P = 64, 8 x 4 M 857 -> 761; P = 128, 16 x 2 M 1569 -> 1415; P = 256, 2 x 3 M 550 -> 524; but P = 16, 2 x 4.3 M 92.1 -> 91.8, P = 12,
+// 2 x 4.3 M 81.9 -> 82.8, 3 x 4 M 110.4 -> 111.9, P = 10, 2 x 20 M 320.7 -> 320 to 323.
 bool range_holds_back(const paro_plan_t *pl) {
-    return pl->dtype[0] == PARO_F32 && pl->P >= PARO_WINDOW_MIN_RANKS && piece_count(update_elems(pl)) >= PARO_WINDOW_F32_MIN_BLOCKS;
+    if (pl->P < PARO_WINDOW_MIN_RANKS) return false;
+    const bool early = pl->dtype[0] == PARO_F32 || pl->P > PARO_BATCH;
+    return piece_count(update_elems(pl)) >= (early ? PARO_RANGE_WINDOW_MIN_BLOCKS : PARO_RANGE_WINDOW_MIN_BLOCKS * 4);
 }
 int window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_WINDOW_F32_WAVES_PER_CU : 0; }
 WriteWindow window_for(int period, int waves, int open, int rest) {
     return WriteWindow{(unsigned)(((uint64_t)1 << 32) / (unsigned)period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU),
                        (unsigned short)open, (unsigned short)rest};
 }
-WriteWindow window_of(const paro_plan_t *pl) {
-    return window_for(std::min(PARO_WINDOW_TICKS_PER_RANK * pl->P, PARO_WINDOW_MAX_PERIOD), window_waves(pl), PARO_WINDOW_TICKS, PARO_WINDOW_REST_TICKS);
+WriteWindow window_of(const paro_plan_t *pl, bool range = false) {
+    const bool soon = range && pl->dtype[0] != PARO_F32;
+    const int per_rank = soon ? PARO_RANGE_WINDOW_TICKS_PER_RANK : PARO_WINDOW_TICKS_PER_RANK;
+    const int most = soon ? PARO_RANGE_WINDOW_MAX_PERIOD : PARO_WINDOW_MAX_PERIOD;
+    return window_for(std::min(per_rank * pl->P, most), window_waves(pl), PARO_WINDOW_TICKS, PARO_WINDOW_REST_TICKS);
 }
 // ... and whether the single sweep over n elements does (chunk layout), whose waves store their state as well: a window takes 0.16 of a
 // period that is twice as long.  Whole steps on the same buffers, without and with windows: P = 64, 100 M elements 2632 -> 2314 us, 30 M 774 -> 690, 8 M 217.5
@@ -1462,8 +1471,8 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
     const bool held = range_holds_back(pl);
-    tab.paced = tab.paced || held;
-    const WriteWindow window = window_of(pl);
+    if (held) tab.paced = pl->dtype[0] == PARO_F32;
+    const WriteWindow window = window_of(pl, true);
     const unsigned lds = throttle_lds(sc.lds_per_cu, held ? window_waves(pl) : fold_waves(fold_loads(pl->P), fold_budget(pl, false)));
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
@@ -1479,7 +1488,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
         }
         if (sumsq_out && first < last) {
             PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
-                hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC, HELD && DT == PARO_F32>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
+                hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC, HELD>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
                                    pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out, sc.partials, rm, src, window);
             })));
             PARO_HIP(hipGetLastError());
@@ -1495,7 +1504,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
             }
         } else {
             PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
-                hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC, HELD && DT == PARO_F32>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
+                hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC, HELD>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
                                    pl->P, 0u, 0u, grad_out, sc.partials, rm, src, window);
             })));
             PARO_HIP(hipGetLastError());
@@ -1511,18 +1520,17 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
 // launch and one per chunk, from how many blocks on:
 //   up to 4 ranks, two bytes, 65 536    P = 2, 2 x 24 M 310 and 294 us, 2 x 120 M 1517 and 1400; P = 4, 2 x 50 M 664 and 643; but 4 x 12 M
 //                                       321 and 331, fp32 2 x 60 M 906 and 918
-//   two bytes, 12 ranks, 131 072        P = 12, 2 x 40 M 731 and 720; P = 16, 2 x 60 M 1251 and 1235; but 4 x 20 M 833 and 841; P = 8, 2 x 60 M
-//                                       920 and 919, 8 x 17 M 1029 and 1083
-//              32 ranks, 65 536         P = 32, 4 x 45 M 2895 and 2751; 4 x 17 M 1075 and 1067; but 4 x 9 M 571 and 578
-//              64 ranks, 32 768         P = 64, 8 x 9 M 2003 and 1862
+//   two bytes, 12 to 99 ranks, 131 072  where the one launch has write windows, P = 16, 2 x 40 M 793 and 788; P = 48, 2 x 40 M 1528 and 1514; P = 24, 2 x 50 M 1252 and 1199;
+//                                       but P = 32, 2 x 18 M 511 and 521, P = 64, 4 x 14 M 1362 and 1380, 8 x 9 M 1717 and 1785; P = 12, 2 x 40 M 700 and 705; P = 32,
+//                                       2 x 32 M 913 and 922; P = 100, 2 x 20 M 1415 and 1452; P = 128, 2 x 20 M 1760 and 1800; P = 8 (no windows),
+//                                       2 x 60 M 920 and 919, 8 x 17 M 1029 and 1083
 //   fp32, 8 to 11 ranks, 131 072        P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277; with 12 and more, where the one launch has write
 //                                       windows, P = 24, 3 x 20 M 1172 and 1202, P = 16, 2 x 60 M 1785 and 1787
 bool chunk_by_chunk(const paro_plan_t *pl) {
     const int P = pl->P;
     int64_t from;
     if (pl->dtype[0] == PARO_F32) from = P < 8 || P >= PARO_WINDOW_MIN_RANKS ? 0 : PARO_RANGE_MAX_BLOCKS * 2;
-    else from = P <= PARO_PAIR_MAX_RANKS ? PARO_RANGE_MAX_BLOCKS : P < 12 ? 0 : P < 32 ? PARO_RANGE_MAX_BLOCKS * 2
-                : P < 64 ? PARO_RANGE_MAX_BLOCKS : PARO_RANGE_MAX_BLOCKS / 2;
+    else from = P <= PARO_PAIR_MAX_RANKS ? PARO_RANGE_MAX_BLOCKS : P < 12 || P >= PARO_RANGE_ALWAYS_RANKS ? 0 : PARO_RANGE_MAX_BLOCKS * 2;
     if (!from) return false;
     const int64_t blocks = (chunk_blocks(pl, PIECE - 1) + 7) & ~(int64_t)7;       // at most
     // (no more than a group of the norm, so that the scratch array does not matter)

@@ -24,14 +24,17 @@ def _fold(paro, plan, contrib, chunk, lo, hi):
 
 # Two-byte contributions of 12 ranks and more from 98 304 blocks on, 24 to 47 ranks from 49 152; fp32 ones from 16 384 on, with fewer
 # than 48 ranks not from 65 536 to 131 071.  The last sizes end inside a block; in a range of two chunks of two-byte contributions, each a
-# launch of its own, the second begins inside one.  A range of fp32 ones is one launch, with windows from 16 384 blocks in all on.
+# launch of its own, the second begins inside one.  A range that is one launch has windows from 16 384 blocks in all on, over two-byte
+# contributions of up to 16 ranks from 65 536 on.
 @pytest.mark.parametrize("P,G,strategy,dtype,blocks,more", [
     (12, 4, "IGG", wl.BF16, 98304, 0), (12, 12, "IGG", wl.BF16, 98303, 8), (11, 11, "IGG", wl.BF16, 98304, 8),
     (16, 8, "IGG", wl.F16, 98303, 0), (24, 8, "IGG", wl.F16, 49151, 248), (24, 6, "IGG", wl.BF16, 49151, 0),
     (47, 47, "IGG", wl.BF16, 49152, 8), (100, 10, "IGG", wl.BF16, 98304, 8), (12, 4, "IGG", wl.F32, 16383, 8),
     (13, 13, "IGG", wl.F32, 16383, 0), (48, 8, "IGG", wl.F32, 65536, 8), (20, 4, "IGG", wl.F32, 65535, 0),
     (20, 4, "IGG", wl.F32, 65536, 0), (12, 6, "III", wl.F32, 131072, 8), (32, 16, "III", wl.BF16, 65536, 8),
-    (12, 6, "III", wl.F32, 8191, 128), (12, 6, "III", wl.F32, 8191, 120), (16, 4, "III", wl.F32, 4096, 8), (20, 20, "NNN", wl.F32, 820, 24)])
+    (12, 6, "III", wl.F32, 8191, 128), (12, 6, "III", wl.F32, 8191, 120), (16, 4, "III", wl.F32, 4096, 8), (20, 20, "NNN", wl.F32, 820, 24),
+    (12, 6, "III", wl.BF16, 32768, 8), (16, 4, "III", wl.F16, 16383, 248), (17, 17, "NNN", wl.BF16, 964, 8), (17, 17, "NNN", wl.F16, 963, 24),
+    (64, 8, "III", wl.BF16, 2050, 8), (32, 16, "III", wl.BF16, 131072, 8), (100, 50, "III", wl.BF16, 131072, 8)])
 def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more):
     L = blocks * 256 + more
     total = P * L - 5
