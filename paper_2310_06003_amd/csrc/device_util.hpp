@@ -239,6 +239,16 @@ namespace {
 #ifndef PARO_FUSED_WINDOW_F32_MAX_PERIOD
 #define PARO_FUSED_WINDOW_F32_MAX_PERIOD 2300
 #endif
+// ... over a range of several chunks of two-byte contributions (see fused_range_holds_back).
+#ifndef PARO_FUSED_RANGE_WINDOW_MIN_RANKS
+#define PARO_FUSED_RANGE_WINDOW_MIN_RANKS 28
+#endif
+#ifndef PARO_FUSED_RANGE_UNPACED_RANKS
+#define PARO_FUSED_RANGE_UNPACED_RANKS 96
+#endif
+#ifndef PARO_FUSED_RANGE_WINDOW_MAX_PERIOD
+#define PARO_FUSED_RANGE_WINDOW_MAX_PERIOD 1800
+#endif
 #ifndef PARO_FUSED_WINDOW_PACE_SLEEP
 #define PARO_FUSED_WINDOW_PACE_SLEEP 3
 #endif

@@ -1080,11 +1080,25 @@ bool fused_holds_back(const paro_plan_t *pl, int64_t n) {
     const int64_t least = (int64_t)PARO_FUSED_WINDOW_MIN_BYTES / 64 * std::max(pl->P, 64);
     return bytes >= PARO_FUSED_WINDOW_RANK_BYTES && n * bytes >= (bytes < PARO_FUSED_WINDOW_MANY_BYTES ? least * 3 / 2 : least);
 }
+// ... over a range of several chunks: two-byte contributions of 28 ranks and more, from 16 384 blocks on or, where a short last batch is a large part of a
+// wave's life, from 768 MB.  Up to 96 ranks their loads are not paced, and a window comes after 18 us at most (more beyond 90 ranks).  Whole steps,
+// without windows and with: P = 28, 2 x 20 M elements 536 -> 513 us; P = 32, 2 x 2 M 62.3 -> 61.2, 2 x 5 M 148 -> 145; P = 48, 2 x 2 M 87.1 -> 84.6; P = 64, 2 x 2 M 108.1 -> 105.7; P = 128, 2 x 2 M 204.5
+// -> 194.6; but P = 36, 3 x 3 M 146.7 -> 148.2, P = 28, 2 x 3 M 83.2 -> 81.7 and 83.5 -> 84.0, 4 x 5 M 258.2 -> 258.9, P = 30, 2 x 5 M 139.6 -> 140.4; P = 24, 2 x 4 M 98.8 -> 98.0, 2 x 2 M 50.0 -> 50.0;
+// P = 16, 2 x 6 M 110 -> 118; P = 32, 2 x 1.5 M 45.2 -> 45.7, P = 64 80.6 -> 81.4.  Paced and with a window as above, and so: P = 32, 8 x 3 M 351 -> 342; P = 40, 4 x 10 M 706 -> 686;
+// P = 48 803 -> 781; P = 64, 4 x 12 M 1155 -> 1148, 8 x 4 M 762 -> 747 and on another box 796 -> 803; P = 96, 4 x 5 M 713 -> 707; but P = 128, 4 x 5 M 867 -> 875.
+bool fused_range_holds_back(const paro_plan_t *pl, int64_t n) {
+    if (pl->dtype[0] == PARO_F32) return fused_holds_back(pl, n);
+    if (pl->P < PARO_FUSED_RANGE_WINDOW_MIN_RANKS) return false;
+    if (pl->P % PARO_BATCH == 0 || pl->P > 3 * PARO_BATCH) return piece_count(n) >= PARO_RANGE_WINDOW_MIN_BLOCKS;
+    return n * pl->P * 2 >= (int64_t)PARO_FUSED_WINDOW_MIN_BYTES * 3 / 2;
+}
+bool fused_range_paces(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 || pl->P > PARO_FUSED_RANGE_UNPACED_RANKS; }
 int fused_window_waves(const paro_plan_t *pl) { return pl->dtype[0] == PARO_F32 ? PARO_FUSED_WINDOW_F32_WAVES_PER_CU : 0; }
-WriteWindow fused_window(const paro_plan_t *pl) {
+WriteWindow fused_window(const paro_plan_t *pl, bool paced = true) {
     const bool f32 = pl->dtype[0] == PARO_F32;
-    const int most = f32 ? PARO_FUSED_WINDOW_F32_MAX_PERIOD : PARO_FUSED_WINDOW_MAX_PERIOD;
-    const int period = std::min(PARO_FUSED_WINDOW_TICKS_PER_BYTE * pl->P * (f32 ? 4 : 2), most), open = period * 4 / 25;
+    const int bytes = pl->P * (f32 ? 4 : 2);
+    const int most = f32 ? PARO_FUSED_WINDOW_F32_MAX_PERIOD : paced ? PARO_FUSED_WINDOW_MAX_PERIOD : std::max(PARO_FUSED_RANGE_WINDOW_MAX_PERIOD, 10 * bytes);
+    const int period = std::min(PARO_FUSED_WINDOW_TICKS_PER_BYTE * bytes, most), open = period * 4 / 25;
     return window_for(period, fused_window_waves(pl), open, open);
 }
 // Whether the waves of a single sweep over one chunk of n elements pause between the loads of their state and those of the
@@ -1376,9 +1390,9 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
                        const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
-    const bool held = fused_holds_back(pl, on);
+    const bool held = fused_range_holds_back(pl, on), held_paced = fused_range_paces(pl);
     const int waves = held ? fused_window_waves(pl) : fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::RANGE, piece_count(on));
-    const WriteWindow window = fused_window(pl);
+    const WriteWindow window = fused_window(pl, held_paced);
     const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
     if (pauses_range(pl, on)) {                                 // (one grid holds what pauses)
         PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
@@ -1386,7 +1400,7 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
-    if (held) tab.paced = 1;
+    if (held) tab.paced = held_paced;
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {

@@ -62,13 +62,16 @@ def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more
 
 
 # The single sweep: 32 two-byte contributions or 16 fp32 ones and more, from 768 MB of them on, 40 and 20 from 512 MB, with more than 64 ranks 8 MB a
-# rank.  It gives what the two calls give whose sweeps it joins.
+# rank.  Over a range of several chunks 32 two-byte ones, and more than 48, from 16 384 blocks on, others of 28 and more from 768 MB; up to 96 without
+# pauses.  It gives what the two calls give whose sweeps it joins.
 @pytest.mark.parametrize("P,G,strategy,dtype,L", [
     (32, 8, "IGG", wl.BF16, 3 << 22), (32, 8, "IGG", wl.BF16, (3 << 22) - 8), (31, 31, "IGG", wl.BF16, (3 << 22) + 264),
     (64, 16, "IGG", wl.F16, (1 << 22) + 8), (100, 10, "IGG", wl.BF16, 1 << 22), (100, 10, "IGG", wl.BF16, (1 << 22) - 8),
     (16, 4, "IGG", wl.F32, (3 << 22) + 200), (16, 4, "IGG", wl.F32, (3 << 22) - 8), (15, 5, "IGG", wl.F32, 3 << 22),
     (32, 8, "III", wl.BF16, (3 << 20) + 8), (32, 8, "III", wl.BF16, (3 << 20) - 8), (40, 40, "NNN", wl.BF16, 168 << 10),
-    (24, 24, "NNN", wl.F32, (233 << 10) + 8)])
+    (24, 24, "NNN", wl.F32, (233 << 10) + 8), (32, 16, "III", wl.BF16, 2 << 20), (32, 16, "III", wl.F16, (2 << 20) - 264),
+    (28, 14, "III", wl.BF16, 7190240), (28, 14, "III", wl.F16, 7190232), (27, 9, "III", wl.BF16, 5 << 20),
+    (96, 48, "III", wl.BF16, (2 << 20) + 8), (98, 49, "III", wl.F16, (2 << 20) + 264)])
 @pytest.mark.parametrize("exempt", [False, True])
 def test_single_sweep(paro, P, G, strategy, dtype, L, exempt):
     sizes = [P * L // 2 + 3, 1000, P * L - P * L // 2 - 1008]                # the last 5 elements are padding
