@@ -718,6 +718,18 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
     return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
 }
 
+// Whether a single sweep is so small that a budget would only keep waves from starting, of which the chip holds all at once: with 10 or 11 per
+// compute unit it takes two or three rounds.  Whole steps, by the budget and with all waves: over a range of two-byte contributions (up to 8192
+// blocks), whose waves walk to their pointers first, P = 14, 2 x 0.9 M elements 17.4 -> 17.0 us; P = 16, 2 x 0.3 M 8.1 -> 7.0, 2 x 0.5 M 11.3 -> 10.4, 2 x 1 M 20.2 -> 19.2;
+// P = 24, 2 x 0.5 M 15.1 -> 13.0, 2 x 1 M 26.5 -> 24.4; P = 32, 2 x 1 M 31.2 -> 29.3; P = 64, 2 x 0.5 M 29.8 -> 25.1, 2 x 1 M 53.6 -> 52.7; P = 128, 2 x 0.4 M 45.3 -> 42.7, 2 x 1 M 98.5 -> 99.4; but beyond that P = 16, 2 x
+// 2 M 38.8 -> 41.9, P = 32, 2 x 1.5 M 45.2 -> 47.2; P = 8, 2 x 0.8 M 11.2 -> 12.5, P = 12, 2 x 0.9 M 15.8 -> 16.1.  Otherwise (up to 4096 blocks and 64 ranks): one chunk, P = 12, 1 M 8.5 -> 8.2; P = 16, 0.7 M 7.3 -> 7.1; P = 32, 0.8 M
+// 12.6 -> 12.4; P = 64, 0.7 M 19.8 -> 17.8; fp32, P = 16, 0.7 M 10.3 -> 10.0, P = 64, 1 M 46.6 -> 45.4, a range, P = 16, 2 x 0.5 M 15.0 -> 14.6, P = 32 24.9 -> 24.4; but P = 128, 1 M 43.6 -> 45.0;
+// P = 32, 2 M 28.9 -> 29.4.
+bool runs_at_once(int P, bool two_byte_range, int64_t blocks) {
+    if (two_byte_range) return P > 12 && blocks <= COMPUTE_UNITS * MAX_WAVES_PER_CU;
+    return P >= 12 && P <= 64 && blocks <= COMPUTE_UNITS * MAX_WAVES_PER_CU / 2;
+}
+
 // Waves per compute unit of a single sweep over `blocks` blocks.  The budget, which was found at P = 16, lets too many waves
 // with few loads each run beside one another: a wave also loads and stores its state, and what counts is the bytes that a
 // compute unit has in flight: 50 KB (P = 2) to 100 (P = 12) with two-byte contributions, 60 to 150 with fp32 ones.  So no
@@ -738,6 +750,7 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
 // but P = 4, 7 M 41.3 and 40.4, P = 3, 7.8 M 43.1 and 42.6).
 enum class Sweep { CHUNK, RANGE, TENSORS_ON_LINES, OTHER_TENSORS };
 int fused_waves(int P, bool f32, Sweep over, int64_t blocks) {
+    if ((over == Sweep::CHUNK || over == Sweep::RANGE) && runs_at_once(P, over == Sweep::RANGE && !f32, blocks)) return 0;
     const int waves = fold_waves(fold_loads(P) + 3, PARO_FUSED_LOADS_PER_CU);
     if (blocks < PARO_FUSED_MIN_BLOCKS || P >= PARO_BATCH || over == Sweep::OTHER_TENSORS) return waves;
     if (over == Sweep::RANGE && !f32 && blocks * P < PARO_FUSED_RANGE_MIN_READS) return waves;
@@ -1484,10 +1497,14 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     int rc;
     SrcTable tab;
     const RangeMap rm = range_map(pl, ob, on, own, contrib, &tab);
-    const bool held = range_holds_back(pl);
+    // A small range of two-byte contributions is launched with all waves that fit.  Whole clipped steps, by the budget and so: P = 16, 2 x 0.5 M elements 15.8 -> 14.3
+    // us, 2 x 1 M 26.9 -> 25.5, 2 x 1.5 M 37.1 -> 36.6; P = 24, 2 x 0.5 M 18.8 -> 17.0; P = 32, 2 x 0.5 M 22.0 -> 19.7, 2 x 1 M 38.1 -> 37.0; P = 64, 2 x 0.5 M 33.7 -> 30.6, 2 x 1.9 M 107.4 -> 107.0; P = 12, 2 x
+    // 1 M 23.8 -> 22.9; P = 10 22.2 -> 21.7; P = 8 21.1 -> 21.0, P = 4 19.3 -> 19.2; fp32, P = 16, 2 x 1 M 36.0 -> 36.2; but P = 12, 2 x 2.2 M 44.7 -> 45.0, 2 x 6 M 107.8 -> 109.2.
+    const bool held = range_holds_back(pl), all = pl->dtype[0] != PARO_F32 && pl->P > 8 && piece_count(on) < PARO_RANGE_WINDOW_MIN_BLOCKS;
+    const int waves = held ? window_waves(pl) : all ? 0 : fold_waves(fold_loads(pl->P), fold_budget(pl, false));
     if (held) tab.paced = pl->dtype[0] == PARO_F32;
     const WriteWindow window = window_of(pl, true);
-    const unsigned lds = throttle_lds(sc.lds_per_cu, held ? window_waves(pl) : fold_waves(fold_loads(pl->P), fold_budget(pl, false)));
+    const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
     int n_sums = 0;

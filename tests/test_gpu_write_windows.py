@@ -25,7 +25,7 @@ def _fold(paro, plan, contrib, chunk, lo, hi):
 # Two-byte contributions of 12 ranks and more from 98 304 blocks on, 24 to 47 ranks from 49 152; fp32 ones from 16 384 on, with fewer
 # than 48 ranks not from 65 536 to 131 071.  The last sizes end inside a block; in a range of two chunks of two-byte contributions, each a
 # launch of its own, the second begins inside one.  A range that is one launch has windows from 16 384 blocks in all on, over two-byte
-# contributions of up to 16 ranks from 65 536 on.
+# contributions of up to 16 ranks from 65 536 on; below 16 384 it has all waves that fit, with more than 8 ranks.
 @pytest.mark.parametrize("P,G,strategy,dtype,blocks,more", [
     (12, 4, "IGG", wl.BF16, 98304, 0), (12, 12, "IGG", wl.BF16, 98303, 8), (11, 11, "IGG", wl.BF16, 98304, 8),
     (16, 8, "IGG", wl.F16, 98303, 0), (24, 8, "IGG", wl.F16, 49151, 248), (24, 6, "IGG", wl.BF16, 49151, 0),
@@ -34,7 +34,8 @@ def _fold(paro, plan, contrib, chunk, lo, hi):
     (20, 4, "IGG", wl.F32, 65536, 0), (12, 6, "III", wl.F32, 131072, 8), (32, 16, "III", wl.BF16, 65536, 8),
     (12, 6, "III", wl.F32, 8191, 128), (12, 6, "III", wl.F32, 8191, 120), (16, 4, "III", wl.F32, 4096, 8), (20, 20, "NNN", wl.F32, 820, 24),
     (12, 6, "III", wl.BF16, 32768, 8), (16, 4, "III", wl.F16, 16383, 248), (17, 17, "NNN", wl.BF16, 964, 8), (17, 17, "NNN", wl.F16, 963, 24),
-    (64, 8, "III", wl.BF16, 2050, 8), (32, 16, "III", wl.BF16, 131072, 8), (100, 50, "III", wl.BF16, 131072, 8)])
+    (64, 8, "III", wl.BF16, 2050, 8), (32, 16, "III", wl.BF16, 131072, 8), (100, 50, "III", wl.BF16, 131072, 8),
+    (9, 3, "III", wl.BF16, 5461, 80), (10, 5, "III", wl.F16, 8192, 0), (64, 32, "III", wl.BF16, 2000, 40)])
 def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more):
     L = blocks * 256 + more
     total = P * L - 5
@@ -63,7 +64,7 @@ def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more
 
 # The single sweep: 32 two-byte contributions or 16 fp32 ones and more, from 768 MB of them on, 40 and 20 from 512 MB, with more than 64 ranks 8 MB a
 # rank.  Over a range of several chunks 32 two-byte ones, and more than 48, from 16 384 blocks on, others of 28 and more from 768 MB; up to 96 without
-# pauses.  It gives what the two calls give whose sweeps it joins.
+# pauses.  Small ones have all waves that fit, up to 8192 blocks of a range of more than 12 two-byte ones, and 4096 otherwise.  It gives what the two calls give whose sweeps it joins.
 @pytest.mark.parametrize("P,G,strategy,dtype,L", [
     (32, 8, "IGG", wl.BF16, 3 << 22), (32, 8, "IGG", wl.BF16, (3 << 22) - 8), (31, 31, "IGG", wl.BF16, (3 << 22) + 264),
     (64, 16, "IGG", wl.F16, (1 << 22) + 8), (100, 10, "IGG", wl.BF16, 1 << 22), (100, 10, "IGG", wl.BF16, (1 << 22) - 8),
@@ -71,7 +72,9 @@ def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more
     (32, 8, "III", wl.BF16, (3 << 20) + 8), (32, 8, "III", wl.BF16, (3 << 20) - 8), (40, 40, "NNN", wl.BF16, 168 << 10),
     (24, 24, "NNN", wl.F32, (233 << 10) + 8), (32, 16, "III", wl.BF16, 2 << 20), (32, 16, "III", wl.F16, (2 << 20) - 264),
     (28, 14, "III", wl.BF16, 7190240), (28, 14, "III", wl.F16, 7190232), (27, 9, "III", wl.BF16, 5 << 20),
-    (96, 48, "III", wl.BF16, (2 << 20) + 8), (98, 49, "III", wl.F16, (2 << 20) + 264)])
+    (96, 48, "III", wl.BF16, (2 << 20) + 8), (98, 49, "III", wl.F16, (2 << 20) + 264),
+    (16, 8, "III", wl.BF16, 1 << 20), (16, 8, "III", wl.F16, (1 << 20) + 8), (13, 13, "NNN", wl.BF16, 40 << 10), (64, 32, "IGG", wl.F32, 1 << 20),
+    (12, 4, "IGG", wl.BF16, (1 << 20) + 8), (64, 32, "III", wl.F32, 1 << 19)])
 @pytest.mark.parametrize("exempt", [False, True])
 def test_single_sweep(paro, P, G, strategy, dtype, L, exempt):
     sizes = [P * L // 2 + 3, 1000, P * L - P * L // 2 - 1008]                # the last 5 elements are padding
