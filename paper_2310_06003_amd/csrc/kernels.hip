@@ -1347,7 +1347,10 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     // P = 8, 59 M elements 672 and 634 us, P = 16 652 and 620, P = 32 544 and 526; a Llama-like list, P = 8 2977 and 2942, P = 32 2970 and 2847)
     const bool f32_large = pl->dev.f32[(size_t)c] && piece_count(n) >= PARO_LARGE_TILES;
     const int budget = f32_large ? PARO_FOLD_F32_LIST_LOADS_PER_CU : small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
-    const unsigned lds = throttle_lds(sc.lds_per_cu, fold_waves(fold_loads(pl->P), budget));
+    // Waves that look up 48 pointers and more want company: all that fit (whole clipped steps, by the budget and so: Llama-like lists, P = 64, 20 M elements 622 and 503 us,
+    // 8 M 256 and 228, 6 M 179.8 and 177.8; P = 128, 10 M 710 and 584; P = 48, 28 M 668 and 662; fp32, P = 64, 11 M 521 and 516; but P = 40, 33 M 543 and 546; GPT-2's, P = 64, 1.9 M 71.2 and 72.2)
+    const bool all = pl->P >= 3 * PARO_BATCH && piece_count(n) >= PARO_ALL_WAVES_MIN_BLOCKS;
+    const unsigned lds = throttle_lds(sc.lds_per_cu, all ? 0 : fold_waves(fold_loads(pl->P), budget));
     PARO_BY_FLAG(keep, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers
             hipLaunchKernelGGL((k_reduce4t<SUMSQ, 1, 8, NT, FEW_SRC, KEEP>), dim3(grid), dim3(WAVE), lds, st, n, tm.pieces,

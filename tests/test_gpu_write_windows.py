@@ -103,3 +103,25 @@ def test_single_sweep(paro, P, G, strategy, dtype, L, exempt):
         results.append((p, m, v, dst))
     for other in results[1:]:
         assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(results[0], other))
+
+
+# Per-tensor gradients: with 48 ranks and more sweep 1 runs all waves that fit from 16 384 blocks on.
+@pytest.mark.parametrize("P,L,dtype", [(48, 1 << 22, wl.BF16), (48, (1 << 22) - 264, wl.BF16), (47, 1 << 22, wl.BF16), (64, (1 << 22) + 8, wl.F16)])
+def test_tensors_of_many_ranks(paro, P, L, dtype):
+    rank = P - 2
+    ob, ol = orc.state_range(orc.layout(P, P, [P * L]), rank, "G")
+    own = [L // 2 + 3, 1000, L - L // 2 - 1003]                             # the rank's chunk; every other is one tensor
+    sizes = [L] * (ob // L) + own + [L] * (P - 1 - ob // L)
+    plan = paro.paro_plan(P, P, "IGG", sizes, grad_dtype=[dtype] * len(sizes))
+    gen = torch.Generator(device=DEV).manual_seed(P)
+    contrib = [torch.randn(ol, generator=gen, device=DEV).mul_(0.01).to(TORCH[dtype]) for _ in range(P)]
+    parts = [[t.clone() for t in torch.split(x, own)] for x in contrib]
+    first = ob // L
+    tables = [torch.tensor([w[t - first if first <= t < first + 3 else 0].data_ptr() for t in range(len(sizes))], dtype=torch.int64, device=DEV)
+              for w in parts]                                               # tensors outside the range: an address that is never read
+    g, ss = torch.full((ol,), -1.0, device=DEV), torch.zeros(1, dtype=torch.float64, device=DEV)
+    paro.paro_reduce_shard(plan, rank, [t.data_ptr() for t in tables], paro.PARO_TENSORS, g.data_ptr(), ss.data_ptr(), stream())
+    want = _fold(paro, plan, contrib, first, 0, L)
+    assert torch.equal(g.view(torch.int32), want.view(torch.int32))
+    norm = float(want.double().square().sum())
+    assert abs(float(ss) - norm) <= 1e-11 * norm
