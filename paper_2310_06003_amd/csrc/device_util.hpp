@@ -319,7 +319,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // segment and is only ever indexed with wave-uniform indices, i.e. read with scalar loads.  Kernels
 // come with room for 16 pointers and for PARO_MAX_RANKS: 2 KB of arguments cost the host 0.2-0.3 us a
 // launch (a small step of one launch: 6.20 -> 5.99 us; of two: 10.2 -> 9.6).
-template <int N>
+template <int N, bool HELD = false>
 struct SrcTableOf {
     const void *p[N];
     int paced;               // the chunk layout's loads go out one by one, with a pause in between
@@ -336,15 +336,15 @@ struct WriteWindow {
     unsigned inverse;
     unsigned short period, waves, open, rest;
 };
-// ... as an argument of the kernels that come with and without.
-template <bool HELD>
-struct WindowArg : WriteWindow {
-    __host__ __device__ WindowArg(const WriteWindow &w) : WriteWindow(w) {}
+// It comes with the pointers of such a launch: as an argument of its own it would be there, if empty, for the others as well.
+template <int N>
+struct SrcTableOf<N, true> : SrcTableOf<N, false> {
+    WriteWindow window;
 };
-template <>
-struct WindowArg<false> {
-    __host__ __device__ WindowArg(const WriteWindow &) {}
-};
+template <int N>
+__device__ __forceinline__ WriteWindow window_of(const SrcTableOf<N, true> &src) { return src.window; }
+template <int N>
+__device__ __forceinline__ WriteWindow window_of(const SrcTableOf<N, false> &) { return WriteWindow(); }
 
 struct AdamConsts {
     float beta1, beta2, omb1, omb2, eps, step_size, sqrt_bc2, decay, wd, grad_scale, max_norm;

@@ -168,10 +168,10 @@ __device__ __forceinline__ State4 load_state4(const float *p, const float *m, co
 // Adam on the thread's 4 elements; state and (optionally) the low-precision copy written back.
 // PART: only elements [lo, hi) of the 4 are the thread's (the others are some other wave's).
 // HELD: the results wait for the chip's next write window (see holds_back).
-template <bool PACK, bool PART, bool HELD>
+template <bool PACK, bool PART = false, bool HELD = false>
 __device__ __forceinline__ void update4(const AdamConsts &a, float sc, const bool decays[4], const float gg[4],
                                         const State4 &s, float *p, float *m, float *v, uint16_t *dst, int64_t e0,
-                                        unsigned elems, int lo, int hi, const WindowArg<HELD> &window) {
+                                        unsigned elems, int lo = 0, int hi = EPT, const WriteWindow &window = WriteWindow()) {
     float pp[4] = {__uint_as_float(s.p.x), __uint_as_float(s.p.y), __uint_as_float(s.p.z), __uint_as_float(s.p.w)},
           mm[4] = {__uint_as_float(s.m.x), __uint_as_float(s.m.y), __uint_as_float(s.m.z), __uint_as_float(s.m.w)},
           vv[4] = {__uint_as_float(s.v.x), __uint_as_float(s.v.y), __uint_as_float(s.v.z), __uint_as_float(s.v.w)};
@@ -267,12 +267,12 @@ __device__ __forceinline__ void store_g4(bool keep, float *g, int64_t e0, unsign
 // one that two chunks share is launched for both.  HELD: results wait for the chip's next write window (see holds_back).
 template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P, int group_len, float *__restrict__ g,
-                                                  double *__restrict__ partials, const SrcTableOf<NSRC> src, const WindowArg<HELD> window) {
+                                                  double *__restrict__ partials, const SrcTableOf<NSRC, HELD> src) {
     const int64_t e0 = (lo & ~(int64_t)(PIECE - 1)) + block_first(), e = e0 + lane_id() * EPT;
     const bool inside = e >= lo && e < hi;
     float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     double acc = 0.0;
-    if constexpr (HELD) leave_window(window);
+    if constexpr (HELD) leave_window(src.window);
     if (inside) {
         constexpr int WIDE = DT == PARO_F32 ? PARO_PACE_WIDE_F32_SLEEP : PARO_PACE_WIDE_SLEEP;
         Chunk4Loader<DT, (HELD ? PARO_WINDOW_PACE_SLEEP : NSRC > FEW_SRC ? WIDE : PARO_PACE_SLEEP)> ld{e};
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P,
     if (SUMSQ) acc = wave_sum(acc);
     if constexpr (HELD) {
         is_formed(X);
-        if (has_followers(window)) wait_for_window(window);
+        if (has_followers(src.window)) wait_for_window(src.window);
         if (inside) store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, hi), X);
     }
     if (SUMSQ && lane_id() == 0) partials[partial_slot()] = acc;
@@ -299,16 +299,16 @@ __global__ __launch_bounds__(WAVE) void k_reduce4(int64_t lo, int64_t hi, int P,
 template <int DT, bool SUMSQ, int NSRC, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_reduce4r(int64_t block0, int64_t n, int P, unsigned part0, unsigned part_n,
                                                    float *__restrict__ g, double *__restrict__ partials, const RangeMap rm,
-                                                   const SrcTableOf<NSRC> src, const WindowArg<HELD> window) {
+                                                   const SrcTableOf<NSRC, HELD> src) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
-    if constexpr (HELD) leave_window(window);
+    if constexpr (HELD) leave_window(src.window);
     double acc = 0.0;
     if (e0 < n) {
         float X[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         const bool counts = fold_range<DT, HELD ? PARO_WINDOW_PACE_SLEEP : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
         if constexpr (HELD) {
             is_formed(X);
-            if (has_followers(window)) wait_for_window(window);
+            if (has_followers(src.window)) wait_for_window(src.window);
         }
         if (e < n) {
             store_g4((unsigned)(e0 / PIECE) >= src.keep_from, g, e0, piece_elems(e0, n), X);
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restri
     if (e >= n) return;
     if (MASK == MASK_TENSORS) decay_flags(tm, pc, loc, decays);
     const float gg[4] = {__uint_as_float(G.x), __uint_as_float(G.y), __uint_as_float(G.z), __uint_as_float(G.w)};
-    update4<PACK, false, false>(a, sc, decays, gg, s, p, m, v, dst, e0, piece_elems(e0, n), 0, EPT, WindowArg<false>(WriteWindow()));
+    update4<PACK>(a, sc, decays, gg, s, p, m, v, dst, e0, piece_elems(e0, n));
 }
 
 // Single sweep when nothing has to wait for the norm (no clipping): fold, Adam and pack; the
@@ -525,14 +525,14 @@ __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restri
 template <bool TENSORS, int DT, int MASK, bool NT, int NSRC, int PAUSE, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
                                                  const paro_piece_info *pieces, unsigned n_pieces, int P, int group_len,
-                                                 const SrcTableOf<NSRC> src, const AdamConsts a, uint16_t *__restrict__ dst, TensorMap tm,
-                                                 const WindowArg<HELD> window) {
+                                                 const SrcTableOf<NSRC, HELD> src, const AdamConsts a, uint16_t *__restrict__ dst,
+                                                 TensorMap tm) {
     tm.pieces = pieces;
     tm.n_pieces = n_pieces;
     Piece pc;
     Located loc;
     int64_t e0 = block_first();
-    if constexpr (HELD) leave_window(window);
+    if constexpr (HELD) leave_window(src.window);
     if constexpr (TENSORS) {
         const Cut c = cut_of(tm, blockIdx.x, n);
         if (c.e0 >= n) return;
@@ -543,8 +543,7 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
             if (c.pc.tensor != -2) fold_part(c, src, P, group_len, X);
             const bool d = MASK == MASK_NONE || c.pc.tensor < 0 || tm.no_decay[c.pc.tensor] == 0;
             const bool decays[4] = {d, d, d, d};
-            update4<true, true, false>(a, a.grad_scale, decays, X, s, p, m, v, dst, c.e0, piece_elems(c.e0, n), c.a, c.b,
-                                       WindowArg<false>(WriteWindow()));
+            update4<true, true>(a, a.grad_scale, decays, X, s, p, m, v, dst, c.e0, piece_elems(c.e0, n), c.a, c.b);
             return;
         }
         e0 = c.e0;
@@ -571,16 +570,16 @@ __global__ __launch_bounds__(WAVE) void k_fused4(int64_t n, float *__restrict__ 
     bool decays[4] = {true, true, true, true};
     if (MASK == MASK_TABLE) decay_flags(tm.decay_tab, (uint32_t)uniform((int)entry), decays);
     if (MASK == MASK_TENSORS) decay_flags(tm, pc, loc, decays);
-    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, elems, 0, EPT, window);
+    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, elems, 0, EPT, window_of(src));
 }
 
 // The same for blocks from block0 on of an update range of several chunks (chunk layout, no mask).
 template <int DT, int NSRC, int PAUSE, bool HELD>
 __global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, float *__restrict__ p, float *__restrict__ m,
-                                                  float *__restrict__ v, int P, const RangeMap rm, const SrcTableOf<NSRC> src, const AdamConsts a,
-                                                  uint16_t *__restrict__ dst, const WindowArg<HELD> window) {
+                                                  float *__restrict__ v, int P, const RangeMap rm, const SrcTableOf<NSRC, HELD> src,
+                                                  const AdamConsts a, uint16_t *__restrict__ dst) {
     const int64_t e0 = (block0 + blockIdx.x) * PIECE, e = e0 + lane_id() * EPT;
-    if constexpr (HELD) leave_window(window);
+    if constexpr (HELD) leave_window(src.window);
     if (e0 >= n) return;
     State4 s;
     if (e < n) s = load_state4(p, m, v, e);
@@ -589,7 +588,7 @@ __global__ __launch_bounds__(WAVE) void k_fused4r(int64_t block0, int64_t n, flo
     fold_range<DT, PAUSE ? 0 : HELD ? PARO_FUSED_WINDOW_PACE_SLEEP : PARO_PACE_SLEEP>(rm, src, P, e0, n, X);
     if (e >= n) return;
     const bool decays[4] = {true, true, true, true};
-    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n), 0, EPT, window);
+    update4<true, false, HELD>(a, a.grad_scale, decays, X, s, p, m, v, dst, e0, piece_elems(e0, n), 0, EPT, window_of(src));
 }
 
 // Low-precision pack alone.
@@ -1074,7 +1073,7 @@ WriteWindow window_for(int period, int waves, int open, int rest) {
     return WriteWindow{(unsigned)(((uint64_t)1 << 32) / (unsigned)period), (unsigned short)period, (unsigned short)(waves ? waves : MAX_WAVES_PER_CU),
                        (unsigned short)open, (unsigned short)rest};
 }
-WriteWindow window_of(const paro_plan_t *pl, bool range = false) {
+WriteWindow fold_window(const paro_plan_t *pl, bool range = false) {
     const bool soon = range && pl->dtype[0] != PARO_F32;
     const int per_rank = soon ? PARO_RANGE_WINDOW_TICKS_PER_RANK : PARO_WINDOW_TICKS_PER_RANK;
     const int most = soon ? PARO_RANGE_WINDOW_MAX_PERIOD : PARO_WINDOW_MAX_PERIOD;
@@ -1239,6 +1238,18 @@ SrcTableOf<FEW_SRC> few_sources(const SrcTable &tab) {
     few.keep_from = tab.keep_from;
     return few;
 }
+// ... with the windows of a launch that holds back (window() works them out), which the others neither need nor wait for.
+template <bool HELD, int N, class Window>
+decltype(auto) with_window(const SrcTableOf<N> &src, Window window) {
+    if constexpr (HELD) {
+        SrcTableOf<N, true> held;
+        static_cast<SrcTableOf<N> &>(held) = src;
+        held.window = window();
+        return held;
+    } else {
+        return (src);
+    }
+}
 // CALL with `src`, the pointer table in the size that the kernels for NSRC pointers take.
 #define PARO_BY_TABLE(P, tab, CALL)              \
     do {                                         \
@@ -1307,7 +1318,7 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
             hipLaunchKernelGGL((k_reduce4<DT, SUMSQ, NSRC, HELD>), dim3(grid), dim3(WAVE), lds, st, lo, lo + n, pl->P, group_len, g_range,
-                               partials, src, window_of(pl));
+                               partials, with_window<HELD>(src, [&] { return fold_window(pl); }));
         })));
         return (int)grid;
     }
@@ -1379,7 +1390,6 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     if (small && large && pl->P > 8 && !pl->dev.f32[(size_t)c]) waves = PARO_FUSED_TL_WAVES_PER_CU;
     const bool held = layout == PARO_CHUNK && fused_holds_back(pl, n);
     if (held) waves = fused_window_waves(pl);
-    const WriteWindow window = fused_window(pl);
     const TensorMap tm = map_for(pl, sc, c * pl->L, true);
     const unsigned grid = piece_grid(n), lds = throttle_lds(sc.lds_per_cu, waves);
     const int mask = !pl->any_no_decay ? MASK_NONE : layout == PARO_CHUNK && tm.decay_tab ? MASK_TABLE : MASK_TENSORS;
@@ -1387,17 +1397,17 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         PARO_BY_TABLE(pl->P, tab, PARO_BY_FLAG(mask != MASK_NONE, MASKED, PARO_BY_LINES(pl->dev.on_lines[(size_t)c] != 0, {
             hipLaunchKernelGGL((k_fused4<true, PARO_BF16, MASKED ? MASK_TENSORS : MASK_NONE, NT, NSRC, 0, false>),
                                dim3(tm.pieces ? tm.n_pieces : grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces, pl->P,
-                               group_len, src, a, dst, tm, window);
+                               group_len, src, a, dst, tm);
         })));
     else if (pauses_single(pl, n))
         PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
             hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, FEW_SRC, PARO_PAUSE_SLEEP, false>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v,
-                               tm.pieces, tm.n_pieces, pl->P, group_len, few_sources(tab), a, dst, tm, window);
+                               tm.pieces, tm.n_pieces, pl->P, group_len, few_sources(tab), a, dst, tm);
         }));
     else
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
             hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
-                               tm.n_pieces, pl->P, group_len, src, a, dst, tm, window);
+                               tm.n_pieces, pl->P, group_len, with_window<HELD>(src, [&] { return fused_window(pl); }), a, dst, tm);
         }))));
 }
 
@@ -1408,11 +1418,10 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     const RangeMap rm = range_map(pl, ob, on, -1, contrib, &tab);
     const bool held = fused_range_holds_back(pl, on), held_paced = fused_range_paces(pl);
     const int waves = held ? fused_window_waves(pl) : fused_waves(pl->P, pl->dtype[0] == PARO_F32, Sweep::RANGE, piece_count(on));
-    const WriteWindow window = fused_window(pl, held_paced);
     const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
     if (pauses_range(pl, on)) {                                 // (one grid holds what pauses)
         PARO_BY_DTYPE(pl->dtype[0], hipLaunchKernelGGL((k_fused4r<DT, FEW_SRC, PARO_PAUSE_SLEEP, false>), dim3(piece_grid(on)), dim3(WAVE), lds, st,
-                                                       (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst, window));
+                                                       (int64_t)0, on, p, m, v, pl->P, rm, few_sources(tab), a, dst));
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
@@ -1420,7 +1429,8 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
-            hipLaunchKernelGGL((k_fused4r<DT, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, b0, on, p, m, v, pl->P, rm, src, a, dst, window);
+            hipLaunchKernelGGL((k_fused4r<DT, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, b0, on, p, m, v, pl->P, rm,
+                               with_window<HELD>(src, [&] { return fused_window(pl, held_paced); }), a, dst);
         })));
         PARO_HIP(hipGetLastError());
     }
@@ -1506,7 +1516,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
     const bool held = range_holds_back(pl), all = pl->dtype[0] != PARO_F32 && pl->P > 8 && piece_count(on) < PARO_RANGE_WINDOW_MIN_BLOCKS;
     const int waves = held ? window_waves(pl) : all ? 0 : fold_waves(fold_loads(pl->P), fold_budget(pl, false));
     if (held) tab.paced = pl->dtype[0] == PARO_F32;
-    const WriteWindow window = window_of(pl, true);
+    const auto window = [&] { return fold_window(pl, true); };
     const unsigned lds = throttle_lds(sc.lds_per_cu, waves);
     const int64_t blocks = (piece_count(on) + 7) & ~(int64_t)7;
     const int64_t step = sumsq_out ? std::min(sc.n_partials, MAX_GRID) : MAX_GRID;
@@ -1523,7 +1533,8 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
         if (sumsq_out && first < last) {
             PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
                 hipLaunchKernelGGL((k_reduce4r<DT, true, NSRC, HELD>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
-                                   pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out, sc.partials, rm, src, window);
+                                   pl->P, (unsigned)(first - b0), (unsigned)(last - first), grad_out, sc.partials, rm,
+                                   with_window<HELD>(src, window));
             })));
             PARO_HIP(hipGetLastError());
             // the next launch reuses the scratch array: this one's partials are added up first
@@ -1539,7 +1550,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
         } else {
             PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
                 hipLaunchKernelGGL((k_reduce4r<DT, false, NSRC, HELD>), dim3((unsigned)grid), dim3(WAVE), lds, st, b0, on,
-                                   pl->P, 0u, 0u, grad_out, sc.partials, rm, src, window);
+                                   pl->P, 0u, 0u, grad_out, sc.partials, rm, with_window<HELD>(src, window));
             })));
             PARO_HIP(hipGetLastError());
         }
