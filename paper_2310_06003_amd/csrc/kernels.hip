@@ -1373,6 +1373,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     return (int)grid;
 }
 
+// Whether there are single sweeps with write windows for NSRC pointers: two-byte contributions have none of up to FEW_SRC ranks.
+template <int DT, int NSRC>
+constexpr bool FUSED_HOLDS = DT == PARO_F32 || NSRC > FEW_SRC;
+static_assert(PARO_FUSED_WINDOW_RANK_BYTES > 2 * FEW_SRC && PARO_FUSED_RANGE_WINDOW_MIN_RANKS > FEW_SRC, "see FUSED_HOLDS");
+
 // Launches the single sweep (no clipping) over chunk c.
 void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const SrcTable &tab, int group_len, int64_t c,
                   const AdamConsts &a, float *p, float *m, float *v, uint16_t *dst, hipStream_t st) {
@@ -1406,8 +1411,9 @@ void launch_fused(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
         }));
     else
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], PARO_BY_MASK(mask, {
-            hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces,
-                               tm.n_pieces, pl->P, group_len, with_window<HELD>(src, [&] { return fused_window(pl); }), a, dst, tm);
+            if constexpr (!HELD || FUSED_HOLDS<DT, NSRC>)
+                hipLaunchKernelGGL((k_fused4<false, DT, MASK, true, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, n, p, m, v, tm.pieces, tm.n_pieces,
+                                   pl->P, group_len, with_window<HELD>(src, [&] { return fused_window(pl); }), a, dst, tm);
         }))));
 }
 
@@ -1429,8 +1435,9 @@ int launch_fused_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int
     for (int64_t b0 = 0, blocks = piece_count(on); b0 < blocks; b0 += MAX_GRID) {
         const unsigned grid = (unsigned)std::min(MAX_GRID, blocks - b0);
         PARO_BY_FLAG(held, HELD, PARO_BY_TABLE(pl->P, tab, PARO_BY_DTYPE(pl->dtype[0], {
-            hipLaunchKernelGGL((k_fused4r<DT, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, b0, on, p, m, v, pl->P, rm,
-                               with_window<HELD>(src, [&] { return fused_window(pl, held_paced); }), a, dst);
+            if constexpr (!HELD || FUSED_HOLDS<DT, NSRC>)
+                hipLaunchKernelGGL((k_fused4r<DT, NSRC, 0, HELD>), dim3(grid), dim3(WAVE), lds, st, b0, on, p, m, v, pl->P, rm,
+                                   with_window<HELD>(src, [&] { return fused_window(pl, held_paced); }), a, dst);
         })));
         PARO_HIP(hipGetLastError());
     }

@@ -138,3 +138,21 @@ def test_launches_without_write_windows_do_not_carry_them(kernels):
     """Not even as an empty argument: what a small step pays for is the launch."""
     assert len(kernels) > 100
     assert [k for k in kernels if "Window" in k] == []
+
+
+def test_no_single_sweep_with_windows_for_few_two_byte_contributions(kernels):
+    """A launch has them from 64 bytes of contributions an element on, over a range of several chunks from 28 two-byte ones on: never with
+    the table of 16 pointers, unless they are of fp32."""
+    sweeps = [Launch(k + "\t0\t0\t0") for k in kernels if k.startswith(("k_fused4<false", "k_fused4r<"))]
+    kinds = {(x.flags[1] if x.kernel == "k_fused4" else x.flags[0], x.flags[-3], x.flags[-1]) for x in sweeps}
+    f32 = str(wl.F32)
+    assert kinds == {(str(d), n, held) for d in (wl.BF16, wl.F16, wl.F32) for n in ("16", "256") for held in ("false", "true")
+                     if held == "false" or n == "256" or str(d) == f32}
+
+
+@pytest.mark.parametrize("P,G,strategy,dtype,L,held", [
+    (32, 8, "IGG", wl.BF16, 40 * M, True), (31, 31, "IGG", wl.BF16, 40 * M, False), (16, 8, "IGG", wl.F32, 13 * M, True),
+    (15, 5, "IGG", wl.F32, 40 * M, False), (28, 14, "III", wl.F16, 8 * M, True), (27, 9, "III", wl.F16, 8 * M, False),
+    (16, 8, "III", wl.F32, 8 * M, True), (16, 8, "III", wl.BF16, 40 * M, False)])
+def test_single_sweeps_with_windows(launches, P, G, strategy, dtype, L, held):
+    assert [x.flags[-1] for x in launches("step", P, G, strategy, 1, dtype, 0, False, [P * L])] == [str(held).lower()]
