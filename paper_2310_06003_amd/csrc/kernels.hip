@@ -480,12 +480,16 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
 // KEPT: the launch before this one stored all of the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS): plain loads.
-// Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).
+// Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).  Not with a mask, where
+// that costs paro_adam_shard alone up to 3 % and brings a whole step nothing (from the end and from the start: the call alone after its gradient was
+// scaled in place and copied in, 6 M elements 31.9, 33.1 and 31.2, 32.4 us, on another box 33.6, 35.0 and 32.4, 34.2; 9 M 44.3, 44.6 and 43.6, 43.8; 30 M 134, 142 and
+// 135, 141, there 137, 143 and 135, 141; 200 M 906, 911 and 910, 915; clipped steps, P = 4, GPT-2's list 199 and 198, its tensors 198 and 197, P = 2 384 and 382; 8 chunks, P = 8, 973
+// and 977; Llama-like lists, P = 8, 42 M 312 and 312, P = 16, 84 M 830 and 828, 421 M 4200 and 4200).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
 __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
                                                 float *__restrict__ v, const double *__restrict__ sums, int n_sums, const AdamConsts a,
                                                 uint16_t *__restrict__ dst, double *__restrict__ sumsq_out, const TensorMap tm) {
-    const unsigned block = KEPT ? blockIdx.x : (unsigned)((n - 1) / PIECE) - blockIdx.x;
+    const unsigned block = KEPT || MASK != MASK_NONE ? blockIdx.x : (unsigned)((n - 1) / PIECE) - blockIdx.x;
     const int64_t e0 = (int64_t)block * PIECE, e = e0 + lane_id() * EPT;
     bool decays[4] = {true, true, true, true};
     Piece pc;
@@ -1639,7 +1643,7 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
         PARO_HIP(hipGetLastError());
         return PARO_OK;
     }
-    for (int64_t c = (ob + on) / pl->L - 1; c >= ob / pl->L; --c) {      // chunk by chunk: each has its own weight-decay table
+    for (int64_t c = ob / pl->L; c < (ob + on) / pl->L; ++c) {      // chunk by chunk: each has its own weight-decay table
         const int64_t lo = c * pl->L - ob;
         const unsigned lds = throttle_lds(sc.lds_per_cu, PARO_ADAM_MASK_WAVES_PER_CU), grid = piece_grid(pl->L);
         const TensorMap tm = map_for(pl, sc, c * pl->L, true);

@@ -21,7 +21,7 @@ def test_large_gradients(paro, strategy, L, dtype):
 @pytest.mark.parametrize("strategy,sizes", [
     ("NNN", [20 * M + 8, 1000, 39 * M + 3, 256]), ("NNG", [57 * M, 512, 56 * M + 256]), ("NNN", [3 * M + 1, 1000, 18 * M, 256])])
 def test_exempt_tensors_and_both_layouts_give_the_same(paro, strategy, sizes):
-    """Sweep 2 in one launch per chunk, the last chunk first; per-tensor gradients whose blocks start on cache lines, and not."""
+    """Sweep 2 in one launch per chunk, from the first on; per-tensor gradients whose blocks start on cache lines, and not."""
     P, rank = 2, 1
     plan = paro.paro_plan(P, 1, strategy, sizes, no_decay=[i % 2 for i in range(len(sizes))])
     lay = orc.layout(P, 1, sizes)

@@ -156,3 +156,9 @@ def test_no_single_sweep_with_windows_for_few_two_byte_contributions(kernels):
     (16, 8, "III", wl.F32, 8 * M, True), (16, 8, "III", wl.BF16, 40 * M, False)])
 def test_single_sweeps_with_windows(launches, P, G, strategy, dtype, L, held):
     assert [x.flags[-1] for x in launches("step", P, G, strategy, 1, dtype, 0, False, [P * L])] == [str(held).lower()]
+
+
+@pytest.mark.parametrize("call,layout", [("step", 0), ("step", 1), ("adam", 0)])
+def test_sweep_2_with_exempt_tensors_goes_from_the_start(launches, call, layout):
+    got = [x for x in launches(call, 4, 2, "III", 1, wl.BF16, layout, True, [20 * M, 1000, 90 * M], [0, 1, 0]) if x.kernel == "k_adam4"]
+    assert len(got) == 2 and got[0].second < got[1].second          # one launch a chunk: where its gradient begins
