@@ -233,6 +233,9 @@ namespace {
 #ifndef PARO_FUSED_WINDOW_MANY_BYTES
 #define PARO_FUSED_WINDOW_MANY_BYTES 80          // with fewer bytes for an element half as many again of all
 #endif
+#ifndef PARO_FUSED_WINDOW_TWO_BATCHES_BYTES
+#define PARO_FUSED_WINDOW_TWO_BATCHES_BYTES ((int64_t)1664 << 20)   // 32 two-byte ranks: of all
+#endif
 #ifndef PARO_FUSED_WINDOW_TICKS_PER_BYTE
 #define PARO_FUSED_WINDOW_TICKS_PER_BYTE 26      // from one window to the next, for each of the element's bytes
 #endif

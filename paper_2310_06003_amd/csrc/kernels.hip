@@ -1091,8 +1091,14 @@ WriteWindow fold_window(const paro_plan_t *pl, bool range = false) {
 // fp32: P = 64, 20 M 992 -> 886; P = 32, 15 M 403 -> 371, 4 M 111.0 -> 107.0; P = 24, 50 M 1028 -> 961; P = 20, 40 M 686 -> 698 and 725 -> 692; P = 16, 80 M 1204 -> 1170, 15 M
 // 228 -> 222, 8 M 122.6 -> 121.8; but P = 14, 60 M 788 -> 799, P = 16, 5 M 80.0 -> 80.6.  Per-tensor gradients of two bytes, whose waves
 // look up their pointers first: P = 32, Llama-like list, 555 -> 618; ragged, 335 -> 366.
+// 32 ranks of two bytes, whose waves end with no short last batch, are fastest of all without (14.2 us a million elements, 33 ranks 14.9, 36 16.0) and gain at every size only
+// from 26 M elements on: 13 M 190 -> 188, 16 M 228 -> 224, 18 M 255 -> 260, 20 M 283.7 -> 288.5, 22 M 321 -> 315, 25 M 354.7 -> 357.8, 26 M 377 -> 371, 27 M 387 -> 380, 28 M
+// 408 -> 396, 35 M 498 -> 492, 60 M 870 -> 844; P = 33, 18 M 269 -> 269, 20 M 296 -> 293, 25 M 371 -> 362; P = 34, 14 M 218 -> 207, 20 M 305 -> 299; P = 36, 14 M 230 -> 216, 20 M 325 -> 304;
+// fp32, P = 16, 13 M 203 -> 188, 20 M 291 -> 280, 32 M 470 -> 450.
 bool fused_holds_back(const paro_plan_t *pl, int64_t n) {
-    const int bytes = pl->P * (pl->dtype[0] == PARO_F32 ? 4 : 2);
+    const bool f32 = pl->dtype[0] == PARO_F32;
+    const int bytes = pl->P * (f32 ? 4 : 2);
+    if (pl->P == 2 * PARO_BATCH && !f32) return n * bytes >= PARO_FUSED_WINDOW_TWO_BATCHES_BYTES;
     const int64_t least = (int64_t)PARO_FUSED_WINDOW_MIN_BYTES / 64 * std::max(pl->P, 64);
     return bytes >= PARO_FUSED_WINDOW_RANK_BYTES && n * bytes >= (bytes < PARO_FUSED_WINDOW_MANY_BYTES ? least * 3 / 2 : least);
 }

@@ -151,7 +151,8 @@ def test_no_single_sweep_with_windows_for_few_two_byte_contributions(kernels):
 
 
 @pytest.mark.parametrize("P,G,strategy,dtype,L,held", [
-    (32, 8, "IGG", wl.BF16, 40 * M, True), (31, 31, "IGG", wl.BF16, 40 * M, False), (16, 8, "IGG", wl.F32, 13 * M, True),
+    (32, 8, "IGG", wl.BF16, 26 * M, True), (32, 8, "IGG", wl.F16, 26 * M - 8, False), (32, 8, "IGG", wl.BF16, 19 * M, False),
+    (33, 11, "IGG", wl.BF16, 13 * M, True), (40, 8, "IGG", wl.BF16, 7 * M, True), (31, 31, "IGG", wl.BF16, 40 * M, False), (16, 8, "IGG", wl.F32, 13 * M, True),
     (15, 5, "IGG", wl.F32, 40 * M, False), (28, 14, "III", wl.F16, 8 * M, True), (27, 9, "III", wl.F16, 8 * M, False),
     (16, 8, "III", wl.F32, 8 * M, True), (16, 8, "III", wl.BF16, 40 * M, False)])
 def test_single_sweeps_with_windows(launches, P, G, strategy, dtype, L, held):
