@@ -110,6 +110,20 @@ namespace {
 #ifndef PARO_FUSED_MIN_BLOCKS
 #define PARO_FUSED_MIN_BLOCKS 8192  // blocks of a single sweep from which on fused_waves thins out its waves
 #endif
+// Blocks of a single sweep up to which it runs all waves that fit (see runs_at_once): over a range of two-byte contributions, other, over one chunk
+// of 17 to 31 two-byte ones, of up to 16 of them this many blocks times ranks.
+#ifndef PARO_AT_ONCE_RANGE_BLOCKS
+#define PARO_AT_ONCE_RANGE_BLOCKS 8192
+#endif
+#ifndef PARO_AT_ONCE_BLOCKS
+#define PARO_AT_ONCE_BLOCKS 4096
+#endif
+#ifndef PARO_AT_ONCE_SHORT_BATCH_BLOCKS
+#define PARO_AT_ONCE_SHORT_BATCH_BLOCKS 3840
+#endif
+#ifndef PARO_AT_ONCE_READS
+#define PARO_AT_ONCE_READS 49152
+#endif
 #ifndef PARO_FUSED_RANGE_MIN_READS
 #define PARO_FUSED_RANGE_MIN_READS 81920   // ... and blocks times ranks of one over several chunks of two-byte contributions
 #endif

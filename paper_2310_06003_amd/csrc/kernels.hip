@@ -724,13 +724,17 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
 // Whether a single sweep is so small that a budget would only keep waves from starting, of which the chip holds all at once: with 10 or 11 per
 // compute unit it takes two or three rounds.  Whole steps, by the budget and with all waves: over a range of two-byte contributions (up to 8192
 // blocks), whose waves walk to their pointers first, P = 14, 2 x 0.9 M elements 17.4 -> 17.0 us; P = 16, 2 x 0.3 M 8.1 -> 7.0, 2 x 0.5 M 11.3 -> 10.4, 2 x 1 M 20.2 -> 19.2;
-// P = 24, 2 x 0.5 M 15.1 -> 13.0, 2 x 1 M 26.5 -> 24.4; P = 32, 2 x 1 M 31.2 -> 29.3; P = 64, 2 x 0.5 M 29.8 -> 25.1, 2 x 1 M 53.6 -> 52.7; P = 128, 2 x 0.4 M 45.3 -> 42.7, 2 x 1 M 98.5 -> 99.4; but beyond that P = 16, 2 x
-// 2 M 38.8 -> 41.9, P = 32, 2 x 1.5 M 45.2 -> 47.2; P = 8, 2 x 0.8 M 11.2 -> 12.5, P = 12, 2 x 0.9 M 15.8 -> 16.1.  Otherwise (up to 4096 blocks and 64 ranks): one chunk, P = 12, 1 M 8.5 -> 8.2; P = 16, 0.7 M 7.3 -> 7.1; P = 32, 0.8 M
-// 12.6 -> 12.4; P = 64, 0.7 M 19.8 -> 17.8; fp32, P = 16, 0.7 M 10.3 -> 10.0, P = 64, 1 M 46.6 -> 45.4, a range, P = 16, 2 x 0.5 M 15.0 -> 14.6, P = 32 24.9 -> 24.4; but P = 128, 1 M 43.6 -> 45.0;
-// P = 32, 2 M 28.9 -> 29.4.
-bool runs_at_once(int P, bool two_byte_range, int64_t blocks) {
-    if (two_byte_range) return P > 12 && blocks <= COMPUTE_UNITS * MAX_WAVES_PER_CU;
-    return P >= 12 && P <= 64 && blocks <= COMPUTE_UNITS * MAX_WAVES_PER_CU / 2;
+// P = 24, 2 x 0.5 M 15.1 -> 13.0, 2 x 1 M 26.5 -> 24.4; P = 32, 2 x 1 M 31.2 -> 29.3; P = 64, 2 x 0.5 M 29.8 -> 25.1, 2 x 1 M 53.6 -> 52.7; P = 128, 2 x 0.4 M 45.3 -> 42.7, 2 x 1 M 98.5 -> 99.4 and 98.5 -> 97.4; but beyond that P = 16, 2 x
+// 2 M 38.8 -> 41.9, P = 32, 2 x 1.5 M 45.2 -> 47.2; P = 8, 2 x 0.8 M 11.2 -> 12.5, P = 12, 2 x 0.9 M 15.8 -> 16.1.  Otherwise up to 64 ranks: fp32 (up to 4096 blocks), P = 16, 0.7 M 10.3 -> 10.0, P = 64, 1 M
+// 46.6 -> 45.4, a range, P = 16, 2 x 0.5 M 15.0 -> 14.6, P = 32 24.9 -> 24.4; but P = 128, 1 M 43.6 -> 45.0; one chunk of two bytes, P = 32, 0.8 M 12.7 -> 12.5, 1 M 15.1 -> 14.8; P = 64, 0.6 M 17.9 -> 15.7,
+// 1 M 24.6 -> 24.4; but P = 32, 2 M 28.9 -> 29.4.  With up to 16 of them each wave asks for all it reads in one go, and beyond 25 MB for the launch that is too much at once: P = 12, 0.75 M 7.2 -> 5.7, 0.9 M 7.8 ->
+// 7.4, 1.045 M 8.8 -> 8.7; P = 14, 0.75 M 7.7 -> 6.2, 0.85 M 8.0 -> 7.7, but 0.95 M 8.6 -> 8.8, 1.045 M 9.3 -> 9.9; P = 15, 0.75 M 7.9 -> 6.5, but 0.95 M 9.2 -> 9.5; P = 16, 0.65 M 7.0 -> 6.7, 0.75 M 7.3 -> 7.3, but
+// 0.85 M 8.0 -> 8.5, 0.9 M 8.5 -> 9.1.  17 to 31: P = 17, 0.7 M 8.2 -> 7.2, 0.98 M 10.8 -> 10.6; P = 24, 0.7 M 9.9 -> 9.4, 0.98 M 12.8 -> 12.7, but 1.02 M 12.8 -> 13.2; P = 26 13.5 -> 13.9; P = 28 14.7 -> 14.8.
+bool runs_at_once(int P, bool f32, bool range, int64_t blocks) {
+    if (range && !f32) return P > 12 && blocks <= PARO_AT_ONCE_RANGE_BLOCKS;
+    if (P < 12 || P > 64) return false;
+    if (f32 || P >= 2 * PARO_BATCH) return blocks <= PARO_AT_ONCE_BLOCKS;
+    return P > PARO_BATCH ? blocks <= PARO_AT_ONCE_SHORT_BATCH_BLOCKS : blocks * P <= PARO_AT_ONCE_READS;
 }
 
 // Waves per compute unit of a single sweep over `blocks` blocks.  The budget, which was found at P = 16, lets too many waves
@@ -753,7 +757,7 @@ bool runs_at_once(int P, bool two_byte_range, int64_t blocks) {
 // but P = 4, 7 M 41.3 and 40.4, P = 3, 7.8 M 43.1 and 42.6).
 enum class Sweep { CHUNK, RANGE, TENSORS_ON_LINES, OTHER_TENSORS };
 int fused_waves(int P, bool f32, Sweep over, int64_t blocks) {
-    if ((over == Sweep::CHUNK || over == Sweep::RANGE) && runs_at_once(P, over == Sweep::RANGE && !f32, blocks)) return 0;
+    if ((over == Sweep::CHUNK || over == Sweep::RANGE) && runs_at_once(P, f32, over == Sweep::RANGE, blocks)) return 0;
     const int waves = fold_waves(fold_loads(P) + 3, PARO_FUSED_LOADS_PER_CU);
     if (blocks < PARO_FUSED_MIN_BLOCKS || P >= PARO_BATCH || over == Sweep::OTHER_TENSORS) return waves;
     if (over == Sweep::RANGE && !f32 && blocks * P < PARO_FUSED_RANGE_MIN_READS) return waves;

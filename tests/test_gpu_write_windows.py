@@ -64,7 +64,8 @@ def test_reduced_gradient_and_its_norm(paro, P, G, strategy, dtype, blocks, more
 
 # The single sweep: 33 two-byte contributions or 16 fp32 ones and more, from 768 MB of them on, 40 and 20 from 512 MB, with more than 64 ranks 8 MB a
 # rank, 32 two-byte ones from 1664 MB.  Over a range of several chunks 32 two-byte ones, and more than 48, from 16 384 blocks on, others of 28 and more from 768 MB; up to 96 without
-# pauses.  Small ones have all waves that fit, up to 8192 blocks of a range of more than 12 two-byte ones, and 4096 otherwise.  It gives what the two calls give whose sweeps it joins.
+# pauses.  Small ones have all waves that fit, up to 8192 blocks of a range of more than 12 two-byte ones, and 4096 or a few
+# less otherwise.  It gives what the two calls give whose sweeps it joins.
 @pytest.mark.parametrize("P,G,strategy,dtype,L", [
     (32, 8, "IGG", wl.BF16, 26 << 20), (32, 8, "IGG", wl.BF16, (26 << 20) - 8), (33, 11, "IGG", wl.F16, 12201616), (33, 11, "IGG", wl.BF16, 12201608),
     (32, 8, "IGG", wl.BF16, 3 << 22), (32, 8, "IGG", wl.BF16, (3 << 22) - 8), (31, 31, "IGG", wl.BF16, (3 << 22) + 264),

@@ -163,3 +163,14 @@ def test_single_sweeps_with_windows(launches, P, G, strategy, dtype, L, held):
 def test_sweep_2_with_exempt_tensors_goes_from_the_start(launches, call, layout):
     got = [x for x in launches(call, 4, 2, "III", 1, wl.BF16, layout, True, [20 * M, 1000, 90 * M], [0, 1, 0]) if x.kernel == "k_adam4"]
     assert len(got) == 2 and got[0].second < got[1].second          # one launch a chunk: where its gradient begins
+
+
+# Over one chunk of two-byte contributions: up to 16 ranks 49 152 blocks times ranks, up to 31 ranks 3840 blocks, then 4096, as with fp32 ones.
+@pytest.mark.parametrize("P,G,strategy,dtype,blocks,all_waves", [
+    (12, 4, "IGG", wl.BF16, 4096, True), (14, 7, "IGG", wl.F16, 3510, True), (14, 7, "IGG", wl.BF16, 3511, False), (16, 8, "IGG", wl.BF16, 3072, True),
+    (16, 8, "IGG", wl.BF16, 3073, False), (17, 17, "IGG", wl.BF16, 3840, True), (31, 31, "IGG", wl.F16, 3841, False), (32, 8, "IGG", wl.BF16, 4096, True),
+    (64, 8, "IGG", wl.BF16, 4097, False), (65, 13, "IGG", wl.BF16, 1000, False), (11, 11, "IGG", wl.BF16, 4000, False), (16, 8, "IGG", wl.F32, 4096, True),
+    (16, 8, "III", wl.BF16, 4096, True), (12, 6, "III", wl.BF16, 1000, False), (24, 12, "III", wl.F32, 2048, True), (128, 64, "III", wl.BF16, 4096, True)])
+def test_small_single_sweeps_with_all_waves(launches, P, G, strategy, dtype, blocks, all_waves):
+    got, = launches("step", P, G, strategy, 1, dtype, 0, False, [P * blocks * 256])
+    assert got.kernel in ("k_fused4", "k_fused4r") and (got.lds == 0) == all_waves
