@@ -218,6 +218,9 @@ namespace {
 #ifndef PARO_ALL_WAVES_MIN_BLOCKS
 #define PARO_ALL_WAVES_MIN_BLOCKS 16384          // tensor layout, 48 ranks and more: from here on sweep 1 runs all waves that fit
 #endif
+#ifndef PARO_ALL_WAVES_F32_LARGE_RANKS
+#define PARO_ALL_WAVES_F32_LARGE_RANKS 56        // ... over a large chunk of fp32 gradients
+#endif
 // ... over a range of several chunks (see range_holds_back).
 #ifndef PARO_RANGE_WINDOW_MIN_BLOCKS
 #define PARO_RANGE_WINDOW_MIN_BLOCKS 16384       // two-byte contributions of up to 16 ranks: four times as many

@@ -1374,7 +1374,11 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const int budget = f32_large ? PARO_FOLD_F32_LIST_LOADS_PER_CU : small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
     // Waves that look up 48 pointers and more want company: all that fit (whole clipped steps, by the budget and so: Llama-like lists, P = 64, 20 M elements 622 and 503 us,
     // 8 M 256 and 228, 6 M 179.8 and 177.8; P = 128, 10 M 710 and 584; P = 48, 28 M 668 and 662; fp32, P = 64, 11 M 521 and 516; but P = 40, 33 M 543 and 546; GPT-2's, P = 64, 1.9 M 71.2 and 72.2)
-    const bool all = pl->P >= 3 * PARO_BATCH && piece_count(n) >= PARO_ALL_WAVES_MIN_BLOCKS;
+    // A large chunk of fp32 gradients keeps its budget up to 55 ranks and where its tensors are many and small (P = 48, 38 M 1447 and 1473, 56 M 2097 and 2142; P = 50, 43 M
+    // 1558 and 1594, P = 52 1819 and 1841; ragged tensors, P = 48 1512 and 1557, P = 64 1925 and 1981; but P = 56, 41 M 1713 and 1561, 64 M 2670 and 2618; P = 64, 39 M 1905 and
+    // 1708; P = 80 2490 and 2402; P = 128, 35 M 3288 and 3161).
+    const bool all = pl->P >= 3 * PARO_BATCH && piece_count(n) >= PARO_ALL_WAVES_MIN_BLOCKS &&
+                     (!f32_large || (!small && pl->P >= PARO_ALL_WAVES_F32_LARGE_RANKS));
     const unsigned lds = throttle_lds(sc.lds_per_cu, all ? 0 : fold_waves(fold_loads(pl->P), budget));
     PARO_BY_FLAG(keep, KEEP, PARO_BY_FLAG(on_lines, NT, {
         if (pl->P <= 8)                                                     // a batch of 8 contributions: fewer registers

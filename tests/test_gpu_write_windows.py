@@ -107,8 +107,9 @@ def test_single_sweep(paro, P, G, strategy, dtype, L, exempt):
         assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(results[0], other))
 
 
-# Per-tensor gradients: with 48 ranks and more sweep 1 runs all waves that fit from 16 384 blocks on.
-@pytest.mark.parametrize("P,L,dtype", [(48, 1 << 22, wl.BF16), (48, (1 << 22) - 264, wl.BF16), (47, 1 << 22, wl.BF16), (64, (1 << 22) + 8, wl.F16)])
+# Per-tensor gradients: with 48 ranks and more sweep 1 runs all waves that fit from 16 384 blocks on (large chunks of fp32 ones see
+# test_launch_rules).
+@pytest.mark.parametrize("P,L,dtype", [(48, 1 << 22, wl.BF16), (48, (1 << 22) - 264, wl.BF16), (47, 1 << 22, wl.BF16), (64, (1 << 22) + 8, wl.F16), (48, 1 << 22, wl.F32)])
 def test_tensors_of_many_ranks(paro, P, L, dtype):
     rank = P - 2
     ob, ol = orc.state_range(orc.layout(P, P, [P * L]), rank, "G")

@@ -174,3 +174,16 @@ def test_sweep_2_with_exempt_tensors_goes_from_the_start(launches, call, layout)
 def test_small_single_sweeps_with_all_waves(launches, P, G, strategy, dtype, blocks, all_waves):
     got, = launches("step", P, G, strategy, 1, dtype, 0, False, [P * blocks * 256])
     assert got.kernel in ("k_fused4", "k_fused4r") and (got.lds == 0) == all_waves
+
+
+# Sweep 1 over per-tensor gradients runs all waves that fit with 48 ranks and more from 16 384 blocks on; large chunks (131 072 blocks) of fp32
+# gradients only with 56 and more, in few large tensors.
+@pytest.mark.parametrize("P,G,dtype,blocks,small,all_waves", [
+    (48, 8, wl.BF16, 16384, False, True), (48, 8, wl.BF16, 16383, False, False), (47, 47, wl.BF16, 16384, False, False), (48, 8, wl.F32, 131071, False, True),
+    (48, 8, wl.F32, 131072, False, False), (55, 11, wl.F32, 131072, False, False), (56, 8, wl.F32, 131072, False, True),
+    (64, 8, wl.F32, 131072, True, False), (64, 8, wl.BF16, 131072, True, True)])
+def test_sweep_1_over_tensors_of_many_ranks(launches, P, G, dtype, blocks, small, all_waves):
+    L = blocks * 256
+    own = [100_000] * (L // 100_000) + [L % 100_000] if small else [L]      # the first rank's chunk; every other is one tensor
+    got = launches("reduce", P, G, "IGG", 0, dtype, 1, True, own + [L] * (P - 1))
+    assert got[0].kernel == "k_reduce4t" and (got[0].lds == 0) == all_waves
