@@ -276,7 +276,7 @@ namespace {
 #define PARO_FUSED_WINDOW_PACE_SLEEP 3
 #endif
 #ifndef PARO_FUSED_WINDOW_F32_WAVES_PER_CU
-#define PARO_FUSED_WINDOW_F32_WAVES_PER_CU 21
+#define PARO_FUSED_WINDOW_F32_WAVES_PER_CU 21    // the registers let 20 run
 #endif
 // A small single sweep whose waves pause (see pauses_single, pauses_range): how long, and the bytes that the launch reads.
 #ifndef PARO_PAUSE_SLEEP
@@ -348,10 +348,11 @@ struct SrcTableOf {
 using SrcTable = SrcTableOf<PARO_MAX_RANKS>;
 constexpr int FEW_SRC = 16;
 
-// Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip
-// shares: one begins at every multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last blocks, as many as run at
-// once with `waves` per compute unit, do not wait.  Waves that arrive within `open` of a window's start store at once, and new ones
-// begin to read after `rest`.
+// Write windows of a launch that holds its results back (see holds_back), in ticks of the constant 100 MHz clock that the whole chip shares: one begins at every
+// multiple of `period`.  inverse: 2^32 / period, rounded down.  The launch's last blocks, `waves` for each compute unit, do not wait: at least as many as run at
+// once.  Where the registers let fewer run than were asked for - 20 for 21 in single sweeps over fp32 contributions, 28 for 32 in launches over a range of several
+// chunks of two-byte ones and in single sweeps that look up exempt tensors - that is up to 1024 of them more than have nobody behind them.  Waves that arrive within
+// `open` of a window's start store at once, and new ones begin to read after `rest`.
 struct WriteWindow {
     unsigned inverse;
     unsigned short period, waves, open, rest;
@@ -512,7 +513,7 @@ __device__ __forceinline__ unsigned window_phase(const WriteWindow &w) {
 __device__ __forceinline__ void leave_window(const WriteWindow &w) {
     for (int i = 0; i < 128 && window_phase(w) < w.rest; ++i) __builtin_amdgcn_s_sleep(2);
 }
-// Whether a block has others behind it that wait for its place.
+// Whether a block has others behind it that wait for its place (of the last ones see WriteWindow).
 __device__ __forceinline__ bool has_followers(const WriteWindow &w) {
     return blockIdx.x + (unsigned)w.waves * COMPUTE_UNITS < gridDim.x;
 }

@@ -480,11 +480,11 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // (0: nobody needs it), which every wave adds up while its state is on its way; the first block writes
 // the total to sumsq_out unless that is null.
 // KEPT: the launch before this one stored all of the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS): plain loads.
-// Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).  Not with a mask, where
-// that costs paro_adam_shard alone up to 3 % and brings a whole step nothing (from the end and from the start: the call alone after its gradient was
-// scaled in place and copied in, 6 M elements 31.9, 33.1 and 31.2, 32.4 us, on another box 33.6, 35.0 and 32.4, 34.2; 9 M 44.3, 44.6 and 43.6, 43.8; 30 M 134, 142 and
-// 135, 141, there 137, 143 and 135, 141; 200 M 906, 911 and 910, 915; clipped steps, P = 4, GPT-2's list 199 and 198, its tensors 198 and 197, P = 2 384 and 382; 8 chunks, P = 8, 973
-// and 977; Llama-like lists, P = 8, 42 M 312 and 312, P = 16, 84 M 830 and 828, 421 M 4200 and 4200).
+// Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).  Not with a mask, where that costs
+// paro_adam_shard alone up to 3 % and brings a whole step nothing (from the end and from the start: the call alone after its gradient was scaled in place and copied
+// in, 6 M elements 31.9, 33.1 and 31.2, 32.4 us, on another box 33.6, 35.0 and 32.4, 34.2; 9 M 44.3, 44.6 and 43.6, 43.8; 30 M 134, 142 and 135, 141, there 137, 143
+// and 135, 141; 200 M 906, 911 and 910, 915; clipped steps, P = 4, GPT-2's list 199 and 198, its tensors 198 and 197, P = 2 384 and 382; 8 chunks, P = 8, 973 and
+// 977; Llama-like lists, P = 8, 42 M 312 and 312, P = 16, 84 M 830 and 828, 421 M 4200 and 4200).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
 __global__ __launch_bounds__(WAVE) void k_adam4(int64_t n, const float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
                                                 float *__restrict__ v, const double *__restrict__ sums, int n_sums, const AdamConsts a,
@@ -721,15 +721,17 @@ int fold_budget(const paro_plan_t *pl, bool paced) {
     return pl->P > PARO_BATCH && !short_batch ? PARO_FOLD_WIDE_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
 }
 
-// Whether a single sweep is so small that a budget would only keep waves from starting, of which the chip holds all at once: with 10 or 11 per
-// compute unit it takes two or three rounds.  Whole steps, by the budget and with all waves: over a range of two-byte contributions (up to 8192
-// blocks), whose waves walk to their pointers first, P = 14, 2 x 0.9 M elements 17.4 -> 17.0 us; P = 16, 2 x 0.3 M 8.1 -> 7.0, 2 x 0.5 M 11.3 -> 10.4, 2 x 1 M 20.2 -> 19.2;
-// P = 24, 2 x 0.5 M 15.1 -> 13.0, 2 x 1 M 26.5 -> 24.4; P = 32, 2 x 1 M 31.2 -> 29.3; P = 64, 2 x 0.5 M 29.8 -> 25.1, 2 x 1 M 53.6 -> 52.7; P = 128, 2 x 0.4 M 45.3 -> 42.7, 2 x 1 M 98.5 -> 99.4 and 98.5 -> 97.4; but beyond that P = 16, 2 x
-// 2 M 38.8 -> 41.9, P = 32, 2 x 1.5 M 45.2 -> 47.2; P = 8, 2 x 0.8 M 11.2 -> 12.5, P = 12, 2 x 0.9 M 15.8 -> 16.1.  Otherwise up to 64 ranks: fp32 (up to 4096 blocks), P = 16, 0.7 M 10.3 -> 10.0, P = 64, 1 M
-// 46.6 -> 45.4, a range, P = 16, 2 x 0.5 M 15.0 -> 14.6, P = 32 24.9 -> 24.4; but P = 128, 1 M 43.6 -> 45.0; one chunk of two bytes, P = 32, 0.8 M 12.7 -> 12.5, 1 M 15.1 -> 14.8; P = 64, 0.6 M 17.9 -> 15.7,
-// 1 M 24.6 -> 24.4; but P = 32, 2 M 28.9 -> 29.4.  With up to 16 of them each wave asks for all it reads in one go, and beyond 25 MB for the launch that is too much at once: P = 12, 0.75 M 7.2 -> 5.7, 0.9 M 7.8 ->
-// 7.4, 1.045 M 8.8 -> 8.7; P = 14, 0.75 M 7.7 -> 6.2, 0.85 M 8.0 -> 7.7, but 0.95 M 8.6 -> 8.8, 1.045 M 9.3 -> 9.9; P = 15, 0.75 M 7.9 -> 6.5, but 0.95 M 9.2 -> 9.5; P = 16, 0.65 M 7.0 -> 6.7, 0.75 M 7.3 -> 7.3, but
-// 0.85 M 8.0 -> 8.5, 0.9 M 8.5 -> 9.1.  17 to 31: P = 17, 0.7 M 8.2 -> 7.2, 0.98 M 10.8 -> 10.6; P = 24, 0.7 M 9.9 -> 9.4, 0.98 M 12.8 -> 12.7, but 1.02 M 12.8 -> 13.2; P = 26 13.5 -> 13.9; P = 28 14.7 -> 14.8.
+// Whether a single sweep is so small that a budget would only keep waves from starting, of which the chip holds all at once: with 10 or 11 per compute unit it takes
+// two or three rounds.  Whole steps, by the budget and with all waves: over a range of two-byte contributions (up to 8192 blocks), whose waves walk to their
+// pointers first, P = 14, 2 x 0.9 M elements 17.4 -> 17.0 us; P = 16, 2 x 0.3 M 8.1 -> 7.0, 2 x 0.5 M 11.3 -> 10.4, 2 x 1 M 20.2 -> 19.2; P = 24, 2 x 0.5 M 15.1 ->
+// 13.0, 2 x 1 M 26.5 -> 24.4; P = 32, 2 x 1 M 31.2 -> 29.3; P = 64, 2 x 0.5 M 29.8 -> 25.1, 2 x 1 M 53.6 -> 52.7; P = 128, 2 x 0.4 M 45.3 -> 42.7, 2 x 1 M 98.5 ->
+// 99.4 and 98.5 -> 97.4; but beyond that P = 16, 2 x 2 M 38.8 -> 41.9, P = 32, 2 x 1.5 M 45.2 -> 47.2; P = 8, 2 x 0.8 M 11.2 -> 12.5, P = 12, 2 x 0.9 M 15.8 ->
+// 16.1.  Otherwise up to 64 ranks: fp32 (up to 4096 blocks), P = 16, 0.7 M 10.3 -> 10.0, P = 64, 1 M 46.6 -> 45.4, a range, P = 16, 2 x 0.5 M 15.0 -> 14.6, P = 32
+// 24.9 -> 24.4; but P = 128, 1 M 43.6 -> 45.0; one chunk of two bytes, P = 32, 0.8 M 12.7 -> 12.5, 1 M 15.1 -> 14.8; P = 64, 0.6 M 17.9 -> 15.7, 1 M 24.6 -> 24.4;
+// but P = 32, 2 M 28.9 -> 29.4.  With up to 16 of them each wave asks for all it reads in one go, and beyond 25 MB for the launch that is too much at once: P = 12,
+// 0.75 M 7.2 -> 5.7, 0.9 M 7.8 -> 7.4, 1.045 M 8.8 -> 8.7; P = 14, 0.75 M 7.7 -> 6.2, 0.85 M 8.0 -> 7.7, but 0.95 M 8.6 -> 8.8, 1.045 M 9.3 -> 9.9; P = 15, 0.75 M
+// 7.9 -> 6.5, but 0.95 M 9.2 -> 9.5; P = 16, 0.65 M 7.0 -> 6.7, 0.75 M 7.3 -> 7.3, but 0.85 M 8.0 -> 8.5, 0.9 M 8.5 -> 9.1.  17 to 31: P = 17, 0.7 M 8.2 -> 7.2,
+// 0.98 M 10.8 -> 10.6; P = 24, 0.7 M 9.9 -> 9.4, 0.98 M 12.8 -> 12.7, but 1.02 M 12.8 -> 13.2; P = 26 13.5 -> 13.9; P = 28 14.7 -> 14.8.
 bool runs_at_once(int P, bool f32, bool range, int64_t blocks) {
     if (range && !f32) return P > 12 && blocks <= PARO_AT_ONCE_RANGE_BLOCKS;
     if (P < 12 || P > 64) return false;
@@ -1040,20 +1042,21 @@ int64_t update_elems(const paro_plan_t *pl) {
 bool paces(const paro_plan_t *pl) {
     return piece_count(pl->L) >= (pl->P < 2 * PARO_BATCH ? PARO_PACE_MIN_BLOCKS : PARO_PACE_MIN_BLOCKS / 2);
 }
-// Whether sweep 1 over one chunk holds its results back for write windows that the whole chip shares.  A trickle of stores among P
-// streams of loads costs the memory far more than its bytes: the fold of 16 ranks reads at 7.1 TB/s while nothing is stored and at 6.4 with
-// its 11 % of stores, that of 64 at 6.9 and 6.0 with 3 %.  So a wave that has its sums waits (asleep, with four registers of results a
-// lane) until the chip's next window, all stores go out within half a microsecond, and waves that start then leave the memory to them.
-// It takes waves to spare: while about half of them wait the others have to keep the memory busy, so they are not thinned out - as many as
-// fit of two-byte contributions, 18 per compute unit of fp32 ones - and a window comes after 0.55 of the time that all their loads
-// take at 7.1 TB/s: 0.36 us a rank for either type, 16 us at most.  Those that have nobody behind them do not wait.
-// Whole clipped steps on the same buffers, without and with windows: P = 64, 100 M elements 2518 -> 2385 us, 35 M 899 -> 869; P = 128, 30 M 1389 ->
-// 1341; P = 100, 40 M 1516 -> 1455; P = 48, 60 M 1222 -> 1187; P = 32, 100 M 1495 -> 1440, 12 M 192.1 -> 189.6; P = 24, 60 M 780 -> 755; P = 16,
-// 100 M 1028 -> 1008, 25 M 257.9 -> 256.7; P = 12, 100 M 889 -> 876; but P = 16, 17 M 175.9 -> 176.2, 8 M 88.4 -> 88.9; P = 20, 12 M 143 -> 144; P = 64, 15 M 378
-// -> 383; P = 10, 60 M 495 -> 497; P = 8, 100 M 747 -> 759.  fp32: P = 64, 30 M 1341 -> 1309; P = 48, 30 M 1047 -> 1016, 8 M 296 -> 289; P = 32, 40 M
-// 1000 -> 960, 6 M 160 -> 154; P = 24, 10 M 216 -> 210; P = 16, 60 M 895 -> 879, 10 M 166 -> 159; P = 12, 10 M 136 -> 133; but P = 16, 17 M 257 -> 262, 30 M 455 -> 457, 2 M
-// 37.0 -> 37.9; P = 10, 60 M 695 -> 700.  Sweep 2 and the single sweep of 16 ranks, half and a quarter of whose bytes are stores, are 9 and 0 to 3 % slower with windows of
-// any length; a wave that folds 2 to 8 blocks before it waits gains no more than one that folds one.
+// Whether sweep 1 over one chunk holds its results back for write windows that the whole chip shares.  A trickle of stores among P streams of loads costs the memory
+// far more than its bytes: the fold of 16 ranks reads at 7.1 TB/s while nothing is stored and at 6.4 with its 11 % of stores, that of 64 at 6.9 and 6.0 with 3
+// %.  So a wave that has its sums waits (asleep, with four registers of results a lane) until the chip's next window, all stores go out within half a microsecond,
+// and waves that start then leave the memory to them.  It takes waves to spare: while about half of them wait the others have to keep the memory busy, so they are
+// not thinned out - as many as fit of two-byte contributions, 18 per compute unit of fp32 ones - and a window comes after 0.36 us a rank for either type, 16 us at
+// most: 0.61 of the time that all their loads take at 7.1 TB/s with two-byte contributions, 0.55 with fp32 ones.  Those that have nobody behind them do not wait.
+// Whole clipped steps on the same buffers, without and with windows: P = 64, 100 M elements 2518 -> 2385 us, 35 M 899 -> 869; P = 128, 30 M 1389 -> 1341; P = 100,
+// 40 M 1516 -> 1455; P = 48, 60 M 1222 -> 1187; P = 32, 100 M 1495 -> 1440, 12 M 192.1 -> 189.6; P = 24, 60 M 780 -> 755; P = 16, 100 M 1028 -> 1008, 25 M 257.9 ->
+// 256.7; P = 12, 100 M 889 -> 876; but P = 16, 17 M 175.9 -> 176.2, 8 M 88.4 -> 88.9; P = 20, 12 M 143 -> 144; P = 64, 15 M 378 -> 383; P = 10, 60 M 495 -> 497; P =
+// 8, 100 M 747 -> 759.  fp32: P = 64, 30 M 1341 -> 1309; P = 48, 30 M 1047 -> 1016, 8 M 296 -> 289; P = 32, 40 M 1000 -> 960, 6 M 160 -> 154; P = 24, 10 M 216 ->
+// 210; P = 16, 60 M 895 -> 879, 10 M 166 -> 159; P = 12, 10 M 136 -> 133; but P = 16, 17 M 257 -> 262, 30 M 455 -> 457, 2 M 37.0 -> 37.9; P = 10, 60 M 695 ->
+// 700.  Between 65 536 and 131 071 blocks fp32 launches of up to 47 ranks, which are paced there and have waves for that, win or lose by the size: on another box P
+// = 24, 17 M 341 -> 334, 24 M 465 -> 465, 33 M 622 -> 636; P = 40, 17 M 503 -> 504, 30 M 848 -> 871; P = 32, 17 M 417 -> 412, 24 M 590 -> 577, 33 M 778 -> 782; P =
+// 20, 30 M 513 -> 506; P = 16, 17 M 255 -> 250, 33 M 479 -> 472.  Sweep 2 and the single sweep of 16 ranks, half and a quarter of whose bytes are stores, are 9 and
+// 0 to 3 % slower with windows of any length; a wave that folds 2 to 8 blocks before it waits gains no more than one that folds one.
 bool holds_back(const paro_plan_t *pl) {
     const int64_t blocks = piece_count(pl->L);
     if (pl->P < PARO_WINDOW_MIN_RANKS) return false;
@@ -1087,18 +1090,18 @@ WriteWindow fold_window(const paro_plan_t *pl, bool range = false) {
     const int most = soon ? PARO_RANGE_WINDOW_MAX_PERIOD : PARO_WINDOW_MAX_PERIOD;
     return window_for(std::min(per_rank * pl->P, most), window_waves(pl), PARO_WINDOW_TICKS, PARO_WINDOW_REST_TICKS);
 }
-// ... and whether the single sweep over n elements does (chunk layout), whose waves store their state as well: a window takes 0.16 of a
-// period that is twice as long.  Whole steps on the same buffers, without and with windows: P = 64, 100 M elements 2632 -> 2314 us, 30 M 774 -> 690, 8 M 217.5
-// -> 203.5; P = 128, 20 M 957 -> 894; P = 256, 6 M 586 -> 539; P = 48, 40 M 811 -> 731; P = 40, 60 M 1037 -> 975, 30 M 518 -> 499; P = 32, 100 M 1458 -> 1451 and on another
-// box 1455 -> 1408, 40 M 572 -> 556, 10 M 149.5 -> 153.2 and 146.3 -> 144.1; a range of 4 x 30 M, P = 32, 1805 -> 1741, 8 x 10 M, P = 64, 2176 -> 1948; but P = 28, 60 M
-// 775 -> 772, P = 24, 100 M 1150 -> 1170, P = 16, 200 M 1796 -> 1870; P = 32, 3 M 46.6 -> 49.0, P = 64, 3 M 79.1 -> 82.8, P = 128, 2 M 94.8 -> 98.2, P = 256, 2 M 184 -> 187.
-// fp32: P = 64, 20 M 992 -> 886; P = 32, 15 M 403 -> 371, 4 M 111.0 -> 107.0; P = 24, 50 M 1028 -> 961; P = 20, 40 M 686 -> 698 and 725 -> 692; P = 16, 80 M 1204 -> 1170, 15 M
-// 228 -> 222, 8 M 122.6 -> 121.8; but P = 14, 60 M 788 -> 799, P = 16, 5 M 80.0 -> 80.6.  Per-tensor gradients of two bytes, whose waves
-// look up their pointers first: P = 32, Llama-like list, 555 -> 618; ragged, 335 -> 366.
-// 32 ranks of two bytes, whose waves end with no short last batch, are fastest of all without (14.2 us a million elements, 33 ranks 14.9, 36 16.0) and gain at every size only
-// from 26 M elements on: 13 M 190 -> 188, 16 M 228 -> 224, 18 M 255 -> 260, 20 M 283.7 -> 288.5, 22 M 321 -> 315, 25 M 354.7 -> 357.8, 26 M 377 -> 371, 27 M 387 -> 380, 28 M
-// 408 -> 396, 35 M 498 -> 492, 60 M 870 -> 844; P = 33, 18 M 269 -> 269, 20 M 296 -> 293, 25 M 371 -> 362; P = 34, 14 M 218 -> 207, 20 M 305 -> 299; P = 36, 14 M 230 -> 216, 20 M 325 -> 304;
-// fp32, P = 16, 13 M 203 -> 188, 20 M 291 -> 280, 32 M 470 -> 450.
+// ... and whether the single sweep over n elements does (chunk layout), whose waves store their state as well: one comes after 0.26 us for each byte of an element's
+// contributions, 28 us at most (fp32 ones: 23), and takes 0.16 of that.  Whole steps on the same buffers, without and with windows: P = 64, 100 M elements 2632 ->
+// 2314 us, 30 M 774 -> 690, 8 M 217.5 -> 203.5; P = 128, 20 M 957 -> 894; P = 256, 6 M 586 -> 539; P = 48, 40 M 811 -> 731; P = 40, 60 M 1037 -> 975, 30 M 518 ->
+// 499; P = 32, 100 M 1458 -> 1451 and on another box 1455 -> 1408, 40 M 572 -> 556, 10 M 149.5 -> 153.2 and 146.3 -> 144.1; a range of 4 x 30 M, P = 32, 1805 ->
+// 1741, 8 x 10 M, P = 64, 2176 -> 1948; but P = 28, 60 M 775 -> 772, P = 24, 100 M 1150 -> 1170, P = 16, 200 M 1796 -> 1870; P = 32, 3 M 46.6 -> 49.0, P = 64, 3 M
+// 79.1 -> 82.8, P = 128, 2 M 94.8 -> 98.2, P = 256, 2 M 184 -> 187.  fp32: P = 64, 20 M 992 -> 886; P = 32, 15 M 403 -> 371, 4 M 111.0 -> 107.0; P = 24, 50 M 1028 ->
+// 961; P = 20, 40 M 686 -> 698 and 725 -> 692; P = 16, 80 M 1204 -> 1170, 15 M 228 -> 222, 8 M 122.6 -> 121.8; but P = 14, 60 M 788 -> 799, P = 16, 5 M 80.0 ->
+// 80.6.  Per-tensor gradients of two bytes, whose waves look up their pointers first: P = 32, Llama-like list, 555 -> 618; ragged, 335 -> 366.
+// 32 ranks of two bytes, whose waves end with no short last batch, are fastest of all without (14.2 us a million elements, 33 ranks 14.9, 36 16.0) and gain at every
+// size only from 26 M elements on: 13 M 190 -> 188, 16 M 228 -> 224, 18 M 255 -> 260, 20 M 283.7 -> 288.5, 22 M 321 -> 315, 25 M 354.7 -> 357.8, 26 M 377 -> 371, 27
+// M 387 -> 380, 28 M 408 -> 396, 35 M 498 -> 492, 60 M 870 -> 844; P = 33, 18 M 269 -> 269, 20 M 296 -> 293, 25 M 371 -> 362; P = 34, 14 M 218 -> 207, 20 M 305 ->
+// 299; P = 36, 14 M 230 -> 216, 20 M 325 -> 304; fp32, P = 16, 13 M 203 -> 188, 20 M 291 -> 280, 32 M 470 -> 450.
 bool fused_holds_back(const paro_plan_t *pl, int64_t n) {
     const bool f32 = pl->dtype[0] == PARO_F32;
     const int bytes = pl->P * (f32 ? 4 : 2);
@@ -1374,9 +1377,9 @@ int launch_reduce(const paro_plan_t *pl, const Scratch &sc, int layout, const Sr
     const int budget = f32_large ? PARO_FOLD_F32_LIST_LOADS_PER_CU : small ? PARO_FOLD_TM_LOADS_PER_CU : PARO_FOLD_LOADS_PER_CU;
     // Waves that look up 48 pointers and more want company: all that fit (whole clipped steps, by the budget and so: Llama-like lists, P = 64, 20 M elements 622 and 503 us,
     // 8 M 256 and 228, 6 M 179.8 and 177.8; P = 128, 10 M 710 and 584; P = 48, 28 M 668 and 662; fp32, P = 64, 11 M 521 and 516; but P = 40, 33 M 543 and 546; GPT-2's, P = 64, 1.9 M 71.2 and 72.2)
-    // A large chunk of fp32 gradients keeps its budget up to 55 ranks and where its tensors are many and small (P = 48, 38 M 1447 and 1473, 56 M 2097 and 2142; P = 50, 43 M
-    // 1558 and 1594, P = 52 1819 and 1841; ragged tensors, P = 48 1512 and 1557, P = 64 1925 and 1981; but P = 56, 41 M 1713 and 1561, 64 M 2670 and 2618; P = 64, 39 M 1905 and
-    // 1708; P = 80 2490 and 2402; P = 128, 35 M 3288 and 3161).
+    // A large chunk of fp32 gradients keeps its budget up to 55 ranks and where its tensors are many and small (P = 48, 38 M 1447 and 1473, 56 M 2097 and 2142; P =
+    // 50, 43 M 1558 and 1594, P = 52 1819 and 1841; ragged tensors, P = 48 1512 and 1557, P = 64 1925 and 1981; but P = 56, 41 M 1713 and 1561, 64 M 2670 and 2618;
+    // P = 64, 39 M 1905 and 1708; P = 80 2490 and 2402; P = 128, 35 M 3288 and 3161).
     const bool all = pl->P >= 3 * PARO_BATCH && piece_count(n) >= PARO_ALL_WAVES_MIN_BLOCKS &&
                      (!f32_large || (!small && pl->P >= PARO_ALL_WAVES_F32_LARGE_RANKS));
     const unsigned lds = throttle_lds(sc.lds_per_cu, all ? 0 : fold_waves(fold_loads(pl->P), budget));
@@ -1591,7 +1594,8 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
 //   up to 4 ranks, two bytes, 65 536    P = 2, 2 x 24 M 310 and 294 us, 2 x 120 M 1517 and 1400; P = 4, 2 x 50 M 664 and 643; but 4 x 12 M
 //                                       321 and 331, fp32 2 x 60 M 906 and 918
 //   two bytes, 12 to 99 ranks, 131 072  where the one launch has write windows, P = 16, 2 x 40 M 793 and 788; P = 48, 2 x 40 M 1528 and 1514; P = 24, 2 x 50 M 1252 and 1199;
-//                                       but P = 32, 2 x 18 M 511 and 521, P = 64, 4 x 14 M 1362 and 1380, 8 x 9 M 1717 and 1785; P = 12, 2 x 40 M 700 and 705; P = 32,
+//                                       but P = 32, 2 x 18 M 511 and 521, P = 64, 4 x 14 M 1362 and 1380, 8 x 9 M 1717 and 1785; P = 12, 2 x 40 M 700 and 705,
+//                                       on another box 702 and 701, 2 x 60 M 1051 and 1040, P = 16, 2 x 35 M 692 and 689, 2 x 60 M 1186 and 1167; P = 32,
 //                                       2 x 32 M 913 and 922; P = 100, 2 x 20 M 1415 and 1452; P = 128, 2 x 20 M 1760 and 1800; P = 8 (no windows),
 //                                       2 x 60 M 920 and 919, 8 x 17 M 1029 and 1083
 //   fp32, 8 to 11 ranks, 131 072        P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277; with 12 and more, where the one launch has write
@@ -1671,10 +1675,12 @@ int launch_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamCo
     return PARO_OK;
 }
 
-// Sweep 2 behind sweep 1, whose gradient may be in the memory-side cache (kept), or with a gradient that another call, or
-// another program's kernel, left anywhere: that is read as it always was.  Plain loads of a gradient that is no longer in the
-// cache drive out of it what other kernels wrote there (paro_adam_shard after 512 MB of something else, P = 8, streaming and
-// plain: 4 M elements 25.0 and 27.6 us, 12 M 58.4 and 65.7; of one just written 24.3 and 23.3, 55.8 and 54.4).
+// Sweep 2 behind sweep 1, whose gradient may be in the memory-side cache (kept), or with a gradient that another call, or another program's kernel, left anywhere:
+// that is read with streaming loads, the last block first unless there is a mask (paro_adam_shard alone, from the start and from the end, P = 8: gradient just
+// copied in, 6 M elements 32.8 and 32.8 us, 30 M 137.5 and 136.9, 50 M 220.6 and 218.4, 120 M 535 and 533, 400 M 1775 and 1776; after 512 MB of something else, 12 M
+// 58.9 and 58.9, 50 M 225.0 and 222.1, 120 M 536 and 533).  Plain loads of a gradient that is no longer in the cache drive out of it what other kernels wrote there
+// (paro_adam_shard after 512 MB of something else, P = 8, streaming and plain: 4 M elements 25.0 and 27.6 us, 12 M 58.4 and 65.7; of one just written 24.3 and 23.3,
+// 55.8 and 54.4).
 int do_adam(const paro_plan_t *pl, const Scratch &sc, int rank, const AdamConsts &a, const float *grad, bool kept,
             const NormSums &norm, float *p, float *m, float *v, uint16_t *dst /* nullable: no pack */, hipStream_t st) {
     return !dst ? launch_adam<false, false>(pl, sc, rank, a, grad, norm, p, m, v, dst, st)

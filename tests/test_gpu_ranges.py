@@ -95,8 +95,9 @@ def test_large_chunks_with_few_ranks_are_launched_one_by_one(paro, P, G, strateg
     (12, 6, wl.BF16, 131072), (32, 16, wl.F16, 65536), (64, 32, wl.BF16, 32768), (8, 4, wl.F32, 131072), (16, 8, wl.F32, 65536)])
 @pytest.mark.parametrize("short", [16, 8, 7])
 def test_more_ranks_where_chunks_begin_to_be_launched_one_by_one(paro, P, G, dtype, first, short):
-    """`first`: the blocks of a chunk, counted with the one more that it may straddle and in eights, from which on each is
-    launched by itself.  16 blocks short of it the range is one launch."""
+    """`first`: the blocks of a chunk, counted with the one more that it may straddle and in eights, around which the sizes lie.  With 12 two-byte
+    and 8 fp32 ranks each chunk is launched by itself from there on, 16 blocks short of it the range is one launch; with the others, for which
+    there once were such lines, it is one launch on both sides (test_launch_rules says how many launches there are)."""
     L = (first - short) * 256 + (8 if short == 7 else 0)
     test_large_chunks_with_few_ranks_are_launched_one_by_one(paro, P, G, "III", orc.HORING, dtype, L)
 

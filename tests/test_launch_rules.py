@@ -187,3 +187,14 @@ def test_sweep_1_over_tensors_of_many_ranks(launches, P, G, dtype, blocks, small
     own = [100_000] * (L // 100_000) + [L % 100_000] if small else [L]      # the first rank's chunk; every other is one tensor
     got = launches("reduce", P, G, "IGG", 0, dtype, 1, True, own + [L] * (P - 1))
     assert got[0].kernel == "k_reduce4t" and (got[0].lds == 0) == all_waves
+
+
+# A chunk's blocks are counted with the one more that it may straddle, and in eights.
+@pytest.mark.parametrize("P,G,dtype,blocks,one_by_one", [
+    (4, 2, wl.BF16, 65536, True), (4, 2, wl.BF16, 65528, False), (8, 4, wl.BF16, 262144, False), (12, 6, wl.BF16, 131072, True), (12, 6, wl.F16, 131064, False),
+    (32, 16, wl.F16, 65536, False), (64, 32, wl.BF16, 32768, False), (99, 33, wl.BF16, 131072, True), (100, 50, wl.BF16, 131072, False),
+    (4, 2, wl.F32, 131072, False), (8, 4, wl.F32, 131072, True), (11, 1, wl.F32, 131072, True), (8, 4, wl.F32, 131064, False),
+    (12, 6, wl.F32, 131072, False), (16, 8, wl.F32, 65536, False)])
+def test_ranges_that_are_swept_chunk_by_chunk(launches, P, G, dtype, blocks, one_by_one):
+    got = [x.kernel for x in launches("step", P, G, "III", 0, dtype, 0, True, [P * (blocks - 8) * 256]) if x.kernel.startswith("k_reduce")]
+    assert got == ["k_reduce4"] * (P // G) if one_by_one else got == ["k_reduce4r"]
