@@ -37,7 +37,7 @@ namespace {
 //   tensors do not mind (GPT-2, P = 16, 249 MB: 3 to 5 % ahead in all but one)
 //   512 MB of something else: P = 2 to 8 ahead by 1 to 4 %, P = 12 by 1 % to behind by 1, P = 16 behind by 0 to 3; P = 32 and 64 were behind by
 //   2 to 4 % from 2 M on, so more than 16 ranks keep only what is small enough to keep its state as well.
-// Beyond these limits the last PARO_KEEP_G_TAIL_ELEMS are kept, 224 MB, and sweep 2 begins at the end.
+// Beyond these limits the last PARO_KEEP_G_TAIL_ELEMS are kept, 224 MB, and sweep 2 begins at the end (not with a mask, see k_adam4).
 #ifndef PARO_KEEP_G_ELEMS
 #define PARO_KEEP_G_ELEMS (16 << 20)
 #endif
