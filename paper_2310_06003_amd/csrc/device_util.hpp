@@ -132,7 +132,7 @@ namespace {
 #endif
 // A large sweep 2, from PARO_LARGE_TILES blocks on, wants one wave less since its waves start at once (whole clipped steps, same buffers, 12,
 // 11 and 10 waves: fp16, P = 8, 124 M elements 955, 946 and 948 us; P = 16, 421 M 4244, 4227 and 4242; P = 8, 62 M 481, 476 and 477; P = 2, 80 M
-// 462, 462 and 467; but 16 M 121.4 and 122.1.  12 and 11 on another box: 949 and 943; 4288 and 4273; 474 and 470; 459 and 457; P = 8, 40 M 304.6 and
+// 462, 462 and 467; but 16 M 121.4 and 122.1.  12 and 11 on another GPU: 949 and 943; 4288 and 4273; 474 and 470; 459 and 457; P = 8, 40 M 304.6 and
 // 304.2).
 #ifndef PARO_ADAM_LARGE_WAVES_PER_CU
 #define PARO_ADAM_LARGE_WAVES_PER_CU 11

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(FINALIZE_TPB) void k_norm_slices_total(const double
 // KEPT: the launch before this one stored all of the gradient to stay in the memory-side cache (see PARO_KEEP_G_ELEMS): plain loads.
 // Otherwise the last blocks come first: it is the end of the gradient that the cache may hold (see PARO_KEEP_G_TAIL_ELEMS).  Not with a mask, where that costs
 // paro_adam_shard alone up to 3 % and brings a whole step nothing (from the end and from the start: the call alone after its gradient was scaled in place and copied
-// in, 6 M elements 31.9, 33.1 and 31.2, 32.4 us, on another box 33.6, 35.0 and 32.4, 34.2; 9 M 44.3, 44.6 and 43.6, 43.8; 30 M 134, 142 and 135, 141, there 137, 143
+// in, 6 M elements 31.9, 33.1 and 31.2, 32.4 us, on another GPU 33.6, 35.0 and 32.4, 34.2; 9 M 44.3, 44.6 and 43.6, 43.8; 30 M 134, 142 and 135, 141, there 137, 143
 // and 135, 141; 200 M 906, 911 and 910, 915; clipped steps, P = 4, GPT-2's list 199 and 198, its tensors 198 and 197, P = 2 384 and 382; 8 chunks, P = 8, 973 and
 // 977; Llama-like lists, P = 8, 42 M 312 and 312, P = 16, 84 M 830 and 828, 421 M 4200 and 4200).
 template <bool PACK, int MASK, bool KEPT, bool MANY>
@@ -1053,7 +1053,7 @@ bool paces(const paro_plan_t *pl) {
 // 256.7; P = 12, 100 M 889 -> 876; but P = 16, 17 M 175.9 -> 176.2, 8 M 88.4 -> 88.9; P = 20, 12 M 143 -> 144; P = 64, 15 M 378 -> 383; P = 10, 60 M 495 -> 497; P =
 // 8, 100 M 747 -> 759.  fp32: P = 64, 30 M 1341 -> 1309; P = 48, 30 M 1047 -> 1016, 8 M 296 -> 289; P = 32, 40 M 1000 -> 960, 6 M 160 -> 154; P = 24, 10 M 216 ->
 // 210; P = 16, 60 M 895 -> 879, 10 M 166 -> 159; P = 12, 10 M 136 -> 133; but P = 16, 17 M 257 -> 262, 30 M 455 -> 457, 2 M 37.0 -> 37.9; P = 10, 60 M 695 ->
-// 700.  Between 65 536 and 131 071 blocks fp32 launches of up to 47 ranks, which are paced there and have waves for that, win or lose by the size: on another box P
+// 700.  Between 65 536 and 131 071 blocks fp32 launches of up to 47 ranks, which are paced there and have waves for that, win or lose by the size: on another GPU P
 // = 24, 17 M 341 -> 334, 24 M 465 -> 465, 33 M 622 -> 636; P = 40, 17 M 503 -> 504, 30 M 848 -> 871; P = 32, 17 M 417 -> 412, 24 M 590 -> 577, 33 M 778 -> 782; P =
 // 20, 30 M 513 -> 506; P = 16, 17 M 255 -> 250, 33 M 479 -> 472.  Sweep 2 and the single sweep of 16 ranks, half and a quarter of whose bytes are stores, are 9 and
 // 0 to 3 % slower with windows of any length; a wave that folds 2 to 8 blocks before it waits gains no more than one that folds one.
@@ -1093,7 +1093,7 @@ WriteWindow fold_window(const paro_plan_t *pl, bool range = false) {
 // ... and whether the single sweep over n elements does (chunk layout), whose waves store their state as well: one comes after 0.26 us for each byte of an element's
 // contributions, 28 us at most (fp32 ones: 23), and takes 0.16 of that.  Whole steps on the same buffers, without and with windows: P = 64, 100 M elements 2632 ->
 // 2314 us, 30 M 774 -> 690, 8 M 217.5 -> 203.5; P = 128, 20 M 957 -> 894; P = 256, 6 M 586 -> 539; P = 48, 40 M 811 -> 731; P = 40, 60 M 1037 -> 975, 30 M 518 ->
-// 499; P = 32, 100 M 1458 -> 1451 and on another box 1455 -> 1408, 40 M 572 -> 556, 10 M 149.5 -> 153.2 and 146.3 -> 144.1; a range of 4 x 30 M, P = 32, 1805 ->
+// 499; P = 32, 100 M 1458 -> 1451 and on another GPU 1455 -> 1408, 40 M 572 -> 556, 10 M 149.5 -> 153.2 and 146.3 -> 144.1; a range of 4 x 30 M, P = 32, 1805 ->
 // 1741, 8 x 10 M, P = 64, 2176 -> 1948; but P = 28, 60 M 775 -> 772, P = 24, 100 M 1150 -> 1170, P = 16, 200 M 1796 -> 1870; P = 32, 3 M 46.6 -> 49.0, P = 64, 3 M
 // 79.1 -> 82.8, P = 128, 2 M 94.8 -> 98.2, P = 256, 2 M 184 -> 187.  fp32: P = 64, 20 M 992 -> 886; P = 32, 15 M 403 -> 371, 4 M 111.0 -> 107.0; P = 24, 50 M 1028 ->
 // 961; P = 20, 40 M 686 -> 698 and 725 -> 692; P = 16, 80 M 1204 -> 1170, 15 M 228 -> 222, 8 M 122.6 -> 121.8; but P = 14, 60 M 788 -> 799, P = 16, 5 M 80.0 ->
@@ -1114,7 +1114,7 @@ bool fused_holds_back(const paro_plan_t *pl, int64_t n) {
 // without windows and with: P = 28, 2 x 20 M elements 536 -> 513 us; P = 32, 2 x 2 M 62.3 -> 61.2, 2 x 5 M 148 -> 145; P = 48, 2 x 2 M 87.1 -> 84.6; P = 64, 2 x 2 M 108.1 -> 105.7; P = 128, 2 x 2 M 204.5
 // -> 194.6; but P = 36, 3 x 3 M 146.7 -> 148.2, P = 28, 2 x 3 M 83.2 -> 81.7 and 83.5 -> 84.0, 4 x 5 M 258.2 -> 258.9, P = 30, 2 x 5 M 139.6 -> 140.4; P = 24, 2 x 4 M 98.8 -> 98.0, 2 x 2 M 50.0 -> 50.0;
 // P = 16, 2 x 6 M 110 -> 118; P = 32, 2 x 1.5 M 45.2 -> 45.7, P = 64 80.6 -> 81.4.  Paced and with a window as above, and so: P = 32, 8 x 3 M 351 -> 342; P = 40, 4 x 10 M 706 -> 686;
-// P = 48 803 -> 781; P = 64, 4 x 12 M 1155 -> 1148, 8 x 4 M 762 -> 747 and on another box 796 -> 803; P = 96, 4 x 5 M 713 -> 707; but P = 128, 4 x 5 M 867 -> 875.
+// P = 48 803 -> 781; P = 64, 4 x 12 M 1155 -> 1148, 8 x 4 M 762 -> 747 and on another GPU 796 -> 803; P = 96, 4 x 5 M 713 -> 707; but P = 128, 4 x 5 M 867 -> 875.
 bool fused_range_holds_back(const paro_plan_t *pl, int64_t n) {
     if (pl->dtype[0] == PARO_F32) return fused_holds_back(pl, n);
     if (pl->P < PARO_FUSED_RANGE_WINDOW_MIN_RANKS) return false;
@@ -1595,7 +1595,7 @@ int do_reduce_range(const paro_plan_t *pl, const Scratch &sc, int64_t ob, int64_
 //                                       321 and 331, fp32 2 x 60 M 906 and 918
 //   two bytes, 12 to 99 ranks, 131 072  where the one launch has write windows, P = 16, 2 x 40 M 793 and 788; P = 48, 2 x 40 M 1528 and 1514; P = 24, 2 x 50 M 1252 and 1199;
 //                                       but P = 32, 2 x 18 M 511 and 521, P = 64, 4 x 14 M 1362 and 1380, 8 x 9 M 1717 and 1785; P = 12, 2 x 40 M 700 and 705,
-//                                       on another box 702 and 701, 2 x 60 M 1051 and 1040, P = 16, 2 x 35 M 692 and 689, 2 x 60 M 1186 and 1167; P = 32,
+//                                       on another GPU 702 and 701, 2 x 60 M 1051 and 1040, P = 16, 2 x 35 M 692 and 689, 2 x 60 M 1186 and 1167; P = 32,
 //                                       2 x 32 M 913 and 922; P = 100, 2 x 20 M 1415 and 1452; P = 128, 2 x 20 M 1760 and 1800; P = 8 (no windows),
 //                                       2 x 60 M 920 and 919, 8 x 17 M 1029 and 1083
 //   fp32, 8 to 11 ranks, 131 072        P = 8, 2 x 40 M 826 and 812; but 8 x 15 M 1232 and 1277; with 12 and more, where the one launch has write
